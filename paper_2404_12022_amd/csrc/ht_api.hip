@@ -88,6 +88,7 @@ struct Buffers {
   void** wt_ptrs;      // device array [k]
   void* attn_scratch;
   void* topk_scratch;
+  void* transfer_scratch;   // bf16: the sources of a transfer in operand order
   std::vector<void*> kc, vc;   // host copies of the per-layer cache pointers
   // bf16 only: projection weights repacked into MFMA-fragment order
   std::vector<PackedW> p_qkv, p_o, p_gu, p_down;
@@ -142,6 +143,8 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
   b.vc_ptrs = cv.take<void*>(c.n_layers);
   b.wt_ptrs = cv.take<void*>(kMaxTransfer);
   b.topk_scratch = cv.take_bytes(topk_scratch_bytes(kMaxRows));
+  // sources of one launch: tree nodes or training rows, no more than rows of a pass
+  b.transfer_scratch = cv.take_bytes(c.dtype == HT_BF16 ? transfer_scratch_bytes(Mp < kMaxTree ? (int)Mp : kMaxTree, (int)d) : 0);
   b.attn_scratch = cv.take_bytes(attn_mfma_scratch_bytes((int)Mp, c.n_heads, c.head_dim));
   b.kc.resize(c.n_layers);
   b.vc.resize(c.n_layers);
@@ -286,7 +289,7 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
     if (join == kTrainStep) {
       if (l == c.transfer_layer[step]) {
         HT_HIP(launch_transfer(c.dtype, b.x, b.train_rows, F, (const void* const*)b.wt_ptrs, b.x + (size_t)M * d, step, 1,
-                               1, d, s));
+                               1, d, b.transfer_scratch, s));
         HT_HIP(add_norm(b.x + (size_t)M * d, 0, 0, m->attn_norm[l], (char*)b.u + (size_t)M * d * es, nullptr,
                         b.ss + (size_t)M * kNormParts, F));
         M += F;
@@ -300,7 +303,7 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
       if (join == kFromTree) {
         extra = F * cnt;                  // row of (node f, step i) = M + f * cnt + (i - i0)
         HT_HIP(launch_transfer(c.dtype, b.x, b.fused_rows, F, (const void* const*)b.wt_ptrs, b.x + (size_t)M * d, i0, cnt,
-                               cnt, d, s));
+                               cnt, d, b.transfer_scratch, s));
       } else {
         extra = cnt;
         HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));
@@ -1025,7 +1028,7 @@ int ht_transfer(ht_model* m, const void* h_src, float* pseudo_out, void* stream)
   for (int g = 0; g < slots; ++g)       // step i reads the source of its own layer
     HT_HIP(launch_transfer(c.dtype, m->b.h_src + (size_t)g * c.d_model, nullptr, 1, (const void* const*)m->b.wt_ptrs,
                            m->b.pseudo + (size_t)m->slot_first[g] * c.d_model, m->slot_first[g], m->slot_count[g], 0,
-                           c.d_model, s));
+                           c.d_model, nullptr, s));
   if (pseudo_out)
     HT_HIP(hipMemcpyAsync(pseudo_out, m->b.pseudo, sizeof(float) * c.k * c.d_model, hipMemcpyDeviceToDevice, s));
   m->transfer_ready = true;
@@ -1142,7 +1145,7 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
     for (int g = 0; g < slots; ++g)
       HT_HIP(launch_transfer(c.dtype, b.h_src + (size_t)g * c.d_model, nullptr, 1, (const void* const*)b.wt_ptrs,
                              b.pseudo + (size_t)m->slot_first[g] * c.d_model, m->slot_first[g], m->slot_count[g], 0,
-                             c.d_model, s));
+                             c.d_model, nullptr, s));
     if ((rc = run_pass(m, b.chain.dev(), 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
     if ((rc = build_tree(m, s))) return rc;

@@ -161,7 +161,12 @@ double launch_mfma_rate(int form, int iters, uint32_t* sink, hipStream_t s);
 // pseudo[f * row_stride + (i - i0)] = W_i h_f for steps i0 <= i < i0 + steps and F sources
 // h_f = h + (src_rows ? src_rows[f] : f) * d
 hipError_t launch_transfer(int dtype, const float* h, const int32_t* src_rows, int F, const void* const* w_dev,
-                           float* pseudo, int i0, int steps, int row_stride, int d, hipStream_t s);
+                           float* pseudo, int i0, int steps, int row_stride, int d, void* scratch, hipStream_t s);
+// the same for several sources of a bf16 model, on the matrix cores (see ht_transfer_mfma.hip)
+bool transfer_split_supported(int F, int d);
+size_t transfer_scratch_bytes(int F, int d);   // device bytes launch_transfer needs for F sources of a bf16 model
+hipError_t launch_transfer_split(const float* h, const int32_t* src_rows, int F, const void* const* w_dev, float* pseudo, int i0,
+                                 int steps, int row_stride, int d, void* scratch, hipStream_t s);
 hipError_t launch_convert_to_f32(int dtype, const void* src, float* dst, int n, hipStream_t s);
 hipError_t launch_convert_to_bf16(const float* src, void* dst, size_t count, hipStream_t s);
 // out[i] = sum_s part[s][i] in the fixed order s = 0, 1, ..

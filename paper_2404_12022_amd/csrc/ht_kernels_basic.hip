@@ -1030,17 +1030,21 @@ __global__ void transfer_kernel(const float* __restrict__ h, const int32_t* __re
   }
 }
 hipError_t launch_transfer(int dtype, const float* h, const int32_t* src_rows, int F, const void* const* w_dev,
-                           float* pseudo, int i0, int steps, int row_stride, int d, hipStream_t s) {
+                           float* pseudo, int i0, int steps, int row_stride, int d, void* scratch, hipStream_t s) {
   if (d % 4) return hipErrorInvalidValue;      // 16-byte pieces of the fp32 sources
   if (F == 1) {      // one source: its re-reads are cheap and one feature per wavefront spreads the rows wider
     HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((transfer_kernel<T, 1, 1>), dim3((d + 3) / 4, steps), dim3(256), 0, s, h,
                                                 src_rows, F, w_dev, pseudo, i0, row_stride, d);)
+  } else if (dtype != 0 && transfer_split_supported(F, d)) {
+    return launch_transfer_split(h, src_rows, F, w_dev, pseudo, i0, steps, row_stride, d, scratch, s);
+  } else if (dtype != 0) {
+    return hipErrorInvalidValue;               // bf16 rows are multiples of 16 bytes (checked when the model is set up)
   } else if (F < 16) {
-    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((transfer_kernel<T, 4, 4>), dim3((d + 15) / 16, steps), dim3(256), 0, s, h,
-                                                src_rows, F, w_dev, pseudo, i0, row_stride, d);)
+    hipLaunchKernelGGL((transfer_kernel<float, 4, 4>), dim3((d + 15) / 16, steps), dim3(256), 0, s, h, src_rows, F, w_dev,
+                       pseudo, i0, row_stride, d);
   } else {           // every node of a tree drafts: sixteen sources per walk over the weight rows (same sums, same order)
-    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((transfer_kernel<T, 16, 4>), dim3((d + 15) / 16, steps), dim3(256), 0, s, h,
-                                                src_rows, F, w_dev, pseudo, i0, row_stride, d);)
+    hipLaunchKernelGGL((transfer_kernel<float, 16, 4>), dim3((d + 15) / 16, steps), dim3(256), 0, s, h, src_rows, F, w_dev,
+                       pseudo, i0, row_stride, d);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,74 @@
+"""The hidden transfer of several sources on the matrix cores, launched directly, against the fp64 product."""
+import ctypes as C
+import gc
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SYMBOL = "_ZN2ht15launch_transferEiPKfPKiiPKPKvPfiiiiPvP12ihipStream_t"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def no_garbage_left():
+    """What earlier tests left in reference cycles is freed here, not in the middle of a later test that watches the
+    allocator's count."""
+    yield
+    gc.collect()
+
+
+def launch(h, rows, F, maps, out, i0, steps, row_stride, d):
+    import paper_2404_12022_amd.binding as B
+    fn = getattr(B.lib, SYMBOL)
+    fn.restype = C.c_int
+    fn.argtypes = [C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p] + [C.c_int] * 4 + [C.c_void_p] * 2
+    scratch = torch.empty((F + 63) // 64 * 4 * 3 * ((d + 63) // 64 * 2) * 1024, dtype=torch.uint8, device="cuda:0")
+    ptrs = torch.tensor([m.data_ptr() for m in maps], dtype=torch.int64, device="cuda:0")
+    assert fn(B.HT_BF16, h.data_ptr(), rows.data_ptr() if rows is not None else None, F, ptrs.data_ptr(), out.data_ptr(), i0, steps,
+              row_stride, d, scratch.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+
+
+# source counts around the operand forms (5 side by side; tiles of 16; 64 per workgroup), widths below one 64-column step,
+# with a ragged last step, with a ragged last row block, and full size
+@pytest.mark.parametrize("F,d,steps", [(2, 8, 1), (5, 24, 3), (6, 40, 2), (4, 200, 3), (16, 328, 1), (17, 136, 2), (32, 264, 1),
+                                       (33, 520, 3), (64, 1032, 2), (65, 72, 1), (127, 256, 1), (5, 4096, 3), (64, 4096, 2)])
+def test_transfer_of_several_sources_matches_the_fp64_product(F, d, steps):
+    g = torch.Generator(device="cuda:0").manual_seed(F * 10007 + d)
+    dev = "cuda:0"
+    i0, images = 1, F + 3
+    maps = [torch.empty(d, d, device=dev).normal_(0, 0.02, generator=g).to(torch.bfloat16) for _ in range(i0 + steps)]
+    h = torch.empty(images, d, device=dev).normal_(0, 1, generator=g)
+    h[:, ::7] *= 1e-4                                                   # values of unlike sizes side by side
+    rows = torch.randperm(images, generator=torch.Generator().manual_seed(d))[:F].to(torch.int32).to(dev)
+    row_stride = steps + 1                                              # a gap that must stay untouched
+    out = torch.full((F * row_stride, d), 7.0, device=dev)
+    print(f"transfer F={F} d={d} steps={steps}", flush=True)
+    launch(h, rows, F, maps, out, i0, steps, row_stride, d)
+    got = out.view(F, row_stride, d)
+    assert bool((got[:, steps] == 7.0).all())
+    src = h[rows.long()].double()
+    for i in range(steps):
+        w = maps[i0 + i].double()
+        ref = src @ w.T
+        # fp32 sums of at most d / 128 + 16 additions each, every one rounded relative to a partial sum that the sum of
+        # magnitudes bounds (the products themselves are exact)
+        bound = (d / 128 + 16) * 2.0 ** -24 * (src.abs() @ w.abs().T)
+        assert bool(((got[:, i].double() - ref).abs() <= bound).all())
+
+
+def test_infinite_and_nan_sources_stay_in_their_row():
+    d, F, dev = 256, 20, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(5)
+    w = torch.empty(d, d, device=dev).normal_(0, 0.02, generator=g).to(torch.bfloat16)
+    w = torch.where(w == 0, torch.full_like(w, 0.01), w)                # infinity times zero would be NaN in any order
+    h = torch.empty(F, d, device=dev).normal_(0, 1, generator=g)
+    h[3, 17], h[5, 40], h[7, 0] = float("inf"), float("nan"), 3.0e38
+    out = torch.zeros(F, d, device=dev)
+    launch(h, None, F, [w], out, 0, 1, 1, d)
+    ref = h.double() @ w.double().T
+    assert bool((out[3] == torch.sign(w[:, 17].float()) * float("inf")).all()) and bool(out[5].isnan().all())
+    ok = [i for i in range(F) if i not in (3, 5)]
+    bound = (d / 128 + 16) * 2.0 ** -24 * (h[ok].double().abs() @ w.double().abs().T)
+    assert bool(((out[ok].double() - ref[ok]).abs() <= bound).all())
