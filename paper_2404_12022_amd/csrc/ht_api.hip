@@ -253,6 +253,63 @@ int attention(ht_model* m, int layer, int n, int M, const TreeDev& tree, hipStre
 // pass reaches that step's layer (training stage, Sec. 3.3).
 enum JoinMode { kNoJoin = 0, kFromTree = 1, kFromBuffer = 2, kTrainStep = 3 };
 
+// The blocks of a pass on an fp32 model: five launches each (norms, rotary, append, SiLU and residual adds ride in the
+// products), no partial sums.  Same rows, joins and end as run_pass, which calls it.
+int run_blocks_f32(ht_model* m, const TreeDev& tree, int M, int layer_from, int layer_stop, bool save_hidden, JoinMode join, int F,
+                   int step, hipStream_t s, int* rows_out) {
+  const ht_config& c = m->cfg;
+  Buffers& b = m->b;
+  const int d = c.d_model, qd = c.n_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, f = c.d_ffn;
+  const size_t slot_stride = (size_t)m->Mp * d;
+  int rc;
+  for (int l = layer_from; l < layer_stop; ++l) {
+    const int slot = m->slot_of_layer[l];
+    if (join == kTrainStep) {
+      if (l == c.transfer_layer[step]) {
+        HT_HIP(launch_transfer(c.dtype, b.x, b.train_rows, F, (const void* const*)b.wt_ptrs, b.x + (size_t)M * d, step, 1, 1, d,
+                               b.transfer_scratch, s));
+        M += F;
+      }
+    } else if (join != kNoJoin && slot >= 0) {
+      const int i0 = m->slot_first[slot], cnt = m->slot_count[slot];
+      if (join == kFromTree) {
+        HT_HIP(launch_transfer(c.dtype, b.x, b.fused_rows, F, (const void* const*)b.wt_ptrs, b.x + (size_t)M * d, i0, cnt, cnt, d,
+                               b.transfer_scratch, s));
+        M += F * cnt;
+      } else {
+        HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));
+        M += cnt;
+      }
+    }
+    if (M == 0) continue;
+    RowsEpilogue qkv, add, act;
+    qkv.cs = b.cs;
+    qkv.q = (float*)b.q;
+    qkv.kc = (float*)b.kc[l];
+    qkv.vc = (float*)b.vc[l];
+    qkv.n = m->n;
+    qkv.Hq = c.n_heads;
+    qkv.Hkv = c.n_kv_heads;
+    qkv.hd = c.head_dim;
+    qkv.cap = c.max_cache;
+    qkv.n_dev = m->n_dev;
+    HT_HIP(launch_rows_f32(ROWS_QKV, b.x, m->attn_norm[l], c.rms_eps, WeightSegs{{m->wq[l], m->wk[l], m->wv[l]}, {qd, kvd, kvd}, 3},
+                           M, (qd + 2 * kvd) / 2, d, qkv, s));
+    if ((rc = attention(m, l, m->n, M, tree, s))) return rc;
+    add.out = b.x;
+    HT_HIP(launch_rows_f32(ROWS_ADD, (const float*)b.attn, nullptr, 0.f, segs1(m->wo[l], d), M, d, qd, add, s));
+    act.out = (float*)b.act;
+    HT_HIP(launch_rows_f32(ROWS_SILU, b.x, m->ffn_norm[l], c.rms_eps, WeightSegs{{m->w_gate[l], m->w_up[l], nullptr}, {f, f, 0}, 2},
+                           M, f, d, act, s));
+    // the residual after block l + 1 is what the acceptance may pick a transfer source from
+    const int done = l + 1 < c.n_layers ? m->slot_of_layer[l + 1] : -1;
+    add.save = save_hidden && done >= 0 ? b.saved_h + done * slot_stride : nullptr;
+    HT_HIP(launch_rows_f32(ROWS_ADD, (const float*)b.act, nullptr, 0.f, segs1(m->w_down[l], d), M, d, f, add, s));
+  }
+  *rows_out = M;
+  return HT_OK;
+}
+
 // Rows already in b.x (M of them, possibly none) go through blocks layer_from+1 .. L (0-based index
 // layer_from .. L-1) together with the rows that join on the way, then the final norm and, if `logits` is given,
 // the LM head and the row arg-max.  `tree` must describe all rows the pass ends with.
@@ -277,9 +334,18 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
   const RowScale rs = parts ? RowScale{b.ss, 1.0f / (float)d, c.rms_eps} : RowScale{};
   auto add_norm = [&](float* x, int nsplit, size_t stride, const void* gain, void* u, float* save, float* ss, int rows) {
     return parts ? launch_add_norm_parts(x, b.part, nsplit, stride, gain, u, save, ss, rows, d, s)
-                 : launch_add_norm(c.dtype, x, b.part, nsplit, stride, gain, u, save, rows, d, c.rms_eps, s);
+                 : launch_add_norm(x, b.part, nsplit, stride, gain, u, save, rows, d, c.rms_eps, s);
   };
   const int layer_stop = layer_end >= 0 ? layer_end : c.n_layers;
+  if (c.dtype == HT_F32) {
+    if ((rc = run_blocks_f32(m, tree, M, layer_from, layer_stop, save_hidden, join, F, step, s, &M))) return rc;
+    if (layer_end >= 0 || !logits) return HT_OK;
+    RowsEpilogue head;
+    head.out = logits;
+    HT_HIP(launch_rows_f32(ROWS_STORE_NORM, b.x, m->final_norm, c.rms_eps, segs1(m->lm_head, c.vocab), M, c.vocab, d, head, s));
+    if (gout) HT_HIP(launch_argmax(logits, gout, M, c.vocab, s));
+    return HT_OK;
+  }
   for (int l = layer_from; l < layer_stop; ++l) {
     const int slot = m->slot_of_layer[l];
     if (M > 0) {
@@ -347,7 +413,7 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
     } else {
       WeightSegs gu{{m->w_gate[l], m->w_up[l], nullptr}, {f, f, 0}, 2};
       if ((rc = product(m, b.u, gu, M, 2 * f, d, b.gu, s))) return rc;
-      HT_HIP(launch_silu_mul(c.dtype, b.gu, b.act, M, f, s));
+      HT_HIP(launch_silu_mul(b.gu, b.act, M, f, s));
       pending = 1;
       if ((rc = product(m, b.act, segs1(m->w_down[l], d), M, d, f, b.part, s))) return rc;
     }

@@ -102,8 +102,8 @@ struct WeightSegs {
 // ------------------------------------------------------------------------------------------------
 hipError_t launch_embed(int dtype, const void* emb, const int32_t* tok, float* x, int M, int d, hipStream_t s);
 hipError_t launch_load_rows(const float* src, float* x, int M, int d, hipStream_t s);
-// x[m] += sum_s part[s][m]; optional save; u[m] = rmsnorm(x[m]) * gain
-hipError_t launch_add_norm(int dtype, float* x, const float* part, int nsplit, size_t part_stride, const void* gain,
+// bf16 models that do not pack: x[m] += part[m] (nsplit 0 or 1); optional save; u[m] = rmsnorm(x[m]) * gain
+hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_stride, const void* gain,
                            void* u, float* save_h, int M, int d, float eps, hipStream_t s);
 // The same with kNormParts workgroups per row (d a multiple of 4 kNormParts): each adds and stores its part of the
 // row, leaves the sum of squares of that part in ss[m][part] and writes u[m] = x[m] * gain WITHOUT the 1/rms factor;
@@ -126,7 +126,7 @@ hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const flo
 hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const float* cs,
                                     void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd, int cap,
                                     hipStream_t s);
-hipError_t launch_silu_mul(int dtype, const float* gu, void* act, int M, int f, hipStream_t s);
+hipError_t launch_silu_mul(const float* gu, void* act, int M, int f, hipStream_t s);
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s);
 // cand[i] = top width[i % period + 1] entries of logit row src_row[i] (row i when src_row is NULL), i < rows;
 // scratch: topk_scratch_bytes(rows) bytes for the per-slice survivors
@@ -174,6 +174,21 @@ hipError_t launch_reduce_splits(const float* part, int nsplit, size_t stride, fl
 
 // generic (any dtype, any shape) product: out[s=0][m][n] = sum_k a[m][k] w[n][k]
 hipError_t launch_gemm_simple(int dtype, const void* a, WeightSegs w, int M, int N, int K, float* out, hipStream_t s);
+// fp32 model: the products of a decoder block with what surrounds them (ht_rows.hip).  STORE: out[m][u]; STORE_NORM: the
+// same on RMS-normalised rows of `a`; ADD: out[m][u] += , kept in `save` too when set; SILU: out[m][u] = silu(gate) * up
+// on normalised rows, w = (gate, up); QKV: normalised rows, w = (q, k, v), one unit per (head, j < hd / 2), rotary, q
+// stored, k and v appended at slot n + m.
+enum RowsEpi { ROWS_STORE, ROWS_STORE_NORM, ROWS_ADD, ROWS_SILU, ROWS_QKV };
+struct RowsEpilogue {
+  float* out = nullptr;
+  float* save = nullptr;
+  const float* cs = nullptr;                 // (cos, sin) table [M][hd / 2]
+  float *q = nullptr, *kc = nullptr, *vc = nullptr;
+  int32_t n = 0, Hq = 0, Hkv = 0, hd = 0, cap = 0;
+  const int32_t* n_dev = nullptr;            // overrides n when set (device-resident loop)
+};
+hipError_t launch_rows_f32(RowsEpi epi, const float* a, const void* gain, float eps, WeightSegs w, int M, int units, int K,
+                           const RowsEpilogue& ep, hipStream_t s);
 // bf16 MFMA product over weights repacked into MFMA-fragment order (see ht_gemm_mfma.hip)
 struct PackedW {
   const bf16_t* p;   // fragment-ordered copy

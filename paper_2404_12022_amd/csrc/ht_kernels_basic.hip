@@ -135,9 +135,9 @@ __device__ inline float block_sum_any(float v, float* red) {
   return t;
 }
 
-template <typename T, int NS>
+template <int NS>
 __global__ void add_norm_kernel(float* __restrict__ x, const float* __restrict__ part, size_t part_stride,
-                                const T* __restrict__ gain, T* __restrict__ u, float* __restrict__ save_h, int d,
+                                const bf16_t* __restrict__ gain, bf16_t* __restrict__ u, float* __restrict__ save_h, int d,
                                 float eps) {
   __shared__ float red[16];
   const int m = blockIdx.x;
@@ -170,11 +170,11 @@ __global__ void add_norm_kernel(float* __restrict__ x, const float* __restrict__
       const int c = (p * blockDim.x + threadIdx.x) * 4;
       if (c < d) {
         const float4 v = keep[p];
-        T* dst = u + (size_t)m * d + c;
-        Conv<T>::store(dst + 0, v.x * scale * Conv<T>::load(gain + c + 0));
-        Conv<T>::store(dst + 1, v.y * scale * Conv<T>::load(gain + c + 1));
-        Conv<T>::store(dst + 2, v.z * scale * Conv<T>::load(gain + c + 2));
-        Conv<T>::store(dst + 3, v.w * scale * Conv<T>::load(gain + c + 3));
+        bf16_t* dst = u + (size_t)m * d + c;
+        Conv<bf16_t>::store(dst + 0, v.x * scale * Conv<bf16_t>::load(gain + c + 0));
+        Conv<bf16_t>::store(dst + 1, v.y * scale * Conv<bf16_t>::load(gain + c + 1));
+        Conv<bf16_t>::store(dst + 2, v.z * scale * Conv<bf16_t>::load(gain + c + 2));
+        Conv<bf16_t>::store(dst + 3, v.w * scale * Conv<bf16_t>::load(gain + c + 3));
       }
     }
   }
@@ -235,21 +235,18 @@ hipError_t launch_add_norm_parts(float* x, const float* part, int nsplit, size_t
   return hipGetLastError();
 }
 
-hipError_t launch_add_norm(int dtype, float* x, const float* part, int nsplit, size_t part_stride, const void* gain,
+hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_stride, const void* gain,
                            void* u, float* save_h, int M, int d, float eps, hipStream_t s) {
-  if (d % 4 || nsplit < 0 || nsplit > kMaxSplitK) return hipErrorInvalidValue;
+  if (d % 4 || nsplit < 0 || nsplit > 1) return hipErrorInvalidValue;      // products that do not pack do not split K
   int nt = 64;
   while (nt < 1024 && nt * 4 < d) nt *= 2;
   if (d > 16 * nt) return hipErrorInvalidValue;
 #define HT_ADD_NORM(NS)                                                                                         \
   case NS:                                                                                                      \
-    hipLaunchKernelGGL((add_norm_kernel<T, NS>), dim3(M), dim3(nt), 0, s, x, part, part_stride, (const T*)gain, \
-                       (T*)u, save_h, d, eps);                                                                  \
+    hipLaunchKernelGGL((add_norm_kernel<NS>), dim3(M), dim3(nt), 0, s, x, part, part_stride, (const bf16_t*)gain, \
+                       (bf16_t*)u, save_h, d, eps);                                                               \
     break;
-  HT_DISPATCH_DTYPE(dtype, switch (nsplit) {
-    HT_ADD_NORM(0) HT_ADD_NORM(1) HT_ADD_NORM(2) HT_ADD_NORM(3) HT_ADD_NORM(4) HT_ADD_NORM(5) HT_ADD_NORM(6)
-    HT_ADD_NORM(7) HT_ADD_NORM(8)
-  })
+  switch (nsplit) { HT_ADD_NORM(0) HT_ADD_NORM(1) }
 #undef HT_ADD_NORM
   return hipGetLastError();
 }
@@ -448,17 +445,15 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
 }
 
 // ------------------------------------------------------------------------------------------------ SwiGLU gate
-template <typename T>
-__global__ void silu_mul_kernel(const float* __restrict__ gu, T* __restrict__ act, int f) {
+__global__ void silu_mul_kernel(const float* __restrict__ gu, bf16_t* __restrict__ act, int f) {
   const int m = blockIdx.y;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= f) return;
   const float g = gu[(size_t)m * 2 * f + j], up = gu[(size_t)m * 2 * f + f + j];
-  Conv<T>::store(act + (size_t)m * f + j, g / (1.0f + expf(-g)) * up);
+  Conv<bf16_t>::store(act + (size_t)m * f + j, g / (1.0f + expf(-g)) * up);
 }
-hipError_t launch_silu_mul(int dtype, const float* gu, void* act, int M, int f, hipStream_t s) {
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(silu_mul_kernel<T>, dim3((f + 255) / 256, M), dim3(256), 0, s, gu,
-                                              (T*)act, f);)
+hipError_t launch_silu_mul(const float* gu, void* act, int M, int f, hipStream_t s) {
+  hipLaunchKernelGGL(silu_mul_kernel, dim3((f + 255) / 256, M), dim3(256), 0, s, gu, (bf16_t*)act, f);
   return hipGetLastError();
 }
 
@@ -1146,45 +1141,25 @@ double launch_mfma_rate(int form, int iters, uint32_t* sink, hipStream_t s) {
   return (double)kGroups * 4 * iters * ((form & 1) == 0 ? 32 * 2.0 * 16 * 16 * 32 : 8 * 2.0 * 32 * 32 * 16);
 }
 
-// ------------------------------------------------------------------------------------------------ generic product
-// out[m][n] = sum_k a[m][k] w[n][k], fp32 accumulation.  One wavefront per output feature n, rows in
-// groups of 4.  Used by the fp32 model path and as the fallback for shapes the MFMA kernel rejects.
-template <typename T>
-__global__ void gemm_simple_kernel(const T* __restrict__ a, WeightSegs w, int M, int N, int K, float* __restrict__ out) {
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (n >= N) return;
-  int seg = 0, local = n;
-  while (seg + 1 < w.nseg && local >= w.rows[seg]) { local -= w.rows[seg]; ++seg; }
-  const T* row = (const T*)w.w[seg] + (size_t)local * K;
-  for (int m0 = 0; m0 < M; m0 += 4) {
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = lane; c < K; c += 64) {
-      const float wv = Conv<T>::load(row + c);
+// ------------------------------------------------------------------------------------------------ generic attention
+// One block per (query head, tree row).  Scores of all visible keys go to LDS (four lanes per key), softmax in fp32, then
+// every thread owns one output element and every (256 / hd)-th piece of VEC keys of it.  Dynamic LDS: (n + M) floats + hd
+// + 256.  Latency bound at the sizes it is used at (fp32 model, tens of keys): VEC elements per load cut the chains of
+// dependent loads, 5.5 -> 3.9 us for 8 rows of 4 heads over 40 keys of 64 floats.
+template <typename T, int VEC> __device__ inline void load_vec(const T* p, float (&v)[VEC]) {
+  if constexpr (VEC == 1) {
+    v[0] = Conv<T>::load(p);
+  } else {
+    const uint4 raw = *(const uint4*)p;               // VEC * sizeof(T) = 16
+    const T* e = (const T*)&raw;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (m0 + r < M) acc[r] += wv * Conv<T>::load(a + (size_t)(m0 + r) * K + c);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = wave_sum(acc[r]);
-      if (lane == 0 && m0 + r < M) out[(size_t)(m0 + r) * N + n] = v;
-    }
+    for (int i = 0; i < VEC; ++i) v[i] = Conv<T>::load(e + i);
   }
 }
-hipError_t launch_gemm_simple(int dtype, const void* a, WeightSegs w, int M, int N, int K, float* out, hipStream_t s) {
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(gemm_simple_kernel<T>, dim3((N + 3) / 4), dim3(256), 0, s, (const T*)a,
-                                              w, M, N, K, out);)
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------ generic attention
-// One block per (query head, tree row).  Scores of all visible keys go to LDS, softmax in fp32, then
-// every thread owns one (output element, key residue class).  Dynamic LDS: (n + M) floats + hd + 256.
-template <typename T>
-__global__ void attn_simple_kernel(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc, int cap,
-                                   int n, int M, TreeDev tree, int Hq, int Hkv, int hd, T* __restrict__ out,
-                                   const int32_t* __restrict__ n_dev) {
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc,
+                                                          int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd,
+                                                          T* __restrict__ out, const int32_t* __restrict__ n_dev) {
   extern __shared__ float smem[];
   __shared__ float red[4];
   n = cache_len(n, n_dev);             // at most the host's n, which sized the dynamic LDS
@@ -1197,20 +1172,28 @@ __global__ void attn_simple_kernel(const T* __restrict__ q, const T* __restrict_
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)hd);
   float mx = -INFINITY;
-  for (int j = tid; j < S; j += 256) {
+  const int quarter = tid & 3;
+  for (int j = tid >> 2; j < (S + 63) / 64 * 64; j += 64) {       // whole wavefronts stay in the loop for the lane exchange
     bool vis = j < n;
-    if (!vis) {
+    if (!vis && j < S) {
       const int u = j - n;
       vis = (tree.anc[(size_t)m * kMaskWords + (u >> 6)] >> (u & 63)) & 1ull;
     }
-    float s = -INFINITY;
+    float dot = 0.f;
     if (vis) {
       const T* kr = kc + ((size_t)j * Hkv + hk) * hd;
-      float dot = 0.f;
-      for (int e = 0; e < hd; ++e) dot += qs[e] * Conv<T>::load(kr + e);
-      s = dot * scale;
+#pragma unroll 4
+      for (int e = quarter * VEC; e < hd; e += 4 * VEC) {
+        float kv[VEC];
+        load_vec<T, VEC>(kr + e, kv);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) dot += qs[e + i] * kv[i];
+      }
     }
-    sc[j] = s;
+    dot += __shfl_xor(dot, 1, 64);
+    dot += __shfl_xor(dot, 2, 64);
+    const float s = vis ? dot * scale : -INFINITY;
+    if (quarter == 0 && j < S) sc[j] = s;
     mx = fmaxf(mx, s);
   }
   mx = block_max_256(mx, red);
@@ -1225,9 +1208,17 @@ __global__ void attn_simple_kernel(const T* __restrict__ q, const T* __restrict_
   const int e = tid % hd, part = tid / hd;
   float o = 0.f;
   if (part < groups) {
-    const T* vr = vc + ((size_t)hk * hd + e) * cap;
-    for (int j = part; j < S; j += groups)
-      if (sc[j] != 0.f) o += sc[j] * Conv<T>::load(vr + j);
+    const T* vr = vc + ((size_t)hk * hd + e) * cap;    // cap is a multiple of 8: whole pieces lie in the row
+#pragma unroll 2
+    for (int j = part * VEC; j < S; j += groups * VEC) {
+      float vv[VEC];
+      load_vec<T, VEC>(vr + j, vv);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        const float p = j + i < S ? sc[j + i] : 0.f;
+        o += p != 0.f ? p * vv[i] : 0.f;               // what no row has written yet may hold anything
+      }
+    }
   }
   acc[tid] = o;
   __syncthreads();
@@ -1241,8 +1232,13 @@ hipError_t launch_attn_simple(int dtype, const void* q, const void* kc, const vo
                               TreeDev tree, int Hq, int Hkv, int hd, void* out, hipStream_t s, const int32_t* n_dev) {
   const size_t smem = (size_t)(n + M + hd + 256) * sizeof(float);
   if (smem > 64 * 1024 || hd > 256) return hipErrorInvalidValue;
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(attn_simple_kernel<T>, dim3(Hq, M), dim3(256), smem, s, (const T*)q,
-                                              (const T*)kc, (const T*)vc, cap, n, M, tree, Hq, Hkv, hd, (T*)out, n_dev);)
+  // 16-byte pieces of key rows and of value columns
+  const bool vec = hd % (dtype == 0 ? 4 : 8) == 0 && cap % 8 == 0 && !((uintptr_t)kc & 15) && !((uintptr_t)vc & 15);
+#define HT_ATTN_SIMPLE(VEC)                                                                                            \
+  hipLaunchKernelGGL((attn_simple_kernel<T, VEC>), dim3(Hq, M), dim3(256), smem, s, (const T*)q, (const T*)kc, (const T*)vc, \
+                     cap, n, M, tree, Hq, Hkv, hd, (T*)out, n_dev)
+  HT_DISPATCH_DTYPE(dtype, if (vec) HT_ATTN_SIMPLE(16 / sizeof(T)); else HT_ATTN_SIMPLE(1);)
+#undef HT_ATTN_SIMPLE
   return hipGetLastError();
 }
 
