@@ -610,6 +610,7 @@ int ht_init_model(const ht_config* cfg, const ht_weights* w, void* workspace, si
   if (e != hipSuccess) return cleanup(fail(HT_EHIP, "init allocation/clear failed: %s", hipGetErrorString(e)));
 
   if (e == hipSuccess && cfg->dtype == HT_BF16) e = attn_mfma_prepare(cfg->head_dim);
+  if (e == hipSuccess && cfg->dtype == HT_BF16) e = gemm_tile_prepare();
   if (e != hipSuccess) return cleanup(fail(HT_EHIP, "kernel set-up failed: %s", hipGetErrorString(e)));
   m->packed = m->use_mfma && shapes_packable(*cfg);
   m->qkv_fused = m->packed && qkv_fusable(cfg->head_dim);
@@ -1026,11 +1027,11 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
         pending = 0;
       }
       HT_HIP(launch_convert_to_bf16(w.x, w.u, (size_t)P * d, s));
-      HT_HIP(launch_gemm_wide(w.u, p_transfer, P, w.x + (size_t)n * d, s));
+      HT_HIP(launch_gemm_wide(w.u, p_transfer, P, w.x + (size_t)n * d, 1, s));
       rows = n + P;
     }
     HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->attn_norm[l], w.u, nullptr, w.ss, rows, d, s));
-    HT_HIP(launch_gemm_wide(w.u, b.p_qkv[l], rows, w.qkv, s, rs));
+    HT_HIP(launch_gemm_wide(w.u, b.p_qkv[l], rows, w.qkv, 1, s, rs));
     // hidden rows: rotary at their own position, K/V to their own cache slot
     HT_HIP(launch_rope_append(c.dtype, w.qkv, 1, w.cs, w.q, b.kc[l], b.vc[l], 0, n, c.n_heads, c.n_kv_heads, c.head_dim,
                               c.max_cache, true, s));
@@ -1049,14 +1050,14 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
                                 w.self_cap, w.attn_scratch));
     }
     HT_HIP(launch_attn_causal(w.q, b.kc[l], b.vc[l], c.max_cache, n, chain, c.n_heads, c.n_kv_heads, c.head_dim, w.attn, s));
-    HT_HIP(launch_gemm_wide(w.attn, b.p_o[l], rows, w.part, s));
+    HT_HIP(launch_gemm_wide(w.attn, b.p_o[l], rows, w.part, 1, s));
     HT_HIP(launch_add_norm_parts(w.x, w.part, 1, (size_t)rows * d, m->ffn_norm[l], w.u, nullptr, w.ss, rows, d, s));
     HT_HIP(launch_gemm_wide_silu(w.u, b.p_gu[l], rows, w.act, s, rs));
-    HT_HIP(launch_gemm_wide(w.act, b.p_down[l], rows, w.part, s));
+    HT_HIP(launch_gemm_wide(w.act, b.p_down[l], rows, w.part, 1, s));
     pending = 1;
   }
   HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->final_norm, w.u, nullptr, w.ss, rows, d, s));
-  HT_HIP(launch_gemm_wide(w.u, b.p_head, rows, w.logits, s, rs));
+  HT_HIP(launch_gemm_wide(w.u, b.p_head, rows, w.logits, 1, s, rs));
   // term j pairs pseudo row j (logits row n + j) with the hidden state it stands for (logits row j + step)
   for (int j0 = 0; j0 < terms; j0 += 32768) {
     const int cnt = terms - j0 < 32768 ? terms - j0 : 32768;

@@ -216,10 +216,13 @@ struct QkvEpilogue {
   int32_t n, Hq, Hkv, hd, cap;
   const int32_t* n_dev = nullptr;            // overrides n when set (device-resident loop)
 };
-// The same products tiled over the tokens too, for passes of any number of rows (the batched forward pass of the
-// training stage): one launch, no K split.  out: fp32 [M][N]; act: bf16 [M][N/2] (w packed from (gate, up)).
-hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, hipStream_t s, RowScale rs = RowScale{});
+// The same products tiled over the tokens too, for passes of any number of rows: out fp32 [nsplit][M][N] (nsplit 1 or
+// gemm_wide_splits); act bf16 [M][N/2] (w packed from (gate, up)); q | k | v as in launch_gemm_packed_qkv.
+int gemm_wide_splits(int M, int N, int K);
+hipError_t gemm_tile_prepare();              // once per device before the first launch that may sit inside a stream capture
+hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs = RowScale{});
 hipError_t launch_gemm_wide_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs = RowScale{});
+hipError_t launch_gemm_wide_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s, RowScale rs = RowScale{});
 bool qkv_fusable(int head_dim);
 bool qkv_prefer_split(int M, int N);
 hipError_t launch_gemm_packed_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s,

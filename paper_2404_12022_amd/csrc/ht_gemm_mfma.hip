@@ -23,6 +23,8 @@
 // wavefront stays in flight.  Split-K over blockIdx.y writes fp32 partial sums that the consumer adds
 // in a fixed order (deterministic).
 #include "ht_common.h"
+#include <atomic>
+#include <type_traits>
 
 namespace ht {
 
@@ -84,8 +86,9 @@ __global__ void repack_kernel(WeightSegs w, int K, int KS, int n_rb, int mode, i
 
 // --------------------------------------------------------------------------------------------- epilogues
 // What a wavefront does with its finished sums acc[r][mt] (row block rb0 + r, token tile mt): the 1/rms factor of
-// the token rows, then fp32 partial sums, SiLU(gate) * up, or rotary + q store / K,V append.
-template <int MT, int R, int EPI>
+// the token rows, then fp32 partial sums, SiLU(gate) * up, or rotary + q store / K,V append.  PAST_L2: fp32 results in
+// amounts that no L2 holds are stored around it.
+template <int MT, int R, int EPI, bool PAST_L2 = false>
 __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float4 (&row_ss)[MT], int rb0, int wg1, int M,
                                             int N, void* __restrict__ outp, const QkvEpilogue& qe, const RowScale& rs,
                                             int row0, int split) {
@@ -109,8 +112,10 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int m = mt * 16 + r16;
-        if (m < M)
-          *(float4*)(dst + (size_t)m * N + n0) = make_float4(acc[r][mt][0], acc[r][mt][1], acc[r][mt][2], acc[r][mt][3]);
+        if (m < M) {
+          if (PAST_L2) __builtin_nontemporal_store(acc[r][mt], (floatx4_t*)(dst + (size_t)m * N + n0));
+          else *(floatx4_t*)(dst + (size_t)m * N + n0) = acc[r][mt];
+        }
       }
     }
   } else if (EPI == EPI_SILU) {
@@ -201,7 +206,7 @@ template <int MT, int R, int WAVES, int EPI, int KC = kChunkCols, int PD = kRing
 __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* __restrict__ a,
                                                                  const bf16_t* __restrict__ wp, int M, int N, int K,
                                                                  int KS, void* __restrict__ outp, int nsplit,
-                                                                 QkvEpilogue qe, RowScale rs, int row0) {
+                                                                 QkvEpilogue qe, RowScale rs) {
   constexpr int STEPS = KC / 32;                         // MFMA steps per chunk
   // LDS row stride in bytes.  Measured with the bank-conflict counter, a 128-bit operand read of the sixteen rows of
   // a fragment takes 4 cycles with rows padded by 32 bytes, 8 with 16 bytes of padding and 16 with none.
@@ -261,7 +266,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
   for (int i = 0; i < APASS; ++i) {
     int p = tid + i * THREADS;
     p = p < PIECES ? p : PIECES - 1;
-    arow[i] = a + (size_t)(row0 + p / (KC / 8)) * K;
+    arow[i] = a + (size_t)(p / (KC / 8)) * K;
     acol[i] = (p % (KC / 8)) * 8;
     alds[i] = (p / (KC / 8)) * ROWB + (p % (KC / 8)) * 16;
   }
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
   if (rs.ss) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const int m = row0 + mt * 16 + r16;
+      const int m = mt * 16 + r16;
       row_ss[mt] = *(const float4*)(rs.ss + (size_t)(m < M ? m : M - 1) * kNormParts);
     }
   }
@@ -349,140 +354,158 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
   for (int p = 0; p < PD - 1; ++p)
     if (c + p < c1) body(wreg[p], areg[p], c + p);                // uniform tail
 
-  finish_rows<MT, R, EPI>(acc, row_ss, rb0, wg1, M, N, outp, qe, rs, row0, blockIdx.y);
+  finish_rows<MT, R, EPI>(acc, row_ss, rb0, wg1, M, N, outp, qe, rs, 0, blockIdx.y);
 }
 
 // --------------------------------------------------------------------------------------------- product, many rows
-// The same product tiled over the tokens as well, for passes of hundreds or thousands of rows (the forward pass of
-// the training stage): a workgroup owns 4 R row blocks of the weights (four wavefronts, R each) and MT * 16 token
-// rows, walks the whole K range, and the grid covers (row-block tiles) x (token tiles).  At R = 4, MT = 16 a
-// workgroup does 256 x 256 outputs per 64 KB it takes in (32 KB of weights, 32 KB of tokens per 64 columns), so the
-// matrix cores, not the memory path, set the pace.  Weights come straight into operand registers as before (ring of
-// two chunks), the token chunk through registers into padded LDS (two stages, the chunk after next in flight), and
-// the token operands are read from LDS four tiles at a time, one group ahead of the matrix cores.
-// Workgroups are numbered so that those of one XCD (every eighth) share weight tiles: XCD x takes the row-block
-// tiles x, x + 8, .. and runs all token tiles of one before the next, so a weight tile is fetched from HBM by one L2.
-template <int MT, int R, int EPI, int AD = 2, int OCC = 1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void gemm_wide_kernel(const bf16_t* __restrict__ a, const bf16_t* __restrict__ wp, int M, int N,
-                                                        int K, int KS, void* __restrict__ outp, QkvEpilogue qe, RowScale rs,
-                                                        int n_tiles, int m_tiles) {
-  constexpr int KC = 64, STEPS = 2, PD = 2;
-  constexpr int ROWB = KC * 2 + kRowPad, ROWS = MT * 16, STAGE = ROWS * ROWB;
-  constexpr int APASS = ROWS * (KC / 8) / 256;
-  static_assert(ROWS * (KC / 8) % 256 == 0 && MT % 4 == 0, "whole passes of pieces; token tiles in groups of four");
-  extern __shared__ __attribute__((aligned(16))) unsigned char wide_lds[];
+// The same product tiled over the tokens as well, for passes of more rows than the weight stream can hide (prompts, the
+// forward pass of the training stage, passes of more than 128 rows): a workgroup of WF x WT wavefronts owns 64 WF weight
+// rows and 16 MT WT token rows and walks its share of K in chunks of 64 columns.
+//
+// Bound: the matrix cores, if the operands reach them.  A compute unit takes in at most about 64 bytes a cycle and its
+// LDS gives about 128, so both operands go through LDS (a chunk of weights and of tokens is fetched once per workgroup),
+// straight from global memory with 16-byte LDS-direct loads, two stages.  A wavefront multiplies 64 weight rows by 16 MT
+// tokens: at MT = 8 it reads 12 KB from LDS for 32 matrix instructions, just under what LDS gives in their time.  So the
+// order of issue is what matters, and it is written out (sched_barrier fences): operands of the next 32 columns are
+// read, a fragment or two at a time, between groups of four matrix instructions on the current ones, and the second half
+// of a chunk also issues the loads of the chunk after next one by one (64 of them in a burst behind the barrier block
+// the memory path for a thousand cycles, in which nothing multiplies: 1.25 -> 1.32 PFLOP/s at 4096^3).  One barrier per
+// chunk, in its middle: there the next chunk has landed (its first operands are read before this chunk's last products)
+// and every wavefront has read the last of this one, whose stage the loads then refill.
+// Measured on random operands, 4096 tokens, against 128 x 256 tiles with weights loaded into registers (the kernel this
+// replaces): 12288 x 4096 421 -> 312 us (1.32 PFLOP/s), 4096 x 4096 123 -> 107 us (1.28), 4096 x 11008 308 -> 259 us
+// (1.43).  Tried: weights straight into registers (1.03 - 1.24 PFLOP/s), four wavefronts of 128 x 128 (0.6 - 1.27).
+//
+// Workgroups are numbered so that those of one XCD (every eighth) work on blocks of 4 weight tiles x 8 token tiles at a
+// time, and results that no L2 can hold leave it alone (nontemporal stores): 361 -> 312 us at 12288 x 4096.
+//
+// LDS layout of a stage: the weight fragments of the chunk, 1 KB each in operand order (tile, step, row block), then the
+// token rows of 128 bytes whose 16-byte pieces are XOR-swizzled by row (an LDS-direct load writes 64 consecutive pieces,
+// so every lane picks the global piece that belongs at its place).
+__device__ __forceinline__ void lds_load16(const void* from, void* to) {
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)from, (void __attribute__((address_space(3)))*)to, 16,
+                                   0, 0);
+}
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
-  // workgroup id -> (row-block tile, token tile), see above
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int tx = xcd + 8 * (slot / m_tiles), ty = slot % m_tiles;
+template <int WF, int WT, int MT> struct TileShape {
+  static constexpr int R = 4, WAVES = WF * WT, FEATURES = WF * R * 16, TOKENS = WT * MT * 16;
+  static constexpr int WBYTES = FEATURES * 128, STAGE = WBYTES + TOKENS * 128, LDS_BYTES = 2 * STAGE;
+  static constexpr int NW = 2 * R / WT, NA = 2 * MT / WF;            // LDS-direct loads per wavefront and chunk: weights, tokens
+  static_assert((WF * R) % kTileBlocks == 0 && 2 * R % WT == 0 && 2 * MT % WF == 0, "whole loads and reads");
+};
+
+template <int WF, int WT, int MT, int EPI>
+__global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(
+    const bf16_t* __restrict__ a, const bf16_t* __restrict__ wp, int M, int N, int K, int KS, void* __restrict__ outp,
+    QkvEpilogue qe, RowScale rs, int n_tiles, int m_tiles, int nsplit) {
+  using TS = TileShape<WF, WT, MT>;
+  constexpr int R = TS::R, NW = TS::NW, NA = TS::NA, STAGE = TS::STAGE, WBYTES = TS::WBYTES;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char tile_lds[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int wf = wave % WF, wt = wave / WF;
+  // workgroup id -> (weight tile, token tile): XCD x takes the weight tiles x, x + 8, .., four of them times eight token
+  // tiles after the other
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per_xcd = (n_tiles + 7) / 8;
+  const int q = slot / (4 * m_tiles), rem = slot % (4 * m_tiles), nw = per_xcd - q * 4 < 4 ? per_xcd - q * 4 : 4;
+  const int mg = rem / (8 * nw), in = rem % (8 * nw), mw = m_tiles - mg * 8 < 8 ? m_tiles - mg * 8 : 8;
+  const int tx = xcd + 8 * (q * 4 + in / mw), ty = mg * 8 + in % mw;
   if (tx >= n_tiles) return;                             // uniform over the workgroup
-  const int row0 = ty * ROWS;
-  const int n_rb = N / 16;
-  const int wg0 = tx * 4 * R, wg1 = wg0 + 4 * R < n_rb ? wg0 + 4 * R : n_rb;
-  const int rb0 = wg0 + wave * R;
-  const int chunks = KS / STEPS, last = chunks - 1;
+  int c0, c1;
+  even_share(KS / 2, nsplit, blockIdx.y, c0, c1);
+  const int chunks = c1 - c0;
+  if (chunks <= 0) return;                               // uniform over the workgroup
+  const int row0 = ty * TS::TOKENS, n_rb = N / 16;
 
-  const u32x4_t* wbase[R];
-  size_t wstep[R];
+  // loads of this wavefront: NW weight fragments, consecutive in the packed tile (past the last row block: the last tile,
+  // results never stored), and NA times eight token rows (past the pass: its last row, results never stored)
+  const int pt_last = (n_rb + kTileBlocks - 1) / kTileBlocks - 1, pt_own = tx * (WF * R / kTileBlocks) + wave * NW / 16;
+  const int pt = pt_own < pt_last ? pt_own : pt_last;
+  const u32x4_t* wsrc = (const u32x4_t*)wp + ((size_t)pt * KS * kTileBlocks + (size_t)c0 * 16 + wave * NW % 16) * 64 + lane;
+  const bf16_t* asrc[NA];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const bool own = rb0 + r < wg1;
-    const int rb = own ? rb0 + r : wg0;
-    wbase[r] = (const u32x4_t*)wp + ((size_t)(rb / kTileBlocks) * KS * kTileBlocks + rb % kTileBlocks) * 64 + lane;
-    wstep[r] = own ? (size_t)kTileBlocks * 64 : 0;
+  for (int i = 0; i < NA; ++i) {
+    const int m = row0 + (wave * NA + i) * 8 + (lane >> 3);
+    asrc[i] = a + (size_t)(m < M ? m : M - 1) * K;
   }
-  auto load_w = [&](Frag (&dst)[R][STEPS], int c) __attribute__((always_inline)) {
-    c = c < last ? c : last;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int s = 0; s < STEPS; ++s) dst[r][s].nat = *(wbase[r] + (size_t)(c * STEPS + s) * wstep[r]);
-  };
-  // token pieces of this thread: pass i covers rows i * 32 + tid / 8, 16-byte column tid % 8
-  const int arow0 = tid >> 3, acol = (tid & 7) * 8;
-  const bf16_t* abase = a + acol;
-  auto load_a = [&](u32x4_t (&dst)[APASS], int c) __attribute__((always_inline)) {
-    c = c < last ? c : last;
-    int k = c * KC;
-    k = k + acol < K - 8 ? k : K - 8 - acol;               // columns past K meet zero-padded weights: any in-bounds piece
-#pragma unroll
-    for (int i = 0; i < APASS; ++i) {
-      int m = row0 + arow0 + i * 32;
-      m = m < M ? m : M - 1;                                // rows past the pass: a valid row, results never stored
-      dst[i] = *(const u32x4_t*)(abase + (size_t)m * K + k);
+  const int pcol = c0 * 64 + ((lane & 7) ^ (lane >> 3)) * 8;
+  auto fetch = [&](int i, int c, int stage) __attribute__((always_inline)) {
+    unsigned char* base = tile_lds + stage * STAGE;
+    if (i < NW) {
+      lds_load16(wsrc + (size_t)c * 16 * 64 + i * 64, base + (wave * NW + i) * 1024);
+    } else {
+      const int k = c * 64 + pcol;                         // columns past K meet zero-padded weights: any in-bounds piece
+      lds_load16(asrc[i - NW] + (k < K - 8 ? k : K - 8), base + WBYTES + (wave * NA + i - NW) * 1024);
     }
   };
-  auto store_a = [&](const u32x4_t (&src)[APASS], int stage) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < APASS; ++i)
-      *(u32x4_t*)(wide_lds + stage * STAGE + (arow0 + i * 32) * ROWB + (tid & 7) * 16) = src[i];
+  const int wfrag = (wf * R / 8 * 16 + wf * R % 8) * 1024 + lane * 16, arow = WBYTES + (wt * MT * 16 + r16) * 128;
+  auto read_w = [&](Frag& w, int stage, int s, int r) __attribute__((always_inline)) {
+    w.nat = *(const u32x4_t*)(tile_lds + stage * STAGE + wfrag + (s * 8 + r) * 1024);
+  };
+  auto read_a = [&](Frag& b, int stage, int s, int t) __attribute__((always_inline)) {
+    b.nat = *(const u32x4_t*)(tile_lds + stage * STAGE + arow + t * 2048 + (((s * 4 + g) ^ (r16 & 7)) << 4));
   };
 
   floatx4_t acc[R][MT];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[r][mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < MT; ++t) acc[r][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
-  Frag wreg[PD][R][STEPS];
-  u32x4_t areg[AD][APASS];
-  {
-    u32x4_t first[APASS];
-    load_a(first, 0);
+  Frag w0[R], w1[R], b0[MT], b1[MT];                     // operands of the first and the second 32 columns of a chunk
+  // Products of one half (w, b) between reads of the next half's operands (wn, bn: half `s` of `stage`) and, with FETCH,
+  // the loads of chunk c into stage `into`.
+  auto half = [&](Frag (&w)[R], Frag (&b)[MT], Frag (&wn)[R], Frag (&bn)[MT], int stage, int s, auto fetching, int c, int into)
+      __attribute__((always_inline)) {
+    constexpr bool FETCH = decltype(fetching)::value;
 #pragma unroll
-    for (int p = 0; p < AD; ++p) load_a(areg[p], 1 + p);
+    for (int t = 0; t < MT; ++t) {
+      if (FETCH) {
 #pragma unroll
-    for (int p = 0; p < PD; ++p) load_w(wreg[p], p);
-    store_a(first, 0);
-  }
-  __syncthreads();
-
-  auto body = [&](Frag (&wslot)[R][STEPS], u32x4_t (&aslot)[APASS], int c) __attribute__((always_inline)) {
-    const int stage = c & 1;
-    const unsigned char* ab = wide_lds + stage * STAGE + r16 * ROWB + g * 16;
-    Frag b[2][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[0][j].nat = *(const u32x4_t*)(ab + j * 16 * ROWB);
-    store_a(aslot, stage ^ 1);                 // token chunk c + 1 becomes visible after the barrier below
-    load_a(aslot, c + AD + 1);
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s)
-#pragma unroll
-      for (int mg = 0; mg < MT / 4; ++mg) {
-        constexpr int G = MT / 4;
-        const int cur = (s * G + mg) & 1;
-        if (s * G + mg + 1 < STEPS * G) {      // the next group of four token tiles, while these multiply
-          const int ns = (s * G + mg + 1) / G, nm = (s * G + mg + 1) % G;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) b[cur ^ 1][j].nat = *(const u32x4_t*)(ab + (nm * 4 + j) * 16 * ROWB + ns * 64);
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[r][mg * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wslot[r][s].v, b[cur][j].v, acc[r][mg * 4 + j], 0, 0, 0);
+        for (int i = t * (NW + NA) / MT; i < (t + 1) * (NW + NA) / MT; ++i) fetch(i, c, into);
       }
-    load_w(wslot, c + PD);
-    __syncthreads();
+      read_a(bn[t], stage, s, t);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (MT >= R ? r == t : r * MT / R == t) read_w(wn[r], stage, s, r);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[r].v, b[t].v, acc[r][t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  static_assert(PD == 2 && (AD == 1 || AD == 2), "the loop below alternates two ring slots");
+  // chunk c in stage `st`; chunk c + 2 goes into its stage (past the end: the last chunk again, never used; loops without
+  // it in a tail of their own cost registers that are not there)
+  auto body = [&](int c, int st) __attribute__((always_inline)) {
+    half(w0, b0, w1, b1, st, 1, std::false_type{}, 0, 0);
+    __syncthreads();                                     // waits for this wavefront's loads and reads, then for the others
+    half(w1, b1, w0, b0, st ^ 1, 0, std::true_type{}, c + 2 < chunks ? c + 2 : chunks - 1, st);
+  };
+#pragma unroll
+  for (int i = 0; i < NW + NA; ++i) fetch(i, 0, 0);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW + NA; ++i) fetch(i, chunks > 1 ? 1 : 0, 1);
+#pragma unroll
+  for (int r = 0; r < R; ++r) read_w(w0[r], 0, 0, r);
+#pragma unroll
+  for (int t = 0; t < MT; ++t) read_a(b0[t], 0, 0, t);
   int c = 0;
   for (; c + 2 <= chunks; c += 2) {
-    body(wreg[0], areg[0], c);
-    body(wreg[1], areg[AD - 1], c + 1);
+    body(c, 0);
+    body(c + 1, 1);
   }
-  if (c < chunks) body(wreg[0], areg[0], c);
-
+  if (c < chunks) body(c, 0);
+  __syncthreads();                                       // nothing may still be writing LDS when the workgroup ends
+  const int rb0 = tx * WF * R + wf * R;
   float4 row_ss[MT];
   if (rs.ss) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const int m = row0 + mt * 16 + r16;
+      const int m = row0 + (wt * MT + mt) * 16 + r16;
       row_ss[mt] = *(const float4*)(rs.ss + (size_t)(m < M ? m : M - 1) * kNormParts);
     }
   }
-  finish_rows<MT, R, EPI>(acc, row_ss, rb0, wg1, M, N, outp, qe, rs, row0, 0);
+  finish_rows<MT, R, EPI, true>(acc, row_ss, rb0, n_rb, M, N, outp, qe, rs, row0 + wt * MT * 16, blockIdx.y);
 }
 
 // Workgroup shape.  R = 2 row blocks per wavefront when that still leaves >= 80 workgroups, else R = 1.
@@ -507,13 +530,13 @@ int wide_split(int M, int N, int K) {
 
 template <int MT>
 hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, int epi, const QkvEpilogue& qe,
-                     const RowScale& rs, hipStream_t s, int row0) {
+                     const RowScale& rs, hipStream_t s) {
   const int n_rb = w.N / 16;
   const int KS = w.Kp / 32;
   constexpr int KC = MT == 1 ? 128 : kChunkCols;     // the chunk must give every thread at least one 16-byte piece
   if (epi == EPI_F32 && wide_split(M, w.N, w.K)) {
     hipLaunchKernelGGL((gemm_packed_kernel<MT, 2, 4, EPI_F32, KC>), dim3((n_rb + 7) / 8, nsplit), dim3(256), 0, s, a,
-                       w.p, M, w.N, w.K, KS, out, nsplit, qe, rs, row0);
+                       w.p, M, w.N, w.K, KS, out, nsplit, qe, rs);
   } else if (epi == EPI_SILU || (epi == EPI_F32 && rows_per_wave(w.N) == 2)) {
     const bool three = waves_per_group(n_rb) == 3;
     // a grid just short of the 256 compute units is topped up to 256 (the kernel shares the row blocks evenly):
@@ -524,17 +547,17 @@ hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int ns
     if (epi == EPI_SILU) {
       if (three)
         hipLaunchKernelGGL((gemm_packed_kernel<MT, 2, 3, EPI_SILU, 128>), grid, dim3(192), 0, s, a, w.p, M, w.N, w.K, KS,
-                           out, 1, qe, rs, row0);
+                           out, 1, qe, rs);
       else
         hipLaunchKernelGGL((gemm_packed_kernel<MT, 2, 4, EPI_SILU, KC>), grid, dim3(256), 0, s, a, w.p, M, w.N, w.K, KS,
-                           out, 1, qe, rs, row0);
+                           out, 1, qe, rs);
     } else {
       if (three)
         hipLaunchKernelGGL((gemm_packed_kernel<MT, 2, 3, EPI_F32, 128>), grid, dim3(192), 0, s, a, w.p, M, w.N, w.K, KS,
-                           out, nsplit, qe, rs, row0);
+                           out, nsplit, qe, rs);
       else
         hipLaunchKernelGGL((gemm_packed_kernel<MT, 2, 4, EPI_F32, KC>), grid, dim3(256), 0, s, a, w.p, M, w.N, w.K, KS,
-                           out, nsplit, qe, rs, row0);
+                           out, nsplit, qe, rs);
     }
   } else if (epi == EPI_QKV) {
     // no split-K here, so one row block per wavefront and three or four wavefronts: 768 row blocks (a 4096-wide
@@ -545,37 +568,42 @@ hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int ns
     if (gx < 256 && n_rb >= 256) gx = 256;
     if (four)
       hipLaunchKernelGGL((gemm_packed_kernel<MT, 1, 4, EPI_QKV, KC>), dim3(gx, 1), dim3(256), 0, s, a, w.p, M, w.N, w.K,
-                         KS, out, 1, qe, rs, row0);
+                         KS, out, 1, qe, rs);
     else
       hipLaunchKernelGGL((gemm_packed_kernel<MT, 1, 3, EPI_QKV, KC>), dim3(gx, 1), dim3(192), 0, s, a, w.p, M, w.N, w.K,
-                         KS, out, 1, qe, rs, row0);
+                         KS, out, 1, qe, rs);
   } else {
     hipLaunchKernelGGL((gemm_packed_kernel<MT, 1, 4, EPI_F32, KC>), dim3((n_rb + 3) / 4, nsplit), dim3(256), 0, s, a,
-                       w.p, M, w.N, w.K, KS, out, nsplit, qe, rs, row0);
+                       w.p, M, w.N, w.K, KS, out, nsplit, qe, rs);
   }
   return hipGetLastError();
 }
 
-// Rows [row0, row0 + rows) of a pass of M rows: the instance with the fewest token tiles that hold them.
-hipError_t launch_rows(const bf16_t* ap, const PackedW& w, int rows, int M, void* out, int nsplit, int epi,
-                       const QkvEpilogue& qe, const RowScale& rs, hipStream_t s, int row0) {
-  if (rows <= 16) return launch_mt<1>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);
-  if (rows <= 32) return launch_mt<2>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);
-  if (rows <= 64) return launch_mt<4>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);
-  if (rows <= 80) return launch_mt<5>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);   // a 64-node tree plus a few pseudo rows
-  if (rows <= 96) return launch_mt<6>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);
-  return launch_mt<8>(ap, w, M, out, nsplit, epi, qe, rs, s, row0);
+// A pass of up to 128 rows: the instance with the fewest token tiles that hold them.
+hipError_t launch_rows(const bf16_t* ap, const PackedW& w, int rows, void* out, int nsplit, int epi,
+                       const QkvEpilogue& qe, const RowScale& rs, hipStream_t s) {
+  if (rows <= 16) return launch_mt<1>(ap, w, rows, out, nsplit, epi, qe, rs, s);
+  if (rows <= 32) return launch_mt<2>(ap, w, rows, out, nsplit, epi, qe, rs, s);
+  if (rows <= 64) return launch_mt<4>(ap, w, rows, out, nsplit, epi, qe, rs, s);
+  if (rows <= 80) return launch_mt<5>(ap, w, rows, out, nsplit, epi, qe, rs, s);   // a 64-node tree plus a few pseudo rows
+  if (rows <= 96) return launch_mt<6>(ap, w, rows, out, nsplit, epi, qe, rs, s);
+  return launch_mt<8>(ap, w, rows, out, nsplit, epi, qe, rs, s);
 }
 
-// A workgroup holds at most 128 token rows (accumulators and the activation ring are registers): a pass of more
-// rows runs as two launches over the same weights, rows 0..127 and the rest, each writing its own rows of the
-// same outputs.  The K split is the caller's and the same for both.
+template <int EPI>
+hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+                       hipStream_t s);
+
+// A workgroup of the streaming kernel holds at most 128 token rows (accumulators and the activation ring are registers):
+// a pass of more rows goes to the token-tiled kernel.  The K split is the caller's.  At 256 rows of 4096 columns, against
+// two launches of 128 rows: 12288 features 72 -> 57 us, 22016 81 -> 76, 4096 24 -> 16, 32000 105 -> 87; 4096 x 11008
+// 51 -> 40.
 hipError_t launch_any(const void* a, const PackedW& w, int M, void* out, int nsplit, int epi, const QkvEpilogue& qe,
                       const RowScale& rs, hipStream_t s) {
-  const bf16_t* ap = (const bf16_t*)a;
-  if (M <= 128) return launch_rows(ap, w, M, M, out, nsplit, epi, qe, rs, s, 0);
-  const hipError_t e = launch_rows(ap, w, 128, M, out, nsplit, epi, qe, rs, s, 0);
-  return e != hipSuccess ? e : launch_rows(ap, w, M - 128, M, out, nsplit, epi, qe, rs, s, 128);
+  if (M <= 128) return launch_rows((const bf16_t*)a, w, M, out, nsplit, epi, qe, rs, s);
+  if (epi == EPI_SILU) return launch_wide<EPI_SILU>(a, w, M, out, 1, qe, rs, s);
+  if (epi == EPI_QKV) return launch_wide<EPI_QKV>(a, w, M, out, 1, qe, rs, s);
+  return launch_wide<EPI_F32>(a, w, M, out, nsplit, qe, rs, s);
 }
 
 }  // namespace
@@ -621,22 +649,104 @@ hipError_t launch_gemm_packed_silu(const void* a, PackedW w, int M, void* act, h
 }
 
 namespace {
-template <int EPI>
-hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, const RowScale& rs, hipStream_t s) {
-  constexpr int MT = 8, R = 4;                            // 128 tokens x 256 features per workgroup, two workgroups per unit
-  const int n_tiles = (w.N / 16 + 4 * R - 1) / (4 * R), m_tiles = (M + MT * 16 - 1) / (MT * 16);
-  const int lds = 2 * MT * 16 * (64 * 2 + kRowPad);
-  hipLaunchKernelGGL((gemm_wide_kernel<MT, R, EPI, 1, 2>), dim3(8 * ((n_tiles + 7) / 8) * m_tiles), dim3(256), lds, s,
-                     (const bf16_t*)a, w.p, M, w.N, w.K, w.Kp / 32, out, QkvEpilogue{}, rs, n_tiles, m_tiles);
+// Above 64 KB of LDS a kernel has to ask: once per device (gemm_tile_prepare does it when a model is set up, so that no
+// launch inside a stream capture has to).
+template <int WF, int WT, int MT, int EPI>
+hipError_t allow_tile_lds() {
+  using TS = TileShape<WF, WT, MT>;
+  if (TS::LDS_BYTES <= 64 * 1024) return hipSuccess;
+  static std::atomic<bool> allowed[64];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!allowed[dev].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute((const void*)gemm_tile_kernel<WF, WT, MT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, TS::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    allowed[dev].store(true, std::memory_order_release);
+  }
+  return hipSuccess;
+}
+
+template <int WF, int WT, int MT, int EPI>
+hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+                       hipStream_t s) {
+  using TS = TileShape<WF, WT, MT>;
+  const int n_tiles = (w.N + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
+  const hipError_t e = allow_tile_lds<WF, WT, MT, EPI>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((gemm_tile_kernel<WF, WT, MT, EPI>), dim3(8 * ((n_tiles + 7) / 8) * m_tiles, nsplit), dim3(64 * TS::WAVES),
+                     TS::LDS_BYTES, s, a, w.p, M, w.N, w.K, w.Kp / 32, out, qe, rs, n_tiles, m_tiles, nsplit);
   return hipGetLastError();
+}
+
+// Tile of a product of M rows with a given K split: rounds of workgroups over the 256 compute units, times what a
+// workgroup takes.  Microseconds per chunk of 64 columns (with as many workgroups per unit as fit, and with one) and per
+// round, fitted to launches of 256 - 4096 rows on 4096 - 27648 features over 4096 - 13824 columns, weights not in any
+// cache; a chunk costs much the same on a half-empty chip, so what a launch of few tiles wants is smaller tiles:
+//   256 x 256   12288 x 4096: 4096 rows 356 us (377 and 404 with the other two), 1024 rows 93 (145, 139)
+//   128 x 128   4096 x 4096: 2048 rows 59 us (77, 60), 512 rows in four K splits 22 (29, 23)
+//   128 x 256   12288 x 4096: 512 rows 68 us (97, 78); 22016 x 4096: 256 rows 76 us (98, 81)
+struct TileCost { int features, tokens, per_unit; float chunk, chunk_alone, round; };
+constexpr TileCost kTileCosts[3] = {{256, 256, 1, 1.35f, 1.35f, 12.f}, {128, 128, 2, 1.05f, 0.75f, 2.f}, {128, 256, 1, 1.03f, 1.03f, 2.f}};
+
+float tile_us(const TileCost& t, int M, int N, int K, int nsplit) {
+  const long groups = (long)((N + t.features - 1) / t.features) * ((M + t.tokens - 1) / t.tokens) * nsplit;
+  const long slots = 256L * t.per_unit, whole = groups / slots, rest = groups % slots;
+  const float chunks = (float)((packed_cols(K) / 64 + nsplit - 1) / nsplit);
+  return (float)whole * (t.round + t.chunk * chunks) + (rest ? t.round + (rest <= 256 ? t.chunk_alone : t.chunk) * chunks : 0.f);
+}
+int best_tile(int M, int N, int K, int nsplit) {
+  int best = 0;
+  for (int i = 1; i < 3; ++i)
+    if (tile_us(kTileCosts[i], M, N, K, nsplit) < tile_us(kTileCosts[best], M, N, K, nsplit)) best = i;
+  return best;
+}
+
+template <int EPI>
+hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+                       hipStream_t s) {
+  const bf16_t* ap = (const bf16_t*)a;
+  switch (best_tile(M, w.N, w.K, nsplit)) {
+    case 0: return launch_tile<4, 2, 8, EPI>(ap, w, M, out, nsplit, qe, rs, s);
+    case 1: return launch_tile<2, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, s);
+    default: return launch_tile<2, 4, 4, EPI>(ap, w, M, out, nsplit, qe, rs, s);
+  }
+}
+
+template <int EPI>
+hipError_t allow_tiles() {
+  const hipError_t e = allow_tile_lds<4, 2, 8, EPI>();
+  return e == hipSuccess ? allow_tile_lds<2, 4, 4, EPI>() : e;
 }
 }  // namespace
 
-hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, hipStream_t s, RowScale rs) {
-  return launch_wide<EPI_F32>(a, w, M, out, rs, s);
+hipError_t gemm_tile_prepare() {
+  hipError_t e = allow_tiles<EPI_F32>();
+  if (e == hipSuccess) e = allow_tiles<EPI_SILU>();
+  if (e == hipSuccess) e = allow_tiles<EPI_QKV>();
+  return e;
+}
+
+// A split pays for its partial sums: written and read once more at 4 bytes each, about 5 TB/s.
+int gemm_wide_splits(int M, int N, int K) {
+  int best = 1;
+  float best_us = tile_us(kTileCosts[best_tile(M, N, K, 1)], M, N, K, 1);
+  for (int sp = 2; sp <= kMaxSplitK && packed_cols(K) / 64 / sp >= 8; ++sp) {      // at least 512 columns per split
+    const float us = tile_us(kTileCosts[best_tile(M, N, K, sp)], M, N, K, sp) + (float)sp * (float)M * (float)N * 1.6e-6f;
+    if (us < best_us) { best = sp; best_us = us; }
+  }
+  return best;
+}
+
+hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs) {
+  return launch_wide<EPI_F32>(a, w, M, out, nsplit, QkvEpilogue{}, rs, s);
 }
 hipError_t launch_gemm_wide_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs) {
-  return launch_wide<EPI_SILU>(a, w, M, act, rs, s);
+  return launch_wide<EPI_SILU>(a, w, M, act, 1, QkvEpilogue{}, rs, s);
+}
+hipError_t launch_gemm_wide_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s, RowScale rs) {
+  return launch_wide<EPI_QKV>(a, w, M, nullptr, 1, qe, rs, s);
 }
 
 bool qkv_fusable(int head_dim) { return head_dim % 32 == 0; }

@@ -1,0 +1,77 @@
+"""The token-tiled product of passes of more than 128 rows, at the edges of its tiles, against the textbook product."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_harness as H
+from oracle import ht_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+class Packed(C.Structure):
+    _fields_ = [("p", C.c_void_p), ("N", C.c_int32), ("K", C.c_int32), ("Kp", C.c_int32)]
+
+
+class RowScale(C.Structure):
+    _fields_ = [("ss", C.c_void_p), ("inv_d", C.c_float), ("eps", C.c_float)]
+
+
+def inputs(M, N, K, seed):
+    g = torch.Generator(device=H.DEV).manual_seed(seed)
+    a = torch.empty(M, K, device=H.DEV).normal_(generator=g).to(torch.bfloat16)
+    w = torch.empty(N, K, device=H.DEV).normal_(0, 0.05, generator=g).to(torch.bfloat16)
+    return a, w
+
+
+def bound(a, w, K):
+    # exact products, fp32 sums: at most K / 32 matrix steps and the splits' sums, each rounded relative to a partial sum
+    # that the sum of magnitudes bounds
+    return (K / 32 + 16) * 2.0 ** -24 * np.abs(H.cpu(a)) @ np.abs(H.cpu(w)).T
+
+
+# rows, features and columns one below, at and one above the tiles of 64, 128 and 256, odd chunk counts, one chunk
+@pytest.mark.parametrize("M,N,K,splits", [(129, 16, 8, 1), (255, 240, 200, 1), (256, 256, 128, 1), (257, 272, 136, 1), (130, 144, 1032, 2),
+                                          (300, 4112, 328, 1), (513, 128, 2056, 4), (1025, 528, 640, 1), (129, 2064, 4096, 8),
+                                          (2047, 1040, 192, 1)])
+def test_token_tiled_product(M, N, K, splits):
+    import paper_2404_12022_amd.binding as B
+    a, w = inputs(M, N, K, M + N + K)
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_weight_pack(w, N, K, packed)
+    fn = getattr(B.lib, "_ZN2ht16launch_gemm_wideEPKvNS_7PackedWEiPfiP12ihipStream_tNS_8RowScaleE")
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_int, C.c_void_p, RowScale]
+    out = torch.full((splits, M, N), float("nan"), device=H.DEV)
+    print(f"tiled product {M} x {N} x {K} / {splits}", flush=True)
+    assert fn(a.data_ptr(), Packed(packed.data_ptr(), N, K, (K + 127) // 128 * 128), M, out.data_ptr(), splits,
+              torch.cuda.current_stream().cuda_stream, RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    got = H.cpu(out.sum(0))
+    assert np.all(np.abs(got - O.linear(H.cpu(a), H.cpu(w))) <= bound(a, w, K))
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 64, 64), (160, 4096, 1024), (193, 528, 2048), (256, 1040, 4104)])
+def test_packed_products_of_more_than_128_rows(M, N, K):
+    """The public calls: plain product (with its K splits) and gate/up with SiLU."""
+    import paper_2404_12022_amd.binding as B
+    a, w = inputs(B.ht_padded_rows(M), N, K, 7 * M + N)
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_weight_pack(w, N, K, packed)
+    scratch = torch.empty(B.ht_skinny_gemm_scratch_bytes(M, N, K), dtype=torch.uint8, device=H.DEV)
+    out = torch.full((M, N), float("nan"), device=H.DEV)
+    B.ht_skinny_gemm_packed(a, packed, M, N, K, out, scratch)
+    torch.cuda.synchronize()
+    want = O.linear(H.cpu(a[:M]), H.cpu(w))
+    assert np.all(np.abs(H.cpu(out) - want) <= bound(a[:M], w, K))
+    f = N // 2 // 16 * 16
+    gate, up = w[:f].contiguous(), w[f:2 * f].contiguous()
+    gu = torch.empty(B.ht_weight_pack_bytes(2 * f, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_gate_up_pack(gate, up, f, K, gu)
+    act = torch.full((M, f), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    B.ht_gate_up_silu_packed(a, gu, M, f, K, act)
+    torch.cuda.synchronize()
+    want = O.silu(O.linear(H.cpu(a[:M]), H.cpu(gate))) * O.linear(H.cpu(a[:M]), H.cpu(up))
+    # one bf16 rounding (half an ulp, 2^-9 relative) on values whose fp32 sums carry far smaller errors
+    assert np.all(np.abs(H.cpu(act) - want) <= 2.0 ** -8 * np.abs(want) + 1e-4 * np.abs(want).max())
