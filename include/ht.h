@@ -59,8 +59,8 @@ typedef struct {
   int32_t max_cache;                         /* KV slots per layer (multiple of 8) */
   int32_t max_tree;                          /* most rows of a pass: tree nodes (root included) plus pseudo
                                                 rows riding in the verify pass; <= HT_MAX_ROWS (a tree itself has
-                                                at most HT_MAX_TREE nodes).  Projections run 128 rows per launch:
-                                                a pass of more rows streams the weights twice. */
+                                                at most HT_MAX_TREE nodes).  Projections of up to 128 rows stream
+                                                the weights; more rows run on token-tiled products. */
 } ht_config;
 
 /* Borrowed weight pointers (device).  They must outlive the model.  Per-layer arrays are host arrays
@@ -135,8 +135,8 @@ int ht_set_dynamic_tree(ht_model *m, int32_t T, int32_t b, void *stream);
  * HT_ESTATE without a tree. */
 int ht_set_fused_nodes(ht_model *m, int32_t count, const int32_t *nodes /*host*/, void *stream);
 
-/* Runs the prompt (host array of n token ids, n >= 1) through the model in chunks with plain causal
- * attention, fills the KV cache, sets the pending root token to the greedy next token and keeps the
+/* Runs the prompt (host array of n token ids, n >= 1) through the model with plain causal attention (packed bf16
+ * models: up to 2048 positions per pass whatever max_tree is, longer prompts in passes of equal length), fills the KV cache, sets the pending root token to the greedy next token and keeps the
  * layer-t residual of the last prompt token as the transfer source.  Resets any previous cache. */
 int ht_prefill(ht_model *m, const int32_t *tokens /*host*/, int32_t n, void *stream);
 

@@ -90,6 +90,13 @@ struct Buffers {
   void* topk_scratch;
   void* transfer_scratch;   // bf16: the sources of a transfer in operand order
   std::vector<void*> kc, vc;   // host copies of the per-layer cache pointers
+  // prompts of packed models: activations of up to `rows` rows of one pass
+  struct Prompt {
+    int rows = 0;
+    size_t part_floats;
+    float *x, *part, *ss, *cs;
+    void *u, *q, *attn, *act;
+  } pf;
   // bf16 only: projection weights repacked into MFMA-fragment order
   std::vector<PackedW> p_qkv, p_o, p_gu, p_down;
   PackedW p_head;
@@ -99,6 +106,16 @@ bool shapes_packable(const ht_config& c) {
   const int qd = c.n_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim;
   return c.dtype == HT_BF16 && qd % 16 == 0 && kvd % 16 == 0 && c.d_model % 16 == 0 && c.d_ffn % 16 == 0 &&
          c.vocab % 16 == 0;
+}
+
+// Rows of a prompt that go through a block in one pass: enough that every product of it fills the chip several times
+// (2048 rows of a 4096-wide model: 34 TFLOP a block), few enough that the activations stay small beside the model.
+constexpr int kPromptRows = 2048;
+int prompt_rows(const ht_config& c) { return c.max_cache < kPromptRows ? c.max_cache : kPromptRows; }
+// Prompts run on the packed weights with the fused q|k|v epilogue and the matrix-core attention, or chunk by chunk on the
+// decode kernels (run_pass).
+bool prompt_passes(const ht_config& c) {
+  return shapes_packable(c) && qkv_fusable(c.head_dim) && attn_mfma_supported(1, c.n_heads, c.n_kv_heads, c.head_dim);
 }
 
 void carve(const ht_config& c, Carver& cv, Buffers& b) {
@@ -145,7 +162,8 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
   b.topk_scratch = cv.take_bytes(topk_scratch_bytes(kMaxRows));
   // sources of one launch: tree nodes or training rows, no more than rows of a pass
   b.transfer_scratch = cv.take_bytes(c.dtype == HT_BF16 ? transfer_scratch_bytes(Mp < kMaxTree ? (int)Mp : kMaxTree, (int)d) : 0);
-  b.attn_scratch = cv.take_bytes(attn_mfma_scratch_bytes((int)Mp, c.n_heads, c.head_dim));
+  // (a prompt of up to 128 rows goes through in one pass whatever max_tree is)
+  b.attn_scratch = cv.take_bytes(attn_mfma_scratch_bytes(prompt_passes(c) && Mp < 128 ? 128 : (int)Mp, c.n_heads, c.head_dim));
   b.kc.resize(c.n_layers);
   b.vc.resize(c.n_layers);
   for (int l = 0; l < c.n_layers; ++l) {
@@ -167,6 +185,21 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
       b.p_down[l] = pk((int)d, c.d_ffn);
     }
     b.p_head = pk(c.vocab, (int)d);
+  }
+  if (prompt_passes(c)) {
+    Buffers::Prompt& p = b.pf;
+    p.rows = prompt_rows(c);
+    // the products of up to 128 rows read whole instances of their kernel
+    const size_t r = p.rows < 128 ? 128 : p.rows, split_rows = (size_t)kMaxSplitK * 128;
+    p.part_floats = (2 * r > split_rows ? 2 * r : split_rows) * d;
+    p.x = cv.take<float>(r * d);
+    p.part = cv.take<float>(p.part_floats);
+    p.ss = cv.take<float>(r * kNormParts);
+    p.cs = cv.take<float>(r * c.head_dim);
+    p.u = cv.take_bytes(r * d * 2);
+    p.q = cv.take_bytes(r * qd * 2);
+    p.attn = cv.take_bytes(r * qd * 2);
+    p.act = cv.take_bytes(r * c.d_ffn * 2);
   }
 }
 
@@ -430,6 +463,59 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
       return rc;
     }
     if (gout) HT_HIP(launch_argmax(logits, gout, M, c.vocab, s));
+  }
+  return HT_OK;
+}
+
+// Rows start .. start + rows - 1 of the prompt through all blocks, causal over the cache, K/V to their own slots.  `last`:
+// the final row's residual at every transfer layer goes to row 0 of that slot's saved rows, its logits to b.logits and
+// its greedy token to b.g[0].
+int prompt_pass(ht_model* m, int start, int rows, bool last, hipStream_t s) {
+  const ht_config& c = m->cfg;
+  Buffers& b = m->b;
+  Buffers::Prompt& p = b.pf;
+  const int d = c.d_model, qd = c.n_heads * c.head_dim, n_qkv = qd + 2 * c.n_kv_heads * c.head_dim, f = c.d_ffn;
+  const size_t pstride = (size_t)rows * d, end = pstride - d;
+  const RowScale rs{p.ss, 1.0f / (float)d, c.rms_eps};
+  auto splits = [&](int K) {
+    int sp = rows > 128 ? gemm_wide_splits(rows, d, K) : gemm_mfma_splits(rows, d, K);
+    while (sp > 1 && sp * pstride > p.part_floats) --sp;
+    return sp;
+  };
+  const int o_splits = splits(qd), down_splits = splits(f);
+  HT_HIP(launch_embed(c.dtype, m->tok_emb, b.prompt + start, p.x, rows, d, s));
+  HT_HIP(launch_rope_table(p.cs, nullptr, start, rows, c.head_dim, c.rope_base, s));
+  int pending = 0;
+  for (int l = 0; l < c.n_layers; ++l) {
+    HT_HIP(launch_add_norm_parts(p.x, p.part, pending, pstride, m->attn_norm[l], p.u, nullptr, p.ss, rows, d, s));
+    const int slot = m->slot_of_layer[l];
+    if (last && slot >= 0) HT_HIP(launch_load_rows(p.x + end, b.saved_h + (size_t)slot * m->Mp * d, 1, d, s));
+    if (rows <= 128 && rows <= m->Mp && qkv_prefer_split(rows, n_qkv)) {
+      const int sp = gemm_mfma_splits(rows, n_qkv, d);
+      HT_HIP(launch_gemm_packed(p.u, b.p_qkv[l], rows, b.qkv, sp, s, rs));
+      HT_HIP(launch_rope_append(c.dtype, b.qkv, sp, p.cs, p.q, b.kc[l], b.vc[l], start, rows, c.n_heads, c.n_kv_heads, c.head_dim,
+                                c.max_cache, true, s));
+    } else {
+      QkvEpilogue qe{p.cs, (bf16_t*)p.q, (bf16_t*)b.kc[l], (bf16_t*)b.vc[l], start, c.n_heads, c.n_kv_heads, c.head_dim,
+                     c.max_cache, nullptr};
+      HT_HIP(launch_gemm_packed_qkv(p.u, b.p_qkv[l], rows, qe, s, rs));
+    }
+    if (rows > 128)
+      HT_HIP(launch_attn_causal(p.q, b.kc[l], b.vc[l], c.max_cache, start, rows, b.chain.dev(), c.n_heads, c.n_kv_heads,
+                                c.head_dim, p.attn, s));
+    else
+      HT_HIP(launch_attn_mfma(p.q, b.kc[l], b.vc[l], c.max_cache, start, rows, b.chain.dev(), c.n_heads, c.n_kv_heads, c.head_dim,
+                              p.attn, b.attn_scratch, s));
+    HT_HIP(launch_gemm_packed(p.attn, b.p_o[l], rows, p.part, o_splits, s));
+    HT_HIP(launch_add_norm_parts(p.x, p.part, o_splits, pstride, m->ffn_norm[l], p.u, nullptr, p.ss, rows, d, s));
+    HT_HIP(launch_gemm_packed_silu(p.u, b.p_gu[l], rows, p.act, s, rs));
+    HT_HIP(launch_gemm_packed(p.act, b.p_down[l], rows, p.part, down_splits, s));
+    pending = down_splits;
+  }
+  if (last) {                                  // only the last row goes on to the head
+    HT_HIP(launch_add_norm_parts(p.x + end, p.part + end, pending, pstride, m->final_norm, p.u, nullptr, p.ss, 1, d, s));
+    HT_HIP(launch_gemm_packed(p.u, b.p_head, 1, b.logits, 1, s, rs));
+    HT_HIP(launch_argmax(b.logits, b.g, 1, c.vocab, s));
   }
   return HT_OK;
 }
@@ -809,6 +895,21 @@ int ht_prefill(ht_model* m, const int32_t* tokens, int32_t n, void* stream) {
   m->has_prefill = m->transfer_ready = m->verify_done = false;
   const TreeDev chain = m->b.chain.dev();
   int rc;
+  if (m->packed && m->qkv_fused && m->b.pf.rows) {
+    // passes of equal length: none is left with a few rows to stream the weights for
+    const int passes = (n + m->b.pf.rows - 1) / m->b.pf.rows;
+    for (int i = 0, start = 0; i < passes; ++i) {
+      const int rows = (n - start + passes - i - 1) / (passes - i);
+      if ((rc = prompt_pass(m, start, rows, i + 1 == passes, s))) return rc;
+      start += rows;
+    }
+    HT_HIP(launch_prefill_finish(m->b.state, m->b.g, m->b.saved_h, (size_t)m->Mp * c.d_model, (int)m->slot_layer.size(),
+                                 m->b.h_src, 0, c.d_model, s));
+    m->n = n;                                  // chain rows are already in their final slots
+    HT_HIP(hipStreamSynchronize(s));
+    m->has_prefill = true;
+    return HT_OK;
+  }
   const int chunk = m->Mp < 128 ? m->Mp : 128;          // more rows a pass would only stream the weights twice
   for (int start = 0; start < n; start += chunk) {
     const int rows = n - start < chunk ? n - start : chunk;
@@ -1045,11 +1146,11 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
       HT_HIP(launch_rope_append(c.dtype, w.qkv + (size_t)n * stride_qkv, 1, w.cs + (size_t)step * c.head_dim,
                                 (char*)w.q + (size_t)n * qd * 2, w.self_k, w.self_v, lead, P, c.n_heads, c.n_kv_heads,
                                 c.head_dim, w.self_cap, true, s));
-      HT_HIP(launch_attn_causal((char*)w.q + (size_t)(n - lead) * qd * 2, b.kc[l], b.vc[l], c.max_cache, n, chain, c.n_heads,
+      HT_HIP(launch_attn_causal((char*)w.q + (size_t)(n - lead) * qd * 2, b.kc[l], b.vc[l], c.max_cache, 0, n, chain, c.n_heads,
                                 c.n_kv_heads, c.head_dim, (char*)w.attn + (size_t)(n - lead) * qd * 2, s, w.self_k, w.self_v,
                                 w.self_cap, w.attn_scratch));
     }
-    HT_HIP(launch_attn_causal(w.q, b.kc[l], b.vc[l], c.max_cache, n, chain, c.n_heads, c.n_kv_heads, c.head_dim, w.attn, s));
+    HT_HIP(launch_attn_causal(w.q, b.kc[l], b.vc[l], c.max_cache, 0, n, chain, c.n_heads, c.n_kv_heads, c.head_dim, w.attn, s));
     HT_HIP(launch_gemm_wide(w.attn, b.p_o[l], rows, w.part, 1, s));
     HT_HIP(launch_add_norm_parts(w.x, w.part, 1, (size_t)rows * d, m->ffn_norm[l], w.u, nullptr, w.ss, rows, d, s));
     HT_HIP(launch_gemm_wide_silu(w.u, b.p_gu[l], rows, w.act, s, rs));

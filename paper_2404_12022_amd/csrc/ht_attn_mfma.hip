@@ -962,28 +962,29 @@ hipError_t attn_mfma_prepare(int hd) {
   return hipSuccess;
 }
 
-// A causal sequence of `rows` rows whose K/V are in the cache already (slot = position): row r sees the keys 0 .. r.
+// A causal sequence of `rows` rows at positions n .. whose K/V are in the cache already (slot = position): row r sees the
+// keys 0 .. n + r.
 // One launch of the tile kernel, rows attending in chunks of kCausalChunk, a workgroup per (query head, 64 rows), every
 // workgroup over all its keys.  `tree` holds the masks of a chain of at least kCausalChunk rows.
-// With `self_k` / `self_v` ([rows][Hkv][hd] and [Hkv][hd][self_cap]) row r sees the keys 0 .. r of the cache and, on
+// With `self_k` / `self_v` ([rows][Hkv][hd] and [Hkv][hd][self_cap]) row r sees the keys 0 .. n + r of the cache and, on
 // top, the key and value of its own row in those buffers: the cache part and the own part meet in the merge kernel
 // (`scratch`: attn_causal_scratch_bytes).
 namespace {
 constexpr int kCausalChunk = 128;
 template <int HD>
-hipError_t launch_causal_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int rows, const uint64_t* anc, int Hq,
+hipError_t launch_causal_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int n, int rows, const uint64_t* anc, int Hq,
                             int Hkv, bf16_t* out, const bf16_t* self_k, const bf16_t* self_v, int self_cap, void* scratch,
                             hipStream_t s) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
   const dim3 grid(Hq, (rows + 63) / 64, 1);
   if (!self_k) {
-    hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, q, kc, vc, cap, 0, rows, anc, Hq, Hkv, out,
+    hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, q, kc, vc, cap, n, rows, anc, Hq, Hkv, out,
                        nullptr, nullptr, 1, scale_log2, nullptr, kCausalChunk);
     return hipGetLastError();
   }
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (size_t)Hq * 2 * rows * HD;
-  hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, q, kc, vc, cap, 0, rows, anc, Hq, Hkv, out, part_o,
+  hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, q, kc, vc, cap, n, rows, anc, Hq, Hkv, out, part_o,
                      part_ml, 2, scale_log2, nullptr, kCausalChunk);
   hipLaunchKernelGGL((attn_self_slice_kernel<HD>), dim3(rows, (Hq + 3) / 4), dim3(256), 0, s, q, self_k, self_v, self_cap, rows,
                      Hq, Hkv, scale_log2, part_o, part_ml, 2, 1);
@@ -997,17 +998,17 @@ size_t attn_causal_scratch_bytes(int rows, int Hq, int hd) {
   return ((size_t)Hq * 2 * rows * hd + (size_t)Hq * 2 * rows * 2) * sizeof(float) + 256;
 }
 
-hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int cap, int rows, TreeDev tree, int Hq, int Hkv,
+hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int cap, int n, int rows, TreeDev tree, int Hq, int Hkv,
                               int hd, void* out, hipStream_t s, const void* self_k, const void* self_v, int self_cap,
                               void* scratch) {
-  if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || rows < 1 || rows > cap) return hipErrorInvalidValue;
+  if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || n < 0 || rows < 1 || n + rows > cap) return hipErrorInvalidValue;
   if ((self_k != nullptr) != (self_v != nullptr) || (self_k && (!scratch || self_cap < rows))) return hipErrorInvalidValue;
   const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;
   if (hd == 128)
-    return launch_causal_hd<128>(qp, kp, vp, cap, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
+    return launch_causal_hd<128>(qp, kp, vp, cap, n, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
                                  (const bf16_t*)self_v, self_cap, scratch, s);
   if (hd == 64)
-    return launch_causal_hd<64>(qp, kp, vp, cap, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
+    return launch_causal_hd<64>(qp, kp, vp, cap, n, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
                                 (const bf16_t*)self_v, self_cap, scratch, s);
   return hipErrorInvalidValue;
 }
