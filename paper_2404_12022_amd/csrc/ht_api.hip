@@ -190,8 +190,11 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
     Buffers::Prompt& p = b.pf;
     p.rows = prompt_rows(c);
     // the products of up to 128 rows read whole instances of their kernel
-    const size_t r = p.rows < 128 ? 128 : p.rows, split_rows = (size_t)kMaxSplitK * 128;
-    p.part_floats = (2 * r > split_rows ? 2 * r : split_rows) * d;
+    const size_t r = p.rows < 128 ? 128 : p.rows;
+    // eight K splits of up to 128 rows, four of 512, two of the most
+    size_t part_rows = (size_t)kMaxSplitK * 128;
+    if (r > 128) part_rows = 4 * (r < 512 ? r : 512) > part_rows ? 4 * (r < 512 ? r : 512) : part_rows;
+    p.part_floats = (2 * r > part_rows ? 2 * r : part_rows) * d;
     p.x = cv.take<float>(r * d);
     p.part = cv.take<float>(p.part_floats);
     p.ss = cv.take<float>(r * kNormParts);
@@ -995,7 +998,7 @@ int ht_training_forward(ht_model* m, int32_t step, const int32_t* tokens, int32_
         return rc;
       int pairs = terms - c0;
       pairs = pairs < 0 ? 0 : pairs > pseudo ? pseudo : pairs;
-      if (pairs) HT_HIP(launch_kl_rows(b.logits, real, step, pairs, c.vocab, b.kl + c0, s));
+      if (pairs) HT_HIP(launch_kl_rows(b.logits + (size_t)real * c.vocab, b.logits + (size_t)step * c.vocab, pairs, c.vocab, b.kl + c0, s));
       // the first `step` rows of a later pass were the lookahead of the pass before, whose loss terms used them: the
       // copy keeps that first version (in bf16 the two passes may round a row differently)
       const int seen = c0 > 0 ? step : 0;
@@ -1028,11 +1031,10 @@ namespace {
 struct WideBuffers {
   float* x;            // residual stream [rows, d]
   void* u;             // normalised rows (bf16, before the 1/rms factor) [rows, d]
-  float* qkv;          // [rows, (Hq + 2 Hkv) hd]
   void* q;             // rotated queries [rows, Hq hd]
   void* attn;          // attention output [rows, Hq hd]
   void* act;           // silu(gate) * up [rows, f]
-  float* part;         // output of the O / down projection [rows, d]
+  float* part;         // output of the O / down projection [2 n, d]: whole sums, or K splits of fewer rows
   float* ss;           // sums of squares of the rows of u [rows, kNormParts]
   float* logits;       // [rows, V]
   float* cs;           // rotary table of positions 0 .. n [n + 1, hd / 2] (cos, sin), the same for every block
@@ -1050,7 +1052,6 @@ WideBuffers carve_wide(const ht_config& c, int n, void* base) {
   const size_t rows = 2 * (size_t)n, d = c.d_model, qd = (size_t)c.n_heads * c.head_dim, kvd = (size_t)c.n_kv_heads * c.head_dim;
   w.x = cv.take<float>(rows * d);
   w.u = cv.take_bytes(rows * d * 2);
-  w.qkv = cv.take<float>(rows * (qd + 2 * kvd));
   w.q = cv.take_bytes(rows * qd * 2);
   w.attn = cv.take_bytes(rows * qd * 2);
   w.act = cv.take_bytes(rows * c.d_ffn * 2);
@@ -1098,8 +1099,7 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
   if (train_ws_bytes < w.total) return fail(HT_EINVAL, "workspace has %zu bytes, %zu needed", train_ws_bytes, w.total);
   hipStream_t s = (hipStream_t)stream;
   Buffers& b = m->b;
-  const int d = c.d_model, qd = c.n_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, f = c.d_ffn, L = c.n_layers;
-  const int stride_qkv = qd + 2 * kvd;
+  const int d = c.d_model, qd = c.n_heads * c.head_dim, L = c.n_layers;
   const int t = c.transfer_layer[step - 1];
   const int P = n - step + 1;                // pseudo states exist for positions j <= n - step
   const int terms = n - step - 1;            // loss terms j = 0 .. n - step - 2 (Sec. 3.3, upper limit of the sum)
@@ -1119,12 +1119,16 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
   HT_HIP(launch_rope_table(w.cs, nullptr, 0, n + 1, c.head_dim, c.rope_base, s));
   int rows = n, pending = 0;
   const TreeDev chain = b.chain.dev();
+  auto splits = [&](int r, int K) {            // w.part holds 2 n rows
+    const int sp = gemm_wide_splits(r, d, K);
+    return sp * r <= 2 * n ? sp : 2 * n / r;
+  };
   for (int l = 0; l < L; ++l) {
     if (l == t) {
       // the residual after t blocks is complete once the last block's sums are in: pseudo states W_i h_j, j < P, as
       // one more product (sources rounded to bf16 like every other product's operand)
       if (pending) {
-        HT_HIP(launch_add_norm_parts(w.x, w.part, 1, (size_t)rows * d, m->attn_norm[l], w.u, nullptr, w.ss, rows, d, s));
+        HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->attn_norm[l], w.u, nullptr, w.ss, rows, d, s));
         pending = 0;
       }
       HT_HIP(launch_convert_to_bf16(w.x, w.u, (size_t)P * d, s));
@@ -1132,43 +1136,59 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
       rows = n + P;
     }
     HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->attn_norm[l], w.u, nullptr, w.ss, rows, d, s));
-    HT_HIP(launch_gemm_wide(w.u, b.p_qkv[l], rows, w.qkv, 1, s, rs));
-    // hidden rows: rotary at their own position, K/V to their own cache slot
-    HT_HIP(launch_rope_append(c.dtype, w.qkv, 1, w.cs, w.q, b.kc[l], b.vc[l], 0, n, c.n_heads, c.n_kv_heads, c.head_dim,
-                              c.max_cache, true, s));
+    // hidden rows: rotary at their own position, K/V to their own cache slot; pseudo row j: at position j + step, K/V to
+    // row lead + j of buffers of their own (below)
+    const int lead = step - 1;
+    QkvEpilogue qe{w.cs, (bf16_t*)w.q, (bf16_t*)b.kc[l], (bf16_t*)b.vc[l], 0, c.n_heads, c.n_kv_heads, c.head_dim, c.max_cache};
+    if (rows > n) {
+      qe.tail_row = n;
+      qe.tail_n = lead;
+      qe.tail_cap = w.self_cap;
+      qe.tail_cs = w.cs + (size_t)step * c.head_dim;
+      qe.tail_kc = (bf16_t*)w.self_k;
+      qe.tail_vc = (bf16_t*)w.self_v;
+    }
+    HT_HIP(launch_gemm_wide_qkv(w.u, b.p_qkv[l], rows, qe, s, rs));
     if (l >= t) {
       // Pseudo row j sits at position j + step and sees the hidden keys 0 .. j + step - 1 and itself (Sec. 3.3): as
       // row j + step - 1 of a causal launch over the hidden keys, with its own key and value, kept in buffers of their
       // own, as one more slice.  The step - 1 rows in front of pseudo row 0 are computed for nothing (their queries
       // are the last hidden rows'), and their outputs land on the last hidden rows of w.attn, which the hidden rows'
       // own launch below writes afterwards.
-      const int lead = step - 1;
-      HT_HIP(launch_rope_append(c.dtype, w.qkv + (size_t)n * stride_qkv, 1, w.cs + (size_t)step * c.head_dim,
-                                (char*)w.q + (size_t)n * qd * 2, w.self_k, w.self_v, lead, P, c.n_heads, c.n_kv_heads,
-                                c.head_dim, w.self_cap, true, s));
       HT_HIP(launch_attn_causal((char*)w.q + (size_t)(n - lead) * qd * 2, b.kc[l], b.vc[l], c.max_cache, 0, n, chain, c.n_heads,
                                 c.n_kv_heads, c.head_dim, (char*)w.attn + (size_t)(n - lead) * qd * 2, s, w.self_k, w.self_v,
                                 w.self_cap, w.attn_scratch));
     }
     HT_HIP(launch_attn_causal(w.q, b.kc[l], b.vc[l], c.max_cache, 0, n, chain, c.n_heads, c.n_kv_heads, c.head_dim, w.attn, s));
-    HT_HIP(launch_gemm_wide(w.attn, b.p_o[l], rows, w.part, 1, s));
-    HT_HIP(launch_add_norm_parts(w.x, w.part, 1, (size_t)rows * d, m->ffn_norm[l], w.u, nullptr, w.ss, rows, d, s));
+    const int o_splits = splits(rows, qd);
+    HT_HIP(launch_gemm_wide(w.attn, b.p_o[l], rows, w.part, o_splits, s));
+    HT_HIP(launch_add_norm_parts(w.x, w.part, o_splits, (size_t)rows * d, m->ffn_norm[l], w.u, nullptr, w.ss, rows, d, s));
     HT_HIP(launch_gemm_wide_silu(w.u, b.p_gu[l], rows, w.act, s, rs));
-    HT_HIP(launch_gemm_wide(w.act, b.p_down[l], rows, w.part, 1, s));
-    pending = 1;
+    pending = splits(rows, c.d_ffn);
+    HT_HIP(launch_gemm_wide(w.act, b.p_down[l], rows, w.part, pending, s));
   }
   HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->final_norm, w.u, nullptr, w.ss, rows, d, s));
-  HT_HIP(launch_gemm_wide(w.u, b.p_head, rows, w.logits, 1, s, rs));
-  // term j pairs pseudo row j (logits row n + j) with the hidden state it stands for (logits row j + step)
+  // The head writes the logits where the caller wants them (a buffer that is not 16-byte aligned gets a copy): at 2047 + 2048
+  // rows of 32000 the two copies took 190 us.
+  auto direct = [](const float* p) { return p && !((uintptr_t)p & 15); };
+  float* z_hidden = direct(logits_hidden_out) ? logits_hidden_out : w.logits;
+  float* z_pseudo = direct(logits_pseudo_out) ? logits_pseudo_out : w.logits + (size_t)n * c.vocab;
+  if (z_hidden == w.logits && z_pseudo == w.logits + (size_t)n * c.vocab) {
+    HT_HIP(launch_gemm_wide(w.u, b.p_head, rows, w.logits, 1, s, rs));
+  } else {
+    HT_HIP(launch_gemm_wide(w.u, b.p_head, n, z_hidden, 1, s, rs));
+    const RowScale rs_pseudo{w.ss + (size_t)n * kNormParts, rs.inv_d, rs.eps};
+    HT_HIP(launch_gemm_wide((char*)w.u + (size_t)n * d * 2, b.p_head, P, z_pseudo, 1, s, rs_pseudo));
+  }
+  // term j pairs pseudo row j with the hidden state it stands for (hidden row j + step)
   for (int j0 = 0; j0 < terms; j0 += 32768) {
     const int cnt = terms - j0 < 32768 ? terms - j0 : 32768;
-    HT_HIP(launch_kl_rows(w.logits, n + j0, step + j0, cnt, c.vocab, b.kl + j0, s));
+    HT_HIP(launch_kl_rows(z_pseudo + (size_t)j0 * c.vocab, z_hidden + (size_t)(step + j0) * c.vocab, cnt, c.vocab, b.kl + j0, s));
   }
-  if (logits_hidden_out)
-    HT_HIP(hipMemcpyAsync(logits_hidden_out, w.logits, sizeof(float) * (size_t)n * c.vocab, hipMemcpyDeviceToDevice, s));
-  if (logits_pseudo_out)
-    HT_HIP(hipMemcpyAsync(logits_pseudo_out, w.logits + (size_t)n * c.vocab, sizeof(float) * (size_t)P * c.vocab,
-                          hipMemcpyDeviceToDevice, s));
+  if (logits_hidden_out && z_hidden != logits_hidden_out)
+    HT_HIP(hipMemcpyAsync(logits_hidden_out, z_hidden, sizeof(float) * (size_t)n * c.vocab, hipMemcpyDeviceToDevice, s));
+  if (logits_pseudo_out && z_pseudo != logits_pseudo_out)
+    HT_HIP(hipMemcpyAsync(logits_pseudo_out, z_pseudo, sizeof(float) * (size_t)P * c.vocab, hipMemcpyDeviceToDevice, s));
   float* h_kl = (float*)m->h_stage;
   HT_HIP(hipStreamSynchronize(s));
   HT_HIP(hipMemcpyAsync(h_kl, b.kl, sizeof(float) * terms, hipMemcpyDeviceToHost, s));
@@ -1607,7 +1627,7 @@ int ht_skinny_gemm(const void* a, const void* w, int32_t M, int32_t N, int32_t K
 int ht_kl_divergence_rows(const float* z, int32_t row_a, int32_t row_b, int32_t pairs, int32_t V, float* kl, void* stream) {
   if (!z || !kl) return fail(HT_EINVAL, "NULL argument");
   if (row_a < 0 || row_b < 0 || pairs < 1 || pairs > 65535 || V < 1) return fail(HT_EINVAL, "bad shape pairs=%d V=%d", pairs, V);
-  HT_HIP(launch_kl_rows(z, row_a, row_b, pairs, V, kl, (hipStream_t)stream));
+  HT_HIP(launch_kl_rows(z + (size_t)row_a * V, z + (size_t)row_b * V, pairs, V, kl, (hipStream_t)stream));
   return HT_OK;
 }
 

@@ -134,8 +134,8 @@ size_t topk_scratch_bytes(int rows);
 hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void* scratch, int rows, int period,
                        const int32_t* src_row, int V, hipStream_t s);
 hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev tree, int32_t* tok, int T, hipStream_t s);
-// kl[p] = KL(softmax(z[row_a + p]) || softmax(z[row_b + p])), p < pairs, z rows of V floats (Sec. 3.3 loss term)
-hipError_t launch_kl_rows(const float* z, int row_a, int row_b, int pairs, int V, float* kl, hipStream_t s);
+// kl[p] = KL(softmax(za[p]) || softmax(zb[p])), p < pairs, rows of V floats (Sec. 3.3 loss term)
+hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, float* kl, hipStream_t s);
 // Tree chosen from the draft distributions: lp[k][kMaxTopK] = log-probabilities of the b best candidates of every
 // draft row (whole-row log-softmax); then the T - 1 best nodes by (summed lp desc, depth asc, rank path asc) fill
 // the tree tables and the token row.  T <= kMaxTree, 1 <= b <= kMaxTopK, 1 <= k <= kMaxTransfer and
@@ -215,6 +215,11 @@ struct QkvEpilogue {
   bf16_t *q, *kc, *vc;
   int32_t n, Hq, Hkv, hd, cap;
   const int32_t* n_dev = nullptr;            // overrides n when set (device-resident loop)
+  // launch_gemm_wide_qkv with tail_kc set: rows from tail_row on take their rotary factors from tail_cs (row 0 on) and go
+  // to slots tail_n .. of caches of their own; their q rows follow the others'
+  int32_t tail_row = 0, tail_n = 0, tail_cap = 0;
+  const float* tail_cs = nullptr;
+  bf16_t *tail_kc = nullptr, *tail_vc = nullptr;
 };
 // The same products tiled over the tokens too, for passes of any number of rows: out fp32 [nsplit][M][N] (nsplit 1 or
 // gemm_wide_splits); act bf16 [M][N/2] (w packed from (gate, up)); q | k | v as in launch_gemm_packed_qkv.

@@ -46,7 +46,7 @@ union Frag {
   bf16x8_t v;
 };
 
-enum { EPI_F32 = 0, EPI_SILU = 1, EPI_QKV = 2 };
+enum { EPI_F32 = 0, EPI_SILU = 1, EPI_QKV = 2, EPI_QKV_TAIL = 3 };     // ..TAIL: rows from qe.tail_row on have caches of their own
 
 // --------------------------------------------------------------------------------------------- repack
 // dst fragment order from row-major segments.  One thread per 16-byte piece.
@@ -158,12 +158,13 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           const int m = mt * 16 + r16;
+          const bool tail = EPI == EPI_QKV_TAIL && m >= qe.tail_row;
+          const float* cs = EPI == EPI_QKV_TAIL && tail ? qe.tail_cs + (ptrdiff_t)(m - qe.tail_row) * hd : qe.cs + (size_t)m * hd;
           float other[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(acc[r][mt][i], 32, 64);
           if (m < M) {
-            const float4 c01 = *(const float4*)(qe.cs + ((size_t)m * half + j) * 2);
-            const float4 c23 = *(const float4*)(qe.cs + ((size_t)m * half + j) * 2 + 4);
+            const float4 c01 = *(const float4*)(cs + j * 2), c23 = *(const float4*)(cs + j * 2 + 4);
             const float cs_[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
             float o[4];
 #pragma unroll
@@ -172,8 +173,9 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
               const float co = cs_[2 * i], si = cs_[2 * i + 1];
               o[i] = upper ? y * co + x * si : x * co - y * si;
             }
-            bf16_t* dst = is_q ? qe.q + ((size_t)m * qe.Hq + h) * hd + j
-                               : qe.kc + ((size_t)(n_now + m) * qe.Hkv + h) * hd + j;
+            bf16_t* dst = is_q   ? qe.q + ((size_t)m * qe.Hq + h) * hd + j
+                          : tail ? qe.tail_kc + ((size_t)(qe.tail_n + m - qe.tail_row) * qe.Hkv + h) * hd + j
+                                 : qe.kc + ((size_t)(n_now + m) * qe.Hkv + h) * hd + j;
             *(uint2*)(dst + (upper ? half : 0)) = pack4_bf16(o[0], o[1], o[2], o[3]);
           }
         }
@@ -184,11 +186,13 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
           const int m = mt * 16 + r16;
           if (m < M) {
             const uint2 v4 = pack4_bf16(acc[r][mt][0], acc[r][mt][1], acc[r][mt][2], acc[r][mt][3]);
-            bf16_t* col = qe.vc + ((size_t)h * hd + e0) * qe.cap + n_now + m;      // feature e0 + i is i * cap further on
+            const bool tail = EPI == EPI_QKV_TAIL && m >= qe.tail_row;
+            const size_t cap = tail ? qe.tail_cap : qe.cap;                        // feature e0 + i is i * cap further on
+            bf16_t* col = (tail ? qe.tail_vc + qe.tail_n + m - qe.tail_row : qe.vc + n_now + m) + ((size_t)h * hd + e0) * cap;
             col[0] = (bf16_t)(v4.x & 0xffffu);
-            col[(size_t)qe.cap] = (bf16_t)(v4.x >> 16);
-            col[2 * (size_t)qe.cap] = (bf16_t)(v4.y & 0xffffu);
-            col[3 * (size_t)qe.cap] = (bf16_t)(v4.y >> 16);
+            col[cap] = (bf16_t)(v4.x >> 16);
+            col[2 * cap] = (bf16_t)(v4.y & 0xffffu);
+            col[3 * cap] = (bf16_t)(v4.y >> 16);
           }
         }
       }
@@ -374,7 +378,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
 // and every wavefront has read the last of this one, whose stage the loads then refill.
 // Measured on random operands, 4096 tokens, against 128 x 256 tiles with weights loaded into registers (the kernel this
 // replaces): 12288 x 4096 421 -> 312 us (1.32 PFLOP/s), 4096 x 4096 123 -> 107 us (1.28), 4096 x 11008 308 -> 259 us
-// (1.43).  Tried: weights straight into registers (1.03 - 1.24 PFLOP/s), four wavefronts of 128 x 128 (0.6 - 1.27).
+// (1.43).  Tried and slower: weights straight into registers (1.25 - 1.39 PFLOP/s over the same three), four wavefronts of
+// 128 x 128 (0.9 - 1.27), a ring of four or five stages of 32 columns (1.20 - 1.26).
 //
 // Workgroups are numbered so that those of one XCD (every eighth) work on blocks of 4 weight tiles x 8 token tiles at a
 // time, and results that no L2 can hold leave it alone (nontemporal stores): 361 -> 312 us at 12288 x 4096.
@@ -725,14 +730,19 @@ hipError_t gemm_tile_prepare() {
   hipError_t e = allow_tiles<EPI_F32>();
   if (e == hipSuccess) e = allow_tiles<EPI_SILU>();
   if (e == hipSuccess) e = allow_tiles<EPI_QKV>();
+  if (e == hipSuccess) e = allow_tiles<EPI_QKV_TAIL>();
   return e;
 }
 
-// A split pays for its partial sums: written and read once more at 4 bytes each, about 5 TB/s.
+// A split pays for its partial sums, written in a burst at the end of the kernel and read by the next one: 1.6 us a million
+// while the memory-side cache holds them beside the operands (2048 rows of 4096 features over 11008 columns: 172 us
+// without, 135 in two splits; 512 rows: 128, 71, and 53 in four), and more than any split saves beyond 64 MB of them (1987
+// rows of 5120 features over 13824 columns: 271 us without, 299 and 319 in two and three).
 int gemm_wide_splits(int M, int N, int K) {
   int best = 1;
   float best_us = tile_us(kTileCosts[best_tile(M, N, K, 1)], M, N, K, 1);
   for (int sp = 2; sp <= kMaxSplitK && packed_cols(K) / 64 / sp >= 8; ++sp) {      // at least 512 columns per split
+    if ((size_t)sp * M * N * sizeof(float) > ((size_t)64 << 20)) break;
     const float us = tile_us(kTileCosts[best_tile(M, N, K, sp)], M, N, K, sp) + (float)sp * (float)M * (float)N * 1.6e-6f;
     if (us < best_us) { best = sp; best_us = us; }
   }
@@ -746,6 +756,7 @@ hipError_t launch_gemm_wide_silu(const void* a, PackedW w, int M, void* act, hip
   return launch_wide<EPI_SILU>(a, w, M, act, 1, QkvEpilogue{}, rs, s);
 }
 hipError_t launch_gemm_wide_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s, RowScale rs) {
+  if (qe.tail_kc) return launch_wide<EPI_QKV_TAIL>(a, w, M, nullptr, 1, qe, rs, s);
   return launch_wide<EPI_QKV>(a, w, M, nullptr, 1, qe, rs, s);
 }
 

@@ -813,14 +813,14 @@ hipError_t launch_tree_dynamic(const int32_t* root, const int32_t* cand, const f
 }
 
 // ---- distillation term of the training stage (Sec. 3.3)
-// kl[p] = KL(softmax(z[row_a + p]) || softmax(z[row_b + p])) = sum_v A_v (log A_v - log B_v) for pairs p of logit
+// kl[p] = KL(softmax(za[p]) || softmax(zb[p])) = sum_v A_v (log A_v - log B_v) for pairs p of logit
 // rows.  One block of 1024 threads per pair: the two maxima, then the two sums of exponentials and the A-weighted sum
 // of the shifted logit differences in one more pass.
-__global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__ z, int row_a, int row_b, int V, int vec,
+__global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__ za_all, const float* __restrict__ zb_all, int V, int vec,
                                                        float* __restrict__ kl) {
   __shared__ float red[16];
-  const float* za = z + (size_t)(row_a + blockIdx.x) * V;
-  const float* zb = z + (size_t)(row_b + blockIdx.x) * V;
+  const float* za = za_all + (size_t)blockIdx.x * V;
+  const float* zb = zb_all + (size_t)blockIdx.x * V;
   const int v4 = vec ? (V & ~3) : 0;
   float ma = -INFINITY, mb = -INFINITY;
   for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {
@@ -857,9 +857,9 @@ __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__
   cross = block_sum_any(cross, red);
   if (threadIdx.x == 0) kl[blockIdx.x] = cross / sa - logf(sa) + logf(sb);
 }
-hipError_t launch_kl_rows(const float* z, int row_a, int row_b, int pairs, int V, float* kl, hipStream_t s) {
-  const int vec = !((uintptr_t)z & 15) && !(V & 3);
-  hipLaunchKernelGGL(kl_rows_kernel, dim3(pairs), dim3(1024), 0, s, z, row_a, row_b, V, vec, kl);
+hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, float* kl, hipStream_t s) {
+  const int vec = !((uintptr_t)za & 15) && !((uintptr_t)zb & 15) && !(V & 3);
+  hipLaunchKernelGGL(kl_rows_kernel, dim3(pairs), dim3(1024), 0, s, za, zb, V, vec, kl);
   return hipGetLastError();
 }
 
