@@ -1465,8 +1465,8 @@ int ht_tree_attention(const void* q, const void* k_new, const void* v_new, void*
   }
   const void* qq = q;
   if (k_new) {
-    HT_HIP(launch_rope_table(a.cs, a.depth, n, T, hd, rope_base, s));
-    HT_HIP(launch_rope_append_split(dtype, q, k_new, v_new, a.cs, a.q_rot, k_cache, v_cache, n, T, Hq, Hkv, hd, cap, s));
+    HT_HIP(launch_rope_append_split(dtype, q, k_new, v_new, a.depth, rope_base, a.cs, a.q_rot, k_cache, v_cache, n, T, Hq, Hkv, hd,
+                                    cap, s));
     qq = a.q_rot;
   }
   const char* env = getenv("HT_FORCE_SIMPLE");

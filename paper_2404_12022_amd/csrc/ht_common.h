@@ -123,9 +123,10 @@ hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int 
 hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const float* cs, void* q, void* kc, void* vc,
                               int n, int M, int Hq, int Hkv, int hd, int cap, bool paired, hipStream_t s,
                               const int32_t* n_dev = nullptr);
-hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const float* cs,
-                                    void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd, int cap,
-                                    hipStream_t s);
+// rows as they come from the caller, at positions n + depth[m]; `cs`: room for the factors of M rows
+hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const int32_t* depth,
+                                    float base, float* cs, void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd,
+                                    int cap, hipStream_t s);
 hipError_t launch_silu_mul(const float* gu, void* act, int M, int f, hipStream_t s);
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s);
 // cand[i] = top width[i % period + 1] entries of logit row src_row[i] (row i when src_row is NULL), i < rows;

@@ -252,18 +252,23 @@ hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_
 }
 
 // ------------------------------------------------------------------------------------------------ rotary
-// cs[m][j] = (cos, sin) of (n + depth[m]) * base^(-2j/hd), evaluated in fp64 and rounded once.
+// (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once
+__device__ inline double rope_inverse(int j, int half, float base) {
+  return exp(-(2.0 * (double)j / (double)(2 * half)) * log((double)base));
+}
+__device__ inline float2 rope_factor(int pos, double inv) {
+  double sn, cn;
+  sincos((double)pos * inv, &sn, &cn);
+  return make_float2((float)cn, (float)sn);
+}
+// cs[m][j]: the factors of row m at position n + depth[m]
 __global__ void rope_table_kernel(float2* __restrict__ cs, const int32_t* __restrict__ depth, int n, int half,
                                   float base, const int32_t* __restrict__ n_dev) {
   n = cache_len(n, n_dev);
   const int m = blockIdx.x;
   const int j = threadIdx.x;
   if (j >= half) return;
-  const double pos = (double)(n + (depth ? depth[m] : m));      // no depth table: row m at position n + m
-  const double inv = exp(-(2.0 * (double)j / (double)(2 * half)) * log((double)base));
-  double sn, cn;
-  sincos(pos * inv, &sn, &cn);
-  cs[(size_t)m * half + j] = make_float2((float)cn, (float)sn);
+  cs[(size_t)m * half + j] = rope_factor(n + (depth ? depth[m] : m), rope_inverse(j, half, base));   // no depth table: position n + m
 }
 hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int hd, float base, hipStream_t s,
                              const int32_t* n_dev) {
@@ -332,20 +337,33 @@ template <> __device__ inline void store4<bf16_t>(bf16_t* p, const float (&v)[4]
   *(uint2*)p = pack4_bf16(v[0], v[1], v[2], v[3]);
 }
 
-// One workgroup per (block of RB rows, head).  q and k heads: four feature pairs per thread and item, 16-byte loads,
+// One workgroup per (block of RB rows, head).  FRESH: it works the rotary factors of its rows out for itself, into LDS (one
+// launch instead of two where a call has no other use for the table).  q and k heads: four feature pairs per thread and item, 16-byte loads,
 // 8-byte stores.  v heads: the value cache is stored key-contiguous ([head][feature][slot]), so the rows go through LDS
 // and every wavefront stores one feature of up to 64 consecutive rows at a time (a 2-byte store per row and feature
 // straight from the row-major input touches a cache line of its own each).
-template <typename T, typename TIN>
+template <typename T, typename TIN, bool FRESH = false>
 __global__ __launch_bounds__(256) void rope_append_rows_kernel(
     const TIN* __restrict__ q_in, int q_stride, const TIN* __restrict__ k_in, int k_stride, const TIN* __restrict__ v_in,
     int v_stride, int nsplit, size_t split_stride, const float* __restrict__ cs, T* __restrict__ q, T* __restrict__ kc,
     T* __restrict__ vc, int n, int M, int RB, int Hq, int Hkv, int hd, int cap, int paired,
-    const int32_t* __restrict__ n_dev) {
+    const int32_t* __restrict__ n_dev, const int32_t* __restrict__ depth, float base) {
   extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];
   n = cache_len(n, n_dev);
   const int m0 = blockIdx.x * RB, hh = blockIdx.y, half = hd / 2;
   const int rows = M - m0 < RB ? M - m0 : RB;
+  float2* table = (float2*)rows_lds;                        // FRESH: [RB][half] (a v head's workgroup has no use for it)
+  if (FRESH && hh < Hq + Hkv) {
+    if (256 % half == 0) {                                  // a thread keeps its j
+      const int j = threadIdx.x % half;
+      const double inv = rope_inverse(j, half, base);
+      for (int r = threadIdx.x / half; r < rows; r += 256 / half) table[r * half + j] = rope_factor(n + depth[m0 + r], inv);
+    } else {
+      for (int i = threadIdx.x; i < rows * half; i += 256)
+        table[i] = rope_factor(n + depth[m0 + i / half], rope_inverse(i % half, half, base));
+    }
+    __syncthreads();
+  }
   if (hh < Hq + Hkv) {
     const int per_row = half / 4;                          // items of four feature pairs
     for (int item = threadIdx.x; item < rows * per_row; item += 256) {
@@ -365,7 +383,8 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) { a[i] += a2[i]; b[i] += b2[i]; }
       }
-      const float4 c01 = *(const float4*)(cs + ((size_t)m * half + j) * 2), c23 = *(const float4*)(cs + ((size_t)m * half + j) * 2 + 4);
+      const float* cr = FRESH ? (const float*)(table + (m - m0) * half + j) : cs + ((size_t)m * half + j) * 2;
+      const float4 c01 = *(const float4*)cr, c23 = *(const float4*)(cr + 4);
       const float c[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
       float ra[4], rb[4];
 #pragma unroll
@@ -415,7 +434,7 @@ hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const flo
     HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, float>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv),
                                                 dim3(256), lds, s, qkv, stride, qkv + (size_t)Hq * hd, stride,
                                                 qkv + (size_t)(Hq + Hkv) * hd, stride, nsplit, (size_t)M * stride, cs,
-                                                (T*)q, (T*)kc, (T*)vc, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev);)
+                                                (T*)q, (T*)kc, (T*)vc, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.f);)
     return hipGetLastError();
   }
   HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_kernel<T, float>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0,
@@ -425,18 +444,29 @@ hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const flo
                                               paired ? 1 : 0, n_dev);)
   return hipGetLastError();
 }
-hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const float* cs,
-                                    void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd, int cap,
-                                    hipStream_t s) {
-  if (hd % 8 == 0) {
-    const int RB = rope_rows_per_block(dtype, hd);
-    const size_t lds = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2);
-    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, T>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv),
-                                                dim3(256), lds, s, (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd,
-                                                (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, RB, Hq,
-                                                Hkv, hd, cap, 0, nullptr);)
+hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const int32_t* depth,
+                                    float base, float* cs, void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd,
+                                    int cap, hipStream_t s) {
+  const int RB = rope_rows_per_block(dtype, hd), row_blocks = (M + RB - 1) / RB;
+  const dim3 grid(row_blocks, Hq + 2 * Hkv);
+#define HT_ROPE_ARGS                                                                                                        \
+  (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, \
+      RB, Hq, Hkv, hd, cap, 0, nullptr, depth, base
+  const size_t values = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2), factors = (size_t)RB * (hd / 2) * sizeof(float2);
+  // Factors worked out by every workgroup for itself as long as that is no more than two per compute unit (128 rows of 64
+  // q and k heads, the most: 5.0 + 3.3 us in two launches, 6.4 in one; 8 rows of 4 heads 2.8 + 2.9 and 3.5).
+  if (hd % 8 == 0 && row_blocks * (Hq + Hkv) <= 512) {
+    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, T, true>), grid, dim3(256),
+                                                values > factors ? values : factors, s, HT_ROPE_ARGS);)
     return hipGetLastError();
   }
+  const hipError_t e = launch_rope_table(cs, depth, n, M, hd, base, s);
+  if (e != hipSuccess) return e;
+  if (hd % 8 == 0) {
+    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, T>), grid, dim3(256), values, s, HT_ROPE_ARGS);)
+    return hipGetLastError();
+  }
+#undef HT_ROPE_ARGS
   HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_kernel<T, T>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0, s,
                                               (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in,
                                               Hkv * hd, 1, (size_t)0, (const float2*)cs, (T*)q, (T*)kc, (T*)vc, n, Hq, Hkv, hd,
@@ -674,18 +704,36 @@ hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev t
 
 // ---- tree chosen from the draft distributions
 // lp[i][r] = log-softmax value of candidate r of draft row i:  z - (max + log(sum exp(z - max))) over the whole row.
-// One block of 1024 threads per row; 16-byte loads when the row allows.
+// One block of 1024 threads per row, few rows: bound by what one compute unit takes in, so rows of up to 32768 floats
+// (KEEP) are read once and stay in registers between the maximum and the sum (3 rows of 32000: 8.1 -> 6.6 us).
+constexpr int kLogprobKeep = 8;               // 16-byte pieces of a row a thread keeps
+template <bool KEEP>
 __global__ __launch_bounds__(1024) void cand_logprob_kernel(const float* __restrict__ d, const int32_t* __restrict__ cand,
                                                             int b, int V, int vec, float* __restrict__ lp) {
   __shared__ float red[16];
   const float* row = d + (size_t)blockIdx.x * V;
   const int v4 = vec ? (V & ~3) : 0;
+  // the candidates' own values are on their way while the row is summed up
+  const float own = (int)threadIdx.x < b ? row[cand[blockIdx.x * kMaxTopK + threadIdx.x]] : 0.f;
   float peak = -INFINITY;
-  for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {
-    const float4 q = *(const float4*)(row + j);
-    peak = fmaxf(fmaxf(peak, fmaxf(q.x, q.y)), fmaxf(q.z, q.w));
+  float4 keep[KEEP ? kLogprobKeep : 1];
+  if (KEEP) {
+#pragma unroll
+    for (int i = 0; i < kLogprobKeep; ++i) {
+      const int j = (i * 1024 + threadIdx.x) * 4;
+      if (j < V) keep[i] = *(const float4*)(row + j);
+    }
+#pragma unroll
+    for (int i = 0; i < kLogprobKeep; ++i)
+      if ((i * 1024 + (int)threadIdx.x) * 4 < V)
+        peak = fmaxf(fmaxf(peak, fmaxf(keep[i].x, keep[i].y)), fmaxf(keep[i].z, keep[i].w));
+  } else {
+    for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {
+      const float4 q = *(const float4*)(row + j);
+      peak = fmaxf(fmaxf(peak, fmaxf(q.x, q.y)), fmaxf(q.z, q.w));
+    }
+    for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) peak = fmaxf(peak, row[j]);
   }
-  for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) peak = fmaxf(peak, row[j]);
   peak = wave_max(peak);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = peak;
@@ -693,18 +741,25 @@ __global__ __launch_bounds__(1024) void cand_logprob_kernel(const float* __restr
   peak = red[0];
   for (int w = 1; w < (int)(blockDim.x >> 6); ++w) peak = fmaxf(peak, red[w]);
   float sum = 0.f;
-  for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {      // second pass: the row is in L2 now
-    const float4 q = *(const float4*)(row + j);
-    sum += (expf(q.x - peak) + expf(q.y - peak)) + (expf(q.z - peak) + expf(q.w - peak));
+  auto four = [&](const float4& q) { sum += (expf(q.x - peak) + expf(q.y - peak)) + (expf(q.z - peak) + expf(q.w - peak)); };
+  if (KEEP) {
+#pragma unroll
+    for (int i = 0; i < kLogprobKeep; ++i)
+      if ((i * 1024 + (int)threadIdx.x) * 4 < V) four(keep[i]);
+  } else {
+    for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) four(*(const float4*)(row + j));      // the row is in L2 now
+    for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) sum += expf(row[j] - peak);
   }
-  for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) sum += expf(row[j] - peak);
   sum = block_sum_any(sum, red);
   const float lse = peak + logf(sum);
-  if ((int)threadIdx.x < b) lp[blockIdx.x * kMaxTopK + threadIdx.x] = row[cand[blockIdx.x * kMaxTopK + threadIdx.x]] - lse;
+  if ((int)threadIdx.x < b) lp[blockIdx.x * kMaxTopK + threadIdx.x] = own - lse;
 }
 hipError_t launch_cand_logprob(const float* d, const int32_t* cand, int rows, int b, int V, float* lp, hipStream_t s) {
   const int vec = !((uintptr_t)d & 15) && !(V & 3);
-  hipLaunchKernelGGL(cand_logprob_kernel, dim3(rows), dim3(1024), 0, s, d, cand, b, V, vec, lp);
+  if (vec && V <= 4096 * kLogprobKeep)
+    hipLaunchKernelGGL(cand_logprob_kernel<true>, dim3(rows), dim3(1024), 0, s, d, cand, b, V, vec, lp);
+  else
+    hipLaunchKernelGGL(cand_logprob_kernel<false>, dim3(rows), dim3(1024), 0, s, d, cand, b, V, vec, lp);
   return hipGetLastError();
 }
 
@@ -713,10 +768,13 @@ hipError_t launch_cand_logprob(const float* d, const int32_t* cand, int rows, in
 // A node never scores above its parent or its previous sibling, and each of the two comes first in that order, so
 // the order is produced by a best-first walk: the frontier holds, for every node taken so far, its next sibling
 // and (once) its first child; the best frontier entry becomes the next node.  The frontier never holds more than
-// T <= 128 entries: slot j lives in the registers of lane j % 64 (two slots per lane), a round is one wave-wide
-// maximum of the lanes' best scores, a ballot that names the winner (a second reduction over depth and path only
-// when several lanes hold the best score), and register updates in two lanes: no barrier and no memory traffic
-// inside the walk but the log-probability table in LDS.  Tables and tokens are written by all lanes at the end.
+// T <= 128 entries: slot j lives in the registers of lane j % 64 (one slot per lane up to T = 64, else two), a round is
+// one wave-wide maximum of the lanes' best scores, a ballot that names the winner (a second reduction over depth and path
+// only when several lanes hold the best score), and register updates in two lanes.  What bounds it is the chain of
+// dependent instructions from one round to the next, so nothing on it waits for memory: the score of every entry's next
+// sibling is at hand before the entry wins (its table read has until the entry wins again), and the best candidate of
+// every level, which a first child adds, sits in a register of the lane of that number.  T = 64, k = 3: 27.6 us with
+// the table reads on the chain and two slots throughout, 21.5 us.  Tables and tokens are written by all lanes at the end.
 __device__ inline float not_nan(float v) { return v == v ? v : -INFINITY; }
 
 // (depth, path) order of two frontier entries with equal scores
@@ -724,6 +782,7 @@ __device__ inline bool tie_first(int depth_a, uint64_t path_a, int depth_b, uint
   return depth_a != depth_b ? depth_a < depth_b : path_a < path_b;
 }
 
+template <int SLOTS>
 __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restrict__ root, const int32_t* __restrict__ cand,
                                                           const float* __restrict__ lp, int k, int b, int T,
                                                           TreeOut tree, int32_t* __restrict__ tok) {
@@ -731,10 +790,20 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
   __shared__ int cand_s[kMaxTransfer * kMaxTopK];
   __shared__ int n_parent[kMaxTree], n_depth[kMaxTree], n_rank[kMaxTree];
   const int lane = threadIdx.x;
-  for (int i = lane; i < k * kMaxTopK; i += 64) {
-    const bool used = i % kMaxTopK < b;
-    lp_s[i] = used ? not_nan(lp[i]) : -INFINITY;
-    cand_s[i] = used ? cand[i] : 0;
+  static_assert(kMaxTopK == 64, "one table entry of a level per lane");
+  float lv[kMaxTransfer];
+  int cv[kMaxTransfer];
+#pragma unroll
+  for (int e = 0; e < kMaxTransfer; ++e) {         // all levels in one round trip; entries not in use read entry 0
+    const int i = e < k && lane < b ? e * kMaxTopK + lane : 0;
+    lv[e] = lp[i];
+    cv[e] = cand[i];
+  }
+  const int root_tok = *root;
+#pragma unroll
+  for (int e = 0; e < kMaxTransfer; ++e) {
+    lp_s[e * kMaxTopK + lane] = e < k && lane < b ? not_nan(lv[e]) : -INFINITY;
+    cand_s[e * kMaxTopK + lane] = cv[e];
   }
   for (int v = lane; v < kMaxTree; v += 64) {      // rows the walk does not reach (none, if the sizes were checked) hang under the root
     n_parent[v] = v ? 0 : -1;
@@ -742,19 +811,30 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
     n_rank[v] = 0;
   }
   __syncthreads();
-  // frontier slot: score, score of the parent, depth (0: empty), parent node, path = ranks from the root down, 6 bits
-  // each, the last rank in the lowest digit
-  float fs0 = -INFINITY, fs1 = -INFINITY, fb0 = 0.f, fb1 = 0.f;
-  int fd0 = 0, fd1 = 0, fp0 = 0, fp1 = 0;
-  uint64_t fq0 = 0, fq1 = 0;
-  if (lane == 0) { fs0 = lp_s[0]; fd0 = 1; }      // first candidate of the first level, under the root
+  const float first = lane < k ? lp_s[lane * kMaxTopK] : 0.f;         // lane e: the best candidate of level e + 1
+  // frontier slot: score, score of its next sibling, score of the parent, depth (0: empty), parent node,
+  // path = ranks from the root down, 6 bits each, the last rank in the lowest digit
+  float fs[SLOTS], fn[SLOTS], fb[SLOTS];
+  int fd[SLOTS], fp[SLOTS];
+  uint64_t fq[SLOTS];
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    fs[i] = fn[i] = -INFINITY;
+    fb[i] = 0.f;
+    fd[i] = fp[i] = 0;
+    fq[i] = 0;
+  }
+  const float top_lp = lp_s[0], next_lp = lp_s[1];
+  if (lane == 0) { fs[0] = top_lp; fn[0] = next_lp; fd[0] = 1; }      // first candidate of the first level, under the root
   int count = 1;
   for (int v = 1; v < T; ++v) {
-    const bool second = fd1 != 0 && (fd0 == 0 || fs1 > fs0 || (fs1 == fs0 && tie_first(fd1, fq1, fd0, fq0)));
-    const float s = second ? fs1 : fs0;
-    const int d = second ? fd1 : fd0;
-    const uint64_t q = second ? fq1 : fq0;
-    const int par_l = second ? fp1 : fp0;
+    const bool second = SLOTS == 2 && fd[SLOTS - 1] != 0 &&
+                        (fd[0] == 0 || fs[SLOTS - 1] > fs[0] ||
+                         (fs[SLOTS - 1] == fs[0] && tie_first(fd[SLOTS - 1], fq[SLOTS - 1], fd[0], fq[0])));
+    const float s = second ? fs[SLOTS - 1] : fs[0];
+    const int d = second ? fd[SLOTS - 1] : fd[0];
+    const uint64_t q = second ? fq[SLOTS - 1] : fq[0];
+    const int par_l = second ? fp[SLOTS - 1] : fp[0];
     const float best = wave_max_dpp(d ? s : -INFINITY);
     const bool top = d != 0 && s == best;
     uint64_t tied = __ballot(top);
@@ -772,22 +852,34 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
     const int win = __builtin_amdgcn_readfirstlane(__builtin_ctzll(tied));
     const int depth = __builtin_amdgcn_readlane(d, win);
     const int par = __builtin_amdgcn_readlane(par_l, win);
-    const float score = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), win));
     const uint64_t path = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(q >> 32), win) << 32 |
                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)q, win);
     const int r = (int)(path & 63);
-    if (lane == 0) { n_parent[v] = par; n_depth[v] = depth; n_rank[v] = r; }
     if (lane == win) {                             // the next sibling takes the slot over
-      const bool more = r + 1 < b;
-      const float sib = more ? lp_s[(depth - 1) * kMaxTopK + r + 1] : 0.f;
-      if (second) { fs1 = fb1 + sib; fq1 += 1; fd1 = more ? fd1 : 0; }
-      else { fs0 = fb0 + sib; fq0 += 1; fd0 = more ? fd0 : 0; }
+#pragma unroll
+      for (int i = 0; i < SLOTS; ++i)
+        if (SLOTS == 1 || second == (i == 1)) {
+          fs[i] = fn[i];
+          fq[i] += 1;
+          fd[i] = r + 1 < b ? depth : 0;
+          if (r + 2 < b) fn[i] = fb[i] + lp_s[(depth - 1) * kMaxTopK + r + 2];
+        }
+      n_parent[v] = par;
+      n_depth[v] = depth;
+      n_rank[v] = r;
     }
     if (depth < k) {                               // the first child goes to a new slot
       if (lane == (count & 63)) {
-        const float cs = score + lp_s[depth * kMaxTopK];
-        if (count >> 6) { fs1 = cs; fb1 = score; fd1 = depth + 1; fp1 = v; fq1 = path << 6; }
-        else { fs0 = cs; fb0 = score; fd0 = depth + 1; fp0 = v; fq0 = path << 6; }
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i)
+          if (SLOTS == 1 || (count >> 6) == i) {
+            fs[i] = best + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(first), depth));
+            fb[i] = best;
+            fd[i] = depth + 1;
+            fp[i] = v;
+            fq[i] = path << 6;
+            fn[i] = best + lp_s[depth * kMaxTopK + 1];
+          }
       }
       ++count;
     }
@@ -798,7 +890,7 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
     tree.parent[v] = n_parent[v];
     tree.depth[v] = depth;
     tree.rank[v] = r;
-    tok[v] = v ? cand_s[(depth - 1) * kMaxTopK + r] : *root;
+    tok[v] = v ? cand_s[(depth - 1) * kMaxTopK + r] : root_tok;
     uint64_t mask[kMaskWords];
     for (int w = 0; w < kMaskWords; ++w) mask[w] = 0;
     for (int u = v, hop = 0; u >= 0 && hop <= kMaxTransfer; u = n_parent[u], ++hop)
@@ -808,7 +900,8 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
 }
 hipError_t launch_tree_dynamic(const int32_t* root, const int32_t* cand, const float* lp, int k, int b, int T,
                                TreeOut tree, int32_t* tok, hipStream_t s) {
-  hipLaunchKernelGGL(tree_dynamic_kernel, dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
+  if (T <= 64) hipLaunchKernelGGL(tree_dynamic_kernel<1>, dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
+  else hipLaunchKernelGGL(tree_dynamic_kernel<2>, dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
   return hipGetLastError();
 }
 
