@@ -313,7 +313,7 @@ int run_blocks_f32(ht_model* m, const TreeDev& tree, int M, int layer_from, int 
                                b.transfer_scratch, s));
         M += F * cnt;
       } else {
-        HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));
+        if (M > 0) HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));   // else: in b.x already
         M += cnt;
       }
     }
@@ -346,12 +346,17 @@ int run_blocks_f32(ht_model* m, const TreeDev& tree, int M, int layer_from, int 
   return HT_OK;
 }
 
-// Rows already in b.x (M of them, possibly none) go through blocks layer_from+1 .. L (0-based index
+// M rows (possibly none) go through blocks layer_from+1 .. L (0-based index
 // layer_from .. L-1) together with the rows that join on the way, then the final norm and, if `logits` is given,
 // the LM head and the row arg-max.  `tree` must describe all rows the pass ends with.
 // layer_end >= 0: the pass stops after block layer_end (0-based index layer_end - 1) and leaves the finished residual
 // rows in b.x (no final norm, no logits).
-int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_hidden, float* logits, int32_t* gout,
+// `from`: where the M rows come from, tokens for the embedding table or fp32 rows (b.x itself is fine).
+struct PassStart {
+  const int32_t* tok;
+  const float* rows;
+};
+int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_from, bool save_hidden, float* logits, int32_t* gout,
              hipStream_t s, JoinMode join = kNoJoin, int F = 0, int step = 0, int layer_end = -1) {
   const ht_config& c = m->cfg;
   Buffers& b = m->b;
@@ -361,7 +366,12 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
   const int n = m->n;
   int rc;
   const int joining = join == kFromTree ? F * c.k : join == kFromBuffer ? c.k : join == kTrainStep ? F : 0;
-  HT_HIP(launch_rope_table(b.cs, tree.depth, n, M + joining, c.head_dim, c.rope_base, s, m->n_dev));
+  // the rows of b.pseudo that join in front of the first block of a pass without rows of its own come in with the start
+  const bool joins_first = join == kFromBuffer && M == 0 && m->slot_of_layer[layer_from] >= 0;
+  if (joins_first) from = PassStart{nullptr, b.pseudo + (size_t)m->slot_first[m->slot_of_layer[layer_from]] * d};
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, from.tok, from.rows, b.x,
+                           joins_first ? m->slot_count[m->slot_of_layer[layer_from]] : M, d, b.cs, tree.depth, n, M + joining,
+                           c.head_dim, c.rope_base, s, m->n_dev));
   int pending = 0;
   // Residual add + RMSNorm.  On packed weights the row is split over kNormParts workgroups (one workgroup per row
   // takes in its 80 KB at the pace of a single compute unit) and the 1/rms factor moves into the epilogue of the
@@ -408,7 +418,7 @@ int run_pass(ht_model* m, const TreeDev& tree, int M, int layer_from, bool save_
                                cnt, d, b.transfer_scratch, s));
       } else {
         extra = cnt;
-        HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));
+        if (M > 0) HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));   // else: in b.x already
       }
       HT_HIP(add_norm(b.x + (size_t)M * d, 0, 0, m->attn_norm[l], (char*)b.u + (size_t)M * d * es, nullptr,
                       b.ss + (size_t)M * kNormParts, extra));
@@ -486,8 +496,8 @@ int prompt_pass(ht_model* m, int start, int rows, bool last, hipStream_t s) {
     return sp;
   };
   const int o_splits = splits(qd), down_splits = splits(f);
-  HT_HIP(launch_embed(c.dtype, m->tok_emb, b.prompt + start, p.x, rows, d, s));
-  HT_HIP(launch_rope_table(p.cs, nullptr, start, rows, c.head_dim, c.rope_base, s));
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, b.prompt + start, nullptr, p.x, rows, d, p.cs, nullptr, start, rows, c.head_dim,
+                           c.rope_base, s));
   int pending = 0;
   for (int l = 0; l < c.n_layers; ++l) {
     HT_HIP(launch_add_norm_parts(p.x, p.part, pending, pstride, m->attn_norm[l], p.u, nullptr, p.ss, rows, d, s));
@@ -917,8 +927,7 @@ int ht_prefill(ht_model* m, const int32_t* tokens, int32_t n, void* stream) {
   for (int start = 0; start < n; start += chunk) {
     const int rows = n - start < chunk ? n - start : chunk;
     const bool last = start + rows == n;
-    HT_HIP(launch_embed(c.dtype, m->tok_emb, m->b.prompt + start, m->b.x, rows, c.d_model, s));
-    if ((rc = run_pass(m, chain, rows, 0, true, last ? m->b.logits : nullptr, m->b.g, s))) return rc;
+    if ((rc = run_pass(m, chain, PassStart{m->b.prompt + start, nullptr}, rows, 0, true, last ? m->b.logits : nullptr, m->b.g, s))) return rc;
     if (last)
       HT_HIP(launch_prefill_finish(m->b.state, m->b.g, m->b.saved_h, (size_t)m->Mp * c.d_model, (int)m->slot_layer.size(),
                                    m->b.h_src, rows - 1, c.d_model, s));
@@ -965,8 +974,7 @@ int ht_training_forward(ht_model* m, int32_t step, const int32_t* tokens, int32_
   for (int b0 = 0; b0 < n; b0 += 2 * C) {
     const int low = n - b0 < 2 * C + step ? n - b0 : 2 * C + step;
     m->n = b0;
-    HT_HIP(launch_embed(c.dtype, m->tok_emb, b.prompt + b0, b.x, low, c.d_model, s));
-    if (t > 0 && (rc = run_pass(m, b.chain.dev(), low, 0, false, nullptr, nullptr, s, kNoJoin, 0, 0, t))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), PassStart{b.prompt + b0, nullptr}, low, 0, false, nullptr, nullptr, s, kNoJoin, 0, 0, t))) return rc;
     HT_HIP(launch_load_rows(b.x, b.saved_h, low, c.d_model, s));
     for (int c0 = b0; c0 < n && c0 < b0 + 2 * C; c0 += C) {
       const int real = n - c0 < C + step ? n - c0 : C + step;
@@ -992,8 +1000,7 @@ int ht_training_forward(ht_model* m, int32_t step, const int32_t* tokens, int32_
         shape_pseudo = pseudo;
       }
       m->n = c0;
-      HT_HIP(launch_load_rows(b.saved_h + (size_t)(c0 - b0) * c.d_model, b.x, real, c.d_model, s));
-      if ((rc = run_pass(m, b.train.dev(), real, t, false, b.logits, nullptr, s, pseudo ? kTrainStep : kNoJoin, pseudo,
+      if ((rc = run_pass(m, b.train.dev(), PassStart{nullptr, b.saved_h + (size_t)(c0 - b0) * c.d_model}, real, t, false, b.logits, nullptr, s, pseudo ? kTrainStep : kNoJoin, pseudo,
                          step - 1)))
         return rc;
       int pairs = terms - c0;
@@ -1115,8 +1122,7 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
   HT_HIP(launch_repack(WeightSegs{{m->w_transfer[step - 1], nullptr, nullptr}, {d, 0, 0}, 1}, d, 0, 0, w.w_transfer, s));
   const PackedW p_transfer{(const bf16_t*)w.w_transfer, d, d, packed_cols(d)};
 
-  HT_HIP(launch_embed(c.dtype, m->tok_emb, b.prompt, w.x, n, d, s));
-  HT_HIP(launch_rope_table(w.cs, nullptr, 0, n + 1, c.head_dim, c.rope_base, s));
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, b.prompt, nullptr, w.x, n, d, w.cs, nullptr, 0, n + 1, c.head_dim, c.rope_base, s));
   int rows = n, pending = 0;
   const TreeDev chain = b.chain.dev();
   auto splits = [&](int r, int K) {            // w.part holds 2 n rows
@@ -1246,17 +1252,17 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
   } else {
     // draft: pseudo rows through blocks t+1..L as a chain at positions n, n+1, ..; their K/V land in
     // slots n.. and are overwritten by the verify pass below
-    if ((rc = run_pass(m, b.chain.dev(), 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), PassStart{nullptr, nullptr}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
     if ((rc = build_tree(m, s))) return rc;
   }
-  HT_HIP(launch_embed(c.dtype, m->tok_emb, b.tok, b.x, T, c.d_model, s));
+  const PassStart from{b.tok, nullptr};
   if (!fused) {
     float* z = logits_out ? logits_out : b.logits;
-    if ((rc = run_pass(m, b.tree.dev(), T, 0, true, z, b.g, s))) return rc;
+    if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, z, b.g, s))) return rc;
   } else {
     // rows T.. of the logits are the draft distributions of the fused nodes (k rows per node)
-    if ((rc = run_pass(m, b.tree.dev(), T, 0, true, b.logits, b.g, s, kFromTree, fused))) return rc;
+    if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, b.g, s, kFromTree, fused))) return rc;
     HT_HIP(launch_topk(b.logits + (size_t)T * c.vocab, b.cand_fused, b.width, b.topk_scratch, fused * c.k, c.k, b.fused_src,
                        c.vocab, s));
     if (logits_out)
@@ -1334,11 +1340,10 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
       HT_HIP(launch_transfer(c.dtype, b.h_src + (size_t)g * c.d_model, nullptr, 1, (const void* const*)b.wt_ptrs,
                              b.pseudo + (size_t)m->slot_first[g] * c.d_model, m->slot_first[g], m->slot_count[g], 0,
                              c.d_model, nullptr, s));
-    if ((rc = run_pass(m, b.chain.dev(), 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), PassStart{nullptr, nullptr}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
     if ((rc = build_tree(m, s))) return rc;
-    HT_HIP(launch_embed(c.dtype, m->tok_emb, b.tok, b.x, T, c.d_model, s));
-    if ((rc = run_pass(m, b.tree.dev(), T, 0, true, b.logits, b.g, s))) return rc;
+    if ((rc = run_pass(m, b.tree.dev(), PassStart{b.tok, nullptr}, T, 0, true, b.logits, b.g, s))) return rc;
     HT_HIP(launch_accept(b.state, b.tree.dev(), b.tok, b.g, T, s, b.log));
     HT_HIP(launch_compact(c.dtype, b.state, b.kc_ptrs, b.vc_ptrs, c.n_layers, 0, c.n_kv_heads, c.head_dim, c.max_cache,
                           b.saved_h, (size_t)m->Mp * c.d_model, slots, b.h_src, c.d_model, s, true));

@@ -100,7 +100,11 @@ struct WeightSegs {
 // ------------------------------------------------------------------------------------------------
 // launchers (definitions in the .hip files); all enqueue on `s` and return the launch status
 // ------------------------------------------------------------------------------------------------
-hipError_t launch_embed(int dtype, const void* emb, const int32_t* tok, float* x, int M, int d, hipStream_t s);
+// x[m] = emb[tok[m]], or rows_in[m] when tok is NULL, m < rows (0: none); cs[m] = rotary factors of position n + depth[m]
+// (n + m without depths), m < cs_rows
+hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, const float* rows_in, float* x, int rows, int d,
+                             float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
+                             const int32_t* n_dev = nullptr);
 hipError_t launch_load_rows(const float* src, float* x, int M, int d, hipStream_t s);
 // bf16 models that do not pack: x[m] += part[m] (nsplit 0 or 1); optional save; u[m] = rmsnorm(x[m]) * gain
 hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_stride, const void* gain,

@@ -589,6 +589,7 @@ hipError_t launch_rows(const bf16_t* ap, const PackedW& w, int rows, void* out, 
                        const QkvEpilogue& qe, const RowScale& rs, hipStream_t s) {
   if (rows <= 16) return launch_mt<1>(ap, w, rows, out, nsplit, epi, qe, rs, s);
   if (rows <= 32) return launch_mt<2>(ap, w, rows, out, nsplit, epi, qe, rs, s);
+  if (rows <= 48) return launch_mt<3>(ap, w, rows, out, nsplit, epi, qe, rs, s);
   if (rows <= 64) return launch_mt<4>(ap, w, rows, out, nsplit, epi, qe, rs, s);
   if (rows <= 80) return launch_mt<5>(ap, w, rows, out, nsplit, epi, qe, rs, s);   // a 64-node tree plus a few pseudo rows
   if (rows <= 96) return launch_mt<6>(ap, w, rows, out, nsplit, epi, qe, rs, s);

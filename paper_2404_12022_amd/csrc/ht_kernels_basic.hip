@@ -59,20 +59,6 @@ __device__ inline float block_max_256(float v, float* red) {
   return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// ------------------------------------------------------------------------------------------------ embed
-template <typename T>
-__global__ void embed_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok, float* __restrict__ x, int d) {
-  const int m = blockIdx.x;                     // blockIdx.y: which share of the row's columns
-  const T* row = emb + (size_t)tok[m] * d;
-  for (int c = blockIdx.y * blockDim.x + threadIdx.x; c < d; c += gridDim.y * blockDim.x)
-    x[(size_t)m * d + c] = Conv<T>::load(row + c);
-}
-hipError_t launch_embed(int dtype, const void* emb, const int32_t* tok, float* x, int M, int d, hipStream_t s) {
-  const int shares = d >= 2048 ? 4 : 1;         // a few workgroups per row: a row is one dependent round trip per pass
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(embed_kernel<T>, dim3(M, shares), dim3(256), 0, s, (const T*)emb, tok, x, d);)
-  return hipGetLastError();
-}
-
 __global__ void copy_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, size_t count) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) dst[i] = src[i];
@@ -108,15 +94,29 @@ hipError_t launch_convert_to_bf16(const float* src, void* dst, size_t count, hip
   return hipGetLastError();
 }
 
-__global__ void reduce_splits_kernel(const float* __restrict__ part, int nsplit, size_t stride, float* __restrict__ out) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Two passes over L2-sized data: bound by the latency of one round trip, so all splits of an element are requested before
+// the first is added, 16 bytes a lane where `out` is aligned (33 rows of 5120 in six splits: 4.3 us with 4-byte loads one
+// after the other).
+template <typename V>
+__global__ __launch_bounds__(256) void reduce_splits_kernel(const V* __restrict__ part, int nsplit, size_t stride, V* __restrict__ out) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= stride) return;
-  float v = part[i];
-  for (int sp = 1; sp < nsplit; ++sp) v += part[sp * stride + i];
+  V p[kMaxSplitK];
+#pragma unroll
+  for (int sp = 0; sp < kMaxSplitK; ++sp) p[sp] = part[(sp < nsplit ? sp : 0) * stride + i];
+  V v = p[0];
+#pragma unroll
+  for (int sp = 1; sp < kMaxSplitK; ++sp)
+    if (sp < nsplit) v += p[sp];
   out[i] = v;
 }
 hipError_t launch_reduce_splits(const float* part, int nsplit, size_t stride, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((stride + 255) / 256)), dim3(256), 0, s, part, nsplit, stride, out);
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  if (stride % 4 == 0 && !((uintptr_t)out & 15) && !((uintptr_t)part & 15))
+    hipLaunchKernelGGL(reduce_splits_kernel<float4v>, dim3((unsigned)((stride / 4 + 255) / 256)), dim3(256), 0, s,
+                       (const float4v*)part, nsplit, stride / 4, (float4v*)out);
+  else
+    hipLaunchKernelGGL(reduce_splits_kernel<float>, dim3((unsigned)((stride + 255) / 256)), dim3(256), 0, s, part, nsplit, stride, out);
   return hipGetLastError();
 }
 
@@ -273,6 +273,43 @@ __global__ void rope_table_kernel(float2* __restrict__ cs, const int32_t* __rest
 hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int hd, float base, hipStream_t s,
                              const int32_t* n_dev) {
   hipLaunchKernelGGL(rope_table_kernel, dim3(M), dim3(hd / 2), 0, s, (float2*)cs, depth, n, hd / 2, base, n_dev);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------ start of a pass
+// The rows of a pass that are there when it starts, from the embedding table (by token) or from a buffer of fp32 rows, and
+// the rotary factors of all rows it will end with, in one launch: workgroups 0 .. rows * shares - 1 copy, the others work
+// out factors (they do not depend on one another; a launch of its own for each was two latencies in a row).
+template <typename T>
+__global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok,
+                                                         const float* __restrict__ rows_in, float* __restrict__ x, int rows,
+                                                         int shares, int d, float2* __restrict__ cs, const int32_t* __restrict__ depth,
+                                                         int n, int cs_rows, int half, float base, const int32_t* __restrict__ n_dev) {
+  const int wg = blockIdx.x;
+  if (wg < rows * shares) {
+    const int m = wg / shares, part = wg % shares;          // part: which share of the row's columns
+    if (tok) {
+      const T* row = emb + (size_t)tok[m] * d;
+      for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = Conv<T>::load(row + c);
+    } else {
+      for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = rows_in[(size_t)m * d + c];
+    }
+    return;
+  }
+  n = cache_len(n, n_dev);
+  const int i = (wg - rows * shares) * 256 + threadIdx.x;
+  if (i >= cs_rows * half) return;
+  const int m = i / half, j = i % half;
+  cs[i] = rope_factor(n + (depth ? depth[m] : m), rope_inverse(j, half, base));
+}
+hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, const float* rows_in, float* x, int rows, int d,
+                             float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
+                             const int32_t* n_dev) {
+  const int shares = d >= 2048 ? 4 : 1;         // a few workgroups per row: a row is one dependent round trip per pass
+  const int groups = rows * shares + (cs_rows * (hd / 2) + 255) / 256;
+  if (!groups) return hipSuccess;
+  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(256), 0, s, (const T*)emb, tok, rows_in, x,
+                                              rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, base, n_dev);)
   return hipGetLastError();
 }
 
@@ -507,7 +544,11 @@ __device__ inline void block_best_any(float& v, int& i, float* sv, int* si) {
     if (better(sv[w], si[w], v, i)) { v = sv[w]; i = si[w]; }
 }
 
-// g[row] = arg-max of a logit row, lowest id on ties.  1024 threads per row, 16-byte loads.
+// g[row] = arg-max of a logit row, lowest id on ties.  1024 threads per row, 16-byte loads.  Few rows: bound by what one
+// compute unit takes in, so rows of up to 32768 floats (AHEAD) are requested whole before the first comparison (one row of
+// 32000: 7.0 us a piece at a time).
+constexpr int kArgmaxAhead = 8;               // 16-byte pieces per thread
+template <bool AHEAD>
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int V,
                                                       int vec) {
   __shared__ float sv[16];
@@ -515,22 +556,37 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
   const float* row = z + (size_t)blockIdx.x * V;
   float bv = -INFINITY;
   int bi = 0x7fffffff;
-  const int v4 = vec ? (V & ~3) : 0;            // vec: rows are 16-byte aligned
-  for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {
-    const float4 q = *(const float4*)(row + j);
+  auto four = [&](const float4& q, int j) {
     if (better(q.x, j, bv, bi)) { bv = q.x; bi = j; }
     if (better(q.y, j + 1, bv, bi)) { bv = q.y; bi = j + 1; }
     if (better(q.z, j + 2, bv, bi)) { bv = q.z; bi = j + 2; }
     if (better(q.w, j + 3, bv, bi)) { bv = q.w; bi = j + 3; }
+  };
+  if (AHEAD) {
+    float4 p[kArgmaxAhead];
+#pragma unroll
+    for (int i = 0; i < kArgmaxAhead; ++i) {
+      const int j = (i * 1024 + threadIdx.x) * 4;
+      p[i] = *(const float4*)(row + (j < V ? j : 0));
+    }
+#pragma unroll
+    for (int i = 0; i < kArgmaxAhead; ++i) {
+      const int j = (i * 1024 + threadIdx.x) * 4;
+      if (j < V) four(p[i], j);
+    }
+  } else {
+    const int v4 = vec ? (V & ~3) : 0;          // vec: rows are 16-byte aligned
+    for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) four(*(const float4*)(row + j), j);
+    for (int j = v4 + threadIdx.x; j < V; j += blockDim.x)
+      if (better(row[j], j, bv, bi)) { bv = row[j]; bi = j; }
   }
-  for (int j = v4 + threadIdx.x; j < V; j += blockDim.x)
-    if (better(row[j], j, bv, bi)) { bv = row[j]; bi = j; }
   block_best_any(bv, bi, sv, si);
   if (threadIdx.x == 0) g[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
 }
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s) {
   const int vec = !((uintptr_t)z & 15) && !(V & 3);
-  hipLaunchKernelGGL(argmax_kernel, dim3(M), dim3(1024), 0, s, z, g, V, vec);
+  if (vec && V <= 4096 * kArgmaxAhead) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, z, g, V, vec);
+  else hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, z, g, V, vec);
   return hipGetLastError();
 }
 
@@ -613,7 +669,9 @@ __device__ inline void wave_select(float (&v)[E], int (&id)[E], int b, float* ou
   }
 }
 
-template <int E, bool FINAL>
+// WHOLE: one stage over a row of up to 2048 entries (rows that short are over before a second launch has started).
+enum TopkStage { SLICE, FINAL, WHOLE };
+template <int E, int STAGE>
 __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict__ d, const float* __restrict__ sv_in,
                                                         const int32_t* __restrict__ si_in, float* __restrict__ sv_out,
                                                         int32_t* __restrict__ si_out, int32_t* __restrict__ cand,
@@ -625,7 +683,8 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
   const int b = width[i % period + 1];      // row i drafts the tree level i % period + 1
   if (b <= 0) return;                       // uniform over the block
   int lo, hi;
-  if (FINAL) { lo = 0; hi = kTopkSlices * b; }
+  if (STAGE == FINAL) { lo = 0; hi = kTopkSlices * b; }
+  else if (STAGE == WHOLE) { lo = 0; hi = V; }
   else {
     const int per = (V + kTopkSlices - 1) / kTopkSlices;
     lo = slice * per;
@@ -633,7 +692,7 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
   }
   const int quarter = (hi - lo + 3) / 4;
   const int w0 = lo + wave * quarter, w1 = w0 + quarter < hi ? w0 + quarter : hi;
-  const size_t base = FINAL ? (size_t)i * kTopkSlices * kMaxTopK : (size_t)(src_row ? src_row[i] : i) * V;
+  const size_t base = STAGE == FINAL ? (size_t)i * kTopkSlices * kMaxTopK : (size_t)(src_row ? src_row[i] : i) * V;
   float v[E];
   int id[E];
 #pragma unroll
@@ -642,8 +701,8 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
     v[e] = -INFINITY;
     id[e] = kNoEntry;
     if (j < w1) {
-      const float x = FINAL ? sv_in[base + j] : d[base + j];
-      const int xi = FINAL ? si_in[base + j] : j;
+      const float x = STAGE == FINAL ? sv_in[base + j] : d[base + j];
+      const int xi = STAGE == FINAL ? si_in[base + j] : j;
       if (x == x && xi != kNoEntry) { v[e] = x; id[e] = xi; }      // NaN never wins
     }
   }
@@ -659,7 +718,7 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
   }
   wave_select<4>(v2, id2, b, list_v[4], list_i[4]);
   if (lane < b) {                           // one wavefront: its LDS writes are ordered before these reads
-    if (FINAL) cand[i * kMaxTopK + lane] = list_i[4][lane] == kNoEntry ? 0 : list_i[4][lane];
+    if (STAGE != SLICE) cand[i * kMaxTopK + lane] = list_i[4][lane] == kNoEntry ? 0 : list_i[4][lane];
     else {
       sv_out[(size_t)i * kTopkSlices * kMaxTopK + slice * b + lane] = list_v[4][lane];
       si_out[(size_t)i * kTopkSlices * kMaxTopK + slice * b + lane] = list_i[4][lane];
@@ -678,13 +737,17 @@ hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void
   const int per_lane = (((V + kTopkSlices - 1) / kTopkSlices + 3) / 4 + 63) / 64;
   const dim3 g1(rows, kTopkSlices), g2(rows, 1);
 #define HT_TOPK_ARGS(in_v, in_i, out_v, out_i) d, in_v, in_i, out_v, out_i, cand, width, period, src_row, V
+  if (V <= 2048) {
+    hipLaunchKernelGGL((topk_wave_kernel<8, WHOLE>), g2, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, nullptr, nullptr));
+    return hipGetLastError();
+  }
   if (per_lane <= 4)
-    hipLaunchKernelGGL((topk_wave_kernel<4, false>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
+    hipLaunchKernelGGL((topk_wave_kernel<4, SLICE>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
   else if (per_lane <= 16)
-    hipLaunchKernelGGL((topk_wave_kernel<16, false>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
+    hipLaunchKernelGGL((topk_wave_kernel<16, SLICE>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
   else          // very large vocabularies: block-wide selection, any row length
     hipLaunchKernelGGL(topk_kernel<false>, g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
-  hipLaunchKernelGGL((topk_wave_kernel<8, true>), g2, dim3(256), 0, s, HT_TOPK_ARGS(sv, si, nullptr, nullptr));
+  hipLaunchKernelGGL((topk_wave_kernel<8, FINAL>), g2, dim3(256), 0, s, HT_TOPK_ARGS(sv, si, nullptr, nullptr));
 #undef HT_TOPK_ARGS
   return hipGetLastError();
 }

@@ -52,8 +52,8 @@ def test_token_tiled_product(M, N, K, splits):
     assert np.all(np.abs(got - O.linear(H.cpu(a), H.cpu(w))) <= bound(a, w, K))
 
 
-@pytest.mark.parametrize("M,N,K", [(129, 64, 64), (160, 4096, 1024), (193, 528, 2048), (256, 1040, 4104)])
-def test_packed_products_of_more_than_128_rows(M, N, K):
+@pytest.mark.parametrize("M,N,K", [(33, 4112, 1032), (47, 2064, 4096), (48, 208, 200), (129, 64, 64), (160, 4096, 1024), (193, 528, 2048), (256, 1040, 4104)])
+def test_packed_products_of_between_32_and_48_and_of_more_than_128_rows(M, N, K):
     """The public calls: plain product (with its K splits) and gate/up with SiLU."""
     import paper_2404_12022_amd.binding as B
     a, w = inputs(B.ht_padded_rows(M), N, K, 7 * M + N)
