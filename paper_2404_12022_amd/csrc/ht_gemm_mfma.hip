@@ -402,7 +402,7 @@ template <int WF, int WT, int MT> struct TileShape {
 template <int WF, int WT, int MT, int EPI>
 __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(
     const bf16_t* __restrict__ a, const bf16_t* __restrict__ wp, int M, int N, int K, int KS, void* __restrict__ outp,
-    QkvEpilogue qe, RowScale rs, int n_tiles, int m_tiles, int nsplit) {
+    QkvEpilogue qe, RowScale rs, int tile0, int n_tiles, int m_tiles, int nsplit) {
   using TS = TileShape<WF, WT, MT>;
   constexpr int R = TS::R, NW = TS::NW, NA = TS::NA, STAGE = TS::STAGE, WBYTES = TS::WBYTES;
   extern __shared__ __attribute__((aligned(1024))) unsigned char tile_lds[];
@@ -413,8 +413,9 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per_xcd = (n_tiles + 7) / 8;
   const int q = slot / (4 * m_tiles), rem = slot % (4 * m_tiles), nw = per_xcd - q * 4 < 4 ? per_xcd - q * 4 : 4;
   const int mg = rem / (8 * nw), in = rem % (8 * nw), mw = m_tiles - mg * 8 < 8 ? m_tiles - mg * 8 : 8;
-  const int tx = xcd + 8 * (q * 4 + in / mw), ty = mg * 8 + in % mw;
-  if (tx >= n_tiles) return;                             // uniform over the workgroup
+  const int tl = xcd + 8 * (q * 4 + in / mw), ty = mg * 8 + in % mw;
+  if (tl >= n_tiles) return;                             // uniform over the workgroup
+  const int tx = tile0 + tl;                             // the launch covers weight tiles tile0 .. tile0 + n_tiles - 1
   int c0, c1;
   even_share(KS / 2, nsplit, blockIdx.y, c0, c1);
   const int chunks = c1 - c0;
@@ -674,15 +675,16 @@ hipError_t allow_tile_lds() {
   return hipSuccess;
 }
 
+// Features [from, to) of the product, `from` a multiple of the tile.
 template <int WF, int WT, int MT, int EPI>
 hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
-                       hipStream_t s) {
+                       int from, int to, hipStream_t s) {
   using TS = TileShape<WF, WT, MT>;
-  const int n_tiles = (w.N + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
+  const int n_tiles = (to - from + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
   const hipError_t e = allow_tile_lds<WF, WT, MT, EPI>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gemm_tile_kernel<WF, WT, MT, EPI>), dim3(8 * ((n_tiles + 7) / 8) * m_tiles, nsplit), dim3(64 * TS::WAVES),
-                     TS::LDS_BYTES, s, a, w.p, M, w.N, w.K, w.Kp / 32, out, qe, rs, n_tiles, m_tiles, nsplit);
+                     TS::LDS_BYTES, s, a, w.p, M, w.N, w.K, w.Kp / 32, out, qe, rs, from / TS::FEATURES, n_tiles, m_tiles, nsplit);
   return hipGetLastError();
 }
 
@@ -714,9 +716,19 @@ hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int ns
                        hipStream_t s) {
   const bf16_t* ap = (const bf16_t*)a;
   switch (best_tile(M, w.N, w.K, nsplit)) {
-    case 0: return launch_tile<4, 2, 8, EPI>(ap, w, M, out, nsplit, qe, rs, s);
-    case 1: return launch_tile<2, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, s);
-    default: return launch_tile<2, 4, 4, EPI>(ap, w, M, out, nsplit, qe, rs, s);
+    case 0: {
+      // A last round that leaves half the chip or more without a tile: its features go in tiles of half the size, twice as
+      // many (2048 rows of 12288 features, 1.5 rounds: 222 us in one launch, 131 + 72 in two; 1987 of 27648 over 5120 columns,
+      // 3.4 rounds: 472 and 360 + 81).
+      const int m_tiles = (M + 255) / 256, n_tiles = (w.N + 255) / 256, whole = n_tiles * m_tiles / 256 * 256 / m_tiles;
+      if (nsplit == 1 && whole > 0 && whole < n_tiles && 2 * (n_tiles - whole) * m_tiles <= 256) {
+        const hipError_t e = launch_tile<4, 2, 8, EPI>(ap, w, M, out, 1, qe, rs, 0, whole * 256, s);
+        return e != hipSuccess ? e : launch_tile<2, 4, 4, EPI>(ap, w, M, out, 1, qe, rs, whole * 256, w.N, s);
+      }
+      return launch_tile<4, 2, 8, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    }
+    case 1: return launch_tile<2, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    default: return launch_tile<2, 4, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
   }
 }
 
