@@ -207,8 +207,8 @@ int gemm_mfma_splits(int M, int N, int K);
 // interleaved block by block (gate block i, up block i, gate block i+1, ..); mode 2: segments (q, k, v), in
 // every q and k head the 16-row block p is followed by its rotary partner block p + head_dim/32
 hipError_t launch_repack(WeightSegs w, int K, int mode, int head_dim, void* dst, hipStream_t s);
-// out[s][m][n], s < nsplit (split-K partial sums, fp32).  M <= kMaxRows; more than 128 rows run as two launches over
-// the same weights (rows 0..127, then the rest).
+// out[s][m][n], s < nsplit (split-K partial sums, fp32).  Up to 128 rows stream the weights, more run on the token-tiled
+// kernel.
 hipError_t launch_gemm_packed(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s,
                               RowScale rs = RowScale{});
 // w packed with mode 1 from (gate, up): act[m][j] = silu(a.gate_j) * (a.up_j), bf16 [M][N/2]

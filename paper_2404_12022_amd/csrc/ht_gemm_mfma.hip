@@ -392,6 +392,9 @@ __device__ __forceinline__ void lds_load16(const void* from, void* to) {
                                    0, 0);
 }
 
+// this wavefront's LDS-direct loads have landed and its LDS reads are done; then the others'
+__device__ __forceinline__ void tile_wait_then_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int WF, int WT, int MT> struct TileShape {
   static constexpr int R = 4, WAVES = WF * WT, FEATURES = WF * R * 16, TOKENS = WT * MT * 16;
   static constexpr int WBYTES = FEATURES * 128, STAGE = WBYTES + TOKENS * 128, LDS_BYTES = 2 * STAGE;
@@ -483,12 +486,13 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
   // it in a tail of their own cost registers that are not there)
   auto body = [&](int c, int st) __attribute__((always_inline)) {
     half(w0, b0, w1, b1, st, 1, std::false_type{}, 0, 0);
-    __syncthreads();                                     // waits for this wavefront's loads and reads, then for the others
+    tile_wait_then_barrier();
+    __builtin_amdgcn_sched_barrier(0);
     half(w1, b1, w0, b0, st ^ 1, 0, std::true_type{}, c + 2 < chunks ? c + 2 : chunks - 1, st);
   };
 #pragma unroll
   for (int i = 0; i < NW + NA; ++i) fetch(i, 0, 0);
-  __syncthreads();
+  tile_wait_then_barrier();
 #pragma unroll
   for (int i = 0; i < NW + NA; ++i) fetch(i, chunks > 1 ? 1 : 0, 1);
 #pragma unroll
@@ -501,7 +505,7 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
     body(c + 1, 1);
   }
   if (c < chunks) body(c, 0);
-  __syncthreads();                                       // nothing may still be writing LDS when the workgroup ends
+  tile_wait_then_barrier();                              // nothing may still be writing LDS when the workgroup ends
   const int rb0 = tx * WF * R + wf * R;
   float4 row_ss[MT];
   if (rs.ss) {
