@@ -411,13 +411,14 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
   extern __shared__ __attribute__((aligned(1024))) unsigned char tile_lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int wf = wave % WF, wt = wave / WF;
-  // workgroup id -> (weight tile, token tile): XCD x takes the weight tiles x, x + 8, .., four of them times eight token
-  // tiles after the other
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per_xcd = (n_tiles + 7) / 8;
-  const int q = slot / (4 * m_tiles), rem = slot % (4 * m_tiles), nw = per_xcd - q * 4 < 4 ? per_xcd - q * 4 : 4;
+  // workgroup id -> (weight tile, token tile): the tiles, four weight tiles wide times eight token tiles after the other,
+  // are dealt to the XCDs in eight runs of equal length.  (Whole weight tiles to an XCD left some with a tile more than
+  // their 32 units take in a round: 1500 rows of 10752 features, 252 tiles, took two rounds.)
+  const int per_xcd = (n_tiles * m_tiles + 7) / 8, at = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (at >= n_tiles * m_tiles) return;                   // uniform over the workgroup
+  const int q = at / (4 * m_tiles), rem = at % (4 * m_tiles), nw = n_tiles - q * 4 < 4 ? n_tiles - q * 4 : 4;
   const int mg = rem / (8 * nw), in = rem % (8 * nw), mw = m_tiles - mg * 8 < 8 ? m_tiles - mg * 8 : 8;
-  const int tl = xcd + 8 * (q * 4 + in / mw), ty = mg * 8 + in % mw;
-  if (tl >= n_tiles) return;                             // uniform over the workgroup
+  const int tl = q * 4 + in / mw, ty = mg * 8 + in % mw;
   const int tx = tile0 + tl;                             // the launch covers weight tiles tile0 .. tile0 + n_tiles - 1
   int c0, c1;
   even_share(KS / 2, nsplit, blockIdx.y, c0, c1);
@@ -687,7 +688,7 @@ hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int 
   const int n_tiles = (to - from + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
   const hipError_t e = allow_tile_lds<WF, WT, MT, EPI>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_tile_kernel<WF, WT, MT, EPI>), dim3(8 * ((n_tiles + 7) / 8) * m_tiles, nsplit), dim3(64 * TS::WAVES),
+  hipLaunchKernelGGL((gemm_tile_kernel<WF, WT, MT, EPI>), dim3(8 * ((n_tiles * m_tiles + 7) / 8), nsplit), dim3(64 * TS::WAVES),
                      TS::LDS_BYTES, s, a, w.p, M, w.N, w.K, w.Kp / 32, out, qe, rs, from / TS::FEATURES, n_tiles, m_tiles, nsplit);
   return hipGetLastError();
 }
@@ -702,10 +703,23 @@ hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int 
 struct TileCost { int features, tokens, per_unit; float chunk, chunk_alone, round; };
 constexpr TileCost kTileCosts[3] = {{256, 256, 1, 1.35f, 1.35f, 12.f}, {128, 128, 2, 1.05f, 0.75f, 2.f}, {128, 256, 1, 1.03f, 1.03f, 2.f}};
 
+// 256 x 256 tiles whose last round would leave half the chip or more without one: the weight tiles of the whole rounds;
+// the other features go in tiles of half the size, twice as many, and a second launch (2048 rows of 12288 features over
+// 4096 columns, 1.5 rounds: 199 us in one launch, 184 in two; 1164 of 15360 over 5120: 235 and 208; 1987 of 27648 over
+// 5120, 3.4 rounds: 517 and 501).  0: one launch.
+int whole_round_tiles(int M, int N, int nsplit) {
+  const int m_tiles = (M + 255) / 256, n_tiles = (N + 255) / 256, whole = (int)((long)n_tiles * m_tiles / 256 * 256 / m_tiles);
+  return nsplit == 1 && whole > 0 && whole < n_tiles && 2L * (n_tiles - whole) * m_tiles <= 256 ? whole : 0;
+}
+
 float tile_us(const TileCost& t, int M, int N, int K, int nsplit) {
-  const long groups = (long)((N + t.features - 1) / t.features) * ((M + t.tokens - 1) / t.tokens) * nsplit;
+  const int m_tiles = (M + t.tokens - 1) / t.tokens;
+  const long groups = (long)((N + t.features - 1) / t.features) * m_tiles * nsplit;
   const long slots = 256L * t.per_unit, whole = groups / slots, rest = groups % slots;
   const float chunks = (float)((packed_cols(K) / 64 + nsplit - 1) / nsplit);
+  if (&t == kTileCosts)
+    if (const int w = whole_round_tiles(M, N, nsplit))
+      return (float)((long)(w * m_tiles + 255) / 256) * (t.round + t.chunk * chunks) + kTileCosts[2].round + kTileCosts[2].chunk * chunks;
   return (float)whole * (t.round + t.chunk * chunks) + (rest ? t.round + (rest <= 256 ? t.chunk_alone : t.chunk) * chunks : 0.f);
 }
 int best_tile(int M, int N, int K, int nsplit) {
@@ -721,11 +735,7 @@ hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int ns
   const bf16_t* ap = (const bf16_t*)a;
   switch (best_tile(M, w.N, w.K, nsplit)) {
     case 0: {
-      // A last round that leaves half the chip or more without a tile: its features go in tiles of half the size, twice as
-      // many (2048 rows of 12288 features, 1.5 rounds: 222 us in one launch, 131 + 72 in two; 1987 of 27648 over 5120 columns,
-      // 3.4 rounds: 472 and 360 + 81).
-      const int m_tiles = (M + 255) / 256, n_tiles = (w.N + 255) / 256, whole = n_tiles * m_tiles / 256 * 256 / m_tiles;
-      if (nsplit == 1 && whole > 0 && whole < n_tiles && 2 * (n_tiles - whole) * m_tiles <= 256) {
+      if (const int whole = whole_round_tiles(M, w.N, nsplit)) {
         const hipError_t e = launch_tile<4, 2, 8, EPI>(ap, w, M, out, 1, qe, rs, 0, whole * 256, s);
         return e != hipSuccess ? e : launch_tile<2, 4, 4, EPI>(ap, w, M, out, 1, qe, rs, whole * 256, w.N, s);
       }

@@ -32,10 +32,11 @@ def bound(a, w, K):
     return (K / 32 + 16) * 2.0 ** -24 * np.abs(H.cpu(a)) @ np.abs(H.cpu(w)).T
 
 
-# rows, features and columns one below, at and one above the tiles of 64, 128 and 256, odd chunk counts, one chunk
+# rows, features and columns one below, at and one above the tiles of 64, 128 and 256, odd chunk counts, one chunk; the last:
+# 295 tiles of 256, dealt unevenly, the last 40 of them as tiles of half the size with 16 features in the last
 @pytest.mark.parametrize("M,N,K,splits", [(129, 16, 8, 1), (255, 240, 200, 1), (256, 256, 128, 1), (257, 272, 136, 1), (130, 144, 1032, 2),
                                           (300, 4112, 328, 1), (513, 128, 2056, 4), (1025, 528, 640, 1), (129, 2064, 4096, 8),
-                                          (2047, 1040, 192, 1)])
+                                          (2047, 1040, 192, 1), (1025, 14864, 2048, 1)])
 def test_token_tiled_product(M, N, K, splits):
     import paper_2404_12022_amd.binding as B
     a, w = inputs(M, N, K, M + N + K)
