@@ -1,6 +1,7 @@
 // Skinny weight-streaming product for bf16 on CDNA4 matrix cores.
 //
-//   out[m][n] = sum_k a[m][k] * w[n][k]        m < M <= 128 tokens, fp32 accumulate
+//   out[m][n] = sum_k a[m][k] * w[n][k]        m < M <= 128 tokens, fp32 accumulate (more rows: the
+//                                                              token-tiled kernel further down)
 //
 // The weights are the big operand (N x K, read from HBM exactly once per pass); the activations are
 // a small panel (M x K) that every workgroup re-reads from L2.  On v_mfma_f32_16x16x32_bf16 the weight

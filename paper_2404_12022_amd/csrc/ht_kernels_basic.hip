@@ -546,7 +546,7 @@ __device__ inline void block_best_any(float& v, int& i, float* sv, int* si) {
 
 // g[row] = arg-max of a logit row, lowest id on ties.  1024 threads per row, 16-byte loads.  Few rows: bound by what one
 // compute unit takes in, so rows of up to 32768 floats (AHEAD) are requested whole before the first comparison (one row of
-// 32000: 7.0 us a piece at a time).
+// 32000: 7.0 -> 5.2 us).
 constexpr int kArgmaxAhead = 8;               // 16-byte pieces per thread
 template <bool AHEAD>
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int V,
@@ -1301,7 +1301,7 @@ double launch_mfma_rate(int form, int iters, uint32_t* sink, hipStream_t s) {
 // One block per (query head, tree row).  Scores of all visible keys go to LDS (four lanes per key), softmax in fp32, then
 // every thread owns one output element and every (256 / hd)-th piece of VEC keys of it.  Dynamic LDS: (n + M) floats + hd
 // + 256.  Latency bound at the sizes it is used at (fp32 model, tens of keys): VEC elements per load cut the chains of
-// dependent loads, 5.5 -> 3.9 us for 8 rows of 4 heads over 40 keys of 64 floats.
+// dependent loads, 7.6 -> 5.1 us (mean; shortest 5.5 -> 4.2) for 8 rows of 4 heads over 40 keys of 64 floats.
 template <typename T, int VEC> __device__ inline void load_vec(const T* p, float (&v)[VEC]) {
   if constexpr (VEC == 1) {
     v[0] = Conv<T>::load(p);

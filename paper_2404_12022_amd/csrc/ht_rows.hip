@@ -10,7 +10,7 @@
 // products, the 1/rms factor multiplies the finished sums, the gain multiplies the weights.  Rotary and K/V append: a
 // wavefront owns the features j and j + hd/2 of a head.  SiLU(gate) * up: a wavefront owns gate and up row j.  The
 // residual add: every output element has one owner, which adds to the residual stream itself.  Five launches per decoder
-// block instead of nine.  At 256 x 256, 8 rows: 16.3 us (scalar loads, four rows a time) -> 2.6 us.
+// block instead of nine.  At 256 x 256, 8 rows: 16.3 us (scalar loads, four rows a time) -> 2.7 us (shortest 2.2).
 #include "ht_common.h"
 
 namespace ht {
