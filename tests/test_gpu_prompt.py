@@ -46,3 +46,44 @@ def test_a_second_prompt_replaces_the_first():
     assert all(torch.equal(x, y) for x, y in zip(want, got)) and torch.equal(root, gpu.ht_get_buffer(B.HT_BUF_ROOT))
     assert gpu.ht_cache_len() == 150
     gpu.close()
+
+
+def test_probabilities_of_a_long_causal_range_are_rounded_below_one():
+    """64 keys, then keys that score a little higher: relative to the first ones the later probabilities would be 1.0035 and
+    lose all of the .0035 in bf16; relative to the running maximum they are 1 and only the first ones (0.9965) are rounded."""
+    import ctypes as C
+    import torch
+    import paper_2404_12022_amd.binding as B
+
+    class Tree(C.Structure):
+        _fields_ = [(f, C.c_void_p) for f in ("parent", "depth", "rank", "anc")]
+
+    rows, Hq, Hkv, hd = 600, 2, 1, 128
+    cap = (rows + 7) // 8 * 8
+    q = torch.zeros(rows, Hq, hd, dtype=torch.bfloat16, device=H.DEV)
+    k = torch.zeros(cap, Hkv, hd, dtype=torch.bfloat16, device=H.DEV)
+    q[:, :, 0] = 1.0
+    k[:64, :, 0] = 1.0
+    k[64:, :, 0] = 1.0390625                           # exp(0.0390625 / sqrt(128)) = 1.00346
+    v = torch.ones(Hkv, hd, cap, dtype=torch.bfloat16, device=H.DEV)
+    v[:, 1] = 2.0
+    anc = torch.zeros(256, B.HT_MAX_ROWS // 64, dtype=torch.int64)
+    for r in range(256):                               # a chain: row r sees rows 0 .. r
+        for w in range(B.HT_MAX_ROWS // 64):
+            bits = min(max(r + 1 - 64 * w, 0), 64)
+            anc[r, w] = -1 if bits == 64 else (1 << bits) - 1
+    anc = anc.to(H.DEV)
+    out = torch.zeros(rows, Hq * hd, dtype=torch.bfloat16, device=H.DEV)
+    fn = getattr(B.lib, "_ZN2ht18launch_attn_causalEPKvS1_S1_iiiNS_7TreeDevEiiiPvP12ihipStream_tS1_S1_iS3_")
+    fn.restype = C.c_int
+    fn.argtypes = [C.c_void_p] * 3 + [C.c_int] * 3 + [Tree] + [C.c_int] * 3 + [C.c_void_p] * 4 + [C.c_int, C.c_void_p]
+    print("causal attention over 600 rows", flush=True)
+    assert fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), cap, 0, rows, Tree(None, None, None, anc.data_ptr()), Hq, Hkv, hd,
+              out.data_ptr(), torch.cuda.current_stream().cuda_stream, None, None, 0, None) == 0
+    torch.cuda.synchronize()
+    want = torch.ones(hd, dtype=torch.float64)
+    want[1] = 2.0
+    err = (out.cpu().double().view(rows, Hq, hd) / want - 1).abs().amax((1, 2))
+    # one bf16 rounding of the result (2^-9 relative) and of the probabilities of the first 64 keys (2^-9 of at most 1 each)
+    bound = 2.0 ** -9 * (1 + 64 / torch.arange(1, rows + 1, dtype=torch.float64))
+    assert bool((err <= bound).all()), (int((err - bound).argmax()), float(err.max()))
