@@ -57,6 +57,14 @@ __device__ inline void wave_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// The sum of the high pieces and that of the lower ones.  An infinite weight times a lower piece of zero is NaN where the
+// weight times the whole value is infinite: what the high pieces say stands when it is not finite.
+__device__ inline floatx4_t plus_lower(floatx4_t hi, floatx4_t lo) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hi[i] = __builtin_isfinite(hi[i]) ? hi[i] + lo[i] : hi[i];
+  return hi;
+}
+
 template <int NT, int R> struct TransferShape {
   static constexpr int TILES = NT ? NT : 1;
   static constexpr int SOURCES = NT ? NT * 16 : kSideBySide;         // sources a workgroup takes
@@ -247,7 +255,7 @@ __global__ __launch_bounds__(256) void transfer_split_kernel(const float* __rest
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
       floatx4_t v = hi[0][r][t] + hi[1][r][t];
-      if (NT) v += lo[NT ? r : 0][t];
+      if (NT) v = plus_lower(v, lo[NT ? r : 0][t]);
       red[((wave * R + r) * TILES + t) * 64 + lane] = v;
     }
   __syncthreads();
@@ -261,7 +269,7 @@ __global__ __launch_bounds__(256) void transfer_split_kernel(const float* __rest
       return v;
     };
     floatx4_t v = sum(lane);
-    if (!NT && r16 < kSideBySide) v += sum(lane + kSideBySide) + sum(lane + 2 * kSideBySide);
+    if (!NT && r16 < kSideBySide) v = plus_lower(v, sum(lane + kSideBySide) + sum(lane + 2 * kSideBySide));
     const int f = t * 16 + r16, o = (rb % nb) * 16 + g * 4;
     if (f < nf && o < d)
       *(float4*)(pseudo + ((size_t)(f0 + f) * row_stride + rb / nb) * d + o) = make_float4(v[0], v[1], v[2], v[3]);

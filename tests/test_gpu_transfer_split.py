@@ -72,3 +72,24 @@ def test_infinite_and_nan_sources_stay_in_their_row():
     ok = [i for i in range(F) if i not in (3, 5)]
     bound = (d / 128 + 16) * 2.0 ** -24 * (h[ok].double().abs() @ w.double().abs().T)
     assert bool(((out[ok].double() - ref[ok]).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("F", [3, 7, 20])
+def test_infinite_and_nan_weights_reach_the_sums_they_belong_to(F):
+    """Sources of few mantissa bits have lower pieces of zero: an infinite weight must give infinity all the same."""
+    d, dev = 264, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(F)
+    w = torch.empty(d, d, device=dev).normal_(0, 0.02, generator=g).to(torch.bfloat16)
+    w[5, 9], w[17, 200], w[100, 3] = float("inf"), float("-inf"), float("nan")
+    h = torch.empty(F, d, device=dev).normal_(0, 1, generator=g)
+    h[::2] = h[::2].to(torch.bfloat16).float()
+    h = torch.where(h == 0, torch.full_like(h, 0.5), h)
+    out = torch.zeros(F, d, device=dev)
+    launch(h, None, F, [w], out, 0, 1, 1, d)
+    inf = float("inf")
+    assert bool((out[:, 5] == torch.sign(h[:, 9]) * inf).all()) and bool((out[:, 17] == -torch.sign(h[:, 200]) * inf).all())
+    assert bool(out[:, 100].isnan().all())
+    rest = [o for o in range(d) if o not in (5, 17, 100)]
+    ref = h.double() @ w[rest].double().T
+    bound = (d / 128 + 16) * 2.0 ** -24 * (h.double().abs() @ w[rest].double().abs().T)
+    assert bool(((out[:, rest].double() - ref).abs() <= bound).all())
