@@ -65,7 +65,7 @@ __device__ inline floatx4_t plus_lower(floatx4_t hi, floatx4_t lo) {
   return hi;
 }
 
-template <int NT, int R> struct TransferShape {
+template <int NT, int R, int DEPTH> struct TransferShape {
   static constexpr int TILES = NT ? NT : 1;
   static constexpr int SOURCES = NT ? NT * 16 : kSideBySide;         // sources a workgroup takes
   static constexpr bool PRECUT = NT >= 2;                            // pieces come from cut_sources_kernel
@@ -73,7 +73,7 @@ template <int NT, int R> struct TransferShape {
   static constexpr int WAVE_BYTES = (R * 16 + PANEL_ROWS) * kRowBytes;
   static constexpr int SUM_BYTES = 4 * R * TILES * 64 * 16;          // the four K quarters' sums, where the operands were
   static constexpr int LDS_BYTES = 4 * WAVE_BYTES > SUM_BYTES ? 4 * WAVE_BYTES : SUM_BYTES;
-  static constexpr int PD = PRECUT ? 2 : 3;
+  static constexpr int PD = PRECUT ? 2 : DEPTH;
 };
 
 // The pieces of many sources in operand order: panel[step of 32 columns][piece][tile of 16 sources][lane], lane l holding
@@ -97,12 +97,12 @@ __global__ __launch_bounds__(256) void cut_sources_kernel(const float* __restric
 
 // NT = 0: up to kSideBySide sources side by side in one operand; else NT tiles of 16 sources.
 // grid = (ceil(row blocks / R), ceil(F / SOURCES)), block = 256
-template <int NT, int R>
+template <int NT, int R, int DEPTH>
 __global__ __launch_bounds__(256) void transfer_split_kernel(const float* __restrict__ h, const int32_t* __restrict__ src_rows,
                                                              int F, const void* const* __restrict__ ws,
                                                              float* __restrict__ pseudo, int i0, int steps, int row_stride,
                                                              int d, const u32x4_t* __restrict__ panel, int ptiles) {
-  using TS = TransferShape<NT, R>;
+  using TS = TransferShape<NT, R, DEPTH>;
   constexpr int TILES = TS::TILES, PD = TS::PD;
   constexpr bool PRECUT = TS::PRECUT;
   constexpr int NQ = PRECUT ? 1 : (TS::SOURCES * (kStepCols / 4) + 63) / 64;   // float4 loads per lane and step for the sources
@@ -276,10 +276,10 @@ __global__ __launch_bounds__(256) void transfer_split_kernel(const float* __rest
   }
 }
 
-template <int NT, int R>
+template <int NT, int R, int DEPTH>
 hipError_t launch_split(const float* h, const int32_t* src_rows, int F, const void* const* w_dev, float* pseudo, int i0, int steps,
                         int row_stride, int d, void* scratch, hipStream_t s) {
-  using TS = TransferShape<NT, R>;
+  using TS = TransferShape<NT, R, DEPTH>;
   static_assert(TS::LDS_BYTES <= 64 * 1024, "no more LDS than a kernel may use without asking");
   const int total = steps * ((d + 15) / 16), groups = (F + TS::SOURCES - 1) / TS::SOURCES, tiles = groups * TS::TILES;
   if (TS::PRECUT) {
@@ -287,15 +287,23 @@ hipError_t launch_split(const float* h, const int32_t* src_rows, int F, const vo
     hipLaunchKernelGGL(cut_sources_kernel, dim3((ksteps * tiles * 64 + 255) / 256), dim3(256), 0, s, h, src_rows, F, d, tiles,
                        ksteps, (u32x4_t*)scratch);
   }
-  hipLaunchKernelGGL((transfer_split_kernel<NT, R>), dim3((total + R - 1) / R, groups), dim3(256), TS::LDS_BYTES, s, h, src_rows, F,
+  hipLaunchKernelGGL((transfer_split_kernel<NT, R, DEPTH>), dim3((total + R - 1) / R, groups), dim3(256), TS::LDS_BYTES, s, h, src_rows, F,
                      w_dev, pseudo, i0, steps, row_stride, d, (const u32x4_t*)scratch, tiles);
   return hipGetLastError();
 }
 
 // Row blocks and source tiles per workgroup.  A compute unit takes in weights and sources at one rate wherever they come
 // from, so what counts is the rounds of 256 workgroups (one per unit) times the bytes of one workgroup per column.
-struct SplitPlan { int nt, r; };
-SplitPlan plan_split(int F, int total) {
+// Up to two row blocks per compute unit (one map of a wide model, all maps of a narrow one) few sources do not share a
+// workgroup between row blocks at all: the launch is over in the time of one walk along K, so what counts is how much of
+// it is in flight.  One map of 4096 x 4096, 4 sources: 17.1 us on two row blocks and a ring of three steps, 14.6 us on one
+// row block, 12.8 us with six steps in flight (the scalar kernel of one source, in groups of four: 14.4 us); of 2048 x 2048
+// 9.9, 8.6 and 8.1 us (9.5); four of 1536 x 1536, one and a half rounds, 9.6 us, 8.9 with four in flight, 10.0 with six.
+// Below 1024 columns a wavefront has fewer than four steps to begin with (512 columns: 3.8 us on a ring of three, 4.0 and
+// 4.2 us on four and six).  768 row blocks: within 3 % of the shared workgroups, on either side.
+struct SplitPlan { int nt, r, depth = 3; };
+SplitPlan plan_split(int F, int total, int d) {
+  if (F <= kSideBySide && total <= 512) return SplitPlan{0, 1, d < 1024 ? 3 : total <= 256 ? 6 : 4};
   static const SplitPlan few[] = {{0, 4}, {0, 3}, {0, 2}}, some[] = {{1, 3}, {1, 2}}, many[] = {{4, 3}, {4, 2}, {4, 1}, {2, 3}, {2, 2}};
   const SplitPlan* list = F <= kSideBySide ? few : F <= 16 ? some : many;
   const int count = F <= kSideBySide ? 3 : F <= 16 ? 2 : 5;
@@ -323,14 +331,14 @@ size_t transfer_scratch_bytes(int F, int d) {
 hipError_t launch_transfer_split(const float* h, const int32_t* src_rows, int F, const void* const* w_dev, float* pseudo, int i0,
                                  int steps, int row_stride, int d, void* scratch, hipStream_t s) {
   if (F > 16 && !scratch) return hipErrorInvalidValue;
-#define HT_SPLIT(NT, R) \
-  if (nt == NT && r == R) return launch_split<NT, R>(h, src_rows, F, w_dev, pseudo, i0, steps, row_stride, d, scratch, s)
-  const SplitPlan p = plan_split(F, steps * ((d + 15) / 16));
-  const int nt = p.nt, r = p.r;
-  HT_SPLIT(0, 2); HT_SPLIT(0, 3); HT_SPLIT(0, 4);
-  HT_SPLIT(1, 2); HT_SPLIT(1, 3);
-  HT_SPLIT(2, 2); HT_SPLIT(2, 3);
-  HT_SPLIT(4, 1); HT_SPLIT(4, 2); HT_SPLIT(4, 3);
+#define HT_SPLIT(NT, R, DEPTH) \
+  if (p.nt == NT && p.r == R && p.depth == DEPTH) \
+  return launch_split<NT, R, DEPTH>(h, src_rows, F, w_dev, pseudo, i0, steps, row_stride, d, scratch, s)
+  const SplitPlan p = plan_split(F, steps * ((d + 15) / 16), d);
+  HT_SPLIT(0, 1, 3); HT_SPLIT(0, 1, 4); HT_SPLIT(0, 1, 6); HT_SPLIT(0, 2, 3); HT_SPLIT(0, 3, 3); HT_SPLIT(0, 4, 3);
+  HT_SPLIT(1, 2, 3); HT_SPLIT(1, 3, 3);
+  HT_SPLIT(2, 2, 3); HT_SPLIT(2, 3, 3);
+  HT_SPLIT(4, 1, 3); HT_SPLIT(4, 2, 3); HT_SPLIT(4, 3, 3);
   return hipErrorInvalidValue;
 #undef HT_SPLIT
 }

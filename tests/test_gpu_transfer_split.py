@@ -58,6 +58,13 @@ def test_transfer_of_several_sources_matches_the_fp64_product(F, d, steps):
         assert bool(((got[:, i].double() - ref).abs() <= bound).all())
 
 
+# up to five sources: one row block per workgroup up to 512 row blocks (rings of three, six and four steps), then four, three
+# and two
+@pytest.mark.parametrize("F,d,steps", [(2, 264, 4), (4, 1016, 4), (5, 1032, 3), (4, 1032, 4), (2, 1024, 8), (4, 2056, 8), (3, 1640, 8), (2, 4800, 8)])
+def test_row_blocks_per_workgroup(F, d, steps):
+    test_transfer_of_several_sources_matches_the_fp64_product(F, d, steps)
+
+
 def test_infinite_and_nan_sources_stay_in_their_row():
     d, F, dev = 256, 20, "cuda:0"
     g = torch.Generator(device=dev).manual_seed(5)
