@@ -932,11 +932,13 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
       n_rank[v] = r;
     }
     if (depth < k) {                               // the first child goes to a new slot
+      // (read here, where all lanes are active: in the one-lane branch the lane of that number would not be)
+      const float child = best + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(first), depth));
       if (lane == (count & 63)) {
 #pragma unroll
         for (int i = 0; i < SLOTS; ++i)
           if (SLOTS == 1 || (count >> 6) == i) {
-            fs[i] = best + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(first), depth));
+            fs[i] = child;
             fb[i] = best;
             fd[i] = depth + 1;
             fp[i] = v;
