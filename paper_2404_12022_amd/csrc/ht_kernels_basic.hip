@@ -97,28 +97,38 @@ hipError_t launch_convert_to_bf16(const float* src, void* dst, size_t count, hip
 
 // Two passes over L2-sized data: bound by the latency of one round trip, so all splits of an element are requested before
 // the first is added, 16 bytes a lane where `out` is aligned (33 rows of 5120 in six splits: 4.3 us with 4-byte loads one
-// after the other).
-template <typename V>
-__global__ __launch_bounds__(256) void reduce_splits_kernel(const V* __restrict__ part, int nsplit, size_t stride, V* __restrict__ out) {
+// after the other), and no more than there are (128 rows of 5120 in two splits: 2.9 us with eight loads whatever the number).
+template <typename V, int NS>
+__global__ __launch_bounds__(256) void reduce_splits_kernel(const V* __restrict__ part, size_t stride, V* __restrict__ out) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= stride) return;
-  V p[kMaxSplitK];
+  V p[NS];
 #pragma unroll
-  for (int sp = 0; sp < kMaxSplitK; ++sp) p[sp] = part[(sp < nsplit ? sp : 0) * stride + i];
+  for (int sp = 0; sp < NS; ++sp) p[sp] = part[sp * stride + i];
   V v = p[0];
 #pragma unroll
-  for (int sp = 1; sp < kMaxSplitK; ++sp)
-    if (sp < nsplit) v += p[sp];
+  for (int sp = 1; sp < NS; ++sp) v += p[sp];
   out[i] = v;
+}
+template <typename V>
+hipError_t launch_reduce_as(const float* part, int nsplit, size_t stride, float* out, hipStream_t s) {
+  stride = stride * sizeof(float) / sizeof(V);
+#define HT_REDUCE(NS)                                                                                                           \
+  case NS:                                                                                                                      \
+    hipLaunchKernelGGL((reduce_splits_kernel<V, NS>), dim3((unsigned)((stride + 255) / 256)), dim3(256), 0, s, (const V*)part,  \
+                       stride, (V*)out);                                                                                        \
+    break;
+  switch (nsplit) {
+    HT_REDUCE(1) HT_REDUCE(2) HT_REDUCE(3) HT_REDUCE(4) HT_REDUCE(5) HT_REDUCE(6) HT_REDUCE(7) HT_REDUCE(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef HT_REDUCE
+  return hipGetLastError();
 }
 hipError_t launch_reduce_splits(const float* part, int nsplit, size_t stride, float* out, hipStream_t s) {
   typedef float float4v __attribute__((ext_vector_type(4)));
-  if (stride % 4 == 0 && !((uintptr_t)out & 15) && !((uintptr_t)part & 15))
-    hipLaunchKernelGGL(reduce_splits_kernel<float4v>, dim3((unsigned)((stride / 4 + 255) / 256)), dim3(256), 0, s,
-                       (const float4v*)part, nsplit, stride / 4, (float4v*)out);
-  else
-    hipLaunchKernelGGL(reduce_splits_kernel<float>, dim3((unsigned)((stride + 255) / 256)), dim3(256), 0, s, part, nsplit, stride, out);
-  return hipGetLastError();
+  const bool vec = stride % 4 == 0 && !((uintptr_t)out & 15) && !((uintptr_t)part & 15);
+  return vec ? launch_reduce_as<float4v>(part, nsplit, stride, out, s) : launch_reduce_as<float>(part, nsplit, stride, out, s);
 }
 
 // ------------------------------------------------------------------------------------------------ residual + RMSNorm
