@@ -1328,20 +1328,21 @@ double launch_mfma_rate(int form, int iters, uint32_t* sink, hipStream_t s) {
 
 // ------------------------------------------------------------------------------------------------ generic attention
 // One block per (query head, tree row).  Scores of all visible keys go to LDS (four lanes per key), softmax in fp32, then
-// every thread owns one output element and every (256 / hd)-th piece of VEC keys of it.  Dynamic LDS: (n + M) floats + hd
-// + 256.  Latency bound at the sizes it is used at (fp32 model, tens of keys): VEC elements per load cut the chains of
+// every thread owns one output element and every (256 / hd)-th piece of VEC keys of it; SKIP: pieces of tree rows that hold
+// no ancestor are not read.  Dynamic LDS: (n + M) floats + hd + 256.  Latency bound at the sizes it is used at (fp32 model, tens of keys): VEC elements per load cut the chains of
 // dependent loads, 7.6 -> 5.1 us (mean; shortest 5.5 -> 4.2) for 8 rows of 4 heads over 40 keys of 64 floats.
 template <typename T, int VEC> __device__ inline void load_vec(const T* p, float (&v)[VEC]) {
   if constexpr (VEC == 1) {
     v[0] = Conv<T>::load(p);
   } else {
-    const uint4 raw = *(const uint4*)p;               // VEC * sizeof(T) = 16
+    typedef unsigned int words_t __attribute__((ext_vector_type(VEC * sizeof(T) / 4)));
+    const words_t raw = *(const words_t*)p;           // 16 or 8 bytes
     const T* e = (const T*)&raw;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) v[i] = Conv<T>::load(e + i);
   }
 }
-template <typename T, int VEC>
+template <typename T, int VEC, bool SKIP>
 __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc,
                                                           int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd,
                                                           T* __restrict__ out, const int32_t* __restrict__ n_dev) {
@@ -1353,7 +1354,9 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
   float* sc = smem;            // [S]
   float* qs = smem + S;        // [hd]
   float* acc = qs + hd;        // [256]
+  uint32_t* seen = (uint32_t*)acc;   // the row's mask, until the scores are there
   for (int e = tid; e < hd; e += 256) qs[e] = Conv<T>::load(q + ((size_t)m * Hq + h) * hd + e);
+  if (tid < 2 * kMaskWords) seen[tid] = ((const uint32_t*)(tree.anc + (size_t)m * kMaskWords))[tid];
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)hd);
   float mx = -INFINITY;
@@ -1362,7 +1365,7 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
     bool vis = j < n;
     if (!vis && j < S) {
       const int u = j - n;
-      vis = (tree.anc[(size_t)m * kMaskWords + (u >> 6)] >> (u & 63)) & 1ull;
+      vis = (seen[u >> 5] >> (u & 31)) & 1u;
     }
     float dot = 0.f;
     if (vis) {
@@ -1383,8 +1386,9 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
   }
   mx = block_max_256(mx, red);
   float sum = 0.f;
-  for (int j = tid; j < S; j += 256) {
-    const float p = sc[j] == -INFINITY ? 0.f : expf(sc[j] - mx);
+  const int Sp = (S + VEC - 1) / VEC * VEC;            // up to a whole piece, over what was qs (hd is a multiple of VEC)
+  for (int j = tid; j < Sp; j += 256) {
+    const float p = j >= S || sc[j] == -INFINITY ? 0.f : expf(sc[j] - mx);
     sc[j] = p;
     sum += p;
   }
@@ -1394,16 +1398,36 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
   float o = 0.f;
   if (part < groups) {
     const T* vr = vc + ((size_t)hk * hd + e) * cap;    // cap is a multiple of 8: whole pieces lie in the row
-#pragma unroll 2
-    for (int j = part * VEC; j < S; j += groups * VEC) {
+    auto probabilities = [&](int j, float (&p)[VEC]) __attribute__((always_inline)) {
+      if constexpr (VEC == 1) {
+        p[0] = sc[j];
+      } else {
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) *(float4*)(p + i) = *(const float4*)(sc + j + i);
+      }
+    };
+    auto add = [&](int j, const float (&p)[VEC]) __attribute__((always_inline)) {
       float vv[VEC];
       load_vec<T, VEC>(vr + j, vv);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) {
-        const float p = j + i < S ? sc[j + i] : 0.f;
-        o += p != 0.f ? p * vv[i] : 0.f;               // what no row has written yet may hold anything
-      }
+      for (int i = 0; i < VEC; ++i) o += p[i] != 0.f ? p[i] * vv[i] : 0.f;      // what no row has written yet may hold anything
+    };
+    int j = part * VEC;
+#pragma unroll 2
+    for (; j < (SKIP ? n : S); j += groups * VEC) {
+      float p[VEC];
+      probabilities(j, p);
+      add(j, p);
     }
+    if (SKIP)
+      for (; j < S; j += groups * VEC) {
+        float p[VEC];
+        probabilities(j, p);
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) any = any || p[i] != 0.f;
+        if (any) add(j, p);
+      }
   }
   acc[tid] = o;
   __syncthreads();
@@ -1417,13 +1441,22 @@ hipError_t launch_attn_simple(int dtype, const void* q, const void* kc, const vo
                               TreeDev tree, int Hq, int Hkv, int hd, void* out, hipStream_t s, const int32_t* n_dev) {
   const size_t smem = (size_t)(n + M + hd + 256) * sizeof(float);
   if (smem > 64 * 1024 || hd > 256) return hipErrorInvalidValue;
-  // 16-byte pieces of key rows and of value columns
+  // 16-byte pieces of key rows and of value columns, or 8-byte ones of bf16 heads that are a multiple of four wide
   const bool vec = hd % (dtype == 0 ? 4 : 8) == 0 && cap % 8 == 0 && !((uintptr_t)kc & 15) && !((uintptr_t)vc & 15);
-#define HT_ATTN_SIMPLE(VEC)                                                                                            \
-  hipLaunchKernelGGL((attn_simple_kernel<T, VEC>), dim3(Hq, M), dim3(256), smem, s, (const T*)q, (const T*)kc, (const T*)vc, \
+  const bool half = dtype != 0 && hd % 4 == 0 && cap % 8 == 0 && !((uintptr_t)kc & 7) && !((uintptr_t)vc & 7);
+  // Many rows: what the value columns of rows that are no ancestors cost adds up, and a look at the probabilities before
+  // each piece pays (trees without a cache: 256 rows of 32 heads of 128 floats 151 us without it, 62 us with it; of 8 heads
+  // 42.6 and 21.7 us).  Few: the look is one more dependent step (chains: 128 rows of 4 heads of 96 floats 13.1 and 16.0 us).
+  const bool skip = (size_t)Hq * M * hd * (dtype == 0 ? 4 : 2) > (vec || half ? 400000 : 50000);
+#define HT_ATTN_SIMPLE_AS(VEC, SKIP)                                                                                   \
+  hipLaunchKernelGGL((attn_simple_kernel<T, VEC, SKIP>), dim3(Hq, M), dim3(256), smem, s, (const T*)q, (const T*)kc, (const T*)vc, \
                      cap, n, M, tree, Hq, Hkv, hd, (T*)out, n_dev)
-  HT_DISPATCH_DTYPE(dtype, if (vec) HT_ATTN_SIMPLE(16 / sizeof(T)); else HT_ATTN_SIMPLE(1);)
+#define HT_ATTN_SIMPLE(VEC)               \
+  if (skip) HT_ATTN_SIMPLE_AS(VEC, true); \
+  else HT_ATTN_SIMPLE_AS(VEC, false)
+  HT_DISPATCH_DTYPE(dtype, if (vec) { HT_ATTN_SIMPLE(16 / sizeof(T)); } else if (half) { HT_ATTN_SIMPLE(4); } else { HT_ATTN_SIMPLE(1); })
 #undef HT_ATTN_SIMPLE
+#undef HT_ATTN_SIMPLE_AS
   return hipGetLastError();
 }
 

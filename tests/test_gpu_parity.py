@@ -221,6 +221,18 @@ def test_tree_attention_small(dtype, case):
         _attention_case(dtype, 256, 61, 2, 2, 64, random_tree(13, 256, 12)[0], 12, rotate=False)
 
 
+# the kernel of fp32 models and odd head widths: pieces of 16 and 8 bytes and single elements, each with few rows (every piece
+# is read) and with many (pieces without an ancestor are not); ends of a piece inside the cache, the tree and past both
+@pytest.mark.parametrize("dtype,T,n,Hq,Hkv,hd", [
+    ("f32", 21, 10, 2, 2, 4), ("f32", 70, 5, 4, 4, 64), ("f32", 200, 3, 4, 2, 128), ("f32", 31, 2, 2, 2, 50), ("f32", 256, 9, 2, 1, 50),
+    ("bf16", 13, 6, 2, 2, 100), ("bf16", 256, 1, 10, 5, 100), ("bf16", 9, 7, 2, 1, 50), ("bf16", 120, 11, 6, 2, 50),
+    ("bf16", 65, 12, 4, 4, 96), ("bf16", 230, 5, 10, 10, 96), ("bf16", 17, 0, 3, 1, 12)])
+def test_generic_attention_forms(dtype, T, n, Hq, Hkv, hd):
+    say(f"generic attention {dtype} T={T} n={n} {Hq}/{Hkv} x {hd}")
+    _attention_case(dtype, T, n, Hq, Hkv, hd, random_tree(T, T, 7)[0], T + hd, poison=True)
+    _attention_case(dtype, T, n, Hq, Hkv, hd, chain_tree(T)[0], T + hd + 1, poison=True)
+
+
 def test_tree_attention_at_the_op_workload_size():
     a = ATTENTION_OP
     say("attention bf16 op workload")
