@@ -1524,11 +1524,22 @@ int ht_gate_up_pack(const void* w_gate, const void* w_up, int32_t f, int32_t K, 
   return HT_OK;
 }
 
+// Passes of more than 128 rows fetch both operands with 16-byte LDS-direct loads, which are only used on 16-byte addresses;
+// other pointers are served in two calls of the streaming kernel, whose plain loads take any address.
+static bool needs_two_calls(int32_t M, const void* a, const void* packed) {
+  return M > 128 && (((uintptr_t)a | (uintptr_t)packed) & 15) != 0;
+}
+
 int ht_gate_up_silu_packed(const void* a, const void* packed, int32_t M, int32_t f, int32_t K, void* act_out,
                            void* stream) {
   if (!a || !packed || !act_out) return fail(HT_EINVAL, "NULL argument");
   if (M < 1 || M > kMaxRows || f < 16 || f % 16 || !ht_weight_pack_bytes(2 * f, K))
     return fail(HT_EINVAL, "bad shape M=%d f=%d K=%d", M, f, K);
+  if (needs_two_calls(M, a, packed)) {
+    const int rc = ht_gate_up_silu_packed(a, packed, 128, f, K, act_out, stream);
+    return rc ? rc : ht_gate_up_silu_packed((const bf16_t*)a + (size_t)128 * K, packed, M - 128, f, K,
+                                            (bf16_t*)act_out + (size_t)128 * f, stream);
+  }
   PackedW pw{(const bf16_t*)packed, 2 * f, K, packed_cols(K)};
   HT_HIP(launch_gemm_packed_silu(a, pw, M, act_out, (hipStream_t)stream));
   return HT_OK;
@@ -1543,6 +1554,11 @@ int ht_skinny_gemm_packed(const void* a, const void* packed, int32_t M, int32_t 
                           size_t scratch_bytes, void* stream) {
   if (!a || !packed || !out) return fail(HT_EINVAL, "NULL argument");
   if (M < 1 || M > kMaxRows || !ht_weight_pack_bytes(N, K)) return fail(HT_EINVAL, "bad shape M=%d N=%d K=%d", M, N, K);
+  if (needs_two_calls(M, a, packed)) {
+    const int rc = ht_skinny_gemm_packed(a, packed, 128, N, K, out, scratch, scratch_bytes, stream);
+    return rc ? rc : ht_skinny_gemm_packed((const bf16_t*)a + (size_t)128 * K, packed, M - 128, N, K, out + (size_t)128 * N,
+                                           scratch, scratch_bytes, stream);
+  }
   hipStream_t s = (hipStream_t)stream;
   PackedW pw{(const bf16_t*)packed, N, K, packed_cols(K)};
   int sp = gemm_mfma_splits(M, N, K);
@@ -1591,6 +1607,11 @@ int ht_skinny_gemm_packed_noalloc(const void* a, const void* packed, int32_t M, 
                                   void* stream) {
   if (!a || !packed || !out) return fail(HT_EINVAL, "NULL argument");
   if (M < 1 || M > kMaxRows || !ht_weight_pack_bytes(N, K)) return fail(HT_EINVAL, "bad shape M=%d N=%d K=%d", M, N, K);
+  if (needs_two_calls(M, a, packed)) {
+    const int rc = ht_skinny_gemm_packed_noalloc(a, packed, 128, N, K, out, stream);
+    return rc ? rc : ht_skinny_gemm_packed_noalloc((const bf16_t*)a + (size_t)128 * K, packed, M - 128, N, K,
+                                                   out + (size_t)128 * N, stream);
+  }
   hipStream_t s = (hipStream_t)stream;
   PackedW pw{(const bf16_t*)packed, N, K, packed_cols(K)};
   const int sp = gemm_mfma_splits(M, N, K);          // the same split as ht_skinny_gemm_packed with enough scratch

@@ -76,3 +76,37 @@ def test_packed_products_of_between_32_and_48_and_of_more_than_128_rows(M, N, K)
     want = O.silu(O.linear(H.cpu(a[:M]), H.cpu(gate))) * O.linear(H.cpu(a[:M]), H.cpu(up))
     # one bf16 rounding (half an ulp, 2^-9 relative) on values whose fp32 sums carry far smaller errors
     assert np.all(np.abs(H.cpu(act) - want) <= 2.0 ** -8 * np.abs(want) + 1e-4 * np.abs(want).max())
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 1040, 1032), (200, 272, 4096), (256, 4096, 264)])
+@pytest.mark.parametrize("off_a,off_w", [(4, 0), (0, 4), (4, 4)])
+def test_operands_that_are_not_16_byte_aligned(M, N, K, off_a, off_w):
+    """Rows and packed weights 8 bytes past a 16-byte address, as a view into a larger buffer gives them."""
+    import paper_2404_12022_amd.binding as B
+    a0, w = inputs(B.ht_padded_rows(M), N, K, M + K)
+    store = torch.zeros(a0.numel() + 8, dtype=torch.bfloat16, device=H.DEV)
+    a = store[off_a:off_a + a0.numel()].view_as(a0).copy_(a0)
+    want = O.linear(H.cpu(a0[:M]), H.cpu(w))
+
+    def packed_for(rows):
+        return torch.empty(B.ht_weight_pack_bytes(rows, K) + 16, dtype=torch.uint8, device=H.DEV)[2 * off_w:]
+
+    print(f"misaligned product {M} x {N} x {K}, offsets {off_a} {off_w}", flush=True)
+    packed = packed_for(N)
+    B.ht_weight_pack(w, N, K, packed)
+    scratch = torch.empty(B.ht_skinny_gemm_scratch_bytes(M, N, K), dtype=torch.uint8, device=H.DEV)
+    for call in (lambda o: B.ht_skinny_gemm_packed(a, packed, M, N, K, o, scratch), lambda o: B.ht_skinny_gemm_packed(a, packed, M, N, K, o),
+                 lambda o: B.ht_skinny_gemm_packed_noalloc(a, packed, M, N, K, o)):
+        out = torch.full((M, N), float("nan"), device=H.DEV)
+        call(out)
+        torch.cuda.synchronize()
+        assert np.all(np.abs(H.cpu(out) - want) <= bound(a0[:M], w, K))
+    f = N // 2 // 16 * 16
+    gate, up = w[:f].contiguous(), w[f:2 * f].contiguous()
+    gu = packed_for(2 * f)
+    B.ht_gate_up_pack(gate, up, f, K, gu)
+    act = torch.full((M, f), float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    B.ht_gate_up_silu_packed(a, gu, M, f, K, act)
+    torch.cuda.synchronize()
+    want = O.silu(O.linear(H.cpu(a0[:M]), H.cpu(gate))) * O.linear(H.cpu(a0[:M]), H.cpu(up))
+    assert np.all(np.abs(H.cpu(act) - want) <= 2.0 ** -8 * np.abs(want) + 1e-4 * np.abs(want).max())
