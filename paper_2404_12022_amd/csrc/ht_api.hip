@@ -1174,9 +1174,11 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
     HT_HIP(launch_gemm_wide(w.act, b.p_down[l], rows, w.part, pending, s));
   }
   HT_HIP(launch_add_norm_parts(w.x, w.part, pending, (size_t)rows * d, m->final_norm, w.u, nullptr, w.ss, rows, d, s));
-  // The head writes the logits where the caller wants them (a buffer that is not 16-byte aligned gets a copy): at 2047 + 2048
-  // rows of 32000 the two copies took 190 us.
-  auto direct = [](const float* p) { return p && !((uintptr_t)p & 15); };
+  // The head writes the logits where the caller wants them (buffers that are not 16-byte aligned or that overlap get copies,
+  // so that the loss never reads what another output has overwritten): at 2047 + 2048 rows of 32000 the two copies took 190 us.
+  const bool apart = !logits_hidden_out || !logits_pseudo_out || logits_hidden_out + (size_t)n * c.vocab <= logits_pseudo_out ||
+                     logits_pseudo_out + (size_t)P * c.vocab <= logits_hidden_out;
+  auto direct = [apart](const float* p) { return apart && p && !((uintptr_t)p & 15); };
   float* z_hidden = direct(logits_hidden_out) ? logits_hidden_out : w.logits;
   float* z_pseudo = direct(logits_pseudo_out) ? logits_pseudo_out : w.logits + (size_t)n * c.vocab;
   if (z_hidden == w.logits && z_pseudo == w.logits + (size_t)n * c.vocab) {

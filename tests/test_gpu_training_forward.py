@@ -238,3 +238,41 @@ def test_batched_training_forward_error_codes():
     kl, loss = gpu.ht_training_forward_batched(1, prompt_of(wl, 20))
     assert len(kl) == 18 and abs(loss - sum(kl)) < 1e-5
     gpu.close()
+
+
+@pytest.mark.parametrize("n,step", [(129, 2), (20, 3)])
+def test_batched_training_forward_logits_wherever_the_caller_wants_them(n, step):
+    """Both outputs, one of them, none; at 16-byte addresses and 4 bytes past one; in one buffer: the same logits, KL terms and
+    loss, and nothing written around them.  The head's sums do not depend on which rows share a launch."""
+    H = _H()
+    wl = _packed_small()
+    gpu = H.gpu_model(wl, max_tree=64)
+    toks, V, P = prompt_of(wl, n), wl.vocab, n - step + 1
+
+    def room(rows, off):
+        store = torch.full((rows * V + 8,), 777.0, device=DEV)
+        return store, store[off:off + rows * V].view(rows, V)
+
+    def guarded(store, off, rows):
+        return bool((store[:off] == 777.0).all()) and bool((store[off + rows * V:] == 777.0).all())
+
+    want_h, want_p = torch.zeros(n, V, device=DEV), torch.zeros(P, V, device=DEV)
+    want = gpu.ht_training_forward_batched(step, toks, want_h, want_p)
+    torch.cuda.synchronize()
+    assert bool(want_h.abs().sum(1).all()) and bool(want_p.abs().sum(1).all())
+    for off_h, off_p in ((None, None), (0, None), (None, 0), (1, None), (None, 1), (1, 1), (4, 1), (1, 4)):
+        say(f"  outputs at offsets {off_h} / {off_p}")
+        store_h, h = room(n, off_h or 0)
+        store_p, p = room(P, off_p or 0)
+        got = gpu.ht_training_forward_batched(step, toks, None if off_h is None else h, None if off_p is None else p)
+        torch.cuda.synchronize()
+        assert got == want
+        if off_h is not None:
+            assert torch.equal(h, want_h) and guarded(store_h, off_h, n)
+        if off_p is not None:
+            assert torch.equal(p, want_p) and guarded(store_p, off_p, P)
+    store, both = room(n, 0)
+    assert gpu.ht_training_forward_batched(step, toks, both, both) == want          # the pseudo rows come last
+    torch.cuda.synchronize()
+    assert torch.equal(both[:P], want_p) and torch.equal(both[P:], want_h[P:])
+    gpu.close()
