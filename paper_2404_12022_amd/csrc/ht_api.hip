@@ -59,13 +59,13 @@ struct TreeTables {
 
 struct Buffers {
   float* x;            // residual stream [Mp, d]
-  void* u;             // normalised rows (dtype) [Mp, d]
-  float* qkv;          // [Mp, (Hq + 2 Hkv) hd]
+  void* u;             // bf16: normalised rows [Mp, d]
+  float* qkv;          // bf16: split-K partial sums [kMaxSplitK][Mp, (Hq + 2 Hkv) hd]
   void* q;             // rotated queries (dtype) [Mp, Hq hd]
   void* attn;          // attention output (dtype) [Mp, Hq hd]
-  float* gu;           // gate | up [Mp, 2 f]
+  float* gu;           // bf16: gate | up [Mp, 2 f]
   void* act;           // silu(gate) * up (dtype) [Mp, f]
-  float* part;         // split-K partial sums [kMaxSplitK][Mp][d]
+  float* part;         // bf16: split-K partial sums [kMaxSplitK][Mp][d]
   float* logits;       // [Mp, V]
   float* dlogits;      // draft logits [k, V]
   float* saved_h;      // residuals of the last verify pass at every distinct transfer layer [slots <= k][Mp, d]
@@ -122,21 +122,22 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
   const size_t es = elem_size(c.dtype);
   const size_t Mp = padded_rows(c.max_tree > c.k ? c.max_tree : c.k);
   const size_t d = c.d_model, qd = (size_t)c.n_heads * c.head_dim, kvd = (size_t)c.n_kv_heads * c.head_dim;
+  const size_t bf16_rows = c.dtype == HT_BF16 ? Mp : 0;      // the products of fp32 models leave nothing between them
   b.x = cv.take<float>(Mp * d);
-  b.u = cv.take_bytes(Mp * d * es);
-  b.qkv = cv.take<float>((size_t)kMaxSplitK * Mp * (qd + 2 * kvd));
+  b.u = cv.take_bytes(bf16_rows * d * es);
+  b.qkv = cv.take<float>((size_t)kMaxSplitK * bf16_rows * (qd + 2 * kvd));
   b.q = cv.take_bytes(Mp * qd * es);
   b.attn = cv.take_bytes(Mp * qd * es);
-  b.gu = cv.take<float>(Mp * 2 * c.d_ffn);
+  b.gu = cv.take<float>(bf16_rows * 2 * c.d_ffn);
   b.act = cv.take_bytes(Mp * c.d_ffn * es);
-  b.part = cv.take<float>((size_t)kMaxSplitK * Mp * d);
+  b.part = cv.take<float>((size_t)kMaxSplitK * bf16_rows * d);
   b.logits = cv.take<float>(Mp * c.vocab);
   b.dlogits = cv.take<float>((size_t)padded_rows(c.k) * c.vocab);
   b.saved_h = cv.take<float>((size_t)c.k * Mp * d);
   b.h_src = cv.take<float>((size_t)c.k * d);
   b.pseudo = cv.take<float>((size_t)c.k * d);
   b.cs = cv.take<float>(Mp * c.head_dim);
-  b.ss = cv.take<float>(Mp * kNormParts);
+  b.ss = cv.take<float>(bf16_rows * kNormParts);
   b.lp = cv.take<float>((size_t)kMaxTransfer * kMaxTopK);
   b.kl = cv.take<float>(c.max_cache);
   b.train_rows = cv.take<int32_t>(kMaxTree);
@@ -191,10 +192,14 @@ void carve(const ht_config& c, Carver& cv, Buffers& b) {
     p.rows = prompt_rows(c);
     // the products of up to 128 rows read whole instances of their kernel
     const size_t r = p.rows < 128 ? 128 : p.rows;
-    // eight K splits of up to 128 rows, four of 512, two of the most
+    // eight K splits of up to 128 rows, four of 512, two of the most; more than 128 rows are never split beyond
+    // gemm_wide_part_bytes
     size_t part_rows = (size_t)kMaxSplitK * 128;
+    const size_t most = gemm_wide_part_bytes() / sizeof(float), few = part_rows * d;
     if (r > 128) part_rows = 4 * (r < 512 ? r : 512) > part_rows ? 4 * (r < 512 ? r : 512) : part_rows;
+    const size_t cap = few > r * d ? few : r * d;
     p.part_floats = (2 * r > part_rows ? 2 * r : part_rows) * d;
+    if (p.part_floats > (cap > most ? cap : most)) p.part_floats = cap > most ? cap : most;
     p.x = cv.take<float>(r * d);
     p.part = cv.take<float>(p.part_floats);
     p.ss = cv.take<float>(r * kNormParts);
@@ -440,7 +445,7 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
         if ((rc = product(m, b.u, qkv, M, qd + 2 * kvd, d, b.qkv, s))) return rc;
       }
       // weights packed for the fused epilogue keep their rotary-pair column order in the plain product's output
-      HT_HIP(launch_rope_append(c.dtype, b.qkv, qsplit, b.cs, b.q, b.kc[l], b.vc[l], n, M, c.n_heads, c.n_kv_heads,
+      HT_HIP(launch_rope_append(b.qkv, qsplit, b.cs, b.q, b.kc[l], b.vc[l], n, M, c.n_heads, c.n_kv_heads,
                                 c.head_dim, c.max_cache, m->qkv_fused, s, m->n_dev));
     }
     if ((rc = attention(m, l, n, M, tree, s))) return rc;
@@ -506,7 +511,7 @@ int prompt_pass(ht_model* m, int start, int rows, bool last, hipStream_t s) {
     if (rows <= 128 && rows <= m->Mp && qkv_prefer_split(rows, n_qkv)) {
       const int sp = gemm_mfma_splits(rows, n_qkv, d);
       HT_HIP(launch_gemm_packed(p.u, b.p_qkv[l], rows, b.qkv, sp, s, rs));
-      HT_HIP(launch_rope_append(c.dtype, b.qkv, sp, p.cs, p.q, b.kc[l], b.vc[l], start, rows, c.n_heads, c.n_kv_heads, c.head_dim,
+      HT_HIP(launch_rope_append(b.qkv, sp, p.cs, p.q, b.kc[l], b.vc[l], start, rows, c.n_heads, c.n_kv_heads, c.head_dim,
                                 c.max_cache, true, s));
     } else {
       QkvEpilogue qe{p.cs, (bf16_t*)p.q, (bf16_t*)b.kc[l], (bf16_t*)b.vc[l], start, c.n_heads, c.n_kv_heads, c.head_dim,

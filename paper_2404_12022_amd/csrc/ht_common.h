@@ -124,7 +124,7 @@ struct RowScale {
 hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int hd, float base, hipStream_t s,
                              const int32_t* n_dev = nullptr);
 // qkv may be `nsplit` split-K partial sums of [M][(Hq + 2 Hkv) hd] each
-hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const float* cs, void* q, void* kc, void* vc,
+hipError_t launch_rope_append(const float* qkv, int nsplit, const float* cs, void* q, void* kc, void* vc,
                               int n, int M, int Hq, int Hkv, int hd, int cap, bool paired, hipStream_t s,
                               const int32_t* n_dev = nullptr);
 // rows as they come from the caller, at positions n + depth[m]; `cs`: room for the factors of M rows
@@ -229,6 +229,7 @@ struct QkvEpilogue {
 // The same products tiled over the tokens too, for passes of any number of rows: out fp32 [nsplit][M][N] (nsplit 1 or
 // gemm_wide_splits); act bf16 [M][N/2] (w packed from (gate, up)); q | k | v as in launch_gemm_packed_qkv.
 int gemm_wide_splits(int M, int N, int K);
+size_t gemm_wide_part_bytes();                // the most partial sums gemm_wide_splits asks for, in bytes
 hipError_t gemm_tile_prepare();              // once per device before the first launch that may sit inside a stream capture
 hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs = RowScale{});
 hipError_t launch_gemm_wide_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs = RowScale{});

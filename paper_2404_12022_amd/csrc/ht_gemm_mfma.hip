@@ -766,11 +766,12 @@ hipError_t gemm_tile_prepare() {
 // while the memory-side cache holds them beside the operands (2048 rows of 4096 features over 11008 columns: 172 us
 // without, 135 in two splits; 512 rows: 128, 71, and 53 in four), and more than any split saves beyond 64 MB of them (1987
 // rows of 5120 features over 13824 columns: 271 us without, 299 and 319 in two and three).
+size_t gemm_wide_part_bytes() { return (size_t)64 << 20; }
 int gemm_wide_splits(int M, int N, int K) {
   int best = 1;
   float best_us = tile_us(kTileCosts[best_tile(M, N, K, 1)], M, N, K, 1);
   for (int sp = 2; sp <= kMaxSplitK && packed_cols(K) / 64 / sp >= 8; ++sp) {      // at least 512 columns per split
-    if ((size_t)sp * M * N * sizeof(float) > ((size_t)64 << 20)) break;
+    if ((size_t)sp * M * N * sizeof(float) > gemm_wide_part_bytes()) break;
     const float us = tile_us(kTileCosts[best_tile(M, N, K, sp)], M, N, K, sp) + (float)sp * (float)M * (float)N * 1.6e-6f;
     if (us < best_us) { best = sp; best_us = us; }
   }

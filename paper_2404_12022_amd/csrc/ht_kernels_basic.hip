@@ -470,32 +470,30 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
 
 // rows per workgroup of rope_append_rows_kernel: 16 (measured: blocks of 64 rows leave too few workgroups for passes of
 // 64 - 128 rows, which are latency bound)
-static int rope_rows_per_block(int dtype, int hd) { (void)dtype; (void)hd; return 16; }
+constexpr int kRopeRows = 16;
 
-hipError_t launch_rope_append(int dtype, const float* qkv, int nsplit, const float* cs, void* q, void* kc, void* vc,
+hipError_t launch_rope_append(const float* qkv, int nsplit, const float* cs, void* q, void* kc, void* vc,
                               int n, int M, int Hq, int Hkv, int hd, int cap, bool paired, hipStream_t s,
                               const int32_t* n_dev) {
   const int stride = (Hq + 2 * Hkv) * hd;
+  const float *k_in = qkv + (size_t)Hq * hd, *v_in = k_in + (size_t)Hkv * hd;
+  bf16_t *qp = (bf16_t*)q, *kp = (bf16_t*)kc, *vp = (bf16_t*)vc;
   if (hd % 8 == 0) {
-    const int RB = rope_rows_per_block(dtype, hd);
-    const size_t lds = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2);
-    HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, float>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv),
-                                                dim3(256), lds, s, qkv, stride, qkv + (size_t)Hq * hd, stride,
-                                                qkv + (size_t)(Hq + Hkv) * hd, stride, nsplit, (size_t)M * stride, cs,
-                                                (T*)q, (T*)kc, (T*)vc, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.f);)
+    const int RB = kRopeRows;
+    hipLaunchKernelGGL((rope_append_rows_kernel<bf16_t, float>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv), dim3(256),
+                       (size_t)RB * (hd + 2) * sizeof(bf16_t), s, qkv, stride, k_in, stride, v_in, stride, nsplit,
+                       (size_t)M * stride, cs, qp, kp, vp, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.f);
     return hipGetLastError();
   }
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_kernel<T, float>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0,
-                                              s, qkv, stride, qkv + (size_t)Hq * hd, stride,
-                                              qkv + (size_t)(Hq + Hkv) * hd, stride, nsplit, (size_t)M * stride,
-                                              (const float2*)cs, (T*)q, (T*)kc, (T*)vc, n, Hq, Hkv, hd, cap,
-                                              paired ? 1 : 0, n_dev);)
+  hipLaunchKernelGGL((rope_append_kernel<bf16_t, float>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0, s, qkv, stride, k_in, stride,
+                     v_in, stride, nsplit, (size_t)M * stride, (const float2*)cs, qp, kp, vp, n, Hq, Hkv, hd, cap, paired ? 1 : 0,
+                     n_dev);
   return hipGetLastError();
 }
 hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_in, const void* v_in, const int32_t* depth,
                                     float base, float* cs, void* q, void* kc, void* vc, int n, int M, int Hq, int Hkv, int hd,
                                     int cap, hipStream_t s) {
-  const int RB = rope_rows_per_block(dtype, hd), row_blocks = (M + RB - 1) / RB;
+  const int RB = kRopeRows, row_blocks = (M + RB - 1) / RB;
   const dim3 grid(row_blocks, Hq + 2 * Hkv);
 #define HT_ROPE_ARGS                                                                                                        \
   (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, \

@@ -197,7 +197,10 @@ hipError_t launch_rows_f32(RowsEpi epi, const float* a, const void* gain, float 
     if (vec) launch_rows_as<float, 4, E>(a, gain, eps, w, M, units, K, ep, s);      \
     else launch_rows_as<float, 1, E>(a, gain, eps, w, M, units, K, ep, s);          \
     break;
-  switch (epi) { HT_ROWS(ROWS_STORE) HT_ROWS(ROWS_STORE_NORM) HT_ROWS(ROWS_ADD) HT_ROWS(ROWS_SILU) HT_ROWS(ROWS_QKV) }
+  switch (epi) {
+    HT_ROWS(ROWS_STORE_NORM) HT_ROWS(ROWS_ADD) HT_ROWS(ROWS_SILU) HT_ROWS(ROWS_QKV)
+    default: return hipErrorInvalidValue;          // the plain product is launch_gemm_simple
+  }
 #undef HT_ROWS
   return hipGetLastError();
 }

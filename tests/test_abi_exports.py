@@ -74,3 +74,23 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and not r.stdout.strip()
+
+
+def test_workspace_holds_what_its_model_reads():
+    """fp32 models keep no K-split partial sums and no gate | up buffer: what a row of a pass adds to the workspace is the
+    residual stream, q, the attention output, the activation, the logits, one saved residual per transfer step and small
+    tables.  bf16 models add the activations of a prompt pass once, however long the cache."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    import paper_2404_12022_amd.binding as B
+    from ht_inputs import WORKLOADS
+    wl = WORKLOADS["llama7b"].with_(n_layers=2, transfer_layers=(1, 1, 1))
+    d, qd, f, v, k = wl.d_model, wl.n_heads * wl.head_dim, wl.d_ffn, wl.vocab, wl.k
+    f32 = wl.with_(dtype="f32")
+    rows = B.ht_workspace_bytes(B.make_config(f32, max_tree=256)) - B.ht_workspace_bytes(B.make_config(f32, max_tree=128))
+    live = 4 * (d + 2 * qd + f + v + k * d + wl.head_dim)
+    attention = 4 * 16 * wl.n_heads * (wl.head_dim + 2)                  # partial outputs of the key slices
+    assert 128 * live <= rows <= 128 * (live + attention + 1024)
+    short, long = (B.ht_workspace_bytes(B.make_config(wl, max_cache=c)) for c in (2048, 8192))
+    cache = 6144 * 2 * 2 * 2 * wl.n_kv_heads * wl.head_dim               # slots x layers x (K, V) x bytes
+    assert cache <= long - short <= cache + 6144 * 16                    # prompt tokens and loss terms beside it
