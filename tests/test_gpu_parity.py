@@ -69,6 +69,52 @@ def test_skinny_product_matches_textbook_product(dtype, M, N, K):
     assert np.max(np.abs(got - want)) <= bound, (np.max(np.abs(got - want)), bound)
 
 
+# the plain product of fp32 operands and of bf16 shapes that do not pack: two, four and eight rows per workgroup, the last also
+# with fewer workgroups than rows ask for, 16-byte pieces and single elements (columns or addresses that allow no pieces)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K,off", [(1, 70, 256, 0), (3, 70, 1032, 0), (6, 2050, 264, 0), (9, 4102, 136, 0), (250, 1030, 72, 0),
+                                       (5, 70, 201, 0), (6, 2050, 65, 0), (19, 4102, 7, 0), (7, 2050, 256, 1), (4, 34, 512, 3)])
+def test_plain_product_forms(dtype, M, N, K, off):
+    B, H = _B(), _H()
+    say(f"plain product {dtype} M={M} N={N} K={K} offset {off}")
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def at_offset(t):
+        store = torch.zeros(t.numel() + 8, dtype=tdt, device=H.DEV)
+        return store[off:off + t.numel()].view_as(t).copy_(t)
+
+    a = at_offset(counter_normal(2, 21, (M, K), 1.0, device=H.DEV, dtype=tdt))
+    w = at_offset(counter_normal(2, 22, (N, K), 0.05, device=H.DEV, dtype=tdt))
+    out = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device=H.DEV)
+    B.ht_skinny_gemm(a, w, M, N, K, B.HT_F32 if dtype == "f32" else B.HT_BF16, out)
+    torch.cuda.synchronize()
+    x, y = H.cpu(a), H.cpu(w)
+    # a lane adds K / 64 products one after the other (each rounded in fp32), then six partial sums of lanes
+    assert np.all(np.abs(H.cpu(out[:M]) - O.linear(x, y)) <= (2 * K / 64 + 40) * 2.0 ** -24 * np.abs(x) @ np.abs(y).T)
+    assert bool(torch.isnan(out[M]).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 4096), (33, 272, 2056), (128, 1040, 1032)])
+@pytest.mark.parametrize("off", [0, 1, 2])
+def test_sums_of_splits_at_any_output_address(M, N, K, off):
+    """Products that split K, into an output 4 and 8 bytes past a 16-byte address: single floats instead of pieces."""
+    B, H = _B(), _H()
+    say(f"split sums M={M} N={N} K={K} offset {off}")
+    a = torch.zeros(B.ht_padded_rows(M), K, dtype=torch.bfloat16, device=H.DEV)
+    a[:M] = counter_normal(3, 31, (M, K), 1.0, device=H.DEV, dtype=torch.bfloat16)
+    w = counter_normal(3, 32, (N, K), 0.05, device=H.DEV, dtype=torch.bfloat16)
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_weight_pack(w, N, K, packed)
+    scratch = torch.empty(B.ht_skinny_gemm_scratch_bytes(M, N, K), dtype=torch.uint8, device=H.DEV)
+    store = torch.full((M * N + 8,), 7.0, device=H.DEV)
+    out = store[off:off + M * N].view(M, N)
+    B.ht_skinny_gemm_packed(a, packed, M, N, K, out, scratch)
+    torch.cuda.synchronize()
+    x, y = H.cpu(a[:M]), H.cpu(w)
+    assert np.all(np.abs(H.cpu(out) - O.linear(x, y)) <= (K / 32 + 16) * 2.0 ** -24 * np.abs(x) @ np.abs(y).T)
+    assert bool((store[:off] == 7).all()) and bool((store[off + M * N:] == 7).all())
+
+
 @pytest.mark.parametrize("M,f,K", [(1, 64, 64), (7, 208, 200), (64, 688, 256), (76, 1376, 512), (128, 4112, 136),
                                    (64, 11008, 128), (131, 688, 256), (256, 1376, 512)])
 def test_fused_gate_up_product_matches_its_definition(M, f, K):

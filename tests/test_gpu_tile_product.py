@@ -110,3 +110,94 @@ def test_operands_that_are_not_16_byte_aligned(M, N, K, off_a, off_w):
     torch.cuda.synchronize()
     want = O.silu(O.linear(H.cpu(a0[:M]), H.cpu(gate))) * O.linear(H.cpu(a0[:M]), H.cpu(up))
     assert np.all(np.abs(H.cpu(act) - want) <= 2.0 ** -8 * np.abs(want) + 1e-4 * np.abs(want).max())
+
+
+class Segs(C.Structure):
+    _fields_ = [("w", C.c_void_p * 3), ("rows", C.c_int32 * 3), ("nseg", C.c_int32)]
+
+
+class Qkv(C.Structure):
+    _fields_ = [(f, C.c_void_p) for f in ("cs", "q", "kc", "vc")] + [(f, C.c_int32) for f in ("n", "Hq", "Hkv", "hd", "cap")] + [
+        ("n_dev", C.c_void_p), ("tail_row", C.c_int32), ("tail_n", C.c_int32), ("tail_cap", C.c_int32)] + [
+        (f, C.c_void_p) for f in ("tail_cs", "tail_kc", "tail_vc")]
+
+
+def factors(rows, first, hd):
+    angle = (first + torch.arange(rows, dtype=torch.float64, device=H.DEV))[:, None] * 10000.0 ** (
+        -torch.arange(hd // 2, dtype=torch.float64, device=H.DEV) / (hd // 2))
+    return torch.stack([angle.cos(), angle.sin()], dim=2).float().contiguous()
+
+
+def rotated(x, cs):
+    co, si = cs[:, None, :, 0].double(), cs[:, None, :, 1].double()
+    a, b = x.chunk(2, dim=2)
+    return torch.cat([a * co - b * si, b * co + a * si], dim=2)
+
+
+# 1800 rows, 48 tiles of 256 features: 32 in whole rounds, the last 16 as tiles of half the size; the seam, feature 8192, lies
+# between two k heads (48 / 24 heads of 128) or two v heads (32 / 32)
+@pytest.mark.parametrize("Hq,Hkv", [(48, 24), (32, 32)])
+@pytest.mark.parametrize("tail", [0, 1100])
+def test_rotary_and_append_across_the_two_launches_of_a_product(Hq, Hkv, tail):
+    import paper_2404_12022_amd.binding as B
+    M, K, hd, n = 1800, 2048, 128, 5
+    qd, kvd = Hq * hd, Hkv * hd
+    N = qd + 2 * kvd
+    assert N == 12288
+    a, w = inputs(M, N, K, Hq + tail)
+    lib, s = B.lib, torch.cuda.current_stream().cuda_stream
+    repack = getattr(lib, "_ZN2ht13launch_repackENS_10WeightSegsEiiiPvP12ihipStream_t")
+    repack.restype, repack.argtypes = C.c_int, [Segs] + [C.c_int] * 3 + [C.c_void_p] * 2
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    parts = [w[:qd], w[qd:qd + kvd], w[qd + kvd:]]
+    assert repack(Segs((C.c_void_p * 3)(*[p.data_ptr() for p in parts]), (C.c_int32 * 3)(qd, kvd, kvd), 3), K, 2, hd, packed.data_ptr(), s) == 0
+    own = tail or M                                   # rows with the first caches; the others have caches of their own
+    cap, tail_n = n + M + 3, 2
+    cap, tail_cap = (cap + 7) // 8 * 8, 808
+    cs, tail_cs = factors(M, n, hd), factors(M, 3, hd)
+    bf = dict(dtype=torch.bfloat16, device=H.DEV)
+    q = torch.full((M, Hq, hd), 7.0, **bf)
+    kc, vc = torch.full((cap, Hkv, hd), 7.0, **bf), torch.full((Hkv, hd, cap), 7.0, **bf)
+    tk, tv = torch.full((tail_cap, Hkv, hd), 7.0, **bf), torch.full((Hkv, hd, tail_cap), 7.0, **bf)
+    qe = Qkv(cs.data_ptr(), q.data_ptr(), kc.data_ptr(), vc.data_ptr(), n, Hq, Hkv, hd, cap, None, tail, tail_n, tail_cap,
+             tail_cs.data_ptr() if tail else None, tk.data_ptr() if tail else None, tv.data_ptr() if tail else None)
+    fn = getattr(lib, "_ZN2ht20launch_gemm_wide_qkvEPKvNS_7PackedWEiNS_11QkvEpilogueEP12ihipStream_tNS_8RowScaleE")
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, Qkv, C.c_void_p, RowScale]
+    print(f"q|k|v over two launches, {Hq}/{Hkv} heads, tail {tail}", flush=True)
+    assert fn(a.data_ptr(), Packed(packed.data_ptr(), N, K, K), M, qe, s, RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    y = a.double() @ w.double().T
+    err = (K / 32 + 16) * 2.0 ** -24 * float((a.double().abs() @ w.double().abs().T).max())
+
+    def close(got, want):                             # one bf16 rounding (half an ulp, 2^-9) on sums that are off by err
+        return bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 4 * err).all())
+
+    both = torch.cat([cs[:own], tail_cs[:M - own]])
+    assert close(q, rotated(y[:, :qd].view(M, Hq, hd), both))
+    k = rotated(y[:, qd:qd + kvd].reshape(M, Hkv, hd), both)
+    v = y[:, qd + kvd:].reshape(M, Hkv, hd)
+    assert close(kc[n:n + own], k[:own]) and close(vc[:, :, n:n + own].permute(2, 0, 1), v[:own])
+    assert bool((kc[:n] == 7).all()) and bool((kc[n + own:] == 7).all()) and bool((vc[:, :, :n] == 7).all()) and bool((vc[:, :, n + own:] == 7).all())
+    if tail:
+        t1 = tail_n + M - own
+        assert close(tk[tail_n:t1], k[own:]) and close(tv[:, :, tail_n:t1].permute(2, 0, 1), v[own:])
+        assert bool((tk[:tail_n] == 7).all()) and bool((tk[t1:] == 7).all()) and bool((tv[:, :, t1:] == 7).all())
+
+
+def test_gate_up_across_the_two_launches_of_a_product():
+    import paper_2404_12022_amd.binding as B
+    M, f, K = 1800, 6144, 2048                        # 48 tiles of 256 interleaved features, the seam at 4096 of 6144
+    a, w = inputs(M, 2 * f, K, 11)
+    packed = torch.empty(B.ht_weight_pack_bytes(2 * f, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_gate_up_pack(w[:f].contiguous(), w[f:].contiguous(), f, K, packed)
+    fn = getattr(B.lib, "_ZN2ht21launch_gemm_wide_siluEPKvNS_7PackedWEiPvP12ihipStream_tNS_8RowScaleE")
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_void_p, RowScale]
+    act = torch.full((M + 1, f), 7.0, dtype=torch.bfloat16, device=H.DEV)
+    print("gate/up over two launches", flush=True)
+    assert fn(a.data_ptr(), Packed(packed.data_ptr(), 2 * f, K, K), M, act.data_ptr(), torch.cuda.current_stream().cuda_stream,
+              RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    gate, up = a.double() @ w[:f].double().T, a.double() @ w[f:].double().T
+    want = gate / (1 + torch.exp(-gate)) * up
+    assert bool(((act[:M].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4 * want.abs().max()).all())
+    assert bool((act[M] == 7).all())
