@@ -91,7 +91,9 @@ int ht_load_layer(ht_model *m, int32_t layer, const void *wq, const void *wk, co
 int ht_load_lm_head(ht_model *m, const void *lm_head, void *stream);
 
 /* Bytes of device workspace `ht_init_model` needs for this configuration (KV cache, activations,
- * tree tables, decoder state). */
+ * tree tables, decoder state; bf16 models on packed weights also their copy of the weights and the activations of a prompt
+ * pass of min(max_cache, 2048) rows, which stay reserved for the model's life: up to 14 d_model + 4 n_heads head_dim +
+ * 2 d_ffn bytes a row, 197 MB at d_model 4096 / d_ffn 11008, 353 MB at 8192 / 28672). */
 int ht_workspace_bytes(const ht_config *cfg, size_t *out_bytes);
 
 /* Validates cfg, carves `workspace` (device, 256-byte aligned, >= ht_workspace_bytes) and clears it on
@@ -128,16 +130,18 @@ int ht_set_dynamic_tree(ht_model *m, int32_t T, int32_t b, void *stream);
  * the next acceptance ends on a listed node, the following `ht_tree_verify_step(tree_tokens = NULL)` builds its
  * tree from those rows and needs no `ht_transfer` and no draft pass (an `ht_transfer(m, NULL, NULL, ..)` in
  * between returns at once); if it ends elsewhere the step drafts after acceptance as without this call.
- * Either way the tokens are the same (the two schedules compute the same distributions).
+ * Either way the tokens are the same (the two schedules compute the same distributions, bf16 models up to rounding:
+ * the maps of several nodes at once are summed in another order than those of one accepted token).
  * nodes: host array of `count` distinct node ids of the current tree, count = 0 switches the feature off (always
  * allowed, also after ht_set_dynamic_tree, where any other count is HT_ESTATE); `ht_set_tree` also switches it off.  The pass then has T + count * k rows, which must fit max_tree (and
  * n + T + count * k must fit max_cache at every step): HT_ECAPACITY otherwise; HT_ETREE for bad ids;
  * HT_ESTATE without a tree. */
 int ht_set_fused_nodes(ht_model *m, int32_t count, const int32_t *nodes /*host*/, void *stream);
 
-/* Runs the prompt (host array of n token ids, n >= 1) through the model with plain causal attention (packed bf16
- * models: up to 2048 positions per pass whatever max_tree is, longer prompts in passes of equal length), fills the KV cache, sets the pending root token to the greedy next token and keeps the
- * layer-t residual of the last prompt token as the transfer source.  Resets any previous cache. */
+/* Runs the prompt (host array of n token ids, n >= 1) through the model with plain causal attention (bf16 models on packed
+ * weights with heads of 64 or 128: up to 2048 positions per pass whatever max_tree is, longer prompts in passes of equal
+ * length; others in chunks of up to min(max_tree, 128) rows), fills the KV cache, sets the pending root token to the greedy
+ * next token and keeps the layer-t residual of the last prompt token as the transfer source.  Resets any previous cache. */
 int ht_prefill(ht_model *m, const int32_t *tokens /*host*/, int32_t n, void *stream);
 
 /* Forward pass of the training stage for transfer step `step` (1-based i of Sec. 3.3) and its distillation loss.

@@ -109,7 +109,7 @@ bool shapes_packable(const ht_config& c) {
 }
 
 // Rows of a prompt that go through a block in one pass: enough that every product of it fills the chip several times
-// (2048 rows of a 4096-wide model: 34 TFLOP a block), few enough that the activations stay small beside the model.
+// (2048 rows of a 4096-wide model: 0.83 TFLOP a block), few enough that the activations stay small beside the model.
 constexpr int kPromptRows = 2048;
 int prompt_rows(const ht_config& c) { return c.max_cache < kPromptRows ? c.max_cache : kPromptRows; }
 // Prompts run on the packed weights with the fused q|k|v epilogue and the matrix-core attention, or chunk by chunk on the
@@ -928,7 +928,9 @@ int ht_prefill(ht_model* m, const int32_t* tokens, int32_t n, void* stream) {
     m->has_prefill = true;
     return HT_OK;
   }
-  const int chunk = m->Mp < 128 ? m->Mp : 128;          // more rows a pass would only stream the weights twice
+  // Models without prompt passes (fp32, shapes that do not pack, heads that are not 64 or 128 wide): chunks of what the
+  // decode buffers hold, at most 128 rows, which is what the attention over a chunk is made for.
+  const int chunk = m->Mp < 128 ? m->Mp : 128;
   for (int start = 0; start < n; start += chunk) {
     const int rows = n - start < chunk ? n - start : chunk;
     const bool last = start + rows == n;

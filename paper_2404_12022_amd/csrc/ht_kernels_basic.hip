@@ -1138,14 +1138,13 @@ hipError_t launch_prefill_finish(StepState* st, const int32_t* g, const float* s
 
 // ------------------------------------------------------------------------------------------------ hidden transfer
 // pseudo[f][i][o] = sum_c W_i[o][c] h_f[c] for F source vectors h_f = h + row(f) * d, row(f) = src_rows[f] (or f
-// when src_rows is NULL).  With several sources a wavefront produces four consecutive output features: the four
-// weight rows are read fully coalesced (16 bytes per lane and row) and every 16-byte piece of a source, which
-// comes from L2, serves all four (one feature per wavefront re-read the sources for every weight row: nine bytes
-// of source per weight byte with four sources, 51 us against 28 us at d = 4096).  Sources go in groups of four (of
-// sixteen from sixteen sources on, which walks the weight rows a quarter as often);
-// one source alone has its own instance with one feature per wavefront.  Every (source,
-// output) sum runs in the same order whatever F is, so one source alone and the same source among several give
-// the same bits.
+// when src_rows is NULL).  One source (either type): a wavefront per output feature, weight rows read fully coalesced.
+// Several sources of an fp32 model: a wavefront produces four consecutive output features, so that every 16-byte piece of a
+// source, which comes from L2, serves all four; sources go in groups of four (of sixteen from sixteen sources on, which
+// walks the weight rows a quarter as often), and every (source, output) sum runs in the same order whatever F is: one
+// source alone and the same source among several give the same bits.  Several sources of a bf16 model go to the matrix
+// cores (ht_transfer_mfma.hip), whose sums run in another order: there the two agree to fp32 rounding.  One source stays
+// here because the walk along K is shorter on a whole wavefront (three maps of 1024 x 1024: 3.7 us, 6.0 us there).
 // Steps i0 .. i0 + gridDim.y - 1 are computed; the output row of (f, i) is f * row_stride + (i - i0).
 // grid = (ceil(d / (4 R)), steps), block = 256.
 template <typename T, int NF, int R>           // R output features per wavefront: a source piece is loaded once for all

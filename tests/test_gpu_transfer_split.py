@@ -100,3 +100,35 @@ def test_infinite_and_nan_weights_reach_the_sums_they_belong_to(F):
     ref = h.double() @ w[rest].double().T
     bound = (d / 128 + 16) * 2.0 ** -24 * (h.double().abs() @ w[rest].double().abs().T)
     assert bool(((out[:, rest].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("d", [256, 1032])
+def test_one_source_alone_and_among_others(d):
+    """fp32 maps: the same bits however many sources share the launch.  bf16 maps, where several sources are summed in another
+    order: within the fp32 rounding of the two sums."""
+    import paper_2404_12022_amd.binding as B
+    fn = getattr(B.lib, SYMBOL)
+    fn.restype = C.c_int
+    fn.argtypes = [C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p] + [C.c_int] * 4 + [C.c_void_p] * 2
+    g, dev = torch.Generator(device="cuda:0").manual_seed(d), "cuda:0"
+    h = torch.empty(20, d, device=dev).normal_(0, 1, generator=g)
+    scratch = torch.empty(4 * 3 * ((d + 63) // 64 * 2) * 1024, dtype=torch.uint8, device=dev)
+    for dtype, code in ((torch.float32, B.HT_F32), (torch.bfloat16, B.HT_BF16)):
+        w = torch.empty(d, d, device=dev).normal_(0, 0.02, generator=g).to(dtype)
+        ptrs = torch.tensor([w.data_ptr()], dtype=torch.int64, device=dev)
+
+        def run(rows):
+            out = torch.zeros(rows, d, device=dev)
+            assert fn(code, h.data_ptr(), None, rows, ptrs.data_ptr(), out.data_ptr(), 0, 1, 1, d, scratch.data_ptr(),
+                      torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            return out
+
+        alone = run(1)
+        bound = 2 * (d / 128 + 16) * 2.0 ** -24 * (h[:1].double().abs() @ w.double().abs().T)
+        for rows in (3, 7, 20):
+            among = run(rows)[:1]
+            if dtype == torch.float32:
+                assert torch.equal(alone, among)
+            else:
+                assert bool(((alone.double() - among.double()).abs() <= bound).all())
