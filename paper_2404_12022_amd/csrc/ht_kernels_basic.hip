@@ -778,79 +778,102 @@ hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev t
 
 // ---- tree chosen from the draft distributions
 // lp[i][r] = log-softmax value of candidate r of draft row i:  z - (max + log(sum exp(z - max))) over the whole row.
-// One block of 1024 threads per row, few rows: bound by what one compute unit takes in, so rows of up to 32768 floats
-// (KEEP) are read once and stay in registers between the maximum and the sum (3 rows of 32000: 8.1 -> 6.6 us).
-constexpr int kLogprobKeep = 8;               // 16-byte pieces of a row a thread keeps
-template <bool KEEP>
+// One block of 1024 threads per row, few rows: bound by what one compute unit takes in (50 GB/s) and by the reductions
+// behind it.  A thread brings in 32 floats at a time, all requested before the first is used (16 bytes each where the rows
+// lie on 16 bytes), and keeps a sum against its own maximum, so a row is read once and maxima and sums meet once at the
+// end.  Three rows, us, with two walks over the row (or a block-wide maximum in the middle) and now: 1000 3.2 and 2.9, 8000 3.9
+// and 3.5, 32000 6.5 and 5.2, 128000 20.3 and 13.3; of odd length 1003 3.1 and 2.8, 32001 11.1 and 6.5, 127999 35.8 and 19.
+// e^x for x <= 0 (NaN stays NaN): 2^(x log2 e) with the product in two parts, t rounded and the rest r of it, 2^(t + r) = 2^t
+// (1 + r ln 2).  At most 2 units in the last place for x > -87; below, results of less than 2^-126 are 0.
+__device__ inline float exp_below(float x) {
+  x = x < -150.f ? -150.f : x;
+  const float t = x * 1.44269504f, r = fmaf(x, 1.44269504f, -t) + x * 1.92596299e-8f, e = __builtin_amdgcn_exp2f(t);
+  return fmaf(e, r * 0.693147181f, e);
+}
+template <int VEC, int PIECES>
 __global__ __launch_bounds__(1024) void cand_logprob_kernel(const float* __restrict__ d, const int32_t* __restrict__ cand,
-                                                            int b, int V, int vec, float* __restrict__ lp) {
-  __shared__ float red[16];
+                                                            int b, int V, float* __restrict__ lp) {
+  __shared__ float2 wave_red[16];
+  constexpr int STEP = 1024 * VEC;
   const float* row = d + (size_t)blockIdx.x * V;
-  const int v4 = vec ? (V & ~3) : 0;
   // the candidates' own values are on their way while the row is summed up
   const float own = (int)threadIdx.x < b ? row[cand[blockIdx.x * kMaxTopK + threadIdx.x]] : 0.f;
-  float peak = -INFINITY;
-  float4 keep[KEEP ? kLogprobKeep : 1];
-  if (KEEP) {
+  float peak = -INFINITY, sum = 0.f;
+  for (int base = 0; base < V; base += PIECES * STEP) {
+    float v[PIECES][VEC];
 #pragma unroll
-    for (int i = 0; i < kLogprobKeep; ++i) {
-      const int j = (i * 1024 + threadIdx.x) * 4;
-      if (j < V) keep[i] = *(const float4*)(row + j);
+    for (int i = 0; i < PIECES; ++i) {
+      const int j = base + i * STEP + threadIdx.x * VEC;
+#pragma unroll
+      for (int u = 0; u < VEC; ++u) v[i][u] = -INFINITY;
+      if (base + i * STEP >= V) continue;                      // uniform
+      if (j < V) {
+        if (VEC == 4) {
+          const float4 q = *(const float4*)(row + j);
+          v[i][0] = q.x, v[i][VEC / 4] = q.y, v[i][VEC / 2] = q.z, v[i][VEC - 1] = q.w;
+        } else {
+          v[i][0] = row[j];
+        }
+      }
     }
+    float high = peak;
 #pragma unroll
-    for (int i = 0; i < kLogprobKeep; ++i)
-      if ((i * 1024 + (int)threadIdx.x) * 4 < V)
-        peak = fmaxf(fmaxf(peak, fmaxf(keep[i].x, keep[i].y)), fmaxf(keep[i].z, keep[i].w));
-  } else {
-    for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) {
-      const float4 q = *(const float4*)(row + j);
-      peak = fmaxf(fmaxf(peak, fmaxf(q.x, q.y)), fmaxf(q.z, q.w));
+    for (int i = 0; i < PIECES; ++i)
+      if (base + i * STEP < V) {
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) high = fmaxf(high, v[i][u]);
+      }
+    const float ref = high == -INFINITY ? 0.f : high;          // (nothing but -inf so far: sums of zeros)
+    sum *= exp_below(peak - ref);
+    peak = high;
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      if (base + i * STEP < V) {
+        float part = 0.f;
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) part += exp_below(v[i][u] - ref);
+        sum += part;
+      }
     }
-    for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) peak = fmaxf(peak, row[j]);
   }
-  peak = wave_max(peak);
+  const float top = wave_max_dpp(peak);
+  sum = wave_sum(sum * exp_below(peak - (top == -INFINITY ? 0.f : top)));
+  if ((threadIdx.x & 63) == 0) wave_red[threadIdx.x >> 6] = make_float2(top, sum);
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = peak;
-  __syncthreads();
-  peak = red[0];
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) peak = fmaxf(peak, red[w]);
-  float sum = 0.f;
-  auto four = [&](const float4& q) { sum += (expf(q.x - peak) + expf(q.y - peak)) + (expf(q.z - peak) + expf(q.w - peak)); };
-  if (KEEP) {
+  peak = wave_red[0].x;
 #pragma unroll
-    for (int i = 0; i < kLogprobKeep; ++i)
-      if ((i * 1024 + (int)threadIdx.x) * 4 < V) four(keep[i]);
-  } else {
-    for (int j = threadIdx.x * 4; j < v4; j += blockDim.x * 4) four(*(const float4*)(row + j));      // the row is in L2 now
-    for (int j = v4 + threadIdx.x; j < V; j += blockDim.x) sum += expf(row[j] - peak);
-  }
-  sum = block_sum_any(sum, red);
+  for (int w = 1; w < 16; ++w) peak = fmaxf(peak, wave_red[w].x);
+  sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) sum += wave_red[w].y * exp_below(wave_red[w].x - peak);
   const float lse = peak + logf(sum);
   if ((int)threadIdx.x < b) lp[blockIdx.x * kMaxTopK + threadIdx.x] = own - lse;
 }
 hipError_t launch_cand_logprob(const float* d, const int32_t* cand, int rows, int b, int V, float* lp, hipStream_t s) {
-  const int vec = !((uintptr_t)d & 15) && !(V & 3);
-  // (short rows are over sooner without: 1000 3.2 and 3.35 us, 6000 3.58 and 3.64, 8000 4.05 and 3.87)
-  if (vec && V > 7168 && V <= 4096 * kLogprobKeep)
-    hipLaunchKernelGGL(cand_logprob_kernel<true>, dim3(rows), dim3(1024), 0, s, d, cand, b, V, vec, lp);
-  else
-    hipLaunchKernelGGL(cand_logprob_kernel<false>, dim3(rows), dim3(1024), 0, s, d, cand, b, V, vec, lp);
+  // (few floats to a thread: the checks of 32 loads that are not there cost a microsecond at 1003 floats)
+  if (!((uintptr_t)d & 15) && !(V & 3)) {
+    if (V <= 4096) hipLaunchKernelGGL((cand_logprob_kernel<4, 1>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+    else hipLaunchKernelGGL((cand_logprob_kernel<4, 8>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+  } else if (V <= 4096) {
+    hipLaunchKernelGGL((cand_logprob_kernel<1, 4>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+  } else if (V <= 8192) {
+    hipLaunchKernelGGL((cand_logprob_kernel<1, 8>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+  } else {
+    hipLaunchKernelGGL((cand_logprob_kernel<1, 32>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+  }
   return hipGetLastError();
 }
 
 // The T - 1 best nodes of the complete b-ary candidate tree of depth k in the order (score descending, depth
 // ascending, rank path ascending), score = sum of lp along the path accumulated in float from the root down.
-// A node never scores above its parent or its previous sibling, and each of the two comes first in that order, so
-// the order is produced by a best-first walk: the frontier holds, for every node taken so far, its next sibling
-// and (once) its first child; the best frontier entry becomes the next node.  The frontier never holds more than
-// T <= 128 entries: slot j lives in the registers of lane j % 64 (one slot per lane in the first 63 rounds, two from then
-// on: T = 128 60.5 us with both looked at throughout, 55.2 us in the kernel with the table reads on the chain), a round is
-// one wave-wide maximum of the lanes' best scores, a ballot that names the winner (a second reduction over depth and path
-// only when several lanes hold the best score), and register updates in two lanes.  What bounds it is the chain of
-// dependent instructions from one round to the next, so nothing on it waits for memory: the score of every entry's next
-// sibling is at hand before the entry wins (its table read has until the entry wins again), and the best candidate of
-// every level, which a first child adds, sits in a register of the lane of that number.  T = 64, k = 3: 27.6 us with
-// the table reads on the chain and two slots throughout, 21.5 us.  Tables and tokens are written by all lanes at the end.
+// Two ways lead there.  tree_walk takes one node at a time; tree_levels takes a level at a time with eight wavefronts
+// and needs rows in order (best first, none above zero), as every softmax gives them.  A table that is not in order has no
+// such order of nodes: there the walk is the definition.  tree_dynamic_kernel looks at the table and decides.
+struct TreeScratch {
+  float lp[kMaxTransfer * kMaxTopK];
+  int cand[kMaxTransfer * kMaxTopK];
+  int parent[kMaxTree], depth[kMaxTree], rank[kMaxTree];
+};
 __device__ inline float not_nan(float v) { return v == v ? v : -INFINITY; }
 
 // (depth, path) order of two frontier entries with equal scores
@@ -858,36 +881,20 @@ __device__ inline bool tie_first(int depth_a, uint64_t path_a, int depth_b, uint
   return depth_a != depth_b ? depth_a < depth_b : path_a < path_b;
 }
 
+// A node never scores above its parent or its previous sibling, and each of the two comes first in that order, so
+// the order is produced by a best-first walk: the frontier holds, for every node taken so far, its next sibling
+// and (once) its first child; the best frontier entry becomes the next node.  The frontier never holds more than
+// T <= 128 entries: slot j lives in the registers of lane j % 64 (one slot per lane in the first 63 rounds, two from then
+// on), a round is one wave-wide maximum of the lanes' best scores, a ballot that names the winner (a second reduction over
+// depth and path only when several lanes hold the best score), and register updates in two lanes.  What bounds it is the
+// chain of dependent instructions from one round to the next, 0.3 us, so nothing on it waits for memory: the score of every
+// entry's next sibling is at hand before the entry wins (its table read has until the entry wins again), and the best
+// candidate of every level, which a first child adds, sits in a register of the lane of that number.
+// One wavefront; rows of `t` that it does not reach keep what they hold.
 template <int SLOTS>
-__global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restrict__ root, const int32_t* __restrict__ cand,
-                                                          const float* __restrict__ lp, int k, int b, int T,
-                                                          TreeOut tree, int32_t* __restrict__ tok) {
-  __shared__ float lp_s[kMaxTransfer * kMaxTopK];
-  __shared__ int cand_s[kMaxTransfer * kMaxTopK];
-  __shared__ int n_parent[kMaxTree], n_depth[kMaxTree], n_rank[kMaxTree];
-  const int lane = threadIdx.x;
-  static_assert(kMaxTopK == 64, "one table entry of a level per lane");
-  float lv[kMaxTransfer];
-  int cv[kMaxTransfer];
-#pragma unroll
-  for (int e = 0; e < kMaxTransfer; ++e) {         // all levels in one round trip; entries not in use read entry 0
-    const int i = e < k && lane < b ? e * kMaxTopK + lane : 0;
-    lv[e] = lp[i];
-    cv[e] = cand[i];
-  }
-  const int root_tok = *root;
-#pragma unroll
-  for (int e = 0; e < kMaxTransfer; ++e) {
-    lp_s[e * kMaxTopK + lane] = e < k && lane < b ? not_nan(lv[e]) : -INFINITY;
-    cand_s[e * kMaxTopK + lane] = cv[e];
-  }
-  for (int v = lane; v < kMaxTree; v += 64) {      // rows the walk does not reach (none, if the sizes were checked) hang under the root
-    n_parent[v] = v ? 0 : -1;
-    n_depth[v] = v ? 1 : 0;
-    n_rank[v] = 0;
-  }
-  __syncthreads();
-  const float first = lane < k ? lp_s[lane * kMaxTopK] : 0.f;         // lane e: the best candidate of level e + 1
+__device__ __forceinline__ void tree_walk(TreeScratch& t, int k, int b, int T) {
+  const int lane = threadIdx.x & 63;
+  const float first = lane < k ? t.lp[lane * kMaxTopK] : 0.f;         // lane e: the best candidate of level e + 1
   // frontier slot: score, score of its next sibling, score of the parent, depth (0: empty), parent node,
   // path = ranks from the root down, 6 bits each, the last rank in the lowest digit
   float fs[SLOTS], fn[SLOTS], fb[SLOTS];
@@ -900,7 +907,7 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
     fd[i] = fp[i] = 0;
     fq[i] = 0;
   }
-  const float top_lp = lp_s[0], next_lp = lp_s[1];
+  const float top_lp = t.lp[0], next_lp = t.lp[1];
   if (lane == 0) { fs[0] = top_lp; fn[0] = next_lp; fd[0] = 1; }      // first candidate of the first level, under the root
   int count = 1;
   auto round = [&](int v, auto both) __attribute__((always_inline)) -> bool {
@@ -939,11 +946,11 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
           fs[i] = fn[i];
           fq[i] += 1;
           fd[i] = r + 1 < b ? depth : 0;
-          if (r + 2 < b) fn[i] = fb[i] + lp_s[(depth - 1) * kMaxTopK + r + 2];
+          if (r + 2 < b) fn[i] = fb[i] + t.lp[(depth - 1) * kMaxTopK + r + 2];
         }
-      n_parent[v] = par;
-      n_depth[v] = depth;
-      n_rank[v] = r;
+      t.parent[v] = par;
+      t.depth[v] = depth;
+      t.rank[v] = r;
     }
     if (depth < k) {                               // the first child goes to a new slot
       // (read here, where all lanes are active: in the one-lane branch the lane of that number would not be)
@@ -957,7 +964,7 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
             fd[i] = depth + 1;
             fp[i] = v;
             fq[i] = path << 6;
-            fn[i] = best + lp_s[depth * kMaxTopK + 1];
+            fn[i] = best + t.lp[depth * kMaxTopK + 1];
           }
       }
       ++count;
@@ -966,7 +973,7 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
   };
   // before round v no more than v entries exist: the second slots stay empty until round 64
   bool more = true;
-  const int alone = SLOTS == 1 ? T : 64;
+  const int alone = SLOTS == 1 || T < 64 ? T : 64;
   for (int v = 1; v < alone; ++v) {
     more = round(v, std::false_type{});
     if (!more) break;
@@ -974,24 +981,313 @@ __global__ __launch_bounds__(64) void tree_dynamic_kernel(const int32_t* __restr
   if (SLOTS == 2 && more)
     for (int v = 64; v < T; ++v)
       if (!round(v, std::integral_constant<bool, SLOTS == 2>{})) break;
+}
+
+// Level by level: `ranked` holds the T - 1 best nodes of the levels so far, in order.  A round appends the children of the
+// last level's nodes among them, counts for every entry how many come before it, and keeps the first T - 1; a node that
+// drops out takes nothing with it that could still get in, because its children come after it.
+//  - The order of the array is the order of ties: older levels first, a level in path order (children are appended parent
+//    by parent in path order, so the same holds for the next level).  So entry j comes before entry i if its score is
+//    higher, or equal and j < i.
+//  - A node (a_1 .. a_e) of ranks a_i - 1 comes after every node of the same or a smaller depth whose ranks are nowhere
+//    larger: sum over f <= e of a_1 .. a_f nodes with itself.  Only nodes with a sum of at most T - 1 are appended, and, once
+//    T - 1 nodes are known, only those that beat the last: at most kLevelRoom a round (2806 for eight levels of 64
+//    candidates and 128 nodes, 10 + 84 + about 100 for three levels of 10 and 64 nodes).
+// Bound: a handful of LDS round trips and barriers a level, and the counting, 2 instructions for every pair of entries.
+constexpr int kTreeWaves = 8;
+static_assert(kMaxTransfer % kTreeWaves == 0, "a wavefront brings in whole levels of the table");
+constexpr int kLevelRoom = 2816;
+constexpr int kLevelMany = 256, kLevelBuckets = 256;
+constexpr int kCountStep = 4;                                  // 16-byte reads of entries in flight while they are compared
+struct LevelScratch {
+  alignas(16) uint32_t key[2][kMaxTree + kLevelRoom + 4 * kCountStep];      // scores as integers in the same order: ranked, then appended
+  uint16_t id[2][kMaxTree];                                   // node ids of the ranked entries
+  uint16_t from[kLevelRoom];                                  // appended entry: index of its parent in the level, rank
+  alignas(16) int place[kMaxTree + kLevelRoom];               // entries that come before it
+  float score[2][kMaxTree];                                   // last level's ranked nodes in path order: score,
+  int prod[2][kMaxTree], sum[2][kMaxTree];                    // a_1 .. a_e and the sum above,
+  uint16_t node[2][kMaxTree];                                 // id
+  uint16_t parent[1 + kMaxTransfer * kMaxTree];               // by id (0: the root): parent's id, rank, depth, place in the tree
+  uint8_t rank[1 + kMaxTransfer * kMaxTree], depth[1 + kMaxTransfer * kMaxTree], at[1 + kMaxTransfer * kMaxTree];
+  int count[2][kTreeWaves];
+};
+
+__device__ inline uint32_t ordered_bits(float v) {             // larger float, larger integer; never 0 for a number
+  const uint32_t u = __float_as_uint(v + 0.0f);                // (-0 and 0 are equal)
+  return u & 0x80000000u ? ~u : u | 0x80000000u;
+}
+
+__device__ inline float from_ordered_bits(uint32_t k) { return __uint_as_float(k & 0x80000000u ? k & 0x7fffffffu : ~k); }
+
+__device__ __forceinline__ void tree_levels(TreeScratch& t, LevelScratch& l, int k, int b, int T) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const uint64_t below = (1ull << lane) - 1;
+  const float inv_b = 1.0f / (float)b;
+  if (tid == 0) {
+    l.score[0][0] = 0.f;
+    l.prod[0][0] = 1;
+    l.sum[0][0] = 0;
+    l.node[0][0] = 0;
+    l.at[0] = 0;
+  }
   __syncthreads();
-  for (int v = lane; v < T; v += 64) {
-    const int depth = n_depth[v], r = n_rank[v];
-    tree.parent[v] = n_parent[v];
+  int m = 0, level = 1, ids = 1;                               // ranked entries, nodes of the last level, ids given out
+  for (int e = 0; e < k && level > 0; ++e) {
+    uint32_t* const key = l.key[e & 1];
+    const int cur = e & 1, nxt = cur ^ 1;
+    const int grid = level * b;                                // child slots, parent by parent
+    const int per_wave = (grid + 64 * kTreeWaves - 1) / (64 * kTreeWaves) * 64, g0 = wave * per_wave;
+    const uint32_t last = m == T - 1 ? key[m - 1] : 0;         // what an appended entry has to beat
+    auto child = [&](int g, uint32_t& score_bits, int& from) __attribute__((always_inline)) -> bool {
+      const int p = (int)(((float)g + 0.5f) * inv_b), r = g - p * b;      // g < 8192: exact
+      if (g >= grid) return false;
+      from = p << 6 | r;
+      score_bits = ordered_bits(l.score[cur][p] + t.lp[e * kMaxTopK + r]);
+      return l.sum[cur][p] + l.prod[cur][p] * (r + 1) <= T - 1 && score_bits > last;
+    };
+    uint32_t bits = 0;
+    int from = 0, mine = 0;
+    bool yes = false;
+    uint64_t all = 0;
+    for (int g = g0; g < g0 + per_wave && g < grid; g += 64) {
+      yes = child(g + lane, bits, from);
+      all = __ballot(yes);
+      mine += __popcll(all);
+    }
+    if (lane == 0) l.count[0][wave] = mine;
+    __syncthreads();
+    int at = m, added = 0;
+    auto take_counts = [&](const int* counts, int& upto, int& total) __attribute__((always_inline)) {
+#pragma unroll
+      for (int w = 0; w < kTreeWaves; ++w) {
+        const int c = counts[w];
+        upto += w < wave ? c : 0;
+        total += c;
+      }
+    };
+    take_counts(l.count[0], at, added);
+    if (m > 0 && m + added > kLevelMany) {
+      // So many that counting would take long: a histogram of how far entries are behind the first (kLevelBuckets of 1/16,
+      // the last one without end) says which buckets the first T - 1 lie in; the others are left out.
+      for (int i = tid; i < kLevelBuckets; i += 64 * kTreeWaves) l.place[i] = 0;
+      __syncthreads();
+      const float top = from_ordered_bits(key[0]);
+      auto bucket = [&](uint32_t score_bits) __attribute__((always_inline)) {
+        return (int)fminf((top - from_ordered_bits(score_bits)) * 16.f, (float)(kLevelBuckets - 1));
+      };
+      for (int i = tid; i < m; i += 64 * kTreeWaves) atomicAdd(&l.place[bucket(key[i])], 1);
+      for (int g = g0; g < g0 + per_wave && g < grid; g += 64)
+        if (child(g + lane, bits, from)) atomicAdd(&l.place[bucket(bits)], 1);
+      __syncthreads();
+      static_assert(kLevelBuckets == 256, "four buckets to a lane");
+      const int4 h = *(const int4*)(l.place + lane * 4);
+      int sum = h.x + h.y + h.z + h.w;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int other = __shfl_up(sum, o, 64);
+        sum += lane >= o ? other : 0;
+      }
+      const uint64_t enough = __ballot(sum >= T - 1);
+      const int limit = enough ? __builtin_ctzll(enough) * 4 + 3 : kLevelBuckets;       // to four buckets
+      auto close = [&](int g) __attribute__((always_inline)) { return child(g, bits, from) && bucket(bits) <= limit; };
+      mine = 0;
+      for (int g = g0; g < g0 + per_wave && g < grid; g += 64) {
+        yes = close(g + lane);
+        all = __ballot(yes);
+        mine += __popcll(all);
+      }
+      if (lane == 0) l.count[1][wave] = mine;
+      __syncthreads();
+      at = m;
+      added = 0;
+      take_counts(l.count[1], at, added);
+      for (int g = g0; g < g0 + per_wave && g < grid; g += 64) {
+        if (per_wave > 64) {
+          yes = close(g + lane);
+          all = __ballot(yes);
+        }
+        if (yes) {
+          const int i = at + __popcll(all & below);
+          key[i] = bits;
+          l.from[i - m] = (uint16_t)from;
+        }
+        at += __popcll(all);
+      }
+    } else {
+      for (int g = g0; g < g0 + per_wave && g < grid; g += 64) {
+        if (per_wave > 64) {                                   // (with one turn everything is still in registers)
+          yes = child(g + lane, bits, from);
+          all = __ballot(yes);
+        }
+        if (yes) {
+          const int i = at + __popcll(all & below);
+          key[i] = bits;
+          l.from[i - m] = (uint16_t)from;
+        }
+        at += __popcll(all);
+      }
+    }
+    const int entries = m + added;
+    if (tid < 4 * kCountStep) key[entries + tid] = 0;          // never before anything: the counts go by so many
+    // 64 entries to a wavefront; where that leaves wavefronts over, 2^lg of them share the entries these are compared with
+    const int blocks = (entries + 63) / 64, lg = blocks == 1 ? 3 : blocks == 2 ? 2 : blocks <= 4 ? 1 : 0;
+    const int steps = (entries + 4 * kCountStep - 1) / (4 * kCountStep), share = (steps + (1 << lg) - 1) >> lg;
+    if (lg)
+      for (int i = tid; i < entries; i += 64 * kTreeWaves) l.place[i] = 0;
+    __syncthreads();
+    for (int block = wave >> lg; block < blocks; block += kTreeWaves) {
+      const int i0 = block * 64, i = i0 + lane, s0 = (wave & ((1 << lg) - 1)) * share, s1 = s0 + share < steps ? s0 + share : steps;
+      const uint32_t own = i < entries ? key[i] : 0, less = own - 1;
+      int before = 0;
+      for (int j0 = s0 * 4 * kCountStep; j0 < s1 * 4 * kCountStep; j0 += 4 * kCountStep) {
+        uint4 v[kCountStep];
+#pragma unroll
+        for (int u = 0; u < kCountStep; ++u) v[u] = *(const uint4*)(key + j0 + u * 4);
+        if (j0 < i0 || j0 >= i0 + 64) {            // all of them in front of this wavefront's entries, or behind
+          const uint32_t bar = j0 < i0 ? less : own;
+#pragma unroll
+          for (int u = 0; u < kCountStep; ++u) before += (v[u].x > bar) + (v[u].y > bar) + (v[u].z > bar) + (v[u].w > bar);
+        } else {
+#pragma unroll
+          for (int u = 0; u < kCountStep; ++u) {
+            const int j = j0 + u * 4;
+            before += (v[u].x > (j < i ? less : own)) + (v[u].y > (j + 1 < i ? less : own)) + (v[u].z > (j + 2 < i ? less : own)) +
+                      (v[u].w > (j + 3 < i ? less : own));
+          }
+        }
+      }
+      if (i < entries) {
+        if (lg) atomicAdd(&l.place[i], before);
+        else l.place[i] = before;
+      }
+    }
+    __syncthreads();
+    const int per = (added + 64 * kTreeWaves - 1) / (64 * kTreeWaves) * 64, a0 = wave * per;
+    mine = 0;
+    for (int a = a0; a < a0 + per && a < added; a += 64)
+      mine += __popcll(__ballot(a + lane < added && l.place[m + a + lane] < T - 1));
+    if (lane == 0) l.count[0][wave] = mine;
+    for (int i = tid; i < m; i += 64 * kTreeWaves) {           // older entries move down
+      const int to = l.place[i];
+      if (to < T - 1) {
+        l.key[nxt][to] = key[i];
+        l.id[nxt][to] = l.id[cur][i];
+      }
+    }
+    __syncthreads();
+    int pos = 0, kept = 0;
+    take_counts(l.count[0], pos, kept);
+    for (int a = a0; a < a0 + per && a < added; a += 64) {
+      const int i = m + a + lane;
+      const int to = a + lane < added ? l.place[i] : T;
+      const bool keep = to < T - 1;
+      const uint64_t stays = __ballot(keep);
+      if (keep) {
+        const int slot = pos + __popcll(stays & below), id = ids + slot, f = l.from[i - m], p = f >> 6, r = f & 63;
+        const int prod = l.prod[cur][p] * (r + 1);
+        l.key[nxt][to] = key[i];
+        l.id[nxt][to] = (uint16_t)id;
+        l.score[nxt][slot] = l.score[cur][p] + t.lp[e * kMaxTopK + r];
+        l.prod[nxt][slot] = prod;
+        l.sum[nxt][slot] = l.sum[cur][p] + prod;
+        l.node[nxt][slot] = (uint16_t)id;
+        l.parent[id] = l.node[cur][p];
+        l.rank[id] = (uint8_t)r;
+        l.depth[id] = (uint8_t)(e + 1);
+      }
+      pos += __popcll(stays);
+    }
+    m = entries < T - 1 ? entries : T - 1;
+    level = kept;
+    ids += kept;
+    if (level == 0 || e + 1 == k) {                            // the ranked entries are where the last round left them
+      __syncthreads();
+      for (int v = 1 + tid; v <= m; v += 64 * kTreeWaves) l.at[l.id[nxt][v - 1]] = (uint8_t)v;
+      __syncthreads();
+      for (int v = 1 + tid; v <= m; v += 64 * kTreeWaves) {
+        const int id = l.id[nxt][v - 1];
+        t.parent[v] = l.at[l.parent[id]];
+        t.depth[v] = l.depth[id];
+        t.rank[v] = l.rank[id];
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// WAVES = kTreeWaves: by levels if the table is in order; WAVES = 1: the walk alone.
+template <int SLOTS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void tree_dynamic_kernel(const int32_t* __restrict__ root, const int32_t* __restrict__ cand,
+                                                                  const float* __restrict__ lp, int k, int b, int T,
+                                                                  TreeOut tree, int32_t* __restrict__ tok) {
+  __shared__ TreeScratch t;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  static_assert(kMaxTopK == 64, "one table entry of a level per lane");
+  constexpr int LV = kMaxTransfer / WAVES;         // levels of the table a wavefront brings in
+  float lv[LV];
+  int cv[LV];
+#pragma unroll
+  for (int i = 0; i < LV; ++i) {                   // all levels in one round trip; entries not in use read entry 0
+    const int e = wave * LV + i, at = e < k && lane < b ? e * kMaxTopK + lane : 0;
+    lv[i] = lp[at];
+    cv[i] = cand[at];
+  }
+  const int root_tok = *root;
+  bool disorder = false;
+#pragma unroll
+  for (int i = 0; i < LV; ++i) {
+    const int e = wave * LV + i;
+    const bool in = e < k && lane < b;
+    const float v = in ? not_nan(lv[i]) : -INFINITY;
+    if (WAVES > 1) {
+      const float next = __shfl_down(v, 1, 64);
+      disorder |= in && (v > 0.f || (lane + 1 < b && next > v));
+    }
+    t.lp[e * kMaxTopK + lane] = v;
+    t.cand[e * kMaxTopK + lane] = cv[i];
+  }
+  for (int v = tid; v < kMaxTree; v += 64 * WAVES) {      // rows that are not reached (none, if the sizes were checked) hang under the root
+    t.parent[v] = v ? 0 : -1;
+    t.depth[v] = v ? 1 : 0;
+    t.rank[v] = 0;
+  }
+  if constexpr (WAVES > 1) {
+    __shared__ LevelScratch l;
+    if (__syncthreads_or(disorder)) {
+      if (wave == 0) tree_walk<SLOTS>(t, k, b, T);
+    } else {
+      tree_levels(t, l, k, b, T);
+    }
+  } else {
+    __syncthreads();
+    tree_walk<SLOTS>(t, k, b, T);
+  }
+  __syncthreads();
+  for (int v = tid; v < T; v += 64 * WAVES) {
+    const int depth = t.depth[v], r = t.rank[v];
+    tree.parent[v] = t.parent[v];
     tree.depth[v] = depth;
     tree.rank[v] = r;
-    tok[v] = v ? cand_s[(depth - 1) * kMaxTopK + r] : root_tok;
+    tok[v] = v ? t.cand[(depth - 1) * kMaxTopK + r] : root_tok;
     uint64_t mask[kMaskWords];
     for (int w = 0; w < kMaskWords; ++w) mask[w] = 0;
-    for (int u = v, hop = 0; u >= 0 && hop <= kMaxTransfer; u = n_parent[u], ++hop)
+    for (int u = v, hop = 0; u >= 0 && hop <= kMaxTransfer; u = t.parent[u], ++hop)
       for (int w = 0; w < kMaskWords; ++w) mask[w] |= w == (u >> 6) ? 1ull << (u & 63) : 0ull;
     for (int w = 0; w < kMaskWords; ++w) tree.anc[(size_t)v * kMaskWords + w] = mask[w];
   }
 }
+// The walk takes 2.4 us and 0.16 a node (0.25 beyond 64 nodes), the levels 3.3 us and 1 to 1.5 a level whatever the number of
+// nodes.  Where they meet (us, walk / levels): k = 1, 8 nodes 4.0 / 4.5, 12 nodes 5.0 / 4.5; k = 2, 12 nodes 5.7 / 6.3; k = 3,
+// 12 nodes 5.7 / 8.2, 24 nodes 9.5 / 8.3; k = 8, 24 nodes 9.4 / 10.4, 64 nodes 21.8 / 10.8.  By size, three levels of 10
+// candidates: 64 nodes 22.4 / 9.1, 96 nodes 37.5 / 9.8, 128 nodes 51.8 / 12.6; eight levels of 64, 128 nodes 53.5 / 18.3.
+bool tree_by_levels(int k, int T) { return T >= 8 + 4 * (k < 5 ? k : 5); }
 hipError_t launch_tree_dynamic(const int32_t* root, const int32_t* cand, const float* lp, int k, int b, int T,
                                TreeOut tree, int32_t* tok, hipStream_t s) {
-  if (T <= 64) hipLaunchKernelGGL(tree_dynamic_kernel<1>, dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
-  else hipLaunchKernelGGL(tree_dynamic_kernel<2>, dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
+  if (!tree_by_levels(k, T)) hipLaunchKernelGGL((tree_dynamic_kernel<1, 1>), dim3(1), dim3(64), 0, s, root, cand, lp, k, b, T, tree, tok);
+  else if (T <= 64)
+    hipLaunchKernelGGL((tree_dynamic_kernel<1, kTreeWaves>), dim3(1), dim3(64 * kTreeWaves), 0, s, root, cand, lp, k, b, T, tree, tok);
+  else
+    hipLaunchKernelGGL((tree_dynamic_kernel<2, kTreeWaves>), dim3(1), dim3(64 * kTreeWaves), 0, s, root, cand, lp, k, b, T, tree, tok);
   return hipGetLastError();
 }
 

@@ -58,6 +58,33 @@ def test_candidate_logprobs_match_log_softmax(rows, V, b):
     assert np.all(got[:, :b] <= 0)
 
 
+@pytest.mark.parametrize("V", [1, 3, 4096, 4097, 4100, 8192, 8193, 32768, 32769, 65540, 65541])
+def test_candidate_logprobs_at_the_edges_of_a_batch(V):
+    """Lengths around what a thread brings in at a time, 16-byte rows and others, rows whose largest entries sit in one batch,
+    impossible entries, a row of nothing else but one entry.  Float32 sums of up to V terms in [0, 1] in any order: 2e-5."""
+    B = _B()
+    say(f"log-probabilities at the edges V={V}")
+    gen = torch.Generator().manual_seed(V)
+    b = min(V, 5)
+    d = torch.randn(4, V, generator=gen) * 3.0
+    d[1, V // 2:] -= 200.0
+    d[2, : V // 2] -= 200.0
+    d[3] = -float("inf")
+    d[3, V - 1] = 2.5
+    top = torch.topk(d, b, dim=1).indices
+    cand = torch.zeros(4, TOPK, dtype=torch.int32)
+    cand[:, :b] = top
+    lp = torch.full((4, TOPK), 7.0, device=DEV)
+    B.ht_candidate_logprobs(d.to(DEV), cand.to(DEV), b, lp)
+    torch.cuda.synchronize()
+    want = torch.log_softmax(d.double(), dim=1).gather(1, top)
+    got = lp[:, :b].double().cpu()
+    finite = torch.isfinite(want)
+    assert torch.equal(finite, torch.isfinite(got)) and torch.equal(got[~finite], want[~finite])
+    # values of 200 and more are spaced 1.5e-5 apart, the sum of such a row's difference takes one such rounding more
+    assert float(((got - want).abs() / want.abs().clamp(min=1.0))[finite].max()) <= 2e-5
+
+
 def _run_tree_kernel(lp_table, cand_table, root, k, b, T):
     """lp_table, cand_table: numpy [k, b].  Returns (parent, depth, rank, anc [T, 2] uint64, tokens)."""
     B = _B()
@@ -120,6 +147,47 @@ def test_tree_choice_is_the_oracle_rule_bit_for_bit(kind):
             _check_tables(parent, depth, rank, anc, tokens, cand, 4242)
             cases += 1
     say(f"{kind}: {cases} trees equal the oracle's")
+
+
+def _best_first(lp, T):
+    """The walk that defines the choice for any table: the best of the next siblings and first children comes next."""
+    k, b = lp.shape
+    lp = np.where(np.isnan(lp), np.float32(-np.inf), lp).astype(np.float32)
+    parent, rank = [-1], [0]
+    frontier = {(0,): (np.float32(0), 0, lp[0, 0])}              # path: score of the parent, the parent, own score
+    while len(parent) < T:
+        path = min(frontier, key=lambda p: (-float(frontier[p][2]), len(p), p))
+        base, par, score = frontier.pop(path)
+        v = len(parent)
+        parent.append(par)
+        rank.append(path[-1])
+        if path[-1] + 1 < b:
+            frontier[path[:-1] + (path[-1] + 1,)] = (base, par, np.float32(base + lp[len(path) - 1, path[-1] + 1]))
+        if len(path) < k:
+            frontier[path + (0,)] = (score, v, np.float32(score + lp[len(path), 0]))
+    return parent, rank
+
+
+@pytest.mark.parametrize("kind", ["softmax", "ties", "uniform", "holes", "unordered", "positive"])
+def test_tree_choice_by_levels_and_by_the_walk_agree_with_the_definition(kind):
+    """Sizes on both sides of the rule that picks the level-by-level way (12, 16, .. 28 nodes), of 64 nodes, and of the size from
+    which on a level is thinned out (many children of many nodes); tables that are not in order stay with the walk."""
+    rng = np.random.default_rng(len(kind))
+    for k, b in [(1, 40), (2, 40), (3, 10), (3, 64), (4, 5), (5, 30), (8, 3), (8, 64)]:
+        room = sum(b ** e for e in range(1, k + 1))
+        if kind == "unordered":
+            lp = -rng.random(size=(k, b)).astype(np.float32) * 3
+        elif kind == "positive":                                 # in order, but a child may score above its parent
+            lp = (0.3 - np.sort(rng.random(size=(k, b)), axis=1)).astype(np.float32)
+        else:
+            lp = _tables(kind, k, b, rng)
+        cand = rng.integers(0, 32000, size=(k, b))
+        line = 8 + 4 * min(k, 5)
+        for T in sorted({t for t in (2, line - 1, line, 63, 64, 65, 100, 127, 128) if t <= room + 1}):
+            say(f"tree choice {kind} k={k} b={b} T={T}")
+            parent, depth, rank, anc, tokens = _run_tree_kernel(lp, cand, 11, k, b, T)
+            assert (parent, rank) == _best_first(lp, T), (kind, k, b, T)
+            _check_tables(parent, depth, rank, anc, tokens, cand, 11)
 
 
 def test_tree_choice_at_the_largest_sizes():
