@@ -9,6 +9,10 @@ import ctypes as C
 import os
 from typing import Dict, List, Optional, Sequence
 
+# torch first: the library and torch must share one HIP runtime, and the one torch loads has to be in the process before
+# libht.so resolves its own dependency (loaded the other way round, the library's runtime finds no device)
+import torch
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libht.so")
 
@@ -57,10 +61,6 @@ def _load() -> C.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it first (python -m paper_2404_12022_amd.build); "
                           "there is no fallback path")
-    # torch first: the library and torch must share one HIP runtime, and the one torch loads has to be in the
-    # process before libht.so resolves its own dependency (loaded the other way round, the library's runtime
-    # finds no device)
-    import torch  # noqa: F401
     lib = C.CDLL(LIB_PATH)
     i32p, f32p, vp, sz = C.POINTER(C.c_int32), C.POINTER(C.c_float), C.c_void_p, C.c_size_t
     sig = {
@@ -121,9 +121,13 @@ def _i32(seq: Sequence[int]):
 
 
 def _stream_ptr(stream=None) -> int:
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    """The stream's handle; None: the current stream of the current device, asked for without the stream object that
+    torch.cuda.current_stream() makes on the way (2 us of a call's 10)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t) -> Optional[int]:
