@@ -249,7 +249,6 @@ class HTModel:
     """Owns the workspace tensor and the pointer tables for one ht_model handle."""
 
     def __init__(self, cfg: ht_config, weights: Dict[str, object], device="cuda:0", stream=None):
-        import torch
         self.torch = torch
         self.cfg = cfg
         self.weights = weights                      # keep the tensors alive

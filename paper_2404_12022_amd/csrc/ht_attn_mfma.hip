@@ -43,16 +43,32 @@ union Frag {
 constexpr int kMaxSplits = 16;
 constexpr float kRescaleStep = 8.0f;    // log2 units the running maximum may lag behind before accumulators are rescaled
 
-template <int HD, int QB>
+// Rows as they come from the caller (FRESH): q is not rotated yet, and the keys and values of the pass are in [M][Hkv][HD]
+// rows of their own, not in the cache.
+struct FreshRows {
+  const bf16_t *k, *v;
+  bf16_t *kc, *vc;                 // the cache they are appended to
+  const int32_t* depth;
+  float base;
+};
+
+// FRESH: rotary, append and attention in one launch (8 rows of 4 heads over 40 keys: 5.1 us in place of 6.6, 16 rows of 32 heads over 500 keys 11.5 of 13.4, over 4000 27.9 of 30.4; a gap
+// between launches less).  Every workgroup works the rotary factors of the pass out for itself while its first keys are on their way
+// and rotates its own queries: a lane holds both partners of a pair, HD / 2 columns apart.  The pass's own keys are one more
+// chunk behind the cache's, which its wavefront takes from the caller's rows and rotates in registers (values go through
+// LDS, transposed); the last slice of the first query head of a group also appends them.  Chunks of the cache that reach
+// past key n - 1 may see these stores happen: keys from n on are neither loaded (K) nor used (V).
+template <int HD, int QB, bool FRESH = false>
 __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
                                                         const bf16_t* __restrict__ vc, int cap, int n, int M,
                                                         const uint64_t* __restrict__ anc, int Hq, int Hkv,
                                                         bf16_t* __restrict__ out, float* __restrict__ part_o,
                                                         float* __restrict__ part_ml, int nsplit, float scale_log2,
-                                                        const int32_t* __restrict__ n_dev) {
+                                                        const int32_t* __restrict__ n_dev, FreshRows fr) {
   n = cache_len(n, n_dev);
   constexpr int ES = HD / 32;      // contraction steps of the score MFMAs
   constexpr int EB = HD / 16;      // 16-row blocks of O^T
+  static_assert(!FRESH || QB == 1, "one block of rows");
   // LDS merge area: per wave, O accumulators [QB][EB][4][64], running max [QB][64], partial sums [QB][64]
   constexpr int O_FLOATS = QB * EB * 4 * 64;
   __shared__ float lds_o[4 * O_FLOATS];
@@ -64,8 +80,9 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
   // the workgroup's wavefronts share QB row blocks and take every 4th chunk of the key slice
   const int m0 = blockIdx.y * QB * 16;
   const int split = blockIdx.z;
-  const int S = n + M;
-  const int chunks = (S + 31) / 32;
+  const int S = FRESH ? n : n + M;                       // keys in the cache
+  const int own = FRESH ? (n + 31) / 32 : -1;            // chunk of the pass's own keys
+  const int chunks = FRESH ? own + 1 : (S + 31) / 32;
   int cs, ce;
   even_share(chunks, nsplit, split, cs, ce);
 
@@ -103,7 +120,8 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       int key = j0 + (r16 >> 2) * 8 + b * 4 + (r16 & 3);
-      key = key < cap ? key : cap - 1;
+      const int end = FRESH ? n : cap;
+      key = key < end ? key : end - 1;
       const bf16_t* krow = kbase + (size_t)key * Hkv * HD;
 #pragma unroll
       for (int es = 0; es < ES; ++es) kf[b][es].nat = *(const u32x4_t*)(krow + es * 32);
@@ -114,9 +132,55 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
     for (int eb = 0; eb < EB; ++eb) vf[eb].nat = *(const u32x4_t*)(vbase + (size_t)eb * 16 * cap + kv);
   };
 
+  // FRESH: rotary factors [16][HD / 2] (rows padded by 16 bytes) and the pass's values, [HD][16 keys] in rows of 48 bytes
+  constexpr int VROW = 24, FROW = HD / 2 + 2;
+  __shared__ __attribute__((aligned(16))) float2 factors[FRESH ? 16 * FROW : 1];
+  __shared__ __attribute__((aligned(16))) bf16_t own_v[FRESH ? HD * VROW : 1];
+  auto rotate = [&](Frag (&f)[ES], int row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int es = 0; es < ES / 2; ++es) {
+      const float4* cs4 = (const float4*)(factors + row * FROW + es * 32 + g * 8);
+#pragma unroll
+      for (int w2 = 0; w2 < 4; ++w2) {
+        const float4 c2 = cs4[w2];                           // two pairs of (cos, sin)
+        const uint32_t ua = f[es].u[w2], ub = f[es + ES / 2].u[w2];
+        const float a0 = __uint_as_float(ua << 16), a1 = __uint_as_float(ua & 0xffff0000u);
+        const float b0 = __uint_as_float(ub << 16), b1 = __uint_as_float(ub & 0xffff0000u);
+        const uint2 r = pack4_bf16(a0 * c2.x - b0 * c2.y, a1 * c2.z - b1 * c2.w, b0 * c2.x + a0 * c2.y, b1 * c2.z + a1 * c2.w);
+        f[es].u[w2] = r.x;
+        f[es + ES / 2].u[w2] = r.y;
+      }
+    }
+  };
+  const bool appends = FRESH && h % (Hq / Hkv) == 0;
+  // the pass's own keys: key u = (r16 >> 2) * 8 + b * 4 + (r16 & 3) of 32, of which the first M are there
+  auto load_own = [&](Frag (&kf)[2][ES], Frag (&vf)[EB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int u = (r16 >> 2) * 8 + b * 4 + (r16 & 3), uc = u < M ? u : M - 1;
+#pragma unroll
+      for (int es = 0; es < ES; ++es) kf[b][es].nat = *(const u32x4_t*)(fr.k + ((size_t)uc * Hkv + hk) * HD + es * 32 + g * 8);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int u = (r16 >> 2) * 8 + b * 4 + (r16 & 3);
+      rotate(kf[b], u < M ? u : M - 1);
+      if (appends && u < M) {
+#pragma unroll
+        for (int es = 0; es < ES; ++es) *(u32x4_t*)(fr.kc + ((size_t)(n + u) * Hkv + hk) * HD + es * 32 + g * 8) = kf[b][es].nat;
+      }
+    }
+#pragma unroll
+    for (int eb = 0; eb < EB; ++eb) {
+      vf[eb].nat = *(const u32x4_t*)(own_v + (eb * 16 + r16) * VROW + (g & 1) * 8);
+      if (g >= 2) vf[eb].nat = u32x4_t{0, 0, 0, 0};
+    }
+  };
+
   auto process = [&](Frag (&kf)[2][ES], Frag (&vf)[EB], int c) __attribute__((always_inline)) {
     const int j0 = c * 32;
-    if (j0 + 32 > S) {            // keys past the last tree row carry no defined values: zero them
+    const bool fresh = FRESH && c == own;                    // uniform over the wavefront
+    if (!fresh && j0 + 32 > S) {            // keys past the last tree row carry no defined values: zero them
       const int first_bad = S - (j0 + g * 8);       // elements >= first_bad are invalid
 #pragma unroll
       for (int eb = 0; eb < EB; ++eb)
@@ -128,7 +192,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
           vf[eb].u[w2] &= keep;
         }
     }
-    const bool need_mask = j0 + 32 > n;
+    const bool need_mask = fresh || j0 + 32 > n;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       floatx4_t s[2];
@@ -147,8 +211,8 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
         float v = s[t >> 2][t & 3];
         if (need_mask) {
           const int j = j0 + g * 8 + t;
-          bool vis = j < n;
-          if (!vis && j < S) {
+          bool vis = fresh ? (amask[qb][0] >> (g * 8 + t)) & 1ull : j < n;
+          if (!FRESH && !vis && j < S) {
             const int u = j - n;
             vis = (amask[qb][u >> 6] >> (u & 63)) & 1ull;
           }
@@ -194,12 +258,39 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
     constexpr int STEP = 4;
     Frag kf0[2][ES], vf0[EB], kf1[2][ES], vf1[EB];
     int c = cs + wave;
-    if (c < ce) load_kv(kf0, vf0, c);
+    if (c < ce && c != own) load_kv(kf0, vf0, c);
+    if constexpr (FRESH) {
+      constexpr int half = HD / 2;
+      const int j = tid % half;
+      const double inv = rope_inverse(j, half, fr.base);
+      for (int r = tid / half; r < M; r += 256 / half) factors[r * FROW + j] = rope_factor(n + fr.depth[r], inv);
+      if (ce == chunks) {
+        const int key = tid & 15, piece = tid >> 4;
+        if (piece < HD / 8) {
+          Frag v;
+          v.nat = u32x4_t{0, 0, 0, 0};
+          if (key < M) v.nat = *(const u32x4_t*)(fr.v + ((size_t)key * Hkv + hk) * HD + piece * 8);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) own_v[(piece * 8 + i) * VROW + key] = (bf16_t)(v.u[i >> 1] >> (16 * (i & 1)));
+        }
+      }
+      __syncthreads();
+      rotate(qf[0], r16 < M ? r16 : M - 1);
+      if (appends && ce == chunks && (tid & 15) < M) {
+        const int key = tid & 15;
+        for (int e = tid >> 4; e < HD; e += 16) fr.vc[((size_t)hk * HD + e) * cap + n + key] = own_v[e * VROW + key];
+      }
+      if (c == own && c < ce) load_own(kf0, vf0);
+    }
+    auto load = [&](Frag (&kf)[2][ES], Frag (&vf)[EB], int at) __attribute__((always_inline)) {
+      if (FRESH && at == own) load_own(kf, vf);
+      else load_kv(kf, vf, at);
+    };
     for (; c < ce; c += 2 * STEP) {
-      if (c + STEP < ce) load_kv(kf1, vf1, c + STEP);
+      if (c + STEP < ce) load(kf1, vf1, c + STEP);
       process(kf0, vf0, c);
       if (c + STEP < ce) {
-        if (c + 2 * STEP < ce) load_kv(kf0, vf0, c + 2 * STEP);
+        if (c + 2 * STEP < ce) load(kf0, vf0, c + 2 * STEP);
         process(kf1, vf1, c + STEP);
       }
     }
@@ -934,17 +1025,20 @@ hipError_t launch_ring(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int 
 
 template <int HD>
 hipError_t launch_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int n, int M, const uint64_t* anc, int Hq,
-                     int Hkv, bf16_t* out, void* scratch, const AttnPlan& p, hipStream_t s, const int32_t* n_dev) {
+                     int Hkv, bf16_t* out, void* scratch, const AttnPlan& p, hipStream_t s, const int32_t* n_dev,
+                     const FreshRows* fresh = nullptr) {
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (size_t)Hq * kMaxSplits * M * HD;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
   const dim3 grid(Hq, p.groups, p.nsplit);
 #define HT_ATTN_ARGS q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit, scale_log2, n_dev
-  if (p.ring_waves) {
+  if (fresh) {
+    hipLaunchKernelGGL((attn_mfma_kernel<HD, 1, true>), grid, dim3(256), 0, s, HT_ATTN_ARGS, *fresh);
+  } else if (p.ring_waves) {
     const hipError_t e = launch_ring<HD, 4>(q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p, scale_log2, s, n_dev);
     if (e != hipSuccess) return e;
   } else if (!p.tiled) {
-    hipLaunchKernelGGL((attn_mfma_kernel<HD, 1>), grid, dim3(256), 0, s, HT_ATTN_ARGS);
+    hipLaunchKernelGGL((attn_mfma_kernel<HD, 1>), grid, dim3(256), 0, s, HT_ATTN_ARGS, FreshRows{});
   } else {
     hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, HT_ATTN_ARGS, 0);
   }
@@ -1016,6 +1110,23 @@ hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int
     return launch_causal_hd<64>(qp, kp, vp, cap, n, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
                                 (const bf16_t*)self_v, self_cap, scratch, s);
   return hipErrorInvalidValue;
+}
+
+// The rows of a call of up to 16 as the caller has them, where the kernel of that size takes them.
+bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n) {
+  if (M > 16 || !attn_mfma_supported(M, Hq, Hkv, hd)) return false;
+  const AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
+  return !p.tiled && !p.ring_waves;
+}
+hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new, const int32_t* depth, float base, void* kc, void* vc,
+                             int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s) {
+  if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || !attn_fresh_supported(M, Hq, Hkv, hd, n)) return hipErrorInvalidValue;
+  const AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
+  const FreshRows fr{(const bf16_t*)k_new, (const bf16_t*)v_new, (bf16_t*)kc, (bf16_t*)vc, depth, base};
+  const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;
+  const hipError_t e = hd == 128 ? launch_hd<128>(qp, kp, vp, cap, n, M, tree.anc, Hq, Hkv, (bf16_t*)out, scratch, p, s, nullptr, &fr)
+                                 : launch_hd<64>(qp, kp, vp, cap, n, M, tree.anc, Hq, Hkv, (bf16_t*)out, scratch, p, s, nullptr, &fr);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 size_t attn_mfma_scratch_bytes(int M, int Hq, int hd) {

@@ -43,6 +43,16 @@ __device__ inline void even_share(unsigned total, unsigned parts, unsigned i, in
   hi = lo + (int)q + (i < rem ? 1 : 0);
 }
 
+// (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once
+__device__ inline double rope_inverse(int j, int half, float base) {
+  return exp(-(2.0 * (double)j / (double)(2 * half)) * log((double)base));
+}
+__device__ inline float2 rope_factor(int pos, double inv) {
+  double sn, cn;
+  sincos((double)pos * inv, &sn, &cn);
+  return make_float2((float)cn, (float)sn);
+}
+
 template <typename T> struct Conv;
 template <> struct Conv<float> {
   __device__ static inline float load(const float* p) { return *p; }
@@ -249,6 +259,11 @@ size_t attn_mfma_scratch_bytes(int M, int Hq, int hd);
 hipError_t attn_mfma_prepare(int hd);
 hipError_t launch_attn_mfma(const void* q, const void* kc, const void* vc, int cap, int n, int M, TreeDev tree, int Hq,
                             int Hkv, int hd, void* out, void* scratch, hipStream_t s, const int32_t* n_dev = nullptr);
+// up to 16 rows as the caller has them: rotary at positions n + depth[m], append at slots n + m, attention, in one launch (and
+// the merge of key slices)
+bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n);
+hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new, const int32_t* depth, float base, void* kc, void* vc,
+                             int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s);
 hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int cap, int n, int rows, TreeDev tree, int Hq, int Hkv,
                               int hd, void* out, hipStream_t s, const void* self_k = nullptr, const void* self_v = nullptr,
                               int self_cap = 0, void* scratch = nullptr);

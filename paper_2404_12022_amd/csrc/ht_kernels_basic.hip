@@ -263,15 +263,6 @@ hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_
 }
 
 // ------------------------------------------------------------------------------------------------ rotary
-// (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once
-__device__ inline double rope_inverse(int j, int half, float base) {
-  return exp(-(2.0 * (double)j / (double)(2 * half)) * log((double)base));
-}
-__device__ inline float2 rope_factor(int pos, double inv) {
-  double sn, cn;
-  sincos((double)pos * inv, &sn, &cn);
-  return make_float2((float)cn, (float)sn);
-}
 // cs[m][j]: the factors of row m at position n + depth[m]
 __global__ void rope_table_kernel(float2* __restrict__ cs, const int32_t* __restrict__ depth, int n, int half,
                                   float base, const int32_t* __restrict__ n_dev) {

@@ -1,0 +1,119 @@
+"""The attention call on up to 16 rows, which rotates, appends and attends in one launch, against float64 and against the
+general route (taken for rows that do not lie on 16 bytes).  Needs a real MI355X.
+
+Caches bit for bit (both routes round the same float32 products once); outputs within the attention call's tolerance: bf16
+probabilities and values, 2^-9 relative each, and float32 sums: 1e-2 in the 2-norm."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+BASE = 10000.0
+
+
+def _B():
+    import paper_2404_12022_amd.binding as B
+    return B
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+def _parents(T, seed):
+    g = torch.Generator().manual_seed(seed)
+    return [-1] + [int(torch.randint(max(0, v - 3), v, (1,), generator=g)) for v in range(1, T)]
+
+
+def _reference(q, k, v, kc, vc, n, parent, Hq, Hkv, hd):
+    T = len(parent)
+    depth, seen = [0] * T, torch.zeros(T, T, dtype=torch.bool)
+    for r in range(T):
+        if parent[r] >= 0:
+            depth[r] = depth[parent[r]] + 1
+            seen[r] = seen[parent[r]]
+        seen[r, r] = True
+    pos = n + torch.tensor(depth, dtype=torch.float64)
+    freq = BASE ** (-torch.arange(hd // 2, dtype=torch.float64) / (hd // 2))
+    angle = (pos[:, None] * freq)[:, None, :]
+    co, si = torch.cos(angle), torch.sin(angle)
+
+    def rot(x):
+        a, b = x[..., :hd // 2], x[..., hd // 2:]
+        return torch.cat([a * co - b * si, b * co + a * si], dim=-1)
+
+    q, k, v = (t.double().cpu() for t in (q, k, v))
+    keys = torch.cat([kc[:n].double().cpu(), rot(k)])
+    vals = torch.cat([vc[:, :, :n].double().cpu().permute(2, 0, 1), v])
+    mask = torch.cat([torch.ones(T, n, dtype=torch.bool), seen], dim=1)
+    qr, out = rot(q), torch.empty(T, Hq, hd, dtype=torch.float64)
+    for h in range(Hq):
+        s = (qr[:, h] @ keys[:, h // (Hq // Hkv)].T / math.sqrt(hd)).masked_fill(~mask, -math.inf)
+        out[:, h] = torch.softmax(s, dim=1) @ vals[:, h // (Hq // Hkv)]
+    return out.reshape(T, Hq * hd)
+
+
+def _call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd, out=None):
+    out = torch.zeros(T, Hq * hd, dtype=torch.bfloat16, device=DEV) if out is None else out
+    scratch = torch.zeros(B.ht_tree_attention_scratch_bytes(T, Hq, hd), dtype=torch.uint8, device=DEV)
+    kc, vc = kc.clone(), vc.clone()
+    B.ht_tree_attention(q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd, B.HT_BF16, BASE, out, scratch)
+    torch.cuda.synchronize()
+    return out, kc, vc
+
+
+def _off(t):
+    """The same values 8 bytes past a 16-byte boundary: the general route."""
+    raw = torch.zeros(t.numel() + 4, dtype=t.dtype, device=t.device)
+    raw[4:] = t.flatten()
+    return raw[4:].view(t.shape)
+
+
+@pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 15, 16])
+@pytest.mark.parametrize("Hq,Hkv,hd", [(4, 4, 64), (8, 1, 64), (6, 3, 128), (32, 32, 128)])
+def test_one_launch_agrees_with_the_general_route_and_with_float64(T, Hq, Hkv, hd):
+    B = _B()
+    for n in (0, 1, 31, 32, 33, 40, 127, 700, 1300):
+        say(f"attention in one launch T={T} heads={Hq}/{Hkv}x{hd} n={n}")
+        g = torch.Generator(device=DEV).manual_seed(T * 1000 + n)
+        cap = (n + T + 7) // 8 * 8                                # no room behind the last row
+        mk = lambda *s: torch.randn(*s, generator=g, device=DEV).bfloat16()
+        q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+        kc[n:], vc[:, :, n:] = float("nan"), float("nan")         # slots that nobody wrote
+        parent = _parents(T, n)
+        out, k1, v1 = _call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+        ref_out, k2, v2 = _call(B, _off(q), k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+        assert torch.equal(k1[:n + T], k2[:n + T]) and torch.equal(v1[:, :, :n + T], v2[:, :, :n + T])
+        assert torch.isnan(k1[n + T:]).all() and torch.isnan(v1[:, :, n + T:]).all()
+        want = _reference(q, k, v, kc, vc, n, parent, Hq, Hkv, hd)
+        err = float((out.double().cpu() - want).norm() / want.norm())
+        err2 = float((ref_out.double().cpu() - want).norm() / want.norm())
+        say(f"  error {err:.2e}, general route {err2:.2e}")
+        assert err <= 1e-2 and err <= 1.2 * err2 + 1e-4
+
+
+def test_rows_that_are_stored_to_take_the_general_route():
+    """In place: `out` over q, k_new in the very cache slots it is appended to (grouped heads)."""
+    B = _B()
+    T, Hq, Hkv, hd, n, cap = 8, 8, 2, 64, 24, 40
+    g = torch.Generator(device=DEV).manual_seed(5)
+    mk = lambda *s: torch.randn(*s, generator=g, device=DEV).bfloat16()
+    q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+    parent = _parents(T, 1)
+    say("attention call in place")
+    want, k1, v1 = _call(B, _off(q), k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+    direct = _call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)[0]
+    over = q.clone()
+    out, _, _ = _call(B, over, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd, out=over.view(T, Hq * hd))
+    assert torch.equal(out, direct)
+    kc2, vc2 = kc.clone(), vc.clone()
+    kc2[n:n + T] = k
+    out = torch.zeros(T, Hq * hd, dtype=torch.bfloat16, device=DEV)
+    scratch = torch.zeros(B.ht_tree_attention_scratch_bytes(T, Hq, hd), dtype=torch.uint8, device=DEV)
+    B.ht_tree_attention(q, kc2[n:n + T], v, kc2, vc2, cap, n, T, parent, Hq, Hkv, hd, B.HT_BF16, BASE, out, scratch)
+    torch.cuda.synchronize()
+    assert torch.equal(kc2, k1) and torch.equal(vc2, v1)
+    assert torch.equal(out, want)
