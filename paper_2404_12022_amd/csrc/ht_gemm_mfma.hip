@@ -364,12 +364,12 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
 
 // --------------------------------------------------------------------------------------------- product, many rows
 // The same product tiled over the tokens as well, for passes of more rows than the weight stream can hide (prompts, the
-// forward pass of the training stage, passes of more than 128 rows): a workgroup of WF x WT wavefronts owns 64 WF weight
+// forward pass of the training stage, passes of more than 128 rows): a workgroup of WF x WT wavefronts owns 16 R WF weight
 // rows and 16 MT WT token rows and walks its share of K in chunks of 64 columns.
 //
 // Bound: the matrix cores, if the operands reach them.  Both operands go through LDS (a chunk of weights and of tokens is
-// fetched once per workgroup), straight from global memory with 16-byte LDS-direct loads, two stages.  A wavefront
-// multiplies 64 weight rows by 16 MT tokens: at MT = 8 it reads 12 KB from LDS for 32 matrix instructions.  Counted on
+// fetched once per workgroup), straight from global memory with 16-byte LDS-direct loads, ST stages.  A wavefront
+// multiplies 16 R weight rows by 16 MT tokens: at R = 4, MT = 8 it reads 12 KB from LDS for 32 matrix instructions.  Counted on
 // gate/up at 4095 tokens: matrix cores busy 0.70 of the time, LDS 0.26 with these reads (no bank conflicts), wavefronts
 // waiting 0.45 of their cycles; what is lost is lost between a read and the products that need it.  So the
 // order of issue is what matters, and it is written out (sched_barrier fences): operands of the next 32 columns are
@@ -383,10 +383,17 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
 // (1.43).  Tried and slower: weights straight into registers (1.25 - 1.39 PFLOP/s over the same three), four wavefronts of
 // 128 x 128 (0.9 - 1.27), a ring of four or five stages of 32 columns (1.20 - 1.26).
 //
+// Smaller tiles, for launches that would not fill the chip with 256 x 256 ones, are bound by what a compute unit takes in: 50
+// GB/s where the weights come from HBM, whatever is in flight beyond 32 KB, half that if the ring runs dry in between.  With
+// two stages nothing is in flight at the barrier in the middle of a chunk (everything has landed by then), so these tiles
+// have as many stages as LDS holds, and the barrier waits for the next chunk only: 256 rows of 12288 features over 4096
+// columns in 128 x 128 tiles 57 us with two stages, 43 with three; 512 rows in 128 x 256 tiles 70 and 54.  Tried and slower: a
+// tail without the loads past the end (3 % on 24 chunks and more; faster below 12).
+//
 // Workgroups are numbered so that those of one XCD (every eighth) work on blocks of 4 weight tiles x 8 token tiles at a
 // time, and results that no L2 can hold leave it alone (nontemporal stores): 361 -> 312 us at 12288 x 4096.
 //
-// LDS layout of a stage: the weight fragments of the chunk, 1 KB each in operand order (tile, step, row block), then the
+// LDS layout of a stage: the weight fragments of the chunk, 1 KB each in operand order (step, row block), then the
 // token rows of 128 bytes whose 16-byte pieces are XOR-swizzled by row (an LDS-direct load writes 64 consecutive pieces,
 // so every lane picks the global piece that belongs at its place).
 __device__ __forceinline__ void lds_load16(const void* from, void* to) {
@@ -394,45 +401,55 @@ __device__ __forceinline__ void lds_load16(const void* from, void* to) {
                                    0, 0);
 }
 
-// this wavefront's LDS-direct loads have landed and its LDS reads are done; then the others'
-__device__ __forceinline__ void tile_wait_then_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// this wavefront's LDS-direct loads but the last N have landed and its LDS reads are done; then the others'
+template <int N> __device__ __forceinline__ void tile_wait_then_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 
-template <int WF, int WT, int MT> struct TileShape {
-  static constexpr int R = 4, WAVES = WF * WT, FEATURES = WF * R * 16, TOKENS = WT * MT * 16;
-  static constexpr int WBYTES = FEATURES * 128, STAGE = WBYTES + TOKENS * 128, LDS_BYTES = 2 * STAGE;
-  static constexpr int NW = 2 * R / WT, NA = 2 * MT / WF;            // LDS-direct loads per wavefront and chunk: weights, tokens
-  static_assert((WF * R) % kTileBlocks == 0 && 2 * R % WT == 0 && 2 * MT % WF == 0, "whole loads and reads");
+template <int WF, int R_, int WT, int MT, int ST> struct TileShape {
+  static constexpr int R = R_, WAVES = WF * WT, BLOCKS = WF * R, FEATURES = BLOCKS * 16, TOKENS = WT * MT * 16;
+  static constexpr int WBYTES = FEATURES * 128, STAGE = WBYTES + TOKENS * 128, LDS_BYTES = ST * STAGE;
+  static constexpr int NW = 2 * BLOCKS / WAVES, NA = TOKENS / 8 / WAVES;   // LDS-direct loads per wavefront and chunk: weights, tokens
+  static_assert(2 * BLOCKS % WAVES == 0 && TOKENS / 8 % WAVES == 0, "whole loads");
+  static_assert((ST - 1) * (NW + NA) < 64, "the outstanding loads are counted in six bits");
 };
 
-template <int WF, int WT, int MT, int EPI>
+template <int WF, int R, int WT, int MT, int ST, int EPI>
 __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(
     const bf16_t* __restrict__ a, const bf16_t* __restrict__ wp, int M, int N, int K, int KS, void* __restrict__ outp,
     QkvEpilogue qe, RowScale rs, int tile0, int n_tiles, int m_tiles, int nsplit) {
-  using TS = TileShape<WF, WT, MT>;
-  constexpr int R = TS::R, NW = TS::NW, NA = TS::NA, STAGE = TS::STAGE, WBYTES = TS::WBYTES;
+  using TS = TileShape<WF, R, WT, MT, ST>;
+  constexpr int FB = TS::BLOCKS, NW = TS::NW, NA = TS::NA, STAGE = TS::STAGE, WBYTES = TS::WBYTES;
   extern __shared__ __attribute__((aligned(1024))) unsigned char tile_lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int wf = wave % WF, wt = wave / WF;
-  // workgroup id -> (weight tile, token tile): the tiles, four weight tiles wide times eight token tiles after the other,
-  // are dealt to the XCDs in eight runs of equal length.  (Whole weight tiles to an XCD left some with a tile more than
-  // their 32 units take in a round: 1500 rows of 10752 features, 252 tiles, took two rounds.)
-  const int per_xcd = (n_tiles * m_tiles + 7) / 8, at = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (at >= n_tiles * m_tiles) return;                   // uniform over the workgroup
+  // workgroup id -> (K split, weight tile, token tile): the tiles of a split, four weight tiles wide times eight token tiles
+  // after the other, split by split, are dealt to the XCDs in eight runs of equal length.  (Whole weight tiles to an XCD left
+  // some with a tile more than their 32 units take in a round: 1500 rows of 10752 features, 252 tiles, took two rounds.  So
+  // did every split dealt by itself: 384 rows of 5120 features over 13824 columns in 3 x 81 tiles 90 us, 59 now.)
+  const int tiles = n_tiles * m_tiles, per_xcd = (tiles * nsplit + 7) / 8, all = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (all >= tiles * nsplit) return;                     // uniform over the workgroup
+  const int split = all / tiles, at = all - split * tiles;
   const int q = at / (4 * m_tiles), rem = at % (4 * m_tiles), nw = n_tiles - q * 4 < 4 ? n_tiles - q * 4 : 4;
   const int mg = rem / (8 * nw), in = rem % (8 * nw), mw = m_tiles - mg * 8 < 8 ? m_tiles - mg * 8 : 8;
   const int tl = q * 4 + in / mw, ty = mg * 8 + in % mw;
   const int tx = tile0 + tl;                             // the launch covers weight tiles tile0 .. tile0 + n_tiles - 1
   int c0, c1;
-  even_share(KS / 2, nsplit, blockIdx.y, c0, c1);
+  even_share(KS / 2, nsplit, split, c0, c1);
   const int chunks = c1 - c0;
   if (chunks <= 0) return;                               // uniform over the workgroup
   const int row0 = ty * TS::TOKENS, n_rb = N / 16;
 
-  // loads of this wavefront: NW weight fragments, consecutive in the packed tile (past the last row block: the last tile,
-  // results never stored), and NA times eight token rows (past the pass: its last row, results never stored)
-  const int pt_last = (n_rb + kTileBlocks - 1) / kTileBlocks - 1, pt_own = tx * (WF * R / kTileBlocks) + wave * NW / 16;
-  const int pt = pt_own < pt_last ? pt_own : pt_last;
-  const u32x4_t* wsrc = (const u32x4_t*)wp + ((size_t)pt * KS * kTileBlocks + (size_t)c0 * 16 + wave * NW % 16) * 64 + lane;
+  // loads of this wavefront: NW of the chunk's weight fragments, counted row block by row block within a step (past the last
+  // packed row block: that block, results never stored), and NA times eight token rows (past the pass: its last row, results
+  // never stored)
+  const int rb_last = (n_rb + kTileBlocks - 1) / kTileBlocks * kTileBlocks - 1;
+  const u32x4_t* wsrc[NW];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int f = wave * NW + i, own = tx * FB + f % FB, rb = own < rb_last ? own : rb_last;
+    wsrc[i] = (const u32x4_t*)wp + (((size_t)(rb / kTileBlocks) * KS + 2 * c0 + f / FB) * kTileBlocks + rb % kTileBlocks) * 64;
+  }
   const bf16_t* asrc[NA];
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
@@ -443,15 +460,15 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
   auto fetch = [&](int i, int c, int stage) __attribute__((always_inline)) {
     unsigned char* base = tile_lds + stage * STAGE;
     if (i < NW) {
-      lds_load16(wsrc + (size_t)c * 16 * 64 + i * 64, base + (wave * NW + i) * 1024);
+      lds_load16(wsrc[i] + (size_t)c * 16 * 64 + lane, base + (wave * NW + i) * 1024);
     } else {
       const int k = c * 64 + pcol;                         // columns past K meet zero-padded weights: any in-bounds piece
       lds_load16(asrc[i - NW] + (k < K - 8 ? k : K - 8), base + WBYTES + (wave * NA + i - NW) * 1024);
     }
   };
-  const int wfrag = (wf * R / 8 * 16 + wf * R % 8) * 1024 + lane * 16, arow = WBYTES + (wt * MT * 16 + r16) * 128;
+  const int wfrag = wf * R * 1024 + lane * 16, arow = WBYTES + (wt * MT * 16 + r16) * 128;
   auto read_w = [&](Frag& w, int stage, int s, int r) __attribute__((always_inline)) {
-    w.nat = *(const u32x4_t*)(tile_lds + stage * STAGE + wfrag + (s * 8 + r) * 1024);
+    w.nat = *(const u32x4_t*)(tile_lds + stage * STAGE + wfrag + (s * FB + r) * 1024);
   };
   auto read_a = [&](Frag& b, int stage, int s, int t) __attribute__((always_inline)) {
     b.nat = *(const u32x4_t*)(tile_lds + stage * STAGE + arow + t * 2048 + (((s * 4 + g) ^ (r16 & 7)) << 4));
@@ -485,30 +502,34 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // chunk c in stage `st`; chunk c + 2 goes into its stage (past the end: the last chunk again, never used; loops without
+  // chunk c in stage `st`; chunk c + ST goes into its stage (past the end: the last chunk again, never used; loops without
   // it in a tail of their own cost registers that are not there)
   auto body = [&](int c, int st) __attribute__((always_inline)) {
     half(w0, b0, w1, b1, st, 1, std::false_type{}, 0, 0);
-    tile_wait_then_barrier();
+    tile_wait_then_barrier<(ST - 2) * (NW + NA)>();
     __builtin_amdgcn_sched_barrier(0);
-    half(w1, b1, w0, b0, st ^ 1, 0, std::true_type{}, c + 2 < chunks ? c + 2 : chunks - 1, st);
+    half(w1, b1, w0, b0, st + 1 == ST ? 0 : st + 1, 0, std::true_type{}, c + ST < chunks ? c + ST : chunks - 1, st);
   };
 #pragma unroll
-  for (int i = 0; i < NW + NA; ++i) fetch(i, 0, 0);
-  tile_wait_then_barrier();
+  for (int p = 0; p < ST - 1; ++p)
 #pragma unroll
-  for (int i = 0; i < NW + NA; ++i) fetch(i, chunks > 1 ? 1 : 0, 1);
+    for (int i = 0; i < NW + NA; ++i) fetch(i, p < chunks ? p : chunks - 1, p);
+  tile_wait_then_barrier<(ST - 2) * (NW + NA)>();
+#pragma unroll
+  for (int i = 0; i < NW + NA; ++i) fetch(i, ST - 1 < chunks ? ST - 1 : chunks - 1, ST - 1);
 #pragma unroll
   for (int r = 0; r < R; ++r) read_w(w0[r], 0, 0, r);
 #pragma unroll
   for (int t = 0; t < MT; ++t) read_a(b0[t], 0, 0, t);
   int c = 0;
-  for (; c + 2 <= chunks; c += 2) {
-    body(c, 0);
-    body(c + 1, 1);
+  for (; c + ST <= chunks; c += ST) {
+#pragma unroll
+    for (int p = 0; p < ST; ++p) body(c + p, p);
   }
-  if (c < chunks) body(c, 0);
-  tile_wait_then_barrier();                              // nothing may still be writing LDS when the workgroup ends
+#pragma unroll
+  for (int p = 0; p < ST - 1; ++p)
+    if (c + p < chunks) body(c + p, p);
+  tile_wait_then_barrier<0>();                           // nothing may still be writing LDS when the workgroup ends
   const int rb0 = tx * WF * R + wf * R;
   float4 row_ss[MT];
   if (rs.ss) {
@@ -518,7 +539,7 @@ __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2,
       row_ss[mt] = *(const float4*)(rs.ss + (size_t)(m < M ? m : M - 1) * kNormParts);
     }
   }
-  finish_rows<MT, R, EPI, true>(acc, row_ss, rb0, n_rb, M, N, outp, qe, rs, row0 + wt * MT * 16, blockIdx.y);
+  finish_rows<MT, R, EPI, true>(acc, row_ss, rb0, n_rb, M, N, outp, qe, rs, row0 + wt * MT * 16, split);
 }
 
 // Workgroup shape.  R = 2 row blocks per wavefront when that still leaves >= 80 workgroups, else R = 1.
@@ -667,9 +688,9 @@ hipError_t launch_gemm_packed_silu(const void* a, PackedW w, int M, void* act, h
 namespace {
 // Above 64 KB of LDS a kernel has to ask: once per device (gemm_tile_prepare does it when a model is set up, so that no
 // launch inside a stream capture has to).
-template <int WF, int WT, int MT, int EPI>
+template <int WF, int R, int WT, int MT, int ST, int EPI>
 hipError_t allow_tile_lds() {
-  using TS = TileShape<WF, WT, MT>;
+  using TS = TileShape<WF, R, WT, MT, ST>;
   if (TS::LDS_BYTES <= 64 * 1024) return hipSuccess;
   static std::atomic<bool> allowed[64];
   int dev = 0;
@@ -677,7 +698,7 @@ hipError_t allow_tile_lds() {
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!allowed[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute((const void*)gemm_tile_kernel<WF, WT, MT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, TS::LDS_BYTES);
+    e = hipFuncSetAttribute((const void*)gemm_tile_kernel<WF, R, WT, MT, ST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, TS::LDS_BYTES);
     if (e != hipSuccess) return e;
     allowed[dev].store(true, std::memory_order_release);
   }
@@ -685,32 +706,42 @@ hipError_t allow_tile_lds() {
 }
 
 // Features [from, to) of the product, `from` a multiple of the tile.
-template <int WF, int WT, int MT, int EPI>
+template <int WF, int R, int WT, int MT, int ST, int EPI>
 hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
                        int from, int to, hipStream_t s) {
-  using TS = TileShape<WF, WT, MT>;
+  using TS = TileShape<WF, R, WT, MT, ST>;
   const int n_tiles = (to - from + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
-  const hipError_t e = allow_tile_lds<WF, WT, MT, EPI>();
+  const hipError_t e = allow_tile_lds<WF, R, WT, MT, ST, EPI>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_tile_kernel<WF, WT, MT, EPI>), dim3(8 * ((n_tiles * m_tiles + 7) / 8), nsplit), dim3(64 * TS::WAVES),
+  hipLaunchKernelGGL((gemm_tile_kernel<WF, R, WT, MT, ST, EPI>), dim3(8 * ((n_tiles * m_tiles * nsplit + 7) / 8)), dim3(64 * TS::WAVES),
                      TS::LDS_BYTES, s, a, w.p, M, w.N, w.K, w.Kp / 32, out, qe, rs, from / TS::FEATURES, n_tiles, m_tiles, nsplit);
   return hipGetLastError();
 }
 
 // Tile of a product of M rows with a given K split: rounds of workgroups over the 256 compute units, times what a
-// workgroup takes.  Microseconds per chunk of 64 columns (with as many workgroups per unit as fit, and with one) and per
-// round, fitted to launches of 256 - 4096 rows on 4096 - 27648 features over 4096 - 13824 columns, weights not in any
-// cache; a chunk costs much the same on a half-empty chip, so what a launch of few tiles wants is smaller tiles:
-//   256 x 256   12288 x 4096: 4096 rows 356 us (377 and 404 with the other two), 1024 rows 93 (145, 139)
-//   128 x 128   4096 x 4096: 2048 rows 59 us (77, 60), 512 rows in four K splits 22 (29, 23)
-//   128 x 256   12288 x 4096: 512 rows 68 us (97, 78); 22016 x 4096: 256 rows 76 us (98, 81)
-struct TileCost { int features, tokens, per_unit; float chunk, chunk_alone, round; };
-constexpr TileCost kTileCosts[3] = {{256, 256, 1, 1.35f, 1.35f, 12.f}, {128, 128, 2, 1.05f, 0.75f, 2.f}, {128, 256, 1, 1.03f, 1.03f, 2.f}};
+// workgroup takes: `round` once (half of it goes with how full the round is: results written), and per chunk of 64 columns
+// `chunk` plus `rows` for token rows that are there (a tile's rows past the pass fetch its last row over and over), `idle`
+// less of both on an empty chip.  Microseconds, fitted to 560 launches of 129 - 4096 rows on 1024 - 57344 features over 1024 -
+// 28672 columns, weights not in any cache: off by 7 % in the mean, and the tile it picks takes 0.6 % longer in the mean than
+// the fastest of them all.  What it picks, and what the three tiles of two stages took that there were before (us):
+//   64 x 64     1024 x 1024: 384 rows 6.7 (9.9)
+//   64 x 128    4096 x 4096, two splits: 256 rows 14.7 (24)
+//   96 x 128    12288 x 4096: 160 rows 30 (56), 256 rows 38 (57)
+//   128 x 128   4096 x 11008, four splits: 256 rows 34 (43)
+//   192 x 128   22016 x 4096: 256 rows 52 (72)
+//   128 x 256   12288 x 4096: 512 rows 54 (67); 32000 x 4096: 256 rows 67 (88)
+//   192 x 256   22016 x 4096: 512 rows 81 (93); 12288 x 4096: 1024 rows 88 (100)
+//   256 x 256   27648 x 5120: 512 rows 122; everything large
+struct TileCost { int features, tokens; float round, chunk, rows, idle; };
+constexpr TileCost kTileCosts[] = {{256, 256, 14.1f, 1.411f, 0.f, 0.15f},   {128, 256, 9.0f, 0.646f, 0.132f, 0.17f},
+                                   {192, 256, 10.4f, 1.154f, 0.f, 0.12f},   {192, 128, 7.4f, 0.541f, 0.090f, 0.08f},
+                                   {128, 128, 5.1f, 0.437f, 0.070f, 0.07f}, {96, 128, 4.4f, 0.320f, 0.106f, 0.f},
+                                   {64, 128, 3.5f, 0.278f, 0.071f, 0.f},    {64, 64, 1.4f, 0.219f, 0.f, 0.f}};
+constexpr int kTiles = sizeof(kTileCosts) / sizeof(kTileCosts[0]);
 
 // 256 x 256 tiles whose last round would leave half the chip or more without one: the weight tiles of the whole rounds;
-// the other features go in tiles of half the size, twice as many, and a second launch (2048 rows of 12288 features over
-// 4096 columns, 1.5 rounds: 199 us in one launch, 184 in two; 1164 of 15360 over 5120: 235 and 208; 1987 of 27648 over
-// 5120, 3.4 rounds: 517 and 501).  0: one launch.
+// the other features go in 128 x 256 tiles, twice as many, and a second launch (2048 rows of 27648 features over 5120
+// columns, 3.4 rounds: 460 us in one launch, 421 in two; 1024 of 22016 over 4096: 179 and 146).  0: one launch.
 int whole_round_tiles(int M, int N, int nsplit) {
   const int m_tiles = (M + 255) / 256, n_tiles = (N + 255) / 256, whole = (int)((long)n_tiles * m_tiles / 256 * 256 / m_tiles);
   return nsplit == 1 && whole > 0 && whole < n_tiles && 2L * (n_tiles - whole) * m_tiles <= 256 ? whole : 0;
@@ -718,18 +749,21 @@ int whole_round_tiles(int M, int N, int nsplit) {
 
 float tile_us(const TileCost& t, int M, int N, int K, int nsplit) {
   const int m_tiles = (M + t.tokens - 1) / t.tokens;
-  const long groups = (long)((N + t.features - 1) / t.features) * m_tiles * nsplit;
-  const long slots = 256L * t.per_unit, whole = groups / slots, rest = groups % slots;
-  const float chunks = (float)((packed_cols(K) / 64 + nsplit - 1) / nsplit);
-  if (&t == kTileCosts)
-    if (const int w = whole_round_tiles(M, N, nsplit))
-      return (float)((long)(w * m_tiles + 255) / 256) * (t.round + t.chunk * chunks) + kTileCosts[2].round + kTileCosts[2].chunk * chunks;
-  return (float)whole * (t.round + t.chunk * chunks) + (rest ? t.round + (rest <= 256 ? t.chunk_alone : t.chunk) * chunks : 0.f);
+  const long groups = (long)((N + t.features - 1) / t.features) * m_tiles * nsplit, whole = groups / 256;
+  const float chunks = (float)((packed_cols(K) / 64 + nsplit - 1) / nsplit), rest = (float)(groups % 256) / 256.f;
+  const float chunk = t.chunk + t.rows * (float)M / (float)(m_tiles * t.tokens);
+  const float last = rest > 0.f ? t.round * 0.5f * (1.f + rest) + chunk * chunks * (1.f - t.idle * (1.f - rest)) : 0.f;
+  return (float)whole * (t.round + chunk * chunks) + last;
 }
-int best_tile(int M, int N, int K, int nsplit) {
-  int best = 0;
-  for (int i = 1; i < 3; ++i)
-    if (tile_us(kTileCosts[i], M, N, K, nsplit) < tile_us(kTileCosts[best], M, N, K, nsplit)) best = i;
+struct TileChoice { int tile, whole; float us; };            // whole > 0: as whole_round_tiles
+TileChoice best_tile(int M, int N, int K, int nsplit) {
+  TileChoice best{0, 0, tile_us(kTileCosts[0], M, N, K, nsplit)};
+  for (int i = 1; i < kTiles; ++i)
+    if (const float us = tile_us(kTileCosts[i], M, N, K, nsplit); us < best.us) best = TileChoice{i, 0, us};
+  if (const int whole = whole_round_tiles(M, N, nsplit)) {
+    const float us = tile_us(kTileCosts[0], M, whole * 256, K, 1) + tile_us(kTileCosts[1], M, N - whole * 256, K, 1);
+    if (us < best.us) best = TileChoice{0, whole, us};
+  }
   return best;
 }
 
@@ -737,23 +771,35 @@ template <int EPI>
 hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
                        hipStream_t s) {
   const bf16_t* ap = (const bf16_t*)a;
-  switch (best_tile(M, w.N, w.K, nsplit)) {
-    case 0: {
-      if (const int whole = whole_round_tiles(M, w.N, nsplit)) {
-        const hipError_t e = launch_tile<4, 2, 8, EPI>(ap, w, M, out, 1, qe, rs, 0, whole * 256, s);
-        return e != hipSuccess ? e : launch_tile<2, 4, 4, EPI>(ap, w, M, out, 1, qe, rs, whole * 256, w.N, s);
-      }
-      return launch_tile<4, 2, 8, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    }
-    case 1: return launch_tile<2, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    default: return launch_tile<2, 4, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+  const TileChoice c = best_tile(M, w.N, w.K, nsplit);
+  const int from = c.whole * 256;
+  if (from) {
+    const hipError_t e = launch_tile<4, 4, 2, 8, 2, EPI>(ap, w, M, out, 1, qe, rs, 0, from, s);
+    return e != hipSuccess ? e : launch_tile<2, 4, 4, 4, 3, EPI>(ap, w, M, out, 1, qe, rs, from, w.N, s);
+  }
+  switch (c.tile) {
+    case 0: return launch_tile<4, 4, 2, 8, 2, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 1: return launch_tile<2, 4, 4, 4, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 2: return launch_tile<2, 6, 4, 4, 2, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 3: return launch_tile<2, 6, 4, 2, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 4: return launch_tile<2, 4, 2, 4, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 5: return launch_tile<1, 6, 4, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    case 6: return launch_tile<1, 4, 4, 2, 5, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+    default: return launch_tile<1, 4, 4, 1, 5, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
   }
 }
 
 template <int EPI>
 hipError_t allow_tiles() {
-  const hipError_t e = allow_tile_lds<4, 2, 8, EPI>();
-  return e == hipSuccess ? allow_tile_lds<2, 4, 4, EPI>() : e;
+  hipError_t e = allow_tile_lds<4, 4, 2, 8, 2, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<2, 4, 4, 4, 3, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<2, 6, 4, 4, 2, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<2, 6, 4, 2, 3, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<2, 4, 2, 4, 3, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<1, 6, 4, 2, 4, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<1, 4, 4, 2, 5, EPI>();
+  if (e == hipSuccess) e = allow_tile_lds<1, 4, 4, 1, 5, EPI>();
+  return e;
 }
 }  // namespace
 
@@ -765,17 +811,17 @@ hipError_t gemm_tile_prepare() {
   return e;
 }
 
-// A split pays for its partial sums, written in a burst at the end of the kernel and read by the next one: 1.6 us a million
-// while the memory-side cache holds them beside the operands (2048 rows of 4096 features over 11008 columns: 172 us
-// without, 135 in two splits; 512 rows: 128, 71, and 53 in four), and more than any split saves beyond 64 MB of them (1987
+// A split pays for its partial sums where they are read: 0.6 us a million more of them in the kernel that adds them up (512
+// rows of 4096: 7.1, 8.4 and 10.7 us for one, two and four; what writing them takes is in the tile's cost).  512 rows of 4096
+// features over 11008 columns: 69 us without, 56 and 46 in two and four.  Beyond 64 MB of them no split saves anything (1987
 // rows of 5120 features over 13824 columns: 271 us without, 299 and 319 in two and three).
 size_t gemm_wide_part_bytes() { return (size_t)64 << 20; }
 int gemm_wide_splits(int M, int N, int K) {
   int best = 1;
-  float best_us = tile_us(kTileCosts[best_tile(M, N, K, 1)], M, N, K, 1);
+  float best_us = best_tile(M, N, K, 1).us;
   for (int sp = 2; sp <= kMaxSplitK && packed_cols(K) / 64 / sp >= 8; ++sp) {      // at least 512 columns per split
     if ((size_t)sp * M * N * sizeof(float) > gemm_wide_part_bytes()) break;
-    const float us = tile_us(kTileCosts[best_tile(M, N, K, sp)], M, N, K, sp) + (float)sp * (float)M * (float)N * 1.6e-6f;
+    const float us = best_tile(M, N, K, sp).us + (float)(sp - 1) * (float)M * (float)N * 0.6e-6f;
     if (us < best_us) { best = sp; best_us = us; }
   }
   return best;

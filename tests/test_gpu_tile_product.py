@@ -53,6 +53,48 @@ def test_token_tiled_product(M, N, K, splits):
     assert np.all(np.abs(got - O.linear(H.cpu(a), H.cpu(w))) <= bound(a, w, K))
 
 
+# every tile there is, with token rows and features left over, fewer chunks than a tile has stages and more, K splits that do
+# not divide over the eight XCDs: 64 x 64, 64 x 128, 96 x 128, 128 x 128, 192 x 128, 128 x 256, 192 x 256, 256 x 256, whole
+# rounds of 256 x 256 and the rest in 128 x 256
+@pytest.mark.parametrize("M,N,K,splits", [(129, 1040, 136, 1), (200, 1040, 1032, 3), (200, 4112, 264, 1), (129, 3088, 1032, 2),
+                                          (641, 1040, 136, 3), (200, 4112, 136, 2), (200, 5136, 136, 3), (257, 5136, 136, 2),
+                                          (385, 3088, 136, 3), (641, 2064, 136, 3), (700, 6256, 392, 1), (129, 10256, 136, 3),
+                                          (385, 5136, 2056, 3), (255, 32016, 136, 1), (1025, 2064, 136, 3), (511, 22032, 264, 1),
+                                          (257, 10256, 136, 3), (770, 12304, 392, 1), (641, 24592, 1032, 1)])
+def test_every_tile_at_its_edges(M, N, K, splits):
+    import paper_2404_12022_amd.binding as B
+    a, w = inputs(M, N, K, M + N + K)
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_weight_pack(w, N, K, packed)
+    fn = getattr(B.lib, "_ZN2ht16launch_gemm_wideEPKvNS_7PackedWEiPfiP12ihipStream_tNS_8RowScaleE")
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_int, C.c_void_p, RowScale]
+    out = torch.full((splits, M + 1, N), float("nan"), device=H.DEV).view(-1)[:splits * M * N + N]
+    out[splits * M * N:] = 7.0
+    stream = torch.cuda.current_stream().cuda_stream
+    print(f"tiled product {M} x {N} x {K} / {splits}", flush=True)
+    assert fn(a.data_ptr(), Packed(packed.data_ptr(), N, K, (K + 127) // 128 * 128), M, out.data_ptr(), splits, stream,
+              RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    want = a.double() @ w.double().T
+    err = (K / 32 + 16) * 2.0 ** -24 * (a.double().abs() @ w.double().abs().T)
+    assert bool(((out[:splits * M * N].view(splits, M, N).sum(0).double() - want).abs() <= err).all())
+    assert bool((out[splits * M * N:] == 7.0).all())
+    f = N // 2 // 16 * 16
+    gate, up = w[:f].contiguous(), w[f:2 * f].contiguous()
+    gu = torch.empty(B.ht_weight_pack_bytes(2 * f, K), dtype=torch.uint8, device=H.DEV)
+    B.ht_gate_up_pack(gate, up, f, K, gu)
+    silu = getattr(B.lib, "_ZN2ht21launch_gemm_wide_siluEPKvNS_7PackedWEiPvP12ihipStream_tNS_8RowScaleE")
+    silu.restype, silu.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_void_p, RowScale]
+    act = torch.full((M + 1, f), 7.0, dtype=torch.bfloat16, device=H.DEV)
+    assert silu(a.data_ptr(), Packed(gu.data_ptr(), 2 * f, K, (K + 127) // 128 * 128), M, act.data_ptr(), stream,
+                RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    g, u = want[:, :f], want[:, f:2 * f]
+    act_want = g / (1 + torch.exp(-g)) * u
+    assert bool(((act[:M].double() - act_want).abs() <= 2.0 ** -8 * act_want.abs() + 1e-4 * act_want.abs().max()).all())
+    assert bool((act[M] == 7.0).all())
+
+
 @pytest.mark.parametrize("M,N,K", [(33, 4112, 1032), (47, 2064, 4096), (48, 208, 200), (129, 64, 64), (160, 4096, 1024), (193, 528, 2048), (256, 1040, 4104)])
 def test_packed_products_of_between_32_and_48_and_of_more_than_128_rows(M, N, K):
     """The public calls: plain product (with its K splits) and gate/up with SiLU."""
