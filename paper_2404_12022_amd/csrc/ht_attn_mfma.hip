@@ -49,7 +49,7 @@ struct FreshRows {
   const bf16_t *k, *v;
   bf16_t *kc, *vc;                 // the cache they are appended to
   const int32_t* depth;
-  float base;
+  double step;                     // rope_step
 };
 
 // FRESH: rotary, append and attention in one launch (8 rows of 4 heads over 40 keys: 5.1 us in place of 6.6, 16 rows of 32 heads over 500 keys 11.5 of 13.4, over 4000 27.9 of 30.4; a gap
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
     if constexpr (FRESH) {
       constexpr int half = HD / 2;
       const int j = tid % half;
-      const double inv = rope_inverse(j, half, fr.base);
-      for (int r = tid / half; r < M; r += 256 / half) factors[r * FROW + j] = rope_factor(n + fr.depth[r], inv);
+      const double turns = rope_turns(j, fr.step);
+      for (int r = tid / half; r < M; r += 256 / half) factors[r * FROW + j] = rope_factor(n + fr.depth[r], turns);
       if (ce == chunks) {
         const int key = tid & 15, piece = tid >> 4;
         if (piece < HD / 8) {
@@ -1122,7 +1122,7 @@ hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new
                              int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s) {
   if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || !attn_fresh_supported(M, Hq, Hkv, hd, n)) return hipErrorInvalidValue;
   const AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
-  const FreshRows fr{(const bf16_t*)k_new, (const bf16_t*)v_new, (bf16_t*)kc, (bf16_t*)vc, depth, base};
+  const FreshRows fr{(const bf16_t*)k_new, (const bf16_t*)v_new, (bf16_t*)kc, (bf16_t*)vc, depth, rope_step(base, hd / 2)};
   const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;
   const hipError_t e = hd == 128 ? launch_hd<128>(qp, kp, vp, cap, n, M, tree.anc, Hq, Hkv, (bf16_t*)out, scratch, p, s, nullptr, &fr)
                                  : launch_hd<64>(qp, kp, vp, cap, n, M, tree.anc, Hq, Hkv, (bf16_t*)out, scratch, p, s, nullptr, &fr);

@@ -1,6 +1,7 @@
 // Internal declarations shared by the HIP sources of libht (not part of the public ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <stddef.h>
 
@@ -43,14 +44,35 @@ __device__ inline void even_share(unsigned total, unsigned parts, unsigned i, in
   hi = lo + (int)q + (i < rem ? 1 : 0);
 }
 
-// (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once
-__device__ inline double rope_inverse(int j, int half, float base) {
-  return exp(-(2.0 * (double)j / (double)(2 * half)) * log((double)base));
+// (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once.  The general functions of the library (a logarithm, an
+// exponential, a sine and cosine of any argument: some 500 instructions) were most of what a launch of this took; here the
+// angle is counted in turns, which leaves nothing to reduce but the whole turns and the quarters, and the rest are Taylor
+// sums short enough for the remaining |angle| <= pi / 4 (first term left out 8e-12) and |exponent| <= 1/2 (2e-16).
+// rope_step: log2(base) / half, from the host.
+inline double rope_step(float base, int half) { return log2((double)base) / (double)half; }
+__device__ inline double rope_turns(int j, double step) {      // base^(-2j/hd) / (2 pi)
+  const double x = -(double)j * step, k = rint(x), f = (x - k) * 0.69314718055994531;
+  double e = 1.0 / 479001600.0;
+  constexpr double c[12] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
+                            1.0 / 3628800, 1.0 / 39916800};
+#pragma unroll
+  for (int i = 11; i >= 0; --i) e = fma(e, f, c[i]);
+  return ldexp(e, (int)k) * 0.15915494309189535;
 }
-__device__ inline float2 rope_factor(int pos, double inv) {
-  double sn, cn;
-  sincos((double)pos * inv, &sn, &cn);
-  return make_float2((float)cn, (float)sn);
+__device__ inline float2 rope_factor(int pos, double turns) {
+  const double u = (double)pos * turns, part = u - rint(u), quarter = rint(4.0 * part);
+  const double a = fma(quarter, -0.25, part) * 6.2831853071795865, z = a * a;
+  double sn = -1.0 / 39916800.0, cn = 1.0 / 479001600.0;
+  constexpr double cs[5] = {1.0, -1.0 / 6, 1.0 / 120, -1.0 / 5040, 1.0 / 362880};
+  constexpr double cc[6] = {1.0, -1.0 / 2, 1.0 / 24, -1.0 / 720, 1.0 / 40320, -1.0 / 3628800};
+#pragma unroll
+  for (int i = 4; i >= 0; --i) sn = fma(sn, z, cs[i]);
+#pragma unroll
+  for (int i = 5; i >= 0; --i) cn = fma(cn, z, cc[i]);
+  const float s = (float)(sn * a), c = (float)cn;
+  const int k = (int)quarter;                                  // -2 .. 2
+  const float2 odd = make_float2(k > 0 ? -s : s, k > 0 ? c : -c), even = make_float2(k ? -c : c, k ? -s : s);
+  return k & 1 ? odd : even;
 }
 
 template <typename T> struct Conv;

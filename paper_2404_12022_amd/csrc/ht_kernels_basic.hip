@@ -265,16 +265,16 @@ hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_
 // ------------------------------------------------------------------------------------------------ rotary
 // cs[m][j]: the factors of row m at position n + depth[m]
 __global__ void rope_table_kernel(float2* __restrict__ cs, const int32_t* __restrict__ depth, int n, int half,
-                                  float base, const int32_t* __restrict__ n_dev) {
+                                  double step, const int32_t* __restrict__ n_dev) {
   n = cache_len(n, n_dev);
   const int m = blockIdx.x;
   const int j = threadIdx.x;
   if (j >= half) return;
-  cs[(size_t)m * half + j] = rope_factor(n + (depth ? depth[m] : m), rope_inverse(j, half, base));   // no depth table: position n + m
+  cs[(size_t)m * half + j] = rope_factor(n + (depth ? depth[m] : m), rope_turns(j, step));   // no depth table: position n + m
 }
 hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int hd, float base, hipStream_t s,
                              const int32_t* n_dev) {
-  hipLaunchKernelGGL(rope_table_kernel, dim3(M), dim3(hd / 2), 0, s, (float2*)cs, depth, n, hd / 2, base, n_dev);
+  hipLaunchKernelGGL(rope_table_kernel, dim3(M), dim3(hd / 2), 0, s, (float2*)cs, depth, n, hd / 2, rope_step(base, hd / 2), n_dev);
   return hipGetLastError();
 }
 
@@ -286,7 +286,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok,
                                                          const float* __restrict__ rows_in, float* __restrict__ x, int rows,
                                                          int shares, int d, float2* __restrict__ cs, const int32_t* __restrict__ depth,
-                                                         int n, int cs_rows, int half, float base, const int32_t* __restrict__ n_dev) {
+                                                         int n, int cs_rows, int half, double step, const int32_t* __restrict__ n_dev) {
   const int wg = blockIdx.x;
   if (wg < rows * shares) {
     const int m = wg / shares, part = wg % shares;          // part: which share of the row's columns
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ e
   const int i = (wg - rows * shares) * 256 + threadIdx.x;
   if (i >= cs_rows * half) return;
   const int m = i / half, j = i % half;
-  cs[i] = rope_factor(n + (depth ? depth[m] : m), rope_inverse(j, half, base));
+  cs[i] = rope_factor(n + (depth ? depth[m] : m), rope_turns(j, step));
 }
 hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, const float* rows_in, float* x, int rows, int d,
                              float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
@@ -311,7 +311,7 @@ hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, con
   const int groups = rows * shares + (cs_rows * (hd / 2) + 255) / 256;
   if (!groups) return hipSuccess;
   HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(256), 0, s, (const T*)emb, tok, rows_in, x,
-                                              rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, base, n_dev);)
+                                              rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, rope_step(base, hd / 2), n_dev);)
   return hipGetLastError();
 }
 
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
     const TIN* __restrict__ q_in, int q_stride, const TIN* __restrict__ k_in, int k_stride, const TIN* __restrict__ v_in,
     int v_stride, int nsplit, size_t split_stride, const float* __restrict__ cs, T* __restrict__ q, T* __restrict__ kc,
     T* __restrict__ vc, int n, int M, int RB, int Hq, int Hkv, int hd, int cap, int paired,
-    const int32_t* __restrict__ n_dev, const int32_t* __restrict__ depth, float base) {
+    const int32_t* __restrict__ n_dev, const int32_t* __restrict__ depth, double step) {
   extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];
   n = cache_len(n, n_dev);
   const int m0 = blockIdx.x * RB, hh = blockIdx.y, half = hd / 2;
@@ -395,11 +395,11 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
   if (FRESH && hh < Hq + Hkv) {
     if (256 % half == 0) {                                  // a thread keeps its j
       const int j = threadIdx.x % half;
-      const double inv = rope_inverse(j, half, base);
-      for (int r = threadIdx.x / half; r < rows; r += 256 / half) table[r * half + j] = rope_factor(n + depth[m0 + r], inv);
+      const double turns = rope_turns(j, step);
+      for (int r = threadIdx.x / half; r < rows; r += 256 / half) table[r * half + j] = rope_factor(n + depth[m0 + r], turns);
     } else {
       for (int i = threadIdx.x; i < rows * half; i += 256)
-        table[i] = rope_factor(n + depth[m0 + i / half], rope_inverse(i % half, half, base));
+        table[i] = rope_factor(n + depth[m0 + i / half], rope_turns(i % half, step));
     }
     __syncthreads();
   }
@@ -473,7 +473,7 @@ hipError_t launch_rope_append(const float* qkv, int nsplit, const float* cs, voi
     const int RB = kRopeRows;
     hipLaunchKernelGGL((rope_append_rows_kernel<bf16_t, float>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv), dim3(256),
                        (size_t)RB * (hd + 2) * sizeof(bf16_t), s, qkv, stride, k_in, stride, v_in, stride, nsplit,
-                       (size_t)M * stride, cs, qp, kp, vp, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.f);
+                       (size_t)M * stride, cs, qp, kp, vp, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.0);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((rope_append_kernel<bf16_t, float>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0, s, qkv, stride, k_in, stride,
@@ -488,7 +488,7 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
   const dim3 grid(row_blocks, Hq + 2 * Hkv);
 #define HT_ROPE_ARGS                                                                                                        \
   (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, \
-      RB, Hq, Hkv, hd, cap, 0, nullptr, depth, base
+      RB, Hq, Hkv, hd, cap, 0, nullptr, depth, rope_step(base, hd / 2)
   const size_t values = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2), factors = (size_t)RB * (hd / 2) * sizeof(float2);
   // Factors worked out by every workgroup for itself as long as that is no more than two per compute unit (128 rows of 64
   // q and k heads, the most: 5.0 + 3.3 us in two launches, 6.4 in one; 8 rows of 4 heads 2.8 + 2.9 and 3.5).
