@@ -271,7 +271,10 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
   for (int i = 0; i < APASS; ++i) {
     int p = tid + i * THREADS;
     p = p < PIECES ? p : PIECES - 1;
-    arow[i] = a + (size_t)(p / (KC / 8)) * K;
+    // rows past the pass fetch its last row, whose lines are on their way already (9 rows of 11008 gated features over 4096
+    // columns 29.6 -> 28.9 us, 33 of 5120 over 13824 27.9 -> 27.3)
+    const int row = p / (KC / 8);
+    arow[i] = a + (size_t)(row < M ? row : M - 1) * K;
     acol[i] = (p % (KC / 8)) * 8;
     alds[i] = (p / (KC / 8)) * ROWB + (p % (KC / 8)) * 16;
   }
