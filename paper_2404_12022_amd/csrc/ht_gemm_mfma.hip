@@ -86,10 +86,22 @@ __global__ void repack_kernel(WeightSegs w, int K, int KS, int n_rb, int mode, i
 }
 
 // --------------------------------------------------------------------------------------------- epilogues
+// Results of two row blocks, a and b, of the sixteen tokens of a tile, a token to a lane of sixteen: exchanged between the
+// halves of the sixteen lanes so that `first` holds both blocks' results of the first eight tokens (a's in the lower lanes, b's
+// in the upper) and `second` those of the others.  A store then touches half as many lines: what a compute unit needs for
+// its results goes with the lines that each sixteen lanes of a store touch, not with the bytes.
+__device__ __forceinline__ void pair_halves(uint32_t a, uint32_t b, bool lower, uint32_t& first, uint32_t& second) {
+  const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(lower ? b : a), 0x128, 0xf, 0xf, true);   // 8 lanes on
+  first = lower ? a : got;
+  second = lower ? got : b;
+}
+// SiLU(gate) * up: 1 ulp reciprocal, bf16 result
+__device__ __forceinline__ float silu_times(float gate, float up) { return gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate)) * up; }
+
 // What a wavefront does with its finished sums acc[r][mt] (row block rb0 + r, token tile mt): the 1/rms factor of
-// the token rows, then fp32 partial sums, SiLU(gate) * up, or rotary + q store / K,V append.  PAST_L2: fp32 results in
-// amounts that no L2 holds are stored around it.
-template <int MT, int R, int EPI, bool PAST_L2 = false>
+// the token rows, then fp32 partial sums, SiLU(gate) * up, or rotary + q store / K,V append.  TILED (even R, rb0 even): the
+// token-tiled kernel, which stores results of two row blocks together.
+template <int MT, int R, int EPI, bool TILED = false>
 __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float4 (&row_ss)[MT], int rb0, int wg1, int M,
                                             int N, void* __restrict__ outp, const QkvEpilogue& qe, const RowScale& rs,
                                             int row0, int split) {
@@ -104,7 +116,31 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
       for (int r = 0; r < R; ++r) acc[r][mt] *= sc;
     }
   }
-  if (EPI == EPI_F32) {
+  if (EPI == EPI_F32 && TILED) {
+    // (nontemporal: amounts that no L2 holds)
+    float* dst = (float*)outp + (size_t)split * M * N;
+    const bool lower = (lane & 8) == 0;
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+      const int rb = rb0 + r + (lower ? 0 : 1), n0 = rb * 16 + g * 4;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        u32x4_t first, second;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t f, l;
+          pair_halves(__float_as_uint(acc[r][mt][i]), __float_as_uint(acc[r + 1][mt][i]), lower, f, l);
+          first[i] = f;
+          second[i] = l;
+        }
+        const int m = row0 + mt * 16 + (lane & 7);
+        if (rb < wg1) {
+          if (m < M) __builtin_nontemporal_store(first, (u32x4_t*)(dst + (size_t)m * N + n0));
+          if (m + 8 < M) __builtin_nontemporal_store(second, (u32x4_t*)(dst + (size_t)(m + 8) * N + n0));
+        }
+      }
+    }
+  } else if (EPI == EPI_F32) {
     float* dst = (float*)outp + (size_t)split * M * N;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -113,32 +149,48 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int m = mt * 16 + r16;
-        if (m < M) {
-          if (PAST_L2) __builtin_nontemporal_store(acc[r][mt], (floatx4_t*)(dst + (size_t)m * N + n0));
-          else *(floatx4_t*)(dst + (size_t)m * N + n0) = acc[r][mt];
-        }
+        if (m < M) *(floatx4_t*)(dst + (size_t)m * N + n0) = acc[r][mt];
       }
     }
   } else if (EPI == EPI_SILU) {
     // row blocks come in pairs: block rb0 + 2 p holds gate rows, rb0 + 2 p + 1 the matching up rows: act = silu(gate) * up
     bf16_t* dst = (bf16_t*)outp;
     const int f = N / 2;
+    auto act = [&](int pr, int mt) __attribute__((always_inline)) {      // (the launchers give this epilogue an even R)
+      float o[4];
 #pragma unroll
-    for (int pr = 0; pr < R / 2; ++pr) {                  // (the launchers give this epilogue an even R)
-      if (rb0 + 2 * pr + 1 >= wg1) continue;
+      for (int i = 0; i < 4; ++i) o[i] = silu_times(acc[2 * pr][mt][i], acc[2 * pr + 1][mt][i]);
+      return pack4_bf16(o[0], o[1], o[2], o[3]);
+    };
+    auto one_pair = [&](int pr) __attribute__((always_inline)) {
+      if (rb0 + 2 * pr + 1 >= wg1) return;
       const int j0 = ((rb0 + 2 * pr) / 2) * 16 + g * 4;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int m = mt * 16 + r16;
-        if (m < M) {
-          float o[4];
+        if (m < M) *(uint2*)(dst + (size_t)m * f + j0) = act(pr, mt);
+      }
+    };
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float gt = acc[2 * pr][mt][i], up = acc[2 * pr + 1][mt][i];
-            o[i] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;      // 1 ulp reciprocal, bf16 result
-          }
-          *(uint2*)(dst + (size_t)m * f + j0) = pack4_bf16(o[0], o[1], o[2], o[3]);
+    for (int pr = 0; pr < R / 2; pr += TILED ? 2 : 1) {
+      if (!TILED || pr + 1 >= R / 2) {
+        one_pair(pr);
+      } else if (rb0 + 2 * pr + 3 < wg1) {
+        const bool lower = (lane & 8) == 0;
+        const int j = ((rb0 + 2 * pr) / 2 + (lower ? 0 : 1)) * 16 + g * 4;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const uint2 a = act(pr, mt), b = act(pr + 1 < R / 2 ? pr + 1 : pr, mt);
+          uint2 first, second;
+          pair_halves(a.x, b.x, lower, first.x, second.x);
+          pair_halves(a.y, b.y, lower, first.y, second.y);
+          const int m = row0 + mt * 16 + (lane & 7);
+          if (m < M) *(uint2*)(dst + (size_t)m * f + j) = first;
+          if (m + 8 < M) *(uint2*)(dst + (size_t)(m + 8) * f + j) = second;
         }
+      } else {
+        one_pair(pr);
+        one_pair(pr + 1 < R / 2 ? pr + 1 : pr);
       }
     }
   } else {
@@ -148,36 +200,55 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
     // the cache.  v rows are appended to the slot-contiguous value cache.
     const int hd = qe.hd, half = hd / 2, hb = hd / 16, n_now = cache_len(qe.n, qe.n_dev);
     const int q_blocks = qe.Hq * hb, qk_blocks = q_blocks + qe.Hkv * hb;
+    const bool upper = g >= 2;
+    // block r, a q or k block: rotated results of this lane's token
+    auto rotated = [&](int r, int mt) __attribute__((always_inline)) {
+      const int rb = rb0 + r, hrb = rb < q_blocks ? rb : rb - q_blocks, j = (hrb % hb) * 8 + (g & 1) * 4;
+      const int own = mt * 16 + r16, m = own < M ? own : M - 1;
+      const bool tail = EPI == EPI_QKV_TAIL && m >= qe.tail_row;
+      const float* cs = EPI == EPI_QKV_TAIL && tail ? qe.tail_cs + (ptrdiff_t)(m - qe.tail_row) * hd : qe.cs + (size_t)m * hd;
+      float o[4], other[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(acc[r][mt][i], 32, 64);
+      const float4 c01 = *(const float4*)(cs + j * 2), c23 = *(const float4*)(cs + j * 2 + 4);
+      const float cs_[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float x = upper ? other[i] : acc[r][mt][i], y = upper ? acc[r][mt][i] : other[i];
+        const float co = cs_[2 * i], si = cs_[2 * i + 1];
+        o[i] = upper ? y * co + x * si : x * co - y * si;
+      }
+      return pack4_bf16(o[0], o[1], o[2], o[3]);
+    };
+    auto put = [&](int rb, int m, uint2 v) __attribute__((always_inline)) {
+      const bool is_q = rb < q_blocks, tail = EPI == EPI_QKV_TAIL && m >= qe.tail_row;
+      const int hrb = is_q ? rb : rb - q_blocks, h = hrb / hb, j = (hrb % hb) * 8 + (g & 1) * 4 + (upper ? half : 0);
+      bf16_t* dst = is_q   ? qe.q + ((size_t)m * qe.Hq + h) * hd + j
+                    : tail ? qe.tail_kc + ((size_t)(qe.tail_n + m - qe.tail_row) * qe.Hkv + h) * hd + j
+                           : qe.kc + ((size_t)(n_now + m) * qe.Hkv + h) * hd + j;
+      *(uint2*)dst = v;
+    };
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int rb = rb0 + r;
       if (rb >= wg1) continue;                                  // uniform over the wavefront
       if (rb < qk_blocks) {
-        const bool is_q = rb < q_blocks, upper = g >= 2;
-        const int hrb = is_q ? rb : rb - q_blocks;
-        const int h = hrb / hb, j = (hrb % hb) * 8 + (g & 1) * 4;
+        if (TILED && (r & 1)) continue;                         // with the block before it: both of one head, whose blocks are even
+        const bool lower = (lane & 8) == 0;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-          const int m = mt * 16 + r16;
-          const bool tail = EPI == EPI_QKV_TAIL && m >= qe.tail_row;
-          const float* cs = EPI == EPI_QKV_TAIL && tail ? qe.tail_cs + (ptrdiff_t)(m - qe.tail_row) * hd : qe.cs + (size_t)m * hd;
-          float other[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(acc[r][mt][i], 32, 64);
-          if (m < M) {
-            const float4 c01 = *(const float4*)(cs + j * 2), c23 = *(const float4*)(cs + j * 2 + 4);
-            const float cs_[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
-            float o[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float x = upper ? other[i] : acc[r][mt][i], y = upper ? acc[r][mt][i] : other[i];
-              const float co = cs_[2 * i], si = cs_[2 * i + 1];
-              o[i] = upper ? y * co + x * si : x * co - y * si;
-            }
-            bf16_t* dst = is_q   ? qe.q + ((size_t)m * qe.Hq + h) * hd + j
-                          : tail ? qe.tail_kc + ((size_t)(qe.tail_n + m - qe.tail_row) * qe.Hkv + h) * hd + j
-                                 : qe.kc + ((size_t)(n_now + m) * qe.Hkv + h) * hd + j;
-            *(uint2*)(dst + (upper ? half : 0)) = pack4_bf16(o[0], o[1], o[2], o[3]);
+          const uint2 a = rotated(r, mt);
+          if (TILED) {
+            const uint2 b = rotated(r + 1 < R ? r + 1 : r, mt);
+            uint2 first, second;
+            pair_halves(a.x, b.x, lower, first.x, second.x);
+            pair_halves(a.y, b.y, lower, first.y, second.y);
+            const int m = row0 + mt * 16 + (lane & 7);
+            if (m < M) put(rb + (lower ? 0 : 1), m, first);
+            if (m + 8 < M) put(rb + (lower ? 0 : 1), m + 8, second);
+          } else {
+            const int m = mt * 16 + r16;
+            if (m < M) put(rb, m, a);
           }
         }
       } else {
