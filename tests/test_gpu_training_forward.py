@@ -49,6 +49,31 @@ def test_kl_rows_match_the_definition(rows, V):
     assert np.all(np.abs(got - want) <= 2e-5 + 1e-5 * np.abs(want)) and abs(got[0]) <= 1e-6
 
 
+@pytest.mark.parametrize("V", [4, 1023, 8192, 8193, 16384, 16388, 24577, 40000])
+def test_kl_rows_with_maxima_that_move(V):
+    """Lengths about the batches of 8192 entries a workgroup takes at once, even and odd in number; the largest logits first,
+    last and in the middle, a tail of ``-inf`` in the second row of a pair.
+
+    Every partial sum is at most 1 + R where R is the range of both rows together, and passes at most V/1024 + 40 roundings
+    of its thread, its rescalings and the meeting of 1024 threads."""
+    B = _B()
+    gen = torch.Generator().manual_seed(V)
+    ramp = torch.linspace(-9, 9, V)
+    z = torch.randn(6, V, generator=gen) + torch.stack([ramp, -ramp, -ramp, ramp, 9 - ramp.abs(), ramp * 0])
+    kl = torch.full((3,), -1.0, dtype=torch.float32, device=DEV)
+    B.ht_kl_divergence_rows(z.to(DEV), 0, 3, 3, kl)
+    torch.cuda.synchronize()
+    zn, got = z.numpy().astype(np.float64), kl.cpu().numpy().astype(np.float64)
+    for p in range(3):
+        want = O.kl_divergence(zn[p], zn[3 + p])
+        tol = (V / 1024 + 40) * 2.0 ** -23 * (1 + np.ptp(zn[p]) + np.ptp(zn[3 + p]))
+        assert abs(got[p] - want) <= tol, (p, got[p], want, tol)
+    z[3, V // 2:] = -float("inf")                                # a token the second row rules out: infinitely far
+    B.ht_kl_divergence_rows(z.to(DEV), 0, 3, 3, kl)
+    torch.cuda.synchronize()
+    assert kl[0].item() == float("inf") and kl[1].item() == got[1]
+
+
 def _compare(wl, tensors_gpu, tensors_cpu, n, step, max_tree, exact, batched=False):
     B, H = _B(), _H()
     model = oracle_model(wl, tensors_cpu)
