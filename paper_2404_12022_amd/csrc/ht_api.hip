@@ -1291,9 +1291,9 @@ int ht_accept_and_compact(ht_model* m, int32_t* n_accepted, int32_t* accepted_to
   hipStream_t s = (hipStream_t)stream;
   const ht_config& c = m->cfg;
   Buffers& b = m->b;
-  HT_HIP(launch_accept(b.state, b.tree.dev(), b.tok, b.g, m->T, s));
-  HT_HIP(launch_compact(c.dtype, b.state, b.kc_ptrs, b.vc_ptrs, c.n_layers, m->n, c.n_kv_heads, c.head_dim, c.max_cache,
-                        b.saved_h, (size_t)m->Mp * c.d_model, (int)m->slot_layer.size(), b.h_src, c.d_model, s));
+  HT_HIP(launch_accept_compact(c.dtype, b.state, b.tree.dev(), b.tok, b.g, m->T, nullptr, m->n, -1, b.kc_ptrs, b.vc_ptrs, c.n_layers,
+                               c.n_kv_heads, c.head_dim, c.max_cache, b.saved_h, (size_t)m->Mp * c.d_model,
+                               (int)m->slot_layer.size(), b.h_src, c.d_model, s));
   HT_HIP(hipMemcpyAsync(m->h_state, b.state, sizeof(StepState), hipMemcpyDeviceToHost, s));
   HT_HIP(hipStreamSynchronize(s));
   const StepState& st = *m->h_state;
@@ -1331,19 +1331,18 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
   hipStream_t s = (hipStream_t)stream;
   HT_HIP(hipStreamSynchronize(s));                     // the staging buffer below may still be in use
   int32_t* init = m->h_stage;
-  init[0] = n0;                                        // n_old
-  init[1] = n0;                                        // n
+  init[0] = init[1] = n0;                              // n
   init[2] = 0;                                         // log_count
-  HT_HIP(hipMemcpyAsync(&b.state->n_old, init, 3 * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  HT_HIP(hipMemcpyAsync(b.state->n, init, 3 * sizeof(int32_t), hipMemcpyHostToDevice, s));
   struct Guard {
     ht_model* m;
     int n;
     ~Guard() { m->n_dev = nullptr; m->n = n; }
   } guard{m, n0};
-  m->n_dev = &b.state->n;
   const int slots = (int)m->slot_layer.size();
   int rc;
   for (int st = 0; st < steps; ++st) {
+    m->n_dev = &b.state->n[st & 1];
     m->n = n0 + st * (c.k + 1);                        // upper bound of the cache length at this step: sizes grids only
     for (int g = 0; g < slots; ++g)
       HT_HIP(launch_transfer(c.dtype, b.h_src + (size_t)g * c.d_model, nullptr, 1, (const void* const*)b.wt_ptrs,
@@ -1353,9 +1352,9 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
     if ((rc = build_tree(m, s))) return rc;
     if ((rc = run_pass(m, b.tree.dev(), PassStart{b.tok, nullptr}, T, 0, true, b.logits, b.g, s))) return rc;
-    HT_HIP(launch_accept(b.state, b.tree.dev(), b.tok, b.g, T, s, b.log));
-    HT_HIP(launch_compact(c.dtype, b.state, b.kc_ptrs, b.vc_ptrs, c.n_layers, 0, c.n_kv_heads, c.head_dim, c.max_cache,
-                          b.saved_h, (size_t)m->Mp * c.d_model, slots, b.h_src, c.d_model, s, true));
+    HT_HIP(launch_accept_compact(c.dtype, b.state, b.tree.dev(), b.tok, b.g, T, b.log, 0, st & 1, b.kc_ptrs, b.vc_ptrs, c.n_layers,
+                                 c.n_kv_heads, c.head_dim, c.max_cache, b.saved_h, (size_t)m->Mp * c.d_model, slots, b.h_src,
+                                 c.d_model, s));
   }
   StepLog* h_log = (StepLog*)m->h_stage;
   HT_HIP(hipMemcpyAsync(h_log, b.log, sizeof(StepLog) * steps, hipMemcpyDeviceToHost, s));
@@ -1370,8 +1369,8 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
       for (int j = 0; j < cnt; ++j) accepted_tokens[total + j] = h_log[st].emitted[j];
     total += cnt;
   }
-  if (m->h_state->n != n0 + total || m->h_state->log_count != steps)
-    return fail(HT_EHIP, "device cache length %d after the loop, expected %d", m->h_state->n, n0 + total);
+  if (m->h_state->n[steps & 1] != n0 + total || m->h_state->log_count != steps)
+    return fail(HT_EHIP, "device cache length %d after the loop, expected %d", m->h_state->n[steps & 1], n0 + total);
   guard.n = n0 + total;
   m->transfer_ready = m->verify_done = false;
   m->drafts_of = -1;

@@ -108,8 +108,8 @@ struct StepState {
   int32_t next_root;
   int32_t path[kMaxTransfer + 1];
   int32_t emitted[kMaxTransfer + 1];
-  // device-resident loop (ht_decode_steps): cache length before / after the last acceptance, steps logged so far
-  int32_t n_old, n, log_count;
+  // device-resident loop (ht_decode_steps): cache length of step i in n[i & 1], steps logged so far
+  int32_t n[2], log_count;
   int32_t pad[1];
 };
 // what one step of the device-resident loop leaves for the host
@@ -184,12 +184,11 @@ struct TreeOut {
 hipError_t launch_cand_logprob(const float* d, const int32_t* cand, int rows, int b, int V, float* lp, hipStream_t s);
 hipError_t launch_tree_dynamic(const int32_t* root /*device*/, const int32_t* cand, const float* lp, int k, int b, int T,
                                TreeOut tree, int32_t* tok, hipStream_t s);
-// log != NULL (device-resident loop): the step is appended to log[st->log_count++] and st->n_old / st->n advance
-hipError_t launch_accept(StepState* st, TreeDev tree, const int32_t* tok, const int32_t* g, int T, hipStream_t s,
-                         StepLog* log = nullptr);
-hipError_t launch_compact(int dtype, const StepState* st, void* const* kc, void* const* vc, int L, int n, int Hkv,
-                          int hd, int cap, const float* saved_h, size_t slot_stride, int slots, float* h_src, int d,
-                          hipStream_t s, bool n_from_state = false);
+// parity >= 0 (device-resident loop): the cache length is st->n[parity], st->n[parity ^ 1] the one after the acceptance, and
+// the step is appended to log[st->log_count++]; parity < 0: the cache length is n
+hipError_t launch_accept_compact(int dtype, StepState* st, TreeDev tree, const int32_t* tok, const int32_t* g, int T, StepLog* log,
+                                 int n, int parity, void* const* kc, void* const* vc, int L, int Hkv, int hd, int cap,
+                                 const float* saved_h, size_t slot_stride, int slots, float* h_src, int d, hipStream_t s);
 hipError_t launch_prefill_finish(StepState* st, const int32_t* g, const float* saved_h, size_t slot_stride, int slots,
                                  float* h_src, int last, int d, hipStream_t s);
 // measurement aid: one pass over `buf` with the weight stream's access pattern; returns the bytes actually read

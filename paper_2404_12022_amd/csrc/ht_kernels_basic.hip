@@ -1383,77 +1383,107 @@ hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, fl
   return hipGetLastError();
 }
 
-// One wavefront: each round, every lane tests a slice of the nodes for "child of cur carrying the
-// greedy token after cur" and the lowest such node index wins.
-__global__ void accept_kernel(StepState* __restrict__ st, TreeDev tree, const int32_t* __restrict__ tok,
-                              const int32_t* __restrict__ g, int T, StepLog* __restrict__ log) {
-  const int lane = threadIdx.x;
-  int cur = 0, m = 1;
-  if (lane == 0) { st->path[0] = 0; st->emitted[0] = tok[0]; }
-  while (m < kMaxTransfer + 1) {
-    const int want = g[cur];
-    int best = 0x7fffffff;
-    for (int c = cur + 1 + lane; c < T; c += 64)
-      if (tree.parent[c] == cur && tok[c] == want) { best = c; break; }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, 64));
-    if (best == 0x7fffffff) break;
-    if (lane == 0) { st->path[m] = best; st->emitted[m] = tok[best]; }
-    cur = best;
-    ++m;
-  }
-  if (lane == 0) {
-    st->m = m;
-    st->next_root = g[cur];
-    st->root = g[cur];
-    if (log) {                       // device-resident loop: the host reads the steps and the cache length afterwards
-      StepLog* e = log + st->log_count;
-      e->m = m;
-      for (int j = 0; j < m; ++j) e->emitted[j] = st->emitted[j];
-      st->log_count += 1;
-      st->n_old = st->n;
-      st->n += m;
-    }
-  }
-}
-hipError_t launch_accept(StepState* st, TreeDev tree, const int32_t* tok, const int32_t* g, int T, hipStream_t s,
-                         StepLog* log) {
-  hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(64), 0, s, st, tree, tok, g, T, log);
-  return hipGetLastError();
-}
-
-// Moves the accepted rows to slots n..n+m-1 (ascending j; path[j] >= j so in place is safe) and makes
-// the last accepted node's saved residual the next transfer source.  blockIdx.y = layer.
+// Acceptance and compaction in one launch.  From the root on, the lowest child that carries the arg-max token of the node so
+// far is accepted; the accepted rows move to slots n..n+m-1 of every layer's cache and the last accepted node's saved residual
+// becomes the next transfer source.  blockIdx.y = layer.
+// Bound: two memory latencies.  Every wavefront walks the tree for itself, two nodes a lane and a ballot per level, so that the
+// moves need no launch of their own behind a single wavefront's walk, and all of a thread's rows are read before the first is
+// written (path[j] >= j and rising, so none of them has been overwritten).  64 nodes at four layers of 4096: 3.6 and 3.5 us
+// with the gap of a launch between them in two, 4.9 in one; eight nodes at two layers of 256 2.9.
+// parity >= 0 (device-resident loop): the cache length is st->n[parity], the one after the acceptance goes to the other slot,
+// which no block reads here, and the step is logged.
 template <typename T>
-__global__ void compact_kernel(const StepState* __restrict__ st, void* const* __restrict__ kcs,
-                               void* const* __restrict__ vcs, int n, int row_elems, int cap,
-                               const float* __restrict__ saved_h, size_t slot_stride, int slots,
-                               float* __restrict__ h_src, int d, int n_from_state) {
-  const int layer = blockIdx.y;
+__global__ __launch_bounds__(256) void accept_compact_kernel(StepState* __restrict__ st, const int32_t* __restrict__ parent,
+                                                             const int32_t* __restrict__ tok, const int32_t* __restrict__ g, int nodes,
+                                                             StepLog* __restrict__ log, int n, int parity, void* const* __restrict__ kcs,
+                                                             void* const* __restrict__ vcs, int row_elems, int cap,
+                                                             const float* __restrict__ saved_h, size_t slot_stride, int slots,
+                                                             float* __restrict__ h_src, int d) {
+  const int lane = threadIdx.x & 63, layer = blockIdx.y;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int m = st->m;
-  if (n_from_state) n = st->n_old;      // device-resident loop: the cache length before this acceptance
+  constexpr int HALVES = kMaxTree / 64;
+  int up[HALVES], own[HALVES], next[HALVES];
+#pragma unroll
+  for (int h = 0; h < HALVES; ++h) {
+    const int c = lane + 64 * h, at = c < nodes ? c : 0;
+    up[h] = c < nodes ? parent[at] : -2;      // no node's number
+    own[h] = tok[at];
+    next[h] = g[at];
+  }
+  if (parity >= 0) n = st->n[parity];
+  auto of_node = [&](const int (&v)[HALVES], int node) __attribute__((always_inline)) {
+    int r = __builtin_amdgcn_readlane(v[0], node & 63);
+#pragma unroll
+    for (int h = 1; h < HALVES; ++h)
+      if (node >> 6 == h) r = __builtin_amdgcn_readlane(v[h], node & 63);
+    return r;
+  };
+  int path[kMaxTransfer + 1], cur = 0, m = 1;
+  path[0] = 0;
+#pragma unroll
+  for (int j = 1; j <= kMaxTransfer; ++j) {
+    path[j] = 0;
+    if (m < j) continue;                      // the walk has ended
+    const int want = of_node(next, cur);
+    int child = -1;
+#pragma unroll
+    for (int h = HALVES - 1; h >= 0; --h) {
+      const uint64_t match = __ballot(up[h] == cur && own[h] == want && lane + 64 * h > cur);
+      if (match) child = 64 * h + __builtin_ctzll(match);
+    }
+    if (child < 0) continue;
+    path[j] = cur = __builtin_amdgcn_readfirstlane(child);
+    m = j + 1;
+  }
   if (e < row_elems) {
     T* kc = (T*)kcs[layer];
     T* vc = (T*)vcs[layer];
-    for (int j = 0; j < m; ++j) {
-      const int src = st->path[j];
-      if (src == j) continue;
-      kc[(size_t)(n + j) * row_elems + e] = kc[(size_t)(n + src) * row_elems + e];
-      vc[(size_t)e * cap + n + j] = vc[(size_t)e * cap + n + src];
-    }
+    T k[kMaxTransfer + 1], v[kMaxTransfer + 1];
+#pragma unroll
+    for (int j = 1; j <= kMaxTransfer; ++j)
+      if (j < m && path[j] != j) {
+        k[j] = kc[(size_t)(n + path[j]) * row_elems + e];
+        v[j] = vc[(size_t)e * cap + n + path[j]];
+      }
+#pragma unroll
+    for (int j = 1; j <= kMaxTransfer; ++j)
+      if (j < m && path[j] != j) {
+        kc[(size_t)(n + j) * row_elems + e] = k[j];
+        vc[(size_t)e * cap + n + j] = v[j];
+      }
   }
   if (layer < slots && e < d)       // one transfer source per distinct transfer layer (slots <= layers)
-    h_src[(size_t)layer * d + e] = saved_h[layer * slot_stride + (size_t)st->path[m - 1] * d + e];
+    h_src[(size_t)layer * d + e] = saved_h[layer * slot_stride + (size_t)cur * d + e];
+  if (blockIdx.x || blockIdx.y || threadIdx.x >= 64) return;
+  StepLog* entry = parity >= 0 ? log + st->log_count : nullptr;
+  const int root = of_node(next, cur);
+#pragma unroll
+  for (int j = 0; j <= kMaxTransfer; ++j) {
+    const int emitted = of_node(own, path[j]);
+    if (j < m && lane == 0) {
+      st->path[j] = path[j];
+      st->emitted[j] = emitted;
+      if (entry) entry->emitted[j] = emitted;
+    }
+  }
+  if (lane) return;
+  st->m = m;
+  st->next_root = st->root = root;
+  if (entry) {                      // the host reads the steps and the cache length afterwards
+    entry->m = m;
+    st->log_count += 1;
+    st->n[parity ^ 1] = n + m;
+  }
 }
-hipError_t launch_compact(int dtype, const StepState* st, void* const* kc, void* const* vc, int L, int n, int Hkv,
-                          int hd, int cap, const float* saved_h, size_t slot_stride, int slots, float* h_src, int d,
-                          hipStream_t s, bool n_from_state) {
+hipError_t launch_accept_compact(int dtype, StepState* st, TreeDev tree, const int32_t* tok, const int32_t* g, int T, StepLog* log,
+                                 int n, int parity, void* const* kc, void* const* vc, int L, int Hkv, int hd, int cap,
+                                 const float* saved_h, size_t slot_stride, int slots, float* h_src, int d, hipStream_t s) {
   const int row = Hkv * hd;
   const int cols = row > d ? row : d;
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(compact_kernel<T>, dim3((cols + 255) / 256, L), dim3(256), 0, s, st, kc,
-                                              vc, n, row, cap, saved_h, slot_stride, slots, h_src, d,
-                                              n_from_state ? 1 : 0);)
+  const int nodes = T;
+  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(accept_compact_kernel<T>, dim3((cols + 255) / 256, L), dim3(256), 0, s, st, tree.parent,
+                                              tok, g, nodes, log, n, parity, kc, vc, row, cap, saved_h, slot_stride, slots,
+                                              h_src, d);)
   return hipGetLastError();
 }
 

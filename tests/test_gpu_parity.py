@@ -763,6 +763,31 @@ def test_forced_acceptance_every_root_path(name):
             sc.gpu.close()
 
 
+@pytest.mark.parametrize("T,path", [(2, (0, 1)), (64, (0, 62)), (65, (0, 63)), (112, (0, 63, 110))])
+def test_acceptance_over_both_halves_of_a_wavefronts_nodes(T, path):
+    """Two children of the path's last inner node carry the right token, on the same side of node 64 or on either: the lower
+    one is accepted.  The root has up to 64 children, node 63 the others."""
+    H = _H()
+    wl = WORKLOADS["tiny_t123"]
+    say(f"acceptance in a tree of {T}")
+    prompt = prompt_of(wl, 10)
+    truth = oracle_model(wl).ar_greedy(prompt, wl.k + 3)
+    wrong = [t for t in range(wl.vocab) if t not in set(truth)]
+    inner = min(T - 1, 64)
+    parent = [-1] + [0] * inner + [63] * (T - 1 - inner)
+    rank = [0] + list(range(inner)) + list(range(T - 1 - inner))
+    sc = H.StepCompare(wl, tree=(parent, rank), prompt=prompt)
+    tok = [wrong[v % len(wrong)] for v in range(T)]
+    for j, node in enumerate(path):
+        tok[node] = truth[j]
+    if T > 2:
+        tok[path[-1] + 1] = truth[len(path) - 1]
+    r = sc.step(forced=tok)
+    assert r["path"] == list(path) and r["emitted"] == truth[:len(path)] and r["root"] == truth[len(path)]
+    sc.check_cache(f"after the path {path}")
+    sc.gpu.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "tiny_bf16"])
 def test_exactly_tied_logits_resolve_to_lowest_ids(name):
     """LM head with only 64 distinct rows tiled over the vocabulary: every logit value occurs 16 times, so every
