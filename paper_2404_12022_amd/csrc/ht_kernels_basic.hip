@@ -490,9 +490,11 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
   (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, \
       RB, Hq, Hkv, hd, cap, 0, nullptr, depth, rope_step(base, hd / 2)
   const size_t values = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2), factors = (size_t)RB * (hd / 2) * sizeof(float2);
-  // Factors worked out by every workgroup for itself as long as that is no more than two per compute unit (128 rows of 64
-  // q and k heads, the most: 5.0 + 3.3 us in two launches, 6.4 in one; 8 rows of 4 heads 2.8 + 2.9 and 3.5).
-  if (hd % 8 == 0 && row_blocks * (Hq + Hkv) <= 512) {
+  // Factors worked out by every workgroup for itself as long as that is no more than six per compute unit: a call with a
+  // launch of its own for the table, and without (us; heads are q and k heads, 100 cached keys): 24 rows of 8 heads 9.1 and 7.6,
+  // 144 rows of 64 19.8 and 18.7 (576 workgroups), 256 rows of 72 30.3 and 29.5 (1152); 256 rows of 128 heads 31.3 and 31.1
+  // (2048), of 256 28.6 and 29.1 (4096).
+  if (hd % 8 == 0 && row_blocks * (Hq + Hkv) <= 1536) {
     HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, T, true>), grid, dim3(256),
                                                 values > factors ? values : factors, s, HT_ROPE_ARGS);)
     return hipGetLastError();
