@@ -52,12 +52,13 @@ struct FreshRows {
   double step;                     // rope_step
 };
 
-// FRESH: rotary, append and attention in one launch (8 rows of 4 heads over 40 keys: 5.1 us in place of 6.6, 16 rows of 32 heads over 500 keys 11.5 of 13.4, over 4000 27.9 of 30.4; a gap
-// between launches less).  Every workgroup works the rotary factors of the pass out for itself while its first keys are on their way
-// and rotates its own queries: a lane holds both partners of a pair, HD / 2 columns apart.  The pass's own keys are one more
-// chunk behind the cache's, which its wavefront takes from the caller's rows and rotates in registers (values go through
-// LDS, transposed); the last slice of the first query head of a group also appends them.  Chunks of the cache that reach
-// past key n - 1 may see these stores happen: keys from n on are neither loaded (K) nor used (V).
+// FRESH: rotary, append and attention in one launch (8 rows of 4 heads over 40 keys: 4.7 us in place of 6.6, 16 rows of 32
+// heads over 500 keys 11.2 of 13.4, over 4000 27.6 of 30.3; a gap between launches less).  Every workgroup works the rotary
+// factors of the pass out for itself while its first keys are on their way and rotates its own queries: a lane holds both
+// partners of a pair, HD / 2 columns apart.  The pass's own keys are one more chunk behind the cache's, which its wavefront
+// takes from the caller's rows and rotates in registers (values go through LDS, transposed); the last slice of the first
+// query head of a group also appends them.  Chunks of the cache that reach past key n - 1 may see these stores happen: keys
+// from n on are neither loaded (K) nor used (V).
 template <int HD, int QB, bool FRESH = false>
 __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
                                                         const bf16_t* __restrict__ vc, int cap, int n, int M,

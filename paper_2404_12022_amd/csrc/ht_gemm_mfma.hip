@@ -705,8 +705,8 @@ hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int ns
 
 // A workgroup of the streaming kernel holds at most 128 token rows (accumulators and the activation ring are registers):
 // a pass of more rows goes to the token-tiled kernel.  The K split is the caller's.  At 256 rows of 4096 columns, against
-// two launches of 128 rows: 12288 features 72 -> 57 us, 22016 81 -> 76, 4096 24 -> 16, 32000 105 -> 87; 4096 x 11008
-// 51 -> 40.
+// two launches of 128 rows: 12288 features 72 -> 39 us, 22016 81 -> 58, 4096 24 -> 18, 32000 105 -> 67; 4096 x 11008
+// 51 -> 34.
 hipError_t launch_any(const void* a, const PackedW& w, int M, void* out, int nsplit, int epi, const QkvEpilogue& qe,
                       const RowScale& rs, hipStream_t s) {
   if (M <= 128) return launch_rows((const bf16_t*)a, w, M, out, nsplit, epi, qe, rs, s);
@@ -798,14 +798,14 @@ hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int 
 // less of both on an empty chip.  Microseconds, fitted to 560 launches of 129 - 4096 rows on 1024 - 57344 features over 1024 -
 // 28672 columns, weights not in any cache: off by 7 % in the mean, and the tile it picks takes 0.6 % longer in the mean than
 // the fastest of them all.  What it picks, and what the three tiles of two stages took that there were before (us):
-//   64 x 64     1024 x 1024: 384 rows 6.7 (9.9)
-//   64 x 128    4096 x 4096, two splits: 256 rows 14.7 (24)
-//   96 x 128    12288 x 4096: 160 rows 30 (56), 256 rows 38 (57)
+//   64 x 64     1024 x 1024: 384 rows 7.1 (12.8)
+//   64 x 128    4096 x 4096, two splits: 256 rows 18.4 (33)
+//   96 x 128    12288 x 4096: 160 rows 31 (58), 256 rows 39 (59)
 //   128 x 128   4096 x 11008, four splits: 256 rows 34 (43)
-//   192 x 128   22016 x 4096: 256 rows 52 (72)
-//   128 x 256   12288 x 4096: 512 rows 54 (67); 32000 x 4096: 256 rows 67 (88)
-//   192 x 256   22016 x 4096: 512 rows 81 (93); 12288 x 4096: 1024 rows 88 (100)
-//   256 x 256   27648 x 5120: 512 rows 122; everything large
+//   192 x 128   22016 x 4096: 256 rows 58 (76)
+//   128 x 256   12288 x 4096: 512 rows 52 (71); 32000 x 4096: 256 rows 67 (89)
+//   192 x 256   22016 x 4096: 512 rows 88 (104); 12288 x 4096: 1024 rows 88 (101)
+//   256 x 256   27648 x 5120: 512 rows 126 (127); 12288 x 4096: 4096 rows 310 (319); everything large
 struct TileCost { int features, tokens; float round, chunk, rows, idle; };
 constexpr TileCost kTileCosts[] = {{256, 256, 14.1f, 1.411f, 0.f, 0.15f},   {128, 256, 9.0f, 0.646f, 0.132f, 0.17f},
                                    {192, 256, 10.4f, 1.154f, 0.f, 0.12f},   {192, 128, 7.4f, 0.541f, 0.090f, 0.08f},
@@ -815,7 +815,8 @@ constexpr int kTiles = sizeof(kTileCosts) / sizeof(kTileCosts[0]);
 
 // 256 x 256 tiles whose last round would leave half the chip or more without one: the weight tiles of the whole rounds;
 // the other features go in 128 x 256 tiles, twice as many, and a second launch (2048 rows of 27648 features over 5120
-// columns, 3.4 rounds: 460 us in one launch, 421 in two; 1024 of 22016 over 4096: 179 and 146).  0: one launch.
+// columns, 3.4 rounds: 460 us in one launch and 421 in two on one machine, 454 in two on another; 1024 of 22016 over 4096: 179
+// and 146 - 166).  0: one launch.
 int whole_round_tiles(int M, int N, int nsplit) {
   const int m_tiles = (M + 255) / 256, n_tiles = (N + 255) / 256, whole = (int)((long)n_tiles * m_tiles / 256 * 256 / m_tiles);
   return nsplit == 1 && whole > 0 && whole < n_tiles && 2L * (n_tiles - whole) * m_tiles <= 256 ? whole : 0;
@@ -887,7 +888,7 @@ hipError_t gemm_tile_prepare() {
 
 // A split pays for its partial sums where they are read: 0.6 us a million more of them in the kernel that adds them up (512
 // rows of 4096: 7.1, 8.4 and 10.7 us for one, two and four; what writing them takes is in the tile's cost).  512 rows of 4096
-// features over 11008 columns: 69 us without, 56 and 46 in two and four.  Beyond 64 MB of them no split saves anything (1987
+// features over 11008 columns: 70 us without, 55 and 44 in two and four.  Beyond 64 MB of them no split saves anything (1987
 // rows of 5120 features over 13824 columns: 271 us without, 299 and 319 in two and three).
 size_t gemm_wide_part_bytes() { return (size_t)64 << 20; }
 int gemm_wide_splits(int M, int N, int K) {
