@@ -117,3 +117,31 @@ def test_rows_that_are_stored_to_take_the_general_route():
     torch.cuda.synchronize()
     assert torch.equal(kc2, k1) and torch.equal(vc2, v1)
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("T,Hq,Hkv", [(144, 32, 32), (250, 64, 8), (256, 64, 64)])
+def test_rows_of_many_heads_on_either_side_of_the_table_launch(T, Hq, Hkv):
+    """More than 16 rows: 576 and 1152 row blocks times q and k heads work their rotary factors out for themselves, 2048 read
+    them from the table of a launch of its own.  Appended keys are float32 products rounded once: at most half a bf16 unit,
+    2^-8 relative."""
+    B = _B()
+    n, hd, cap = 40, 128, 304
+    g = torch.Generator().manual_seed(T)
+    mk = lambda *s: torch.randn(*s, generator=g).to(DEV).bfloat16()
+    q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+    parent = _parents(T, T)
+    out, kc1, vc1 = _call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+    want = _reference(q, k, v, kc, vc, n, parent, Hq, Hkv, hd)
+    err = (out.double().cpu() - want).norm() / want.norm()
+    say(f"{T} rows of {Hq} + {Hkv} heads: error {err:.2e}")
+    assert err <= 1e-2
+    assert torch.equal(vc1[:, :, n:n + T], v.permute(1, 2, 0)) and torch.equal(kc1[:n], kc[:n])
+    assert torch.equal(kc1[n + T:], kc[n + T:]) and torch.equal(vc1[:, :, n + T:], vc[:, :, n + T:])
+    depth = [0] * T
+    for r in range(1, T):
+        depth[r] = depth[parent[r]] + 1
+    angle = (n + torch.tensor(depth, dtype=torch.float64))[:, None] * BASE ** (-torch.arange(hd // 2, dtype=torch.float64) / (hd // 2))
+    co, si = torch.cos(angle)[:, None], torch.sin(angle)[:, None]
+    a, b = k.double().cpu()[..., :hd // 2], k.double().cpu()[..., hd // 2:]
+    rot = torch.cat([a * co - b * si, b * co + a * si], dim=-1)
+    assert ((kc1[n:n + T].double().cpu() - rot).abs() <= 2.0 ** -8 * rot.abs() + 1e-6).all()
