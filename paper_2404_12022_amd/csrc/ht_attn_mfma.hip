@@ -147,7 +147,8 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
         const uint32_t ua = f[es].u[w2], ub = f[es + ES / 2].u[w2];
         const float a0 = __uint_as_float(ua << 16), a1 = __uint_as_float(ua & 0xffff0000u);
         const float b0 = __uint_as_float(ub << 16), b1 = __uint_as_float(ub & 0xffff0000u);
-        const uint2 r = pack4_bf16(a0 * c2.x - b0 * c2.y, a1 * c2.z - b1 * c2.w, b0 * c2.x + a0 * c2.y, b1 * c2.z + a1 * c2.w);
+        const float2 p0 = make_float2(c2.x, c2.y), p1 = make_float2(c2.z, c2.w);
+        const uint2 r = pack4_bf16(rope_low(a0, b0, p0), rope_low(a1, b1, p1), rope_high(a0, b0, p0), rope_high(a1, b1, p1));
         f[es].u[w2] = r.x;
         f[es + ES / 2].u[w2] = r.y;
       }

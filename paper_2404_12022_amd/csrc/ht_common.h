@@ -75,6 +75,12 @@ __device__ inline float2 rope_factor(int pos, double turns) {
   return k & 1 ? odd : even;
 }
 
+// The rotated pair of (a, b), a of the lower half of a head, b its partner: a cos - b sin, b cos + a sin.  Which of the two
+// products is rounded before the sum is written out: left to the compiler it was one in one kernel and the other in the next
+// (and for some elements of one kernel), and the keys of a prompt then depended on the tile that its rows were multiplied in.
+__device__ inline float rope_low(float a, float b, float2 cs) { return fmaf(a, cs.x, -(b * cs.y)); }
+__device__ inline float rope_high(float a, float b, float2 cs) { return fmaf(b, cs.x, a * cs.y); }
+
 template <typename T> struct Conv;
 template <> struct Conv<float> {
   __device__ static inline float load(const float* p) { return *p; }

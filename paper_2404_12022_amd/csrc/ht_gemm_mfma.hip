@@ -214,9 +214,8 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
       const float cs_[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float x = upper ? other[i] : acc[r][mt][i], y = upper ? acc[r][mt][i] : other[i];
-        const float co = cs_[2 * i], si = cs_[2 * i + 1];
-        o[i] = upper ? y * co + x * si : x * co - y * si;
+        const float2 f = make_float2(cs_[2 * i], cs_[2 * i + 1]);
+        o[i] = upper ? rope_high(other[i], acc[r][mt][i], f) : rope_low(acc[r][mt][i], other[i], f);
       }
       return pack4_bf16(o[0], o[1], o[2], o[3]);
     };

@@ -339,7 +339,7 @@ __global__ void rope_append_kernel(const TIN* __restrict__ q_in, int q_stride, c
       a += Conv<TIN>::load(src + sp * split_stride + ja);
       b += Conv<TIN>::load(src + sp * split_stride + jb);
     }
-    const float ra = a * c.x - b * c.y, rb = b * c.x + a * c.y;
+    const float ra = rope_low(a, b, c), rb = rope_high(a, b, c);
     T* dst = hh < Hq ? q + ((size_t)m * Hq + hh) * hd : kc + ((size_t)(n + m) * Hkv + (hh - Hq)) * hd;
     Conv<T>::store(dst + j, ra);
     Conv<T>::store(dst + j + half, rb);
@@ -424,10 +424,10 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
       }
       const float* cr = FRESH ? (const float*)(table + (m - m0) * half + j) : cs + ((size_t)m * half + j) * 2;
       const float4 c01 = *(const float4*)cr, c23 = *(const float4*)(cr + 4);
-      const float c[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
+      const float2 c[4] = {make_float2(c01.x, c01.y), make_float2(c01.z, c01.w), make_float2(c23.x, c23.y), make_float2(c23.z, c23.w)};
       float ra[4], rb[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { ra[i] = a[i] * c[i] - b[i] * sn[i]; rb[i] = b[i] * c[i] + a[i] * sn[i]; }
+      for (int i = 0; i < 4; ++i) { ra[i] = rope_low(a[i], b[i], c[i]); rb[i] = rope_high(a[i], b[i], c[i]); }
       T* dst = hh < Hq ? q + ((size_t)m * Hq + hh) * hd : kc + ((size_t)(n + m) * Hkv + (hh - Hq)) * hd;
       store4<T>(dst + j, ra);
       store4<T>(dst + j + half, rb);

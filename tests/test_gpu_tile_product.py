@@ -226,6 +226,44 @@ def test_rotary_and_append_across_the_two_launches_of_a_product(Hq, Hkv, tail):
         assert bool((tk[:tail_n] == 7).all()) and bool((tk[t1:] == 7).all()) and bool((tv[:, :, t1:] == 7).all())
 
 
+# 512 rows: 192 x 128 tiles, 300 and 129 rows: smaller ones.  At 512 rows six of 2.6 million keys once came out of the other order.
+@pytest.mark.parametrize("M,Hq,Hkv,hd,K", [(512, 32, 32, 128, 4096), (300, 32, 8, 64, 1024), (129, 8, 8, 96, 512)])
+def test_rotary_products_are_rounded_in_one_order(M, Hq, Hkv, hd, K):
+    """Every rotated value, bit for bit: low half fma(a, cos, -(b sin)), high half fma(b, cos, a sin) of the plain product's
+    sums, whatever tile multiplied the row."""
+    import paper_2404_12022_amd.binding as B
+    n, qd, kvd = 3, Hq * hd, Hkv * hd
+    N, cap = qd + 2 * kvd, (n + M + 7) // 8 * 8
+    a, w = inputs(M, N, K, M + hd)
+    lib, s = B.lib, torch.cuda.current_stream().cuda_stream
+    repack = getattr(lib, "_ZN2ht13launch_repackENS_10WeightSegsEiiiPvP12ihipStream_t")
+    repack.restype, repack.argtypes = C.c_int, [Segs] + [C.c_int] * 3 + [C.c_void_p] * 2
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    parts = [w[:qd], w[qd:qd + kvd], w[qd + kvd:]]
+    assert repack(Segs((C.c_void_p * 3)(*[p.data_ptr() for p in parts]), (C.c_int32 * 3)(qd, kvd, kvd), 3), K, 2, hd, packed.data_ptr(), s) == 0
+    weights = Packed(packed.data_ptr(), N, K, (K + 127) // 128 * 128)
+    bf = dict(dtype=torch.bfloat16, device=H.DEV)
+    q, kc, vc = torch.zeros(M, Hq, hd, **bf), torch.zeros(cap, Hkv, hd, **bf), torch.zeros(Hkv, hd, cap, **bf)
+    cs = factors(M, n, hd)
+    fn = getattr(lib, "_ZN2ht20launch_gemm_wide_qkvEPKvNS_7PackedWEiNS_11QkvEpilogueEP12ihipStream_tNS_8RowScaleE")
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, Qkv, C.c_void_p, RowScale]
+    print(f"order of the rotary products {M} x {N} x {K}", flush=True)
+    qe = Qkv(cs.data_ptr(), q.data_ptr(), kc.data_ptr(), vc.data_ptr(), n, Hq, Hkv, hd, cap, None, 0, 0, 0, None, None, None)
+    assert fn(a.data_ptr(), weights, M, qe, s, RowScale(None, 0.0, 0.0)) == 0
+    plain = getattr(lib, "_ZN2ht16launch_gemm_wideEPKvNS_7PackedWEiPfiP12ihipStream_tNS_8RowScaleE")
+    plain.restype, plain.argtypes = C.c_int, [C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_int, C.c_void_p, RowScale]
+    sums = torch.empty(M, N, device=H.DEV)
+    assert plain(a.data_ptr(), weights, M, sums.data_ptr(), 1, s, RowScale(None, 0.0, 0.0)) == 0
+    torch.cuda.synchronize()
+    # packed order of a head: eight features, then their eight partners
+    x = sums[:, :qd + kvd].view(M, Hq + Hkv, hd // 16, 2, 8)
+    low, high = x[:, :, :, 0].reshape(M, Hq + Hkv, hd // 2), x[:, :, :, 1].reshape(M, Hq + Hkv, hd // 2)
+    co, si = cs[:, None, :, 0], cs[:, None, :, 1]
+    fma = lambda p, f, c: (p.double() * f.double() + c.double()).float()
+    want = torch.cat([fma(low, co, -(high * si)), fma(high, co, low * si)], dim=2).to(torch.bfloat16)
+    assert torch.equal(q, want[:, :Hq]) and torch.equal(kc[n:n + M], want[:, Hq:])
+
+
 def test_gate_up_across_the_two_launches_of_a_product():
     import paper_2404_12022_amd.binding as B
     M, f, K = 1800, 6144, 2048                        # 48 tiles of 256 interleaved features, the seam at 4096 of 6144
