@@ -49,7 +49,7 @@ struct FreshRows {
   const bf16_t *k, *v;
   bf16_t *kc, *vc;                 // the cache they are appended to
   const int32_t* depth;
-  double step;                     // rope_step
+  double2 step;                    // rope_step
 };
 
 // FRESH: rotary, append and attention in one launch (8 rows of 4 heads over 40 keys: 4.7 us in place of 6.6, 16 rows of 32
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
     if constexpr (FRESH) {
       constexpr int half = HD / 2;
       const int j = tid % half;
-      const double turns = rope_turns(j, fr.step);
+      const double2 turns = rope_turns(j, fr.step);
       for (int r = tid / half; r < M; r += 256 / half) factors[r * FROW + j] = rope_factor(n + fr.depth[r], turns);
       if (ce == chunks) {
         const int key = tid & 15, piece = tid >> 4;

@@ -47,28 +47,42 @@ __device__ inline void even_share(unsigned total, unsigned parts, unsigned i, in
 // (cos, sin) of pos * base^(-2j/hd), evaluated in fp64 and rounded once.  The general functions of the library (a logarithm, an
 // exponential, a sine and cosine of any argument: some 500 instructions) were most of what a launch of this took; here the
 // angle is counted in turns, which leaves nothing to reduce but the whole turns and the quarters, and the rest are Taylor
-// sums short enough for the remaining |angle| <= pi / 4 (first term left out 8e-12) and |exponent| <= 1/2 (2e-16).
-// rope_step: log2(base) / half, from the host.
-inline double rope_step(float base, int half) { return log2((double)base) / (double)half; }
-__device__ inline double rope_turns(int j, double step) {      // base^(-2j/hd) / (2 pi)
-  const double x = -(double)j * step, k = rint(x), f = (x - k) * 0.69314718055994531;
-  double e = 1.0 / 479001600.0;
-  constexpr double c[12] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
-                            1.0 / 3628800, 1.0 / 39916800};
-#pragma unroll
-  for (int i = 11; i >= 0; --i) e = fma(e, f, c[i]);
-  return ldexp(e, (int)k) * 0.15915494309189535;
+// sums: the first term left out is 4e-18 of the result for |exponent| <= 1/2 and 5e-17 for |angle| <= pi / 4.  What an angle of
+// thousands of turns multiplies, the frequency, is carried in two doubles.  Floats that are not the rounded exact value (positions
+// below 8192, bases 100 to 10^6, heads of 64 to 128, 4.0 million): 1, with the general functions 16.
+// rope_step: log2(base) / half, from the host, in two doubles of which the first has 24 bits (times j: exact).
+inline double2 rope_step(float base, int half) {
+  const long double step = log2l((long double)base) / half;
+  const double hi = (double)(float)step;
+  return make_double2(hi, (double)(step - (long double)hi));
 }
-__device__ inline float2 rope_factor(int pos, double turns) {
-  const double u = (double)pos * turns, part = u - rint(u), quarter = rint(4.0 * part);
-  const double a = fma(quarter, -0.25, part) * 6.2831853071795865, z = a * a;
-  double sn = -1.0 / 39916800.0, cn = 1.0 / 479001600.0;
-  constexpr double cs[5] = {1.0, -1.0 / 6, 1.0 / 120, -1.0 / 5040, 1.0 / 362880};
-  constexpr double cc[6] = {1.0, -1.0 / 2, 1.0 / 24, -1.0 / 720, 1.0 / 40320, -1.0 / 3628800};
+__device__ inline double2 rope_turns(int j, double2 step) {      // base^(-2j/hd) / (2 pi)
+  constexpr double ln2 = 0.69314718055994531, ln2_rest = 2.3190468138462996e-17;
+  constexpr double per_turn = 0.15915494309189535, per_turn_rest = -9.8393383375912429e-18;
+  const double x = -(double)j * step.x, k = rint(x), f = x - k, y = fma(f, ln2, fma(f, ln2_rest, -(double)j * step.y * ln2));
+  double p = 1.0 / 6227020800.0;
+  constexpr double c[12] = {1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
+                            1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
 #pragma unroll
-  for (int i = 4; i >= 0; --i) sn = fma(sn, z, cs[i]);
+  for (int i = 11; i >= 0; --i) p = fma(p, y, c[i]);
+  p *= y;
+  const double e = 1.0 + p, e_rest = p - (e - 1.0), t = e * per_turn;
+  const double t_rest = fma(e, per_turn, -t) + fma(e, per_turn_rest, e_rest * per_turn);
+  return make_double2(ldexp(t, (int)k), ldexp(t_rest, (int)k));
+}
+__device__ inline float2 rope_factor(int pos, double2 turns) {
+#pragma clang fp contract(off)
+  // (u rounded: its rest is added below, and a product fused into the subtraction would count it twice)
+  const double n = (double)pos, u = n * turns.x, u_rest = fma(n, turns.x, -u) + n * turns.y;
+  const double part = u - rint(u), quarter = rint(4.0 * part);
+  const double a = (fma(quarter, -0.25, part) + u_rest) * 6.2831853071795865, z = a * a;
+  double sn = -1.0 / 1307674368000.0, cn = 1.0 / 20922789888000.0;
+  constexpr double cs[7] = {1.0, -1.0 / 6, 1.0 / 120, -1.0 / 5040, 1.0 / 362880, -1.0 / 39916800, 1.0 / 6227020800.0};
+  constexpr double cc[8] = {1.0, -1.0 / 2, 1.0 / 24, -1.0 / 720, 1.0 / 40320, -1.0 / 3628800, 1.0 / 479001600, -1.0 / 87178291200.0};
 #pragma unroll
-  for (int i = 5; i >= 0; --i) cn = fma(cn, z, cc[i]);
+  for (int i = 6; i >= 0; --i) sn = fma(sn, z, cs[i]);
+#pragma unroll
+  for (int i = 7; i >= 0; --i) cn = fma(cn, z, cc[i]);
   const float s = (float)(sn * a), c = (float)cn;
   const int k = (int)quarter;                                  // -2 .. 2
   const float2 odd = make_float2(k > 0 ? -s : s, k > 0 ? c : -c), even = make_float2(k ? -c : c, k ? -s : s);

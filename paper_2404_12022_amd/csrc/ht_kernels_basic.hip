@@ -265,7 +265,7 @@ hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_
 // ------------------------------------------------------------------------------------------------ rotary
 // cs[m][j]: the factors of row m at position n + depth[m]
 __global__ void rope_table_kernel(float2* __restrict__ cs, const int32_t* __restrict__ depth, int n, int half,
-                                  double step, const int32_t* __restrict__ n_dev) {
+                                  double2 step, const int32_t* __restrict__ n_dev) {
   n = cache_len(n, n_dev);
   const int m = blockIdx.x;
   const int j = threadIdx.x;
@@ -286,7 +286,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok,
                                                          const float* __restrict__ rows_in, float* __restrict__ x, int rows,
                                                          int shares, int d, float2* __restrict__ cs, const int32_t* __restrict__ depth,
-                                                         int n, int cs_rows, int half, double step, const int32_t* __restrict__ n_dev) {
+                                                         int n, int cs_rows, int half, double2 step, const int32_t* __restrict__ n_dev) {
   const int wg = blockIdx.x;
   if (wg < rows * shares) {
     const int m = wg / shares, part = wg % shares;          // part: which share of the row's columns
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
     const TIN* __restrict__ q_in, int q_stride, const TIN* __restrict__ k_in, int k_stride, const TIN* __restrict__ v_in,
     int v_stride, int nsplit, size_t split_stride, const float* __restrict__ cs, T* __restrict__ q, T* __restrict__ kc,
     T* __restrict__ vc, int n, int M, int RB, int Hq, int Hkv, int hd, int cap, int paired,
-    const int32_t* __restrict__ n_dev, const int32_t* __restrict__ depth, double step) {
+    const int32_t* __restrict__ n_dev, const int32_t* __restrict__ depth, double2 step) {
   extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];
   n = cache_len(n, n_dev);
   const int m0 = blockIdx.x * RB, hh = blockIdx.y, half = hd / 2;
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256) void rope_append_rows_kernel(
   if (FRESH && hh < Hq + Hkv) {
     if (256 % half == 0) {                                  // a thread keeps its j
       const int j = threadIdx.x % half;
-      const double turns = rope_turns(j, step);
+      const double2 turns = rope_turns(j, step);
       for (int r = threadIdx.x / half; r < rows; r += 256 / half) table[r * half + j] = rope_factor(n + depth[m0 + r], turns);
     } else {
       for (int i = threadIdx.x; i < rows * half; i += 256)
@@ -473,7 +473,7 @@ hipError_t launch_rope_append(const float* qkv, int nsplit, const float* cs, voi
     const int RB = kRopeRows;
     hipLaunchKernelGGL((rope_append_rows_kernel<bf16_t, float>), dim3((M + RB - 1) / RB, Hq + 2 * Hkv), dim3(256),
                        (size_t)RB * (hd + 2) * sizeof(bf16_t), s, qkv, stride, k_in, stride, v_in, stride, nsplit,
-                       (size_t)M * stride, cs, qp, kp, vp, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, 0.0);
+                       (size_t)M * stride, cs, qp, kp, vp, n, M, RB, Hq, Hkv, hd, cap, paired ? 1 : 0, n_dev, nullptr, double2{});
     return hipGetLastError();
   }
   hipLaunchKernelGGL((rope_append_kernel<bf16_t, float>), dim3(M, Hq + 2 * Hkv), dim3(hd / 2), 0, s, qkv, stride, k_in, stride,
