@@ -74,6 +74,21 @@ def test_kl_rows_with_maxima_that_move(V):
     assert kl[0].item() == float("inf") and kl[1].item() == got[1]
 
 
+@pytest.mark.parametrize("far", [86.0, 90.0, 100.0, 103.0])
+@pytest.mark.parametrize("V,ruled_out,best", [(4, 1, 2), (9000, 8300, 8299), (9000, 107, 8299), (24577, 5, 5 + 16384), (24577, 24576, 3)])
+def test_kl_is_infinite_where_a_small_probability_meets_a_ruled_out_token(V, ruled_out, best, far):
+    """The first row gives a token e^-far of its best one's probability, a denormal float beyond 87, the second row none:
+    infinitely far, whichever of the two a thread sees first, in one batch or in two, or another thread does."""
+    B = _B()
+    z = torch.zeros(2, V)
+    z[0] = -60.0
+    z[0, best], z[0, ruled_out], z[1, ruled_out] = 3.0, 3.0 - far, -float("inf")
+    kl = torch.full((1,), -1.0, dtype=torch.float32, device=DEV)
+    B.ht_kl_divergence_rows(z.to(DEV), 0, 1, 1, kl)
+    torch.cuda.synchronize()
+    assert kl.item() == float("inf"), kl.item()
+
+
 def _compare(wl, tensors_gpu, tensors_cpu, n, step, max_tree, exact, batched=False):
     B, H = _B(), _H()
     model = oracle_model(wl, tensors_cpu)
