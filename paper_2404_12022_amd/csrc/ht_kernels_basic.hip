@@ -1293,6 +1293,10 @@ hipError_t launch_tree_dynamic(const int32_t* root, const int32_t* cand, const f
 // parts meet at the end.  2046 pairs of 32000: 151 us with the maxima in a pass of their own, whose rows the second pass no
 // longer found in an L2, 82 now, 6.4 TB/s; 256 pairs 24.8 and 16.2, one pair 14.1 and 10.3, 500 pairs of 4000 10.4 and 6.9.
 // 256 threads a pair take 22.5 at 256 pairs, 14.4 at one, and as long as these at 2046.
+// Masks of the lowest float are numbers like others here: a difference of 3.4e38 times a weight that is 1 only until a thread
+// meets a larger logit must not overflow, so weighted differences are summed in units of 2^40, and sums are lowered before
+// they are multiplied by the step down.
+constexpr float kKlUnit = 1.0f / 1099511627776.0f;
 template <int VEC>
 __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__ za_all, const float* __restrict__ zb_all, int V,
                                                          float* __restrict__ kl) {
@@ -1328,8 +1332,8 @@ __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__
       }
     const float fa = ha == -INFINITY ? 0.f : ha, fb = hb == -INFINITY ? 0.f : hb;      // (nothing but -inf so far)
     const float da = ma == -INFINITY ? 0.f : ma - fa, db = mb == -INFINITY ? 0.f : mb - fb, down = exp_below(da);
-    cross = (cross + sa * (da - db)) * down;
     sa *= down;
+    cross = cross * down + sa * ((da - db) * kKlUnit);
     sb *= exp_below(db);
     ma = ha;
     mb = hb;
@@ -1341,7 +1345,7 @@ __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__
           const float x = a[buf][i][u], y = b[buf][i][u], e = exp_below(x - fa);
           sa += e;
           sb += exp_below(y - fb);
-          cross += e * ((x - fa) - (y - fb));
+          cross += e * (((x - fa) - (y - fb)) * kKlUnit);
         }
       }
   };
@@ -1356,8 +1360,8 @@ __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__
   // the parts' sums against the maxima of all: first in a wavefront, then over the wavefronts
   auto lower = [&](float ta, float tb) __attribute__((always_inline)) {
     const float da = ma == -INFINITY ? 0.f : ma - ta, db = mb == -INFINITY ? 0.f : mb - tb, down = exp_below(da);
-    cross = (cross + sa * (da - db)) * down;
     sa *= down;
+    cross = cross * down + sa * ((da - db) * kKlUnit);
     sb *= exp_below(db);
   };
   const float wa = wave_max_dpp(ma), wb = wave_max_dpp(mb);
@@ -1379,7 +1383,7 @@ __global__ __launch_bounds__(1024) void kl_rows_kernel(const float* __restrict__
   sa = wave_sum(sa);
   sb = wave_sum(sb);
   cross = wave_sum(cross);
-  if (threadIdx.x == 0) kl[blockIdx.x] = cross / sa - logf(sa) + logf(sb);
+  if (threadIdx.x == 0) kl[blockIdx.x] = cross / sa / kKlUnit - logf(sa) + logf(sb);
 }
 hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, float* kl, hipStream_t s) {
   const int vec = !((uintptr_t)za & 15) && !((uintptr_t)zb & 15) && !(V & 3);

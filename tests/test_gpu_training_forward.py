@@ -89,6 +89,32 @@ def test_kl_is_infinite_where_a_small_probability_meets_a_ruled_out_token(V, rul
     assert kl.item() == float("inf"), kl.item()
 
 
+@pytest.mark.parametrize("V", [64, 8192, 8193, 40000])
+def test_kl_of_rows_masked_with_the_lowest_float(V):
+    """Masked in the first row: nothing, finite and close to the oracle's, also where a thread meets masked tokens only, or
+    meets them first.  Masked in the second row alone: 3.4e38 times the first one's probability, a finite number as long as
+    that is."""
+    B = _B()
+    low = torch.finfo(torch.float32).min
+    z = torch.randn(6, V, generator=torch.Generator().manual_seed(V)) * 2
+    z[0, :V - V // 4] = low                                    # pair 0: most of the first row
+    z[1, :V // 2] = low                                        # pair 1: half of both
+    z[4, :V // 2] = low
+    z[2, 4:8] = -9.0                                           # pair 2: three unlikely tokens, in the second row
+    z[2, V // 2] = 12.0
+    z[5, 4:7] = low
+    kl = torch.full((3,), -1.0, dtype=torch.float32, device=DEV)
+    B.ht_kl_divergence_rows(z.to(DEV), 0, 3, 3, kl)
+    torch.cuda.synchronize()
+    zn, got = z.numpy().astype(np.float64), kl.cpu().numpy().astype(np.float64)
+    want = np.array([O.kl_divergence(zn[p], zn[3 + p]) for p in range(3)])
+    assert np.all(np.isfinite(want)) and want[2] > 1e28
+    tol = (V / 1024 + 40) * 2.0 ** -23                         # as above
+    assert abs(got[0] - want[0]) <= tol * (1 + np.ptp(zn[0, V - V // 4:]) + np.ptp(zn[3])), (got[0], want[0])
+    assert abs(got[1] - want[1]) <= tol * (1 + np.ptp(zn[1, V // 2:]) + np.ptp(zn[4, V // 2:])), (got[1], want[1])
+    assert abs(got[2] / want[2] - 1) <= tol, (got[2], want[2])
+
+
 def _compare(wl, tensors_gpu, tensors_cpu, n, step, max_tree, exact, batched=False):
     B, H = _B(), _H()
     model = oracle_model(wl, tensors_cpu)
