@@ -58,15 +58,12 @@ struct FreshRows {
 // partners of a pair, HD / 2 columns apart.  The pass's own keys are one more chunk behind the cache's, which its wavefront
 // takes from the caller's rows and rotates in registers (values go through LDS, transposed); the last slice of the first
 // query head of a group also appends them.  Chunks of the cache that reach past key n - 1 may see these stores happen: keys
-// from n on are neither loaded (K) nor used (V).
-template <int HD, int QB, bool FRESH = false>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
-                                                        const bf16_t* __restrict__ vc, int cap, int n, int M,
-                                                        const uint64_t* __restrict__ anc, int Hq, int Hkv,
-                                                        bf16_t* __restrict__ out, float* __restrict__ part_o,
-                                                        float* __restrict__ part_ml, int nsplit, float scale_log2,
-                                                        const int32_t* __restrict__ n_dev, FreshRows fr) {
-  n = cache_len(n, n_dev);
+// from n on are neither loaded (K) nor used (V).  So the cache is loaded from and stored to in one launch, and `out` may be q:
+// none of them is __restrict__ in attn_fresh_kernel.
+template <int HD, int QB, bool FRESH>
+__device__ __forceinline__ void attn_rows(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int n, int M,
+                                          const uint64_t* anc, int Hq, int Hkv, bf16_t* out, float* part_o, float* part_ml,
+                                          int nsplit, float scale_log2, const FreshRows& fr) {
   constexpr int ES = HD / 32;      // contraction steps of the score MFMAs
   constexpr int EB = HD / 16;      // 16-row blocks of O^T
   static_assert(!FRESH || QB == 1, "one block of rows");
@@ -355,6 +352,23 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict
       ml[1] = lsum;
     }
   }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256) void attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+                                                        const bf16_t* __restrict__ vc, int cap, int n, int M,
+                                                        const uint64_t* __restrict__ anc, int Hq, int Hkv,
+                                                        bf16_t* __restrict__ out, float* __restrict__ part_o,
+                                                        float* __restrict__ part_ml, int nsplit, float scale_log2,
+                                                        const int32_t* __restrict__ n_dev) {
+  attn_rows<HD, 1, false>(q, kc, vc, cap, cache_len(n, n_dev), M, anc, Hq, Hkv, out, part_o, part_ml, nsplit, scale_log2, FreshRows{});
+}
+
+template <int HD>
+__global__ __launch_bounds__(256) void attn_fresh_kernel(const bf16_t* q, int cap, int n, int M, const uint64_t* __restrict__ anc,
+                                                         int Hq, int Hkv, bf16_t* out, float* __restrict__ part_o,
+                                                         float* __restrict__ part_ml, int nsplit, float scale_log2, FreshRows fr) {
+  attn_rows<HD, 1, true>(q, fr.kc, fr.vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, nsplit, scale_log2, fr);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1035,12 +1049,13 @@ hipError_t launch_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int ca
   const dim3 grid(Hq, p.groups, p.nsplit);
 #define HT_ATTN_ARGS q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit, scale_log2, n_dev
   if (fresh) {
-    hipLaunchKernelGGL((attn_mfma_kernel<HD, 1, true>), grid, dim3(256), 0, s, HT_ATTN_ARGS, *fresh);
+    hipLaunchKernelGGL((attn_fresh_kernel<HD>), grid, dim3(256), 0, s, q, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit,
+                       scale_log2, *fresh);
   } else if (p.ring_waves) {
     const hipError_t e = launch_ring<HD, 4>(q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p, scale_log2, s, n_dev);
     if (e != hipSuccess) return e;
   } else if (!p.tiled) {
-    hipLaunchKernelGGL((attn_mfma_kernel<HD, 1>), grid, dim3(256), 0, s, HT_ATTN_ARGS, FreshRows{});
+    hipLaunchKernelGGL((attn_mfma_kernel<HD>), grid, dim3(256), 0, s, HT_ATTN_ARGS);
   } else {
     hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, HT_ATTN_ARGS, 0);
   }
