@@ -1479,15 +1479,16 @@ int ht_tree_attention(const void* q, const void* k_new, const void* v_new, void*
   const char* env = getenv("HT_FORCE_SIMPLE");
   const bool simple = env && env[0] == '1';
   const void* qq = q;
-  // In one launch, if the rows may be read where they are: on 16 bytes (it loads so much at a time), and nowhere that one of
-  // its workgroups stores to while another still reads (the caches, `out`; `out` = q row for row is the same workgroup's)
+  // In one launch, if the rows may be read and the keys stored where they are: on 16 bytes (it moves so much at a time; the
+  // general append stores 8 and less), and nowhere that one of its workgroups stores to while another still reads (the caches,
+  // `out`; `out` = q row for row is the same workgroup's)
   auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
     return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
   };
   const size_t q_bytes = (size_t)T * Hq * hd * 2, kv_bytes = (size_t)T * Hkv * hd * 2, cache_bytes = (size_t)cap * Hkv * hd * 2;
   if (k_new && dtype == HT_BF16 && !simple && attn_fresh_supported(T, Hq, Hkv, hd, n) &&
-      !(((uintptr_t)q | (uintptr_t)k_new | (uintptr_t)v_new) & 15) && apart(k_new, kv_bytes, k_cache, cache_bytes) &&
-      apart(v_new, kv_bytes, k_cache, cache_bytes) && apart(q, q_bytes, k_cache, cache_bytes) &&
+      !(((uintptr_t)q | (uintptr_t)k_new | (uintptr_t)v_new | (uintptr_t)k_cache | (uintptr_t)v_cache) & 15) &&
+      apart(k_new, kv_bytes, k_cache, cache_bytes) && apart(v_new, kv_bytes, k_cache, cache_bytes) && apart(q, q_bytes, k_cache, cache_bytes) &&
       apart(k_new, kv_bytes, v_cache, cache_bytes) && apart(v_new, kv_bytes, v_cache, cache_bytes) &&
       apart(q, q_bytes, v_cache, cache_bytes) && apart(k_new, kv_bytes, out, q_bytes) && apart(v_new, kv_bytes, out, q_bytes) &&
       (q == out || apart(q, q_bytes, out, q_bytes))) {

@@ -119,6 +119,27 @@ def test_rows_that_are_stored_to_take_the_general_route():
     assert torch.equal(out, want)
 
 
+@pytest.mark.parametrize("which", ["k", "v", "both"])
+def test_caches_off_a_16_byte_address_take_the_general_route(which):
+    """Caches that are views 8 bytes past a 16-byte address: what the general route gives, bit for bit (its sums meet in
+    another order than the one launch's, so some values tell the two apart)."""
+    B = _B()
+    T, Hq, Hkv, hd, n, cap = 9, 8, 4, 128, 77, 88
+    g = torch.Generator(device=DEV).manual_seed(11)
+    mk = lambda *s: torch.randn(*s, generator=g, device=DEV).bfloat16()
+    q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+    parent = _parents(T, 1)
+    say(f"attention call, offset cache: {which}")
+    want, k1, v1 = _call(B, _off(q), k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+    assert not torch.equal(_call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)[0], want)
+    kc2, vc2 = _off(kc) if which != "v" else kc.clone(), _off(vc) if which != "k" else vc.clone()
+    out = torch.zeros(T, Hq * hd, dtype=torch.bfloat16, device=DEV)
+    scratch = torch.zeros(B.ht_tree_attention_scratch_bytes(T, Hq, hd), dtype=torch.uint8, device=DEV)
+    B.ht_tree_attention(q, k, v, kc2, vc2, cap, n, T, parent, Hq, Hkv, hd, B.HT_BF16, BASE, out, scratch)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and torch.equal(kc2, k1) and torch.equal(vc2, v1)
+
+
 @pytest.mark.parametrize("T,Hq,Hkv", [(144, 32, 32), (250, 64, 8), (256, 64, 64)])
 def test_rows_of_many_heads_on_either_side_of_the_table_launch(T, Hq, Hkv):
     """More than 16 rows: 576 and 1152 row blocks times q and k heads work their rotary factors out for themselves, 2048 read
