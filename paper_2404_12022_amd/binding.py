@@ -126,7 +126,10 @@ def _stream_ptr(stream=None) -> int:
     if stream is not None:
         return stream.cuda_stream
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:                      # names of torch's own, not promised to every build
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -67,6 +67,23 @@ def test_binding_constants_match_the_header():
     assert B.lib.ht_padded_rows(129) == 256 and B.lib.ht_padded_rows(256) == 256
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_internals(monkeypatch, missing):
+    """A torch build without the short way to the current stream's handle: the long one."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    import types
+    import torch
+    import paper_2404_12022_amd.binding as B
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 40 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 2, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=7))
+    assert B._stream_ptr() == 42
+    monkeypatch.delattr(torch._C, missing)
+    assert B._stream_ptr() == 7 and B._stream_ptr(types.SimpleNamespace(cuda_stream=9)) == 9
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is the whole target: `bench.py --gpus N` with N > 1 exits with a message and prints no result line."""
     import subprocess
