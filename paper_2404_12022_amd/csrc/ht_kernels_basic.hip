@@ -772,10 +772,11 @@ hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev t
 // ---- tree chosen from the draft distributions
 // lp[i][r] = log-softmax value of candidate r of draft row i:  z - (max + log(sum exp(z - max))) over the whole row.
 // One block of 1024 threads per row, few rows: bound by what one compute unit takes in (50 GB/s) and by the reductions
-// behind it.  A thread brings in 32 floats at a time, all requested before the first is used (16 bytes each where the rows
+// behind it.  A thread brings in up to 32 floats at a time, all requested before the first is used (16 bytes each where the rows
 // lie on 16 bytes), and keeps a sum against its own maximum, so a row is read once and maxima and sums meet once at the
-// end.  Three rows, us, with two walks over the row (or a block-wide maximum in the middle) and now: 1000 3.2 and 2.9, 8000 3.9
-// and 3.5, 32000 6.5 and 5.2, 128000 20.3 and 13.3; of odd length 1003 3.1 and 2.8, 32001 11.1 and 6.5, 127999 35.8 and 19.
+// end.  Three rows, us, with two walks over the row (or a block-wide maximum in the middle) and now: 1000 3.3 and 3.2, 5000 3.6
+// and 3.6, 8000 4.0 and 3.6, 32000 6.8 and 6.1, 128000 20.4 and 16.3; of odd length 1003 3.2 and 3.1, 8193 5.1 and 4.4, 32001
+// 11.2 and 7.5, 127999 36 and 22.
 // e^x for x <= 0 (NaN stays NaN, -inf gives 0): 2^(k + f), k the integer next to x log2 e and f the rest of that product, made
 // in two parts and rounded once.  At most 0.86 units in the last place (0.26 in the mean) over x > -87 and 0.9 of the smallest
 // denormal below, both as expf, whose range checks three rows of 1000 floats notice (3.5 us instead of 3.4), 32000 more so (6.8, 6.2).
@@ -845,14 +846,16 @@ __global__ __launch_bounds__(1024) void cand_logprob_kernel(const float* __restr
   if ((int)threadIdx.x < b) lp[blockIdx.x * kMaxTopK + threadIdx.x] = own - lse;
 }
 hipError_t launch_cand_logprob(const float* d, const int32_t* cand, int rows, int b, int V, float* lp, hipStream_t s) {
-  // (few floats to a thread: the checks of 32 loads that are not there cost a microsecond at 1003 floats)
+  // As many pieces as the row has, up to eight of 16 bytes: loads that are not there are checked for all the same (5000 floats
+  // in eight 3.9 us, in two 3.6; 16384 in eight 4.53, in four 4.48, in two 4.50).  Single floats four at a time up to 24576,
+  // where the rounds cost less than the checks (8193: in 32 5.8, in four 4.35; 20001 6.6 and 5.95; 32001 7.5 and 8.0).
   if (!((uintptr_t)d & 15) && !(V & 3)) {
     if (V <= 4096) hipLaunchKernelGGL((cand_logprob_kernel<4, 1>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+    else if (V <= 8192) hipLaunchKernelGGL((cand_logprob_kernel<4, 2>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
+    else if (V <= 16384) hipLaunchKernelGGL((cand_logprob_kernel<4, 4>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
     else hipLaunchKernelGGL((cand_logprob_kernel<4, 8>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
-  } else if (V <= 4096) {
+  } else if (V <= 24576) {
     hipLaunchKernelGGL((cand_logprob_kernel<1, 4>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
-  } else if (V <= 8192) {
-    hipLaunchKernelGGL((cand_logprob_kernel<1, 8>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
   } else {
     hipLaunchKernelGGL((cand_logprob_kernel<1, 32>), dim3(rows), dim3(1024), 0, s, d, cand, b, V, lp);
   }

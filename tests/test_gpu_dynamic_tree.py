@@ -58,7 +58,7 @@ def test_candidate_logprobs_match_log_softmax(rows, V, b):
     assert np.all(got[:, :b] <= 0)
 
 
-@pytest.mark.parametrize("V", [1, 3, 4096, 4097, 4100, 8192, 8193, 32768, 32769, 65540, 65541])
+@pytest.mark.parametrize("V", [1, 3, 4096, 4097, 4100, 8192, 8193, 8196, 16384, 16388, 24576, 24577, 32768, 32769, 65540, 65541])
 def test_candidate_logprobs_at_the_edges_of_a_batch(V):
     """Lengths around what a thread brings in at a time, 16-byte rows and others, rows whose largest entries sit in one batch,
     impossible entries, a row of nothing else but one entry.  Float32 sums of up to V terms in [0, 1] in any order: 2e-5."""
