@@ -285,6 +285,10 @@ hipError_t gemm_tile_prepare();              // once per device before the first
 hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs = RowScale{});
 hipError_t launch_gemm_wide_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs = RowScale{});
 hipError_t launch_gemm_wide_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s, RowScale rs = RowScale{});
+// for tests: the tile that these take (0 .. 7, the order of their table; 8: whole rounds of the first, the rest in the second),
+// and a launch with a given one, `epi` 0 fp32 sums, 1 SiLU(gate) * up, 2 q | k | v, 3 the same with tail rows
+int gemm_tile_of(int M, int N, int K, int nsplit);
+hipError_t launch_gemm_tile(int tile, int epi, const void* a, PackedW w, int M, void* out, int nsplit, QkvEpilogue qe, hipStream_t s);
 bool qkv_fusable(int head_dim);
 bool qkv_prefer_split(int M, int N);
 hipError_t launch_gemm_packed_qkv(const void* a, PackedW w, int M, QkvEpilogue qe, hipStream_t s,

@@ -841,26 +841,31 @@ TileChoice best_tile(int M, int N, int K, int nsplit) {
   return best;
 }
 
+// `tile`: index into kTileCosts
+template <int EPI>
+hipError_t launch_tile_of(int tile, const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe,
+                          const RowScale& rs, int from, int to, hipStream_t s) {
+  switch (tile) {
+    case 0: return launch_tile<4, 4, 2, 8, 2, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 1: return launch_tile<2, 4, 4, 4, 3, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 2: return launch_tile<2, 6, 4, 4, 2, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 3: return launch_tile<2, 6, 4, 2, 3, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 4: return launch_tile<2, 4, 2, 4, 3, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 5: return launch_tile<1, 6, 4, 2, 4, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 6: return launch_tile<1, 4, 4, 2, 5, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+    case 7: return launch_tile<1, 4, 4, 1, 5, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 template <int EPI>
 hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
                        hipStream_t s) {
   const bf16_t* ap = (const bf16_t*)a;
   const TileChoice c = best_tile(M, w.N, w.K, nsplit);
-  const int from = c.whole * 256;
-  if (from) {
-    const hipError_t e = launch_tile<4, 4, 2, 8, 2, EPI>(ap, w, M, out, 1, qe, rs, 0, from, s);
-    return e != hipSuccess ? e : launch_tile<2, 4, 4, 4, 3, EPI>(ap, w, M, out, 1, qe, rs, from, w.N, s);
-  }
-  switch (c.tile) {
-    case 0: return launch_tile<4, 4, 2, 8, 2, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 1: return launch_tile<2, 4, 4, 4, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 2: return launch_tile<2, 6, 4, 4, 2, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 3: return launch_tile<2, 6, 4, 2, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 4: return launch_tile<2, 4, 2, 4, 3, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 5: return launch_tile<1, 6, 4, 2, 4, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    case 6: return launch_tile<1, 4, 4, 2, 5, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-    default: return launch_tile<1, 4, 4, 1, 5, EPI>(ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
-  }
+  if (!c.whole) return launch_tile_of<EPI>(c.tile, ap, w, M, out, nsplit, qe, rs, 0, w.N, s);
+  const hipError_t e = launch_tile_of<EPI>(0, ap, w, M, out, 1, qe, rs, 0, c.whole * 256, s);
+  return e != hipSuccess ? e : launch_tile_of<EPI>(1, ap, w, M, out, 1, qe, rs, c.whole * 256, w.N, s);
 }
 
 template <int EPI>
@@ -899,6 +904,22 @@ int gemm_wide_splits(int M, int N, int K) {
     if (us < best_us) { best = sp; best_us = us; }
   }
   return best;
+}
+
+int gemm_tile_of(int M, int N, int K, int nsplit) {
+  const TileChoice c = best_tile(M, N, K, nsplit);
+  return c.whole ? kTiles : c.tile;
+}
+hipError_t launch_gemm_tile(int tile, int epi, const void* a, PackedW w, int M, void* out, int nsplit, QkvEpilogue qe, hipStream_t s) {
+  const bf16_t* ap = (const bf16_t*)a;
+  if (tile < 0 || tile >= kTiles || (epi != EPI_F32 && nsplit != 1)) return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_F32: return launch_tile_of<EPI_F32>(tile, ap, w, M, out, nsplit, qe, RowScale{}, 0, w.N, s);
+    case EPI_SILU: return launch_tile_of<EPI_SILU>(tile, ap, w, M, out, 1, qe, RowScale{}, 0, w.N, s);
+    case EPI_QKV: return launch_tile_of<EPI_QKV>(tile, ap, w, M, out, 1, qe, RowScale{}, 0, w.N, s);
+    case EPI_QKV_TAIL: return launch_tile_of<EPI_QKV_TAIL>(tile, ap, w, M, out, 1, qe, RowScale{}, 0, w.N, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_wide(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs) {

@@ -84,6 +84,22 @@ def test_current_stream_without_torch_internals(monkeypatch, missing):
     assert B._stream_ptr() == 7 and B._stream_ptr(types.SimpleNamespace(cuda_stream=9)) == 9
 
 
+def test_the_tile_that_a_product_takes():
+    """The rule that picks the tile of a product of more than 128 rows, at the shapes its comment names (M, N, K, splits): 0 to 7
+    256 x 256, 128 x 256, 192 x 256, 192 x 128, 128 x 128, 96 x 128, 64 x 128, 64 x 64; 8 whole rounds and the rest."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    import ctypes as C
+    import paper_2404_12022_amd.binding as B
+    tile = getattr(B.lib, "_ZN2ht12gemm_tile_ofEiiii")
+    tile.restype, tile.argtypes = C.c_int, [C.c_int] * 4
+    for shape, want in {(384, 1024, 1024, 1): 7, (256, 4096, 4096, 2): 6, (160, 12288, 4096, 1): 5, (256, 12288, 4096, 1): 5,
+                        (256, 4096, 11008, 4): 4, (256, 22016, 4096, 1): 3, (512, 12288, 4096, 1): 3, (256, 32000, 4096, 1): 1,
+                        (512, 22016, 4096, 1): 2, (1024, 12288, 4096, 1): 2, (512, 27648, 5120, 1): 0, (4096, 12288, 4096, 1): 0,
+                        (2048, 27648, 5120, 1): 8, (1024, 22016, 4096, 1): 8, (1025, 14864, 2048, 1): 3, (1800, 12288, 2048, 1): 8}.items():
+        assert tile(*shape) == want, (shape, tile(*shape))
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is the whole target: `bench.py --gpus N` with N > 1 exits with a message and prints no result line."""
     import subprocess

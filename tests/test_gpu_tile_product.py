@@ -32,8 +32,8 @@ def bound(a, w, K):
     return (K / 32 + 16) * 2.0 ** -24 * np.abs(H.cpu(a)) @ np.abs(H.cpu(w)).T
 
 
-# rows, features and columns one below, at and one above the tiles of 64, 128 and 256, odd chunk counts, one chunk; the last:
-# 295 tiles of 256, dealt unevenly, the last 40 of them as tiles of half the size with 16 features in the last
+# rows, features and columns one below, at and one above 64, 128 and 256, odd chunk counts, one chunk, whatever tile the rule
+# takes (mostly 64 x 64; the tiles one by one are below); the last: 78 tiles of 192 features in nine of 128 rows, 80 in the last
 @pytest.mark.parametrize("M,N,K,splits", [(129, 16, 8, 1), (255, 240, 200, 1), (256, 256, 128, 1), (257, 272, 136, 1), (130, 144, 1032, 2),
                                           (300, 4112, 328, 1), (513, 128, 2056, 4), (1025, 528, 640, 1), (129, 2064, 4096, 8),
                                           (2047, 1040, 192, 1), (1025, 14864, 2048, 1)])
@@ -281,3 +281,98 @@ def test_gate_up_across_the_two_launches_of_a_product():
     want = gate / (1 + torch.exp(-gate)) * up
     assert bool(((act[:M].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4 * want.abs().max()).all())
     assert bool((act[M] == 7).all())
+
+
+# ---- each tile by its index: features and tokens
+TILES = [(256, 256), (128, 256), (192, 256), (192, 128), (128, 128), (96, 128), (64, 128), (64, 64)]
+
+
+def tile_launch(B):
+    fn = getattr(B.lib, "_ZN2ht16launch_gemm_tileEiiPKvNS_7PackedWEiPviNS_11QkvEpilogueEP12ihipStream_t")
+    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_void_p, Packed, C.c_int, C.c_void_p, C.c_int, Qkv, C.c_void_p]
+    return fn
+
+
+@pytest.mark.parametrize("tile", range(8))
+@pytest.mark.parametrize("K,splits", [(72, 1), (264, 1), (1032, 3)])
+def test_tile_sums_and_gated_features_at_its_edges(tile, K, splits):
+    """One tile after the other, whatever the rule would take: a row and seven more than two tiles of rows, one feature block
+    more than three tiles and one less than two; two chunks, fewer than a ring holds, five, and an odd number in three splits."""
+    import paper_2404_12022_amd.binding as B
+    lib, stream = tile_launch(B), torch.cuda.current_stream().cuda_stream
+    F, R = TILES[tile]
+    for M, N in ((2 * R + 1, 3 * F + 16), (2 * R + 7, 2 * F - 16), (R - 1, F)):
+        a, w = inputs(M, N, K, M + N + K)
+        packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+        B.ht_weight_pack(w, N, K, packed)
+        out = torch.full((splits * M * N + N,), 7.0, device=H.DEV)
+        out[:splits * M * N] = float("nan")
+        print(f"tile {F} x {R}: {M} x {N} x {K} / {splits}", flush=True)
+        assert lib(tile, 0, a.data_ptr(), Packed(packed.data_ptr(), N, K, (K + 127) // 128 * 128), M, out.data_ptr(), splits, Qkv(), stream) == 0
+        torch.cuda.synchronize()
+        want = a.double() @ w.double().T
+        err = (K / 32 + 16) * 2.0 ** -24 * (a.double().abs() @ w.double().abs().T)
+        assert bool(((out[:splits * M * N].view(splits, M, N).sum(0).double() - want).abs() <= err).all())
+        assert bool((out[splits * M * N:] == 7.0).all())
+        if splits > 1:
+            continue
+        f = N // 32 * 16                                  # an odd number of pairs of blocks among them
+        gu = torch.empty(B.ht_weight_pack_bytes(2 * f, K), dtype=torch.uint8, device=H.DEV)
+        B.ht_gate_up_pack(w[:f].contiguous(), w[f:2 * f].contiguous(), f, K, gu)
+        act = torch.full((M + 1, f), 7.0, dtype=torch.bfloat16, device=H.DEV)
+        assert lib(tile, 1, a.data_ptr(), Packed(gu.data_ptr(), 2 * f, K, (K + 127) // 128 * 128), M, act.data_ptr(), 1, Qkv(), stream) == 0
+        torch.cuda.synchronize()
+        g, u = want[:, :f], want[:, f:2 * f]
+        act_want = g / (1 + torch.exp(-g)) * u
+        assert bool(((act[:M].double() - act_want).abs() <= 2.0 ** -8 * act_want.abs() + 1e-4 * act_want.abs().max()).all())
+        assert bool((act[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("tile", range(8))
+@pytest.mark.parametrize("hd", [32, 64, 96, 128])
+def test_tile_rotates_and_appends_at_its_edges(tile, hd):
+    """Five q heads, three k and three v heads: the seams between q, k and v fall inside tiles of most sizes, the borders of
+    tiles of 96 and 192 features inside heads.  With and without rows that have caches of their own."""
+    import paper_2404_12022_amd.binding as B
+    K, n, Hq, Hkv = 136, 5, 5, 3
+    M = TILES[tile][1] + 9
+    qd, kvd = Hq * hd, Hkv * hd
+    N = qd + 2 * kvd
+    a, w = inputs(M, N, K, M + hd)
+    lib, s = tile_launch(B), torch.cuda.current_stream().cuda_stream
+    repack = getattr(B.lib, "_ZN2ht13launch_repackENS_10WeightSegsEiiiPvP12ihipStream_t")
+    repack.restype, repack.argtypes = C.c_int, [Segs] + [C.c_int] * 3 + [C.c_void_p] * 2
+    packed = torch.empty(B.ht_weight_pack_bytes(N, K), dtype=torch.uint8, device=H.DEV)
+    parts = [w[:qd], w[qd:qd + kvd], w[qd + kvd:]]
+    assert repack(Segs((C.c_void_p * 3)(*[p.data_ptr() for p in parts]), (C.c_int32 * 3)(qd, kvd, kvd), 3), K, 2, hd, packed.data_ptr(), s) == 0
+    y = a.double() @ w.double().T
+    err = (K / 32 + 16) * 2.0 ** -24 * float((a.double().abs() @ w.double().abs().T).max())
+    cs, tail_cs = factors(M, n, hd), factors(M, 3, hd)
+    bf = dict(dtype=torch.bfloat16, device=H.DEV)
+
+    def close(got, want):                             # one bf16 rounding (half an ulp, 2^-9) on sums that are off by err
+        return bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 4 * err).all())
+
+    for tail in (0, M // 2 + 3):
+        own = tail or M
+        cap, tail_n, tail_cap = (n + M + 10) // 8 * 8, 2, (M + 10) // 8 * 8
+        q = torch.full((M + 1, Hq, hd), 7.0, **bf)
+        kc, vc = torch.full((cap, Hkv, hd), 7.0, **bf), torch.full((Hkv, hd, cap), 7.0, **bf)
+        tk, tv = torch.full((tail_cap, Hkv, hd), 7.0, **bf), torch.full((Hkv, hd, tail_cap), 7.0, **bf)
+        qe = Qkv(cs.data_ptr(), q.data_ptr(), kc.data_ptr(), vc.data_ptr(), n, Hq, Hkv, hd, cap, None, tail, tail_n, tail_cap,
+                 tail_cs.data_ptr() if tail else None, tk.data_ptr() if tail else None, tv.data_ptr() if tail else None)
+        print(f"tile {TILES[tile]}: q|k|v of heads of {hd}, tail {tail}", flush=True)
+        assert lib(tile, 3 if tail else 2, a.data_ptr(), Packed(packed.data_ptr(), N, K, (K + 127) // 128 * 128), M, None, 1, qe, s) == 0
+        torch.cuda.synchronize()
+        both = torch.cat([cs[:own], tail_cs[:M - own]])
+        k, v = rotated(y[:, qd:qd + kvd].reshape(M, Hkv, hd), both), y[:, qd + kvd:].reshape(M, Hkv, hd)
+        assert close(q[:M], rotated(y[:, :qd].reshape(M, Hq, hd), both)) and bool((q[M] == 7).all())
+        assert close(kc[n:n + own], k[:own]) and close(vc[:, :, n:n + own].permute(2, 0, 1), v[:own])
+        assert bool((kc[:n] == 7).all()) and bool((kc[n + own:] == 7).all())
+        assert bool((vc[:, :, :n] == 7).all()) and bool((vc[:, :, n + own:] == 7).all())
+        t1 = tail_n + M - own
+        if tail:
+            assert close(tk[tail_n:t1], k[own:]) and close(tv[:, :, tail_n:t1].permute(2, 0, 1), v[own:])
+        first, last = (tail_n, t1) if tail else (0, 0)
+        assert bool((tk[:first] == 7).all()) and bool((tk[last:] == 7).all())
+        assert bool((tv[:, :, :first] == 7).all()) and bool((tv[:, :, last:] == 7).all())
