@@ -490,11 +490,12 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
   (const T*)q_in, Hq * hd, (const T*)k_in, Hkv * hd, (const T*)v_in, Hkv * hd, 1, (size_t)0, cs, (T*)q, (T*)kc, (T*)vc, n, M, \
       RB, Hq, Hkv, hd, cap, 0, nullptr, depth, rope_step(base, hd / 2)
   const size_t values = (size_t)RB * (hd + 2) * (dtype == 0 ? 4 : 2), factors = (size_t)RB * (hd / 2) * sizeof(float2);
-  // Factors worked out by every workgroup for itself as long as that is no more than six per compute unit: a call with a
-  // launch of its own for the table, and without (us; heads are q and k heads, 100 cached keys): 24 rows of 8 heads 9.1 and 7.6,
-  // 144 rows of 64 19.8 and 18.7 (576 workgroups), 256 rows of 72 30.3 and 29.5 (1152); 256 rows of 128 heads 31.3 and 31.1
-  // (2048), of 256 28.6 and 29.1 (4096).
-  if (hd % 8 == 0 && row_blocks * (Hq + Hkv) <= 1536) {
+  // Factors worked out by every workgroup for itself as long as all of them together work out no more than a million (8 hd
+  // each): a factor costs as many instructions every time, a launch for the table 1.5 us once.  Table and append in two
+  // launches / in one, us, by workgroups.  As many k heads as q heads, heads of 128: 128 5.0 / 3.5, 512 6.2 / 5.0, 576 6.6 / 5.7,
+  // 1024 7.4 / 7.2, 1152 7.9 / 8.0, 2048 10.3 / 11.4; heads of 64: 512 5.3 / 3.8, 1024 6.0 / 5.0, 2048 7.6 / 7.6, 2304 8.2 / 8.5.
+  // A k head to four q heads, heads of 128: 640 6.0 / 5.0, 1280 7.0 / 7.2; heads of 64: 1440 6.1 / 5.6, 2560 7.1 / 7.8.
+  if (hd % 8 == 0 && (size_t)row_blocks * (Hq + Hkv) * hd <= 131072) {
     HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL((rope_append_rows_kernel<T, T, true>), grid, dim3(256),
                                                 values > factors ? values : factors, s, HT_ROPE_ARGS);)
     return hipGetLastError();

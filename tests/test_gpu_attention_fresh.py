@@ -140,10 +140,10 @@ def test_caches_off_a_16_byte_address_take_the_general_route(which):
     assert torch.equal(out, want) and torch.equal(kc2, k1) and torch.equal(vc2, v1)
 
 
-@pytest.mark.parametrize("T,Hq,Hkv", [(144, 32, 32), (250, 64, 8), (256, 64, 64)])
+@pytest.mark.parametrize("T,Hq,Hkv", [(144, 32, 32), (250, 64, 8), (256, 64, 64), (256, 32, 32)])
 def test_rows_of_many_heads_on_either_side_of_the_table_launch(T, Hq, Hkv):
-    """More than 16 rows: 576 and 1152 row blocks times q and k heads work their rotary factors out for themselves, 2048 read
-    them from the table of a launch of its own.  Appended keys are float32 products rounded once: at most half a bf16 unit,
+    """More than 16 rows: 576 and 1024 row blocks times q and k heads of 128 (the most) work their rotary factors out for
+    themselves, 1152 and 2048 read them from the table of a launch of its own.  Appended keys are float32 products rounded once: at most half a bf16 unit,
     2^-8 relative."""
     B = _B()
     n, hd, cap = 40, 128, 304
