@@ -801,8 +801,8 @@ hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int 
 //   64 x 128    4096 x 4096, two splits: 256 rows 18.4 (33)
 //   96 x 128    12288 x 4096: 160 rows 31 (58), 256 rows 39 (59)
 //   128 x 128   4096 x 11008, four splits: 256 rows 34 (43)
-//   192 x 128   22016 x 4096: 256 rows 58 (76)
-//   128 x 256   12288 x 4096: 512 rows 52 (71); 32000 x 4096: 256 rows 67 (89)
+//   192 x 128   22016 x 4096: 256 rows 58 (76); 12288 x 4096: 512 rows 55 (128 x 256: 57), 300 rows 48 (52)
+//   128 x 256   32000 x 4096: 256 rows 67 (89)
 //   192 x 256   22016 x 4096: 512 rows 88 (104); 12288 x 4096: 1024 rows 88 (101)
 //   256 x 256   27648 x 5120: 512 rows 126 (127); 12288 x 4096: 4096 rows 310 (319); everything large
 struct TileCost { int features, tokens; float round, chunk, rows, idle; };
