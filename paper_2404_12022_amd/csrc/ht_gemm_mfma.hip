@@ -443,8 +443,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* _
 // Bound: the matrix cores, if the operands reach them.  Both operands go through LDS (a chunk of weights and of tokens is
 // fetched once per workgroup), straight from global memory with 16-byte LDS-direct loads, ST stages.  A wavefront
 // multiplies 16 R weight rows by 16 MT tokens: at R = 4, MT = 8 it reads 12 KB from LDS for 32 matrix instructions.  Counted on
-// gate/up at 4095 tokens: matrix cores busy 0.70 of the time, LDS 0.26 with these reads (no bank conflicts), wavefronts
-// waiting 0.45 of their cycles; what is lost is lost between a read and the products that need it.  So the
+// gate/up at 4095 tokens: matrix cores busy 0.70 of the time, LDS 0.27 with these reads (no bank conflicts), wavefronts
+// waiting 0.46 of their cycles; what is lost is lost between a read and the products that need it.  So the
 // order of issue is what matters, and it is written out (sched_barrier fences): operands of the next 32 columns are
 // read, a fragment or two at a time, between groups of four matrix instructions on the current ones, and the second half
 // of a chunk also issues the loads of the chunk after next one by one (64 of them in a burst behind the barrier block

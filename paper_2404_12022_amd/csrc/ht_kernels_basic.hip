@@ -1294,9 +1294,9 @@ hipError_t launch_tree_dynamic(const int32_t* root, const int32_t* cand, const f
 // kl[p] = KL(softmax(za[p]) || softmax(zb[p])) = sum_v A_v (log A_v - log B_v) for pairs p of logit rows.
 // Bound: reading the logits, which are read once: every thread keeps its sums of exponentials and of the A-weighted
 // differences against its own maxima so far, eight entries of both rows at a time with the next eight on their way, and the
-// parts meet at the end.  2046 pairs of 32000: 151 us with the maxima in a pass of their own, whose rows the second pass no
-// longer found in an L2, 82 now, 6.4 TB/s; 256 pairs 24.8 and 16.2, one pair 14.1 and 10.3, 500 pairs of 4000 10.4 and 6.9.
-// 256 threads a pair take 22.5 at 256 pairs, 14.4 at one, and as long as these at 2046.
+// parts meet at the end.  2046 pairs of 32000: 155 us with the maxima in a pass of their own, whose rows the second pass no
+// longer found in an L2, 98 now, 5.3 TB/s; 256 pairs 23.6 and 16.3, one pair 13.5 and 10.6, 500 pairs of 4000 11.2 and 7.3.
+// 256 threads a pair took 22.5 at 256 pairs and 14.4 at one (16.2 and 10.3 then), and as long as these at 2046.
 // Masks of the lowest float are numbers like others here: a difference of 3.4e38 times a weight that is 1 only until a thread
 // meets a larger logit must not overflow, so weighted differences are summed in units of 2^40, and sums are lowered before
 // they are multiplied by the step down.
