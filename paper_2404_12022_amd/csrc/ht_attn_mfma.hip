@@ -16,7 +16,7 @@
 // A workgroup works on one query head and one slice of the keys.  Two kernels share this scheme:
 //   attn_mfma_kernel (<= 16 rows): K and V fragments are loaded from global memory straight into MFMA
 //     operand registers, the four wavefronts take 32-key chunks round-robin and merge (max, sum, O)
-//     through LDS;
+//     through LDS (attn_fresh_kernel: the same with the rows of the pass as the caller has them);
 //   attn_tile_kernel (more rows): every wavefront owns 16 or 32 rows, 64-key tiles of K and V^T are staged
 //     in LDS with fully coalesced loads and shared by the wavefronts (per-lane operand loads from global
 //     memory cost one L1 tag lookup per lane and made the first version L1-bound).
