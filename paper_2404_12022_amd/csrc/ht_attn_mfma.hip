@@ -16,7 +16,8 @@
 // A workgroup works on one query head and one slice of the keys.  Two kernels share this scheme:
 //   attn_mfma_kernel (<= 16 rows): K and V fragments are loaded from global memory straight into MFMA
 //     operand registers, the four wavefronts take 32-key chunks round-robin and merge (max, sum, O)
-//     through LDS (attn_fresh_kernel: the same with the rows of the pass as the caller has them);
+//     through LDS (attn_fresh_kernel: the same with the rows of the pass as the caller has them; attn_ring_fresh_kernel
+//     for 17 to 128 of them);
 //   attn_tile_kernel (more rows): every wavefront owns 16 or 32 rows, 64-key tiles of K and V^T are staged
 //     in LDS with fully coalesced loads and shared by the wavefronts (per-lane operand loads from global
 //     memory cost one L1 tag lookup per lane and made the first version L1-bound).
@@ -675,6 +676,17 @@ __global__ __launch_bounds__(64 * NW) void attn_tile_kernel(const bf16_t* __rest
 // of a tile is that of attn_tile_kernel (XOR-swizzled 16-byte pieces); an LDS-direct load writes 64 consecutive
 // pieces, so every lane picks the global piece that belongs at its place.  Same arithmetic in the same order as
 // attn_tile_kernel: the two give the same bits.
+//
+// FRESH (the attention call on up to 128 rows as the caller has them): rotary, append and attention in one launch instead of
+// two or three, whatever the number of keys.  What bounds it is latency: a workgroup needs its depths, then the factors, then
+// its first rotated tile, one after the other.  So the first tiles of the cache are requested before anything else and arrive
+// meanwhile; the factors are worked out once per depth, not per row (a factor is some 75 double precision instructions; by
+// rows, 64 of them, they were 3 us of the start, by depths 0.4); and the pass's own keys are tiles of their own, in front of
+// the cache's (rows of the caller have no other place in LDS that is free this early: the stage the loads use last), shared
+// out over the key slices with the others.  The last workgroup of a head needs all of them and appends them.  Us before / now:
+// 128 rows of 32 heads over 4096 keys 31.1 / 27.9, 64 over 512 16.9 / 14.3, 17 of 4 heads of 64 over 40 8.3 / 7.1, 20 of 40 on 5
+// heads over 6000 33.2 / 24.5, 90 of 40 over 1400 27.9 / 19.2.  129 - 256 rows keep the general route: at 128-wide heads a table
+// for them does not fit beside the ring.
 template <int N> __device__ __forceinline__ void attn_wait_vm_then_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
@@ -687,16 +699,13 @@ template <int HD> struct RingShape {
   static constexpr int AHEAD = 63 / NL < 2 ? 63 / NL : 2;              // tiles that may be in flight at a barrier
   static constexpr int STAGES = AHEAD + 2;
   static constexpr int LDS_BYTES = STAGES * STAGE;
+  static constexpr int fresh_bytes(int M) { return LDS_BYTES + (M <= 64 ? 64 : 128) * (HD / 2) * (int)sizeof(float2); }   // rotary factors by depth
 };
 
-template <int HD, int NCW>
-__global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
-                                                                   const bf16_t* __restrict__ vc, int cap, int n, int M,
-                                                                   const uint64_t* __restrict__ anc, int Hq, int Hkv,
-                                                                   bf16_t* __restrict__ out, float* __restrict__ part_o,
-                                                                   float* __restrict__ part_ml, int nsplit, float scale_log2,
-                                                                   const int32_t* __restrict__ n_dev) {
-  n = cache_len(n, n_dev);
+template <int HD, int NCW, bool FRESH>
+__device__ __forceinline__ void ring_attention(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int n, int M,
+                                               const uint64_t* anc, int Hq, int Hkv, bf16_t* out, float* part_o, float* part_ml,
+                                               int nsplit, float scale_log2, const FreshRows& fr) {
   using RS = RingShape<HD>;
   constexpr int TK = RS::TK, ES = HD / 32, EB = HD / 16, PK = HD / 8;
   constexpr int KBYTES = RS::KBYTES, STAGE = RS::STAGE, NL = RS::NL, NLK = KBYTES / 1024, AHEAD = RS::AHEAD, ST = RS::STAGES;
@@ -705,10 +714,19 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int hk = blockIdx.x, group = Hq / Hkv, split = blockIdx.z;
-  const int S = n + M;
+  const int row_blocks = (M + 15) / 16, blocks = group * row_blocks, blk0 = blockIdx.y * NCW;
+  const int S = FRESH ? n : n + M;                        // keys in the cache
   const int tiles = (S + TK - 1) / TK;
+  // FRESH: tiles of the pass's own keys, in front of the cache's: as far as the last row of the workgroup's blocks (a row's
+  // ancestors come before it), in the last workgroup of a head all of them
+  const int blk1 = blk0 + NCW < blocks ? blk0 + NCW - 1 : blocks - 1;
+  const int own = !FRESH ? 0 : (blk1 / row_blocks != blk0 / row_blocks ? row_blocks - 1 : blk1 % row_blocks) * 16 / TK + 1;
+  constexpr int OWN = 2;                                  // an own tile takes 2.0 us to make and multiply, a tile of the cache 0.9
   int ts, te;
-  even_share(tiles, nsplit, split, ts, te);
+  even_share(OWN * own + tiles, nsplit, split, ts, te);
+  const int os = ts < OWN * own ? (ts + OWN - 1) / OWN : own, oe = te < OWN * own ? (te + OWN - 1) / OWN : own;
+  ts = ts < OWN * own ? 0 : ts - OWN * own;
+  te = te < OWN * own ? 0 : te - OWN * own;
   const bool empty = ts >= te;                            // a slice without tiles still leaves its (neutral) partials
   int tmid = n / TK;                                      // tiles below tmid hold cache keys only
   tmid = tmid < ts ? ts : (tmid > te ? te : tmid);
@@ -717,7 +735,7 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
 
   if (wave == NCW) {
     // ---- load wavefront.  Piece li < NLK of a tile is K (64 / PK key rows), the others V^T (eight rows e of 64 keys)
-    if (empty) return;
+    if (!FRESH && empty) return;
     const bf16_t* kbase = kc + (size_t)hk * HD;
     const bf16_t* vbase = vc + (size_t)hk * HD * cap;
     const unsigned krow_stride = (unsigned)(Hkv * HD);
@@ -749,13 +767,28 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
     auto clear_tail = [&](int stage) __attribute__((always_inline)) {
       const int valid = S - (tiles - 1) * TK;               // keys of the tile that carry data, 1 .. TK - 1
       unsigned char* vb = ring + stage * STAGE + KBYTES;
-      for (int idx = lane; idx < HD * (TK - valid); idx += 64) {
-        const int e = idx / (TK - valid), key = valid + idx % (TK - valid);
-        *(bf16_t*)(vb + e * (TK * 2) + (((key >> 3) ^ ((e >> 1) & 7)) << 4) + (key & 7) * 2) = 0;
+#pragma unroll 4
+      for (int idx = lane; idx < HD * (TK / 8); idx += 64) {                  // a piece of eight keys at a time
+        const int e = idx / (TK / 8), p = idx % (TK / 8), keep = valid - p * 8;
+        u32x4_t* at = (u32x4_t*)(vb + e * (TK * 2) + ((p ^ ((e >> 1) & 7)) << 4));
+        if (keep >= 8) continue;
+        u32x4_t piece = {0, 0, 0, 0};
+        if (keep > 0) {
+          piece = *at;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) piece[w] &= (2 * w < keep ? 0x0000ffffu : 0u) | (2 * w + 1 < keep ? 0xffff0000u : 0u);
+        }
+        *at = piece;
       }
     };
+    if (!FRESH || !empty) {
 #pragma unroll
-    for (int p = 0; p < ST - 1; ++p) fetch(ts + p, p);
+      for (int p = 0; p < ST - 1; ++p) fetch(ts + p, p);
+    }
+    if constexpr (FRESH) {
+      for (int i = 0; i <= 2 * (oe - os); ++i) asm volatile("s_barrier" ::: "memory");   // those of the factors and the own tiles
+      if (empty) return;
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD * NL) : "memory");      // tile ts has landed
     if (tail_tile && iters == 1) clear_tail(0);
     attn_wait_vm_then_barrier<AHEAD * NL>();
@@ -772,8 +805,7 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
   }
 
   // ---- arithmetic wavefronts: one block of 16 query columns each
-  const int row_blocks = (M + 15) / 16, blocks = group * row_blocks;
-  const int blk = blockIdx.y * NCW + wave;
+  const int blk = blk0 + wave;
   const bool live = blk < blocks;
   const int bc = live ? blk : blocks - 1;
   const int h = hk * group + bc / row_blocks, m0 = (bc % row_blocks) * 16;
@@ -798,8 +830,10 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
 #pragma unroll
   for (int sub = 0; sub < 2; ++sub) vfo[sub] = KBYTES + r16 * (TK * 2) + (((sub * 4 + g) ^ ((r16 >> 1) & 7)) << 4);
 
-  auto process = [&](auto masked, int stage, int t) __attribute__((always_inline)) {
-    constexpr bool MASKED = decltype(masked)::value;
+  // MODE 0: a tile of cache keys; 1: the tiles that reach past key n - 1; 2: tile t of the pass's own keys (FRESH)
+  auto process = [&](auto mode, int stage, int t) __attribute__((always_inline)) {
+    constexpr int MODE = decltype(mode)::value;
+    constexpr bool MASKED = MODE != 0;
     const unsigned char* base = ring + stage * STAGE;
     const int j0 = t * TK;
     Frag kf[2][2][ES];
@@ -827,8 +861,8 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
 #pragma unroll
       for (int x = 0; x < 16; ++x) {
         const int j = j0 + (x >> 3) * 32 + g * 8 + (x & 7);
-        bool vis = j < n;
-        if (!vis && j < S) {
+        bool vis = MODE == 2 ? ((t ? amask[1] : amask[0]) >> (j - j0)) & 1ull : j < n;    // (128 rows at most)
+        if (!FRESH && !vis && j < S) {
           const int u = j - n;
           vis = (amask[u >> 6] >> (u & 63)) & 1ull;
         }
@@ -874,16 +908,111 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
     }
   };
 
+  if constexpr (FRESH) {
+    // Rotary factors by depth, [deepest row + 1][HD / 2], shared by queries and keys (a tree of a hundred rows is a few deep; no
+    // row is deeper than its number, which bounds the table).
+    constexpr int half = HD / 2, PAIRS = PK / 2, KI = TK * PAIRS / (64 * NCW), VPW = PK / NCW;
+    float2* factors = (float2*)(ring + ST * STAGE);
+    const int dep0 = fr.depth[lane < M ? lane : M - 1], dep1 = fr.depth[lane + 64 < M ? lane + 64 : M - 1];     // (128 rows at most)
+    auto depth_of = [&](int row) __attribute__((always_inline)) {
+      const int a = __shfl(dep0, row & 63, 64), b = __shfl(dep1, row & 63, 64);
+      return row < 64 ? a : b;
+    };
+    // rows of own tile o: values a key to a lane, the wavefront's share of the pieces; keys both partners of eight pairs to a thread
+    Frag v[VPW];
+    u32x4_t ka[KI], kb[KI];
+    auto load_own = [&](int o) __attribute__((always_inline)) {
+      const int uv = o * TK + lane;
+#pragma unroll
+      for (int i = 0; i < VPW; ++i) {
+        v[i].nat = u32x4_t{0, 0, 0, 0};                                        // past the last row: zero times a zero probability
+        if (uv < M) v[i].nat = *(const u32x4_t*)(fr.v + ((size_t)uv * Hkv + hk) * HD + (wave * VPW + i) * 8);
+      }
+#pragma unroll
+      for (int i = 0; i < KI; ++i) {
+        const int item = i * 64 * NCW + tid, u = o * TK + item / PAIRS;
+        const bf16_t* krow = fr.k + ((size_t)(u < M ? u : M - 1) * Hkv + hk) * HD + item % PAIRS * 8;
+        ka[i] = *(const u32x4_t*)krow;
+        kb[i] = *(const u32x4_t*)(krow + half);
+      }
+    };
+    auto rotate8 = [&](u32x4_t& a, u32x4_t& b, const float2* f) __attribute__((always_inline)) {
+#pragma unroll
+      for (int w2 = 0; w2 < 4; ++w2) {
+        const float4 c2 = *(const float4*)(f + 2 * w2);                        // two pairs of (cos, sin)
+        const float a0 = __uint_as_float(a[w2] << 16), a1 = __uint_as_float(a[w2] & 0xffff0000u);
+        const float b0 = __uint_as_float(b[w2] << 16), b1 = __uint_as_float(b[w2] & 0xffff0000u);
+        const float2 p0 = make_float2(c2.x, c2.y), p1 = make_float2(c2.z, c2.w);
+        const uint2 r = pack4_bf16(rope_low(a0, b0, p0), rope_low(a1, b1, p1), rope_high(a0, b0, p0), rope_high(a1, b1, p1));
+        a[w2] = r.x;
+        b[w2] = r.y;
+      }
+    };
+    if (os < oe) load_own(os);
+    {
+      const int j = lane % half;
+      const double2 turns = rope_turns(j, fr.step);
+      int deepest = dep0 > dep1 ? dep0 : dep1;
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        const int other = __shfl_xor(deepest, off, 64);
+        deepest = other > deepest ? other : deepest;
+      }
+      for (int r = tid / half; r <= deepest; r += 64 * NCW / half) factors[r * half + j] = rope_factor(n + r, turns);
+    }
+    attn_wait_lds_then_barrier();                                              // the factors are there
+    {
+      const float2* row = factors + depth_of(m0 + r16 < M ? m0 + r16 : M - 1) * half + g * 8;
+#pragma unroll
+      for (int es = 0; es < ES / 2; ++es) rotate8(qf[es].nat, qf[es + ES / 2].nat, row + es * 32);
+    }
+    const bool appends = blockIdx.y == gridDim.y - 1;
+    unsigned char* tile = ring + (ST - 1) * STAGE;                             // the stage that the first tiles of the cache leave free
+    for (int o = os; o < oe; ++o) {
+      const int uv = o * TK + lane;
+      int place = lane;                                      // opaque: addresses worked out ahead of the loop, a hundred of them, would spill
+      asm volatile("" : "+v"(place));
+      bf16_t* column = fr.vc + ((size_t)hk * HD + wave * VPW * 8) * cap + n + o * TK + place;
+#pragma unroll
+      for (int i = 0; i < KI; ++i) {
+        const int item = i * 64 * NCW + tid, kl = item / PAIRS, pc = item % PAIRS, u = o * TK + kl;
+        rotate8(ka[i], kb[i], factors + depth_of(u < M ? u : M - 1) * half + pc * 8);
+        const int sw = ((((kl >> 3) & 3) << 2) | (kl & 3)) & (PK - 1);
+        *(u32x4_t*)(tile + kl * (HD * 2) + ((pc ^ sw) << 4)) = ka[i];
+        *(u32x4_t*)(tile + kl * (HD * 2) + (((pc + PAIRS) ^ sw) << 4)) = kb[i];
+        if (appends && u < M) {
+          bf16_t* krow = fr.kc + ((size_t)(n + u) * Hkv + hk) * HD + pc * 8;
+          *(u32x4_t*)krow = ka[i];
+          *(u32x4_t*)(krow + half) = kb[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < VPW; ++i)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int e = (wave * VPW + i) * 8 + x;
+          const bf16_t val = (bf16_t)(v[i].u[x >> 1] >> (16 * (x & 1)));
+          *(bf16_t*)(tile + KBYTES + e * (TK * 2) + (((place >> 3) ^ ((e >> 1) & 7)) << 4) + (place & 7) * 2) = val;
+          if (appends && uv < M) *column = val;
+          column += cap;
+        }
+      if (o + 1 < oe) load_own(o + 1);
+      attn_wait_lds_then_barrier();                                            // the tile is there
+      if (live) process(std::integral_constant<int, 2>{}, ST - 1, o);
+      attn_wait_lds_then_barrier();                                            // and may be written over
+    }
+  }
+
   if (!empty) {
     attn_wait_lds_then_barrier();                           // tile ts is in LDS
     int stage = 0, t = ts;
     for (; t < tmid; ++t) {
-      if (live) process(std::false_type{}, stage, t);
+      if (live) process(std::integral_constant<int, 0>{}, stage, t);
       stage = stage + 1 == ST ? 0 : stage + 1;
       attn_wait_lds_then_barrier();
     }
     for (; t < te; ++t) {                                   // the few tiles that reach past the cache
-      if (live) process(std::true_type{}, stage, t);
+      if (live) process(std::integral_constant<int, 1>{}, stage, t);
       stage = stage + 1 == ST ? 0 : stage + 1;
       attn_wait_lds_then_barrier();
     }
@@ -911,6 +1040,25 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t*
     ml[0] = mrun;
     ml[1] = lsum;
   }
+}
+
+template <int HD, int NCW>
+__global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+                                                                   const bf16_t* __restrict__ vc, int cap, int n, int M,
+                                                                   const uint64_t* __restrict__ anc, int Hq, int Hkv,
+                                                                   bf16_t* __restrict__ out, float* __restrict__ part_o,
+                                                                   float* __restrict__ part_ml, int nsplit, float scale_log2,
+                                                                   const int32_t* __restrict__ n_dev) {
+  ring_attention<HD, NCW, false>(q, kc, vc, cap, cache_len(n, n_dev), M, anc, Hq, Hkv, out, part_o, part_ml, nsplit, scale_log2,
+                                 FreshRows{});
+}
+
+template <int HD, int NCW>
+__global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_fresh_kernel(const bf16_t* q, int cap, int n, int M,
+                                                                         const uint64_t* __restrict__ anc, int Hq, int Hkv, bf16_t* out,
+                                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
+                                                                         int nsplit, float scale_log2, FreshRows fr) {
+  ring_attention<HD, NCW, true>(q, fr.kc, fr.vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, nsplit, scale_log2, fr);
 }
 
 // out[m][h] = sum_s exp2(m_s - m*) O_s / sum_s exp2(m_s - m*) l_s, splits added in index order.
@@ -973,6 +1121,21 @@ __global__ __launch_bounds__(256) void attn_self_slice_kernel(const bf16_t* __re
 // each wavefront owning 16 rows (two row groups of workgroups above 64 rows).
 struct AttnPlan { int qb, waves, groups, nsplit; bool tiled; int ring_waves; };
 
+// The ring kernel over `tiles` 64-key tiles: its tiles fill the LDS of a compute unit, so the slices are cut for one workgroup
+// per unit.
+AttnPlan plan_ring(int M, int Hq, int Hkv, int tiles) {
+  AttnPlan p;
+  p.qb = 1;
+  p.waves = p.ring_waves = 4;      // eight wavefronts on half as many workgroups run as fast, but double the slices to merge
+  p.tiled = M > 16;
+  p.groups = ((Hq / Hkv) * ((M + 15) / 16) + p.ring_waves - 1) / p.ring_waves;
+  int s = 256 / (Hkv * p.groups);
+  if (s > tiles / 2) s = tiles / 2;
+  if (s > kMaxSplits) s = kMaxSplits;
+  p.nsplit = s < 1 ? 1 : s;
+  return p;
+}
+
 AttnPlan plan_attention(int M, int Hq, int Hkv, int S) {
   AttnPlan p;
   p.tiled = M > 16;
@@ -983,22 +1146,11 @@ AttnPlan plan_attention(int M, int Hq, int Hkv, int S) {
   const int units = p.tiled ? (S + 63) / 64 : (S + 31) / 32;     // tiles or chunks
   // Long key ranges, or query heads that share key/value heads: the ring kernel (measured at 128-wide heads, 64 rows:
   // 40 heads over 2112 keys 14.2 -> 13.2 us, 64 query on 8 key/value heads over 4160 keys 25.1 -> 20.7 us; 128 rows
-  // of 32 heads over 4224 keys 23.7 -> 22.8 us; over 576 keys the tile kernel stays ahead, 7.0 against 7.3 us).  Its
-  // three-tile ring fills the LDS of a compute unit, so the slices are cut for one workgroup per unit.
+  // of 32 heads over 4224 keys 23.7 -> 22.8 us; over 576 keys the tile kernel stays ahead, 7.0 against 7.3 us).
   // With four or more query heads per key/value head it also takes the passes of up to 16 rows (one-token step, draft
   // rows), whose own kernel streams the tiles once per query head.
-  const int blocks = (Hq / Hkv) * ((M + 15) / 16);
   const int tiles = (S + 63) / 64;
-  if (tiles >= 24 && M <= 128 && (p.tiled || Hq / Hkv >= 4)) {
-    const int units = tiles;
-    p.ring_waves = 4;      // eight wavefronts on half as many workgroups run as fast, but double the slices to merge
-    p.groups = (blocks + p.ring_waves - 1) / p.ring_waves;
-    int s = 256 / (Hkv * p.groups);
-    if (s > units / 2) s = units / 2;
-    if (s > kMaxSplits) s = kMaxSplits;
-    p.nsplit = s < 1 ? 1 : s;
-    return p;
-  }
+  if (tiles >= 24 && M <= 128 && (p.tiled || Hq / Hkv >= 4)) return plan_ring(M, Hq, Hkv, tiles);
   int s = (512 + Hq * p.groups - 1) / (Hq * p.groups);           // about two workgroups per compute unit
   // per slice: every wavefront has work; slices of under four tiles only pay off on short caches (measured)
   const int min_units = !p.tiled ? 4 : (units >= 16 ? 4 : 2);
@@ -1011,7 +1163,7 @@ AttnPlan plan_attention(int M, int Hq, int Hkv, int S) {
 
 // The ring's LDS is more than a kernel may use without asking: asked for once per device (attn_mfma_prepare does it
 // when a model is set up, so that no launch inside a stream capture has to).
-template <int HD, int NCW>
+template <int HD, int NCW, bool FRESH>
 hipError_t allow_ring_lds() {
   static bool allowed[64] = {};
   int dev = 0;
@@ -1019,8 +1171,9 @@ hipError_t allow_ring_lds() {
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!allowed[dev]) {
-    e = hipFuncSetAttribute((const void*)attn_ring_kernel<HD, NCW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            RingShape<HD>::LDS_BYTES);
+    const void* kernel = FRESH ? (const void*)attn_ring_fresh_kernel<HD, NCW> : (const void*)attn_ring_kernel<HD, NCW>;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            FRESH ? RingShape<HD>::fresh_bytes(128) : RingShape<HD>::LDS_BYTES);
     if (e != hipSuccess) return e;
     allowed[dev] = true;
   }
@@ -1030,10 +1183,15 @@ hipError_t allow_ring_lds() {
 template <int HD, int NCW>
 hipError_t launch_ring(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int cap, int n, int M, const uint64_t* anc, int Hq,
                        int Hkv, bf16_t* out, float* part_o, float* part_ml, const AttnPlan& p, float scale_log2, hipStream_t s,
-                       const int32_t* n_dev) {
+                       const int32_t* n_dev, const FreshRows* fresh) {
   constexpr int lds = RingShape<HD>::LDS_BYTES;            // above the 64 KB a kernel may use without asking
-  const hipError_t ea = allow_ring_lds<HD, NCW>();
+  const hipError_t ea = fresh ? allow_ring_lds<HD, NCW, true>() : allow_ring_lds<HD, NCW, false>();
   if (ea != hipSuccess) return ea;
+  if (fresh) {
+    hipLaunchKernelGGL((attn_ring_fresh_kernel<HD, NCW>), dim3(Hkv, p.groups, p.nsplit), dim3(64 * (NCW + 1)), RingShape<HD>::fresh_bytes(M),
+                       s, q, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit, scale_log2, *fresh);
+    return hipSuccess;
+  }
   hipLaunchKernelGGL((attn_ring_kernel<HD, NCW>), dim3(Hkv, p.groups, p.nsplit), dim3(64 * (NCW + 1)), lds, s, q, kc, vc, cap, n,
                      M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit, scale_log2, n_dev);
   return hipSuccess;
@@ -1048,11 +1206,11 @@ hipError_t launch_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int ca
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
   const dim3 grid(Hq, p.groups, p.nsplit);
 #define HT_ATTN_ARGS q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit, scale_log2, n_dev
-  if (fresh) {
+  if (fresh && !p.ring_waves) {
     hipLaunchKernelGGL((attn_fresh_kernel<HD>), grid, dim3(256), 0, s, q, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p.nsplit,
                        scale_log2, *fresh);
   } else if (p.ring_waves) {
-    const hipError_t e = launch_ring<HD, 4>(q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p, scale_log2, s, n_dev);
+    const hipError_t e = launch_ring<HD, 4>(q, kc, vc, cap, n, M, anc, Hq, Hkv, out, part_o, part_ml, p, scale_log2, s, n_dev, fresh);
     if (e != hipSuccess) return e;
   } else if (!p.tiled) {
     hipLaunchKernelGGL((attn_mfma_kernel<HD>), grid, dim3(256), 0, s, HT_ATTN_ARGS);
@@ -1073,8 +1231,8 @@ bool attn_mfma_supported(int M, int Hq, int Hkv, int hd) {
 }
 
 hipError_t attn_mfma_prepare(int hd) {
-  if (hd == 128) return allow_ring_lds<128, 4>();
-  if (hd == 64) return allow_ring_lds<64, 4>();
+  if (hd == 128) return allow_ring_lds<128, 4, false>();
+  if (hd == 64) return allow_ring_lds<64, 4, false>();
   return hipSuccess;
 }
 
@@ -1129,16 +1287,17 @@ hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int
   return hipErrorInvalidValue;
 }
 
-// The rows of a call of up to 16 as the caller has them, where the kernel of that size takes them.
-bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n) {
-  if (M > 16 || !attn_mfma_supported(M, Hq, Hkv, hd)) return false;
-  const AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
-  return !p.tiled && !p.ring_waves;
-}
+// The rows of a call of up to 128 as the caller has them.
+bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n) { return M <= 128 && attn_mfma_supported(M, Hq, Hkv, hd); }
 hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new, const int32_t* depth, float base, void* kc, void* vc,
                              int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s) {
   if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || !attn_fresh_supported(M, Hq, Hkv, hd, n)) return hipErrorInvalidValue;
-  const AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
+  AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
+  if (p.tiled || p.ring_waves) {
+    const int units = (n + 63) / 64 + 2 * ((M + 63) / 64);                // as the kernel shares them out
+    p = plan_ring(M, Hq, Hkv, units);
+    if (units < 6) p.nsplit = 1;       // a unit takes 1 us, the merge 3 (128 rows of 40 heads over 60 keys 13.0 us, in two slices 14.9)
+  }
   const FreshRows fr{(const bf16_t*)k_new, (const bf16_t*)v_new, (bf16_t*)kc, (bf16_t*)vc, depth, rope_step(base, hd / 2)};
   const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;
   const hipError_t e = hd == 128 ? launch_hd<128>(qp, kp, vp, cap, n, M, tree.anc, Hq, Hkv, (bf16_t*)out, scratch, p, s, nullptr, &fr)

@@ -166,3 +166,32 @@ def test_rows_of_many_heads_on_either_side_of_the_table_launch(T, Hq, Hkv):
     a, b = k.double().cpu()[..., :hd // 2], k.double().cpu()[..., hd // 2:]
     rot = torch.cat([a * co - b * si, b * co + a * si], dim=-1)
     assert ((kc1[n:n + T].double().cpu() - rot).abs() <= 2.0 ** -8 * rot.abs() + 1e-6).all()
+
+
+@pytest.mark.parametrize("T", [9, 17, 31, 48, 63, 64, 65, 100, 127, 128])
+@pytest.mark.parametrize("Hq,Hkv,hd", [(4, 4, 64), (8, 1, 64), (6, 3, 128), (32, 32, 128), (40, 5, 128)])
+def test_one_launch_of_up_to_128_rows_agrees_with_the_general_route_and_with_float64(T, Hq, Hkv, hd):
+    """The ring kernel on the caller's rows (up to 16 of them where many heads share long caches): own keys in tiles of 64 of
+    their own, cut into slices with the cache's, which end before, at and behind a tile and an eight-key piece; shallow trees
+    and a chain, as deep as a tree can be."""
+    B = _B()
+    for n in (0, 1, 63, 64, 72, 300, 1531):
+        say(f"attention in one launch T={T} heads={Hq}/{Hkv}x{hd} n={n}")
+        g = torch.Generator(device=DEV).manual_seed(T * 1000 + n)
+        cap = (n + T + 7) // 8 * 8
+        mk = lambda *s: torch.randn(*s, generator=g, device=DEV).bfloat16()
+        q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+        kc[n:], vc[:, :, n:] = float("nan"), float("nan")
+        parent = _parents(T, n) if n % 2 else [(r - 1) if n == 72 or r == 0 else (r - 1) // 3 for r in range(T)]
+        out, k1, v1 = _call(B, q, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+        ref_out, k2, v2 = _call(B, _off(q), k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd)
+        assert torch.equal(k1[:n + T], k2[:n + T]) and torch.equal(v1[:, :, :n + T], v2[:, :, :n + T])
+        assert torch.isnan(k1[n + T:]).all() and torch.isnan(v1[:, :, n + T:]).all()
+        want = _reference(q, k, v, kc, vc, n, parent, Hq, Hkv, hd)
+        err = float((out.double().cpu() - want).norm() / want.norm())
+        err2 = float((ref_out.double().cpu() - want).norm() / want.norm())
+        say(f"  error {err:.2e}, general route {err2:.2e}")
+        assert err <= 1e-2 and err <= 1.2 * err2 + 1e-4
+        over = q.clone()
+        again, _, _ = _call(B, over, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd, out=over.view(T, Hq * hd))
+        assert torch.equal(again, out)
