@@ -4,6 +4,7 @@
 #include "../../include/ht.h"
 #include "ht_common.h"
 
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -259,7 +260,9 @@ struct ht_model {
   int dyn_b = 0;                // > 0: every drafting step chooses its own tree among the dyn_b best candidates per level
   // pinned host staging
   int32_t* h_stage = nullptr;     // [max(max_cache, two table images)] + the pointer tables
-  StepState* h_state = nullptr;
+  StepState* h_state = nullptr;   // behind it the number of the step that it is of
+  int32_t* h_state_dev = nullptr; // the same memory as the device addresses it
+  int32_t step_number = 0;
   // device-resident loop: while set, the kernels of a pass read the cache length here and `n` is an upper bound
   const int32_t* n_dev = nullptr;
 };
@@ -709,7 +712,9 @@ int ht_init_model(const ht_config* cfg, const ht_weights* w, void* workspace, si
   size_t stage_ints = (size_t)cfg->max_cache > 2 * kTableInts ? (size_t)cfg->max_cache : 2 * kTableInts;
   stage_ints += 3 * (size_t)L * 2 + 64;     // per-layer pointer tables (as 8-byte entries) follow the ints
   hipError_t e = hipHostMalloc((void**)&m->h_stage, stage_ints * sizeof(int32_t) + 16, hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&m->h_state, sizeof(StepState), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&m->h_state, sizeof(StepState) + sizeof(int32_t), hipHostMallocMapped | hipHostMallocCoherent);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&m->h_state_dev, m->h_state, 0);
+  if (e == hipSuccess) *(int32_t*)(m->h_state + 1) = 0;
   if (e == hipSuccess) e = hipMemsetAsync(workspace, 0, need, s);
   if (e != hipSuccess) return cleanup(fail(HT_EHIP, "init allocation/clear failed: %s", hipGetErrorString(e)));
 
@@ -1284,6 +1289,26 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
   return HT_OK;
 }
 
+namespace {
+// Until the state of step `step_number` is there.  A wait of the runtime's own takes some 10 us longer to come back (a caller
+// that waits for the device all the same pays 30 us there, 3 after the runtime's wait: loops of steps do not); it follows where
+// a step takes so long (a prompt in front of it, a device shared with others) that it no longer matters, and where an error keeps
+// the state from ever coming.
+int wait_for_state(ht_model* m, hipStream_t s) {
+  const int32_t* number = (const int32_t*)(m->h_state + 1);
+  const auto start = std::chrono::steady_clock::now();
+  for (unsigned spins = 1; __atomic_load_n(number, __ATOMIC_ACQUIRE) != m->step_number; ++spins) {
+    asm volatile("pause");
+    if (spins % 256 == 0 && std::chrono::steady_clock::now() - start > std::chrono::milliseconds(20)) {
+      HT_HIP(hipStreamSynchronize(s));
+      if (__atomic_load_n(number, __ATOMIC_ACQUIRE) != m->step_number) return fail(HT_EHIP, "the step's state did not arrive");
+      break;
+    }
+  }
+  return HT_OK;
+}
+}  // namespace
+
 int ht_accept_and_compact(ht_model* m, int32_t* n_accepted, int32_t* accepted_tokens, int32_t* next_root,
                           int32_t* path_out, void* stream) {
   if (!m) return fail(HT_EINVAL, "model is NULL");
@@ -1294,8 +1319,9 @@ int ht_accept_and_compact(ht_model* m, int32_t* n_accepted, int32_t* accepted_to
   HT_HIP(launch_accept_compact(c.dtype, b.state, b.tree.dev(), b.tok, b.g, m->T, nullptr, m->n, -1, b.kc_ptrs, b.vc_ptrs, c.n_layers,
                                c.n_kv_heads, c.head_dim, c.max_cache, b.saved_h, (size_t)m->Mp * c.d_model,
                                (int)m->slot_layer.size(), b.h_src, c.d_model, s));
-  HT_HIP(hipMemcpyAsync(m->h_state, b.state, sizeof(StepState), hipMemcpyDeviceToHost, s));
-  HT_HIP(hipStreamSynchronize(s));
+  HT_HIP(launch_publish_state(b.state, m->h_state_dev, ++m->step_number, s));
+  int rc;
+  if ((rc = wait_for_state(m, s))) return rc;
   const StepState& st = *m->h_state;
   if (st.m < 1 || st.m > c.k + 1) return fail(HT_EHIP, "accept kernel returned an impossible count %d", st.m);
   m->n += st.m;

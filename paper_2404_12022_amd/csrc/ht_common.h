@@ -209,6 +209,8 @@ hipError_t launch_tree_dynamic(const int32_t* root /*device*/, const int32_t* ca
 hipError_t launch_accept_compact(int dtype, StepState* st, TreeDev tree, const int32_t* tok, const int32_t* g, int T, StepLog* log,
                                  int n, int parity, void* const* kc, void* const* vc, int L, int Hkv, int hd, int cap,
                                  const float* saved_h, size_t slot_stride, int slots, float* h_src, int d, hipStream_t s);
+// *st to `host` (device-visible host memory, one word more than a StepState holds), then `number` to the word behind it
+hipError_t launch_publish_state(const StepState* st, int32_t* host, int32_t number, hipStream_t s);
 hipError_t launch_prefill_finish(StepState* st, const int32_t* g, const float* saved_h, size_t slot_stride, int slots,
                                  float* h_src, int last, int d, hipStream_t s);
 // measurement aid: one pass over `buf` with the weight stream's access pattern; returns the bytes actually read
