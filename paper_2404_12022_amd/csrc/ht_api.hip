@@ -360,12 +360,24 @@ int run_blocks_f32(ht_model* m, const TreeDev& tree, int M, int layer_from, int 
 // layer_end >= 0: the pass stops after block layer_end (0-based index layer_end - 1) and leaves the finished residual
 // rows in b.x (no final norm, no logits).
 // `from`: where the M rows come from, tokens for the embedding table or fp32 rows (b.x itself is fine).
+// `first`: where the logits of the M rows go, in place of `logits` (packed models).
 struct PassStart {
-  const int32_t* tok;
-  const float* rows;
+  TokenSource tokens;
+  const float* rows = nullptr;
 };
+PassStart tokens_at(const int32_t* tok, int32_t* keep = nullptr) {
+  PassStart p;
+  p.tokens.tok = tok;
+  p.tokens.keep = keep;
+  return p;
+}
+PassStart rows_at(const float* rows) {
+  PassStart p;
+  p.rows = rows;
+  return p;
+}
 int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_from, bool save_hidden, float* logits, int32_t* gout,
-             hipStream_t s, JoinMode join = kNoJoin, int F = 0, int step = 0, int layer_end = -1) {
+             hipStream_t s, JoinMode join = kNoJoin, int F = 0, int step = 0, int layer_end = -1, float* first = nullptr) {
   const ht_config& c = m->cfg;
   Buffers& b = m->b;
   const int d = c.d_model, qd = c.n_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, f = c.d_ffn;
@@ -376,8 +388,9 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
   const int joining = join == kFromTree ? F * c.k : join == kFromBuffer ? c.k : join == kTrainStep ? F : 0;
   // the rows of b.pseudo that join in front of the first block of a pass without rows of its own come in with the start
   const bool joins_first = join == kFromBuffer && M == 0 && m->slot_of_layer[layer_from] >= 0;
-  if (joins_first) from = PassStart{nullptr, b.pseudo + (size_t)m->slot_first[m->slot_of_layer[layer_from]] * d};
-  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, from.tok, from.rows, b.x,
+  if (joins_first) from = rows_at(b.pseudo + (size_t)m->slot_first[m->slot_of_layer[layer_from]] * d);
+  const int first_rows = M;
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, from.tokens, from.rows, b.x,
                            joins_first ? m->slot_count[m->slot_of_layer[layer_from]] : M, d, b.cs, tree.depth, n, M + joining,
                            c.head_dim, c.rope_base, s, m->n_dev));
   int pending = 0;
@@ -479,7 +492,7 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
   HT_HIP(add_norm(b.x, pending, pstride, m->final_norm, logits ? b.u : nullptr, nullptr, b.ss, M));
   if (logits) {
     if (m->packed) {
-      HT_HIP(launch_gemm_packed(b.u, b.p_head, M, logits, 1, s, rs));      // vocab-sized N: never split
+      HT_HIP(launch_gemm_packed(b.u, b.p_head, M, logits, 1, s, rs, first, first_rows));      // vocab-sized N: never split
     } else if ((rc = product(m, b.u, segs1(m->lm_head, c.vocab), M, c.vocab, d, logits, s))) {
       return rc;
     }
@@ -504,7 +517,7 @@ int prompt_pass(ht_model* m, int start, int rows, bool last, hipStream_t s) {
     return sp;
   };
   const int o_splits = splits(qd), down_splits = splits(f);
-  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, b.prompt + start, nullptr, p.x, rows, d, p.cs, nullptr, start, rows, c.head_dim,
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, tokens_at(b.prompt + start).tokens, nullptr, p.x, rows, d, p.cs, nullptr, start, rows, c.head_dim,
                            c.rope_base, s));
   int pending = 0;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -612,15 +625,23 @@ int candidate_tree_room(int k, int b) {
   return room < kMaxTree ? room : kMaxTree;
 }
 
-// Tokens of the tree from the candidates of the last draft: into the fixed tree, or (ht_set_dynamic_tree) into the
-// tree this step chooses from the candidates' log-probabilities, which also rewrites the tree tables.
-int build_tree(ht_model* m, hipStream_t s) {
+// Tokens of the fixed tree from candidates that lie [level][kMaxTopK]: put together by the launch that starts the pass.
+PassStart tree_tokens_of(ht_model* m, const int32_t* cand) {
+  Buffers& b = m->b;
+  PassStart p;
+  p.tokens = TokenSource{nullptr, b.state, cand, b.tree.depth, b.tree.rank, b.tok};
+  return p;
+}
+// Tokens of the tree from the candidates of the last draft: of the fixed tree, or (ht_set_dynamic_tree) of the tree this
+// step chooses from the candidates' log-probabilities, which also rewrites the tree tables.
+int build_tree(ht_model* m, PassStart& from, hipStream_t s) {
   Buffers& b = m->b;
   const ht_config& c = m->cfg;
   if (!m->dyn_b) {
-    HT_HIP(launch_tree_build(b.state, b.cand, b.tree.dev(), b.tok, m->T, s));
+    from = tree_tokens_of(m, b.cand);
     return HT_OK;
   }
+  from = tokens_at(b.tok);
   HT_HIP(launch_cand_logprob(b.dlogits, b.cand, c.k, m->dyn_b, c.vocab, b.lp, s));
   HT_HIP(launch_tree_dynamic(&b.state->root, b.cand, b.lp, c.k, m->dyn_b, m->T, b.tree.out(), b.tok, s));
   return HT_OK;
@@ -939,7 +960,7 @@ int ht_prefill(ht_model* m, const int32_t* tokens, int32_t n, void* stream) {
   for (int start = 0; start < n; start += chunk) {
     const int rows = n - start < chunk ? n - start : chunk;
     const bool last = start + rows == n;
-    if ((rc = run_pass(m, chain, PassStart{m->b.prompt + start, nullptr}, rows, 0, true, last ? m->b.logits : nullptr, m->b.g, s))) return rc;
+    if ((rc = run_pass(m, chain, tokens_at(m->b.prompt + start), rows, 0, true, last ? m->b.logits : nullptr, m->b.g, s))) return rc;
     if (last)
       HT_HIP(launch_prefill_finish(m->b.state, m->b.g, m->b.saved_h, (size_t)m->Mp * c.d_model, (int)m->slot_layer.size(),
                                    m->b.h_src, rows - 1, c.d_model, s));
@@ -986,7 +1007,7 @@ int ht_training_forward(ht_model* m, int32_t step, const int32_t* tokens, int32_
   for (int b0 = 0; b0 < n; b0 += 2 * C) {
     const int low = n - b0 < 2 * C + step ? n - b0 : 2 * C + step;
     m->n = b0;
-    if ((rc = run_pass(m, b.chain.dev(), PassStart{b.prompt + b0, nullptr}, low, 0, false, nullptr, nullptr, s, kNoJoin, 0, 0, t))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), tokens_at(b.prompt + b0), low, 0, false, nullptr, nullptr, s, kNoJoin, 0, 0, t))) return rc;
     HT_HIP(launch_load_rows(b.x, b.saved_h, low, c.d_model, s));
     for (int c0 = b0; c0 < n && c0 < b0 + 2 * C; c0 += C) {
       const int real = n - c0 < C + step ? n - c0 : C + step;
@@ -1012,7 +1033,7 @@ int ht_training_forward(ht_model* m, int32_t step, const int32_t* tokens, int32_
         shape_pseudo = pseudo;
       }
       m->n = c0;
-      if ((rc = run_pass(m, b.train.dev(), PassStart{nullptr, b.saved_h + (size_t)(c0 - b0) * c.d_model}, real, t, false, b.logits, nullptr, s, pseudo ? kTrainStep : kNoJoin, pseudo,
+      if ((rc = run_pass(m, b.train.dev(), rows_at(b.saved_h + (size_t)(c0 - b0) * c.d_model), real, t, false, b.logits, nullptr, s, pseudo ? kTrainStep : kNoJoin, pseudo,
                          step - 1)))
         return rc;
       int pairs = terms - c0;
@@ -1134,7 +1155,7 @@ extern "C" int ht_training_forward_batched(ht_model* m, int32_t step, const int3
   HT_HIP(launch_repack(WeightSegs{{m->w_transfer[step - 1], nullptr, nullptr}, {d, 0, 0}, 1}, d, 0, 0, w.w_transfer, s));
   const PackedW p_transfer{(const bf16_t*)w.w_transfer, d, d, packed_cols(d)};
 
-  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, b.prompt, nullptr, w.x, n, d, w.cs, nullptr, 0, n + 1, c.head_dim, c.rope_base, s));
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, tokens_at(b.prompt).tokens, nullptr, w.x, n, d, w.cs, nullptr, 0, n + 1, c.head_dim, c.rope_base, s));
   int rows = n, pending = 0;
   const TreeDev chain = b.chain.dev();
   auto splits = [&](int r, int K) {            // w.part holds 2 n rows
@@ -1258,28 +1279,30 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
   hipStream_t s = (hipStream_t)stream;
   Buffers& b = m->b;
   int rc;
+  PassStart from;
   if (tree_tokens) {
-    HT_HIP(hipMemcpyAsync(b.tok, tree_tokens, sizeof(int32_t) * T, hipMemcpyDeviceToDevice, s));
+    from = tokens_at(tree_tokens, b.tok);
   } else if (m->drafts_of >= 0 && !m->transfer_ready) {
     // the last verify pass carried pseudo rows for the node the acceptance ended on: its candidates are the tree
-    HT_HIP(launch_tree_build(b.state, b.cand_fused + (size_t)m->drafts_of * c.k * kMaxTopK, b.tree.dev(), b.tok, T, s));
+    from = tree_tokens_of(m, b.cand_fused + (size_t)m->drafts_of * c.k * kMaxTopK);
   } else {
     // draft: pseudo rows through blocks t+1..L as a chain at positions n, n+1, ..; their K/V land in
     // slots n.. and are overwritten by the verify pass below
-    if ((rc = run_pass(m, b.chain.dev(), PassStart{nullptr, nullptr}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), PassStart{}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
-    if ((rc = build_tree(m, s))) return rc;
+    if ((rc = build_tree(m, from, s))) return rc;
   }
-  const PassStart from{b.tok, nullptr};
   if (!fused) {
     float* z = logits_out ? logits_out : b.logits;
     if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, z, b.g, s))) return rc;
   } else {
     // rows T.. of the logits are the draft distributions of the fused nodes (k rows per node)
-    if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, b.g, s, kFromTree, fused))) return rc;
+    // the head stores the tree's rows where the caller wants them, if it may (16 bytes at a time)
+    float* const first = m->packed && !((uintptr_t)logits_out & 15) ? logits_out : nullptr;
+    if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, nullptr, s, kFromTree, fused, 0, -1, first))) return rc;
     HT_HIP(launch_topk(b.logits + (size_t)T * c.vocab, b.cand_fused, b.width, b.topk_scratch, fused * c.k, c.k, b.fused_src,
-                       c.vocab, s));
-    if (logits_out)
+                       c.vocab, s, first ? first : b.logits, b.g, T));
+    if (logits_out && !first)
       HT_HIP(hipMemcpyAsync(logits_out, b.logits, sizeof(float) * T * c.vocab, hipMemcpyDeviceToDevice, s));
   }
   if (argmax_out) HT_HIP(hipMemcpyAsync(argmax_out, b.g, sizeof(int32_t) * T, hipMemcpyDeviceToDevice, s));
@@ -1374,10 +1397,11 @@ int ht_decode_steps(ht_model* m, int32_t steps, int32_t* n_accepted, int32_t* ac
       HT_HIP(launch_transfer(c.dtype, b.h_src + (size_t)g * c.d_model, nullptr, 1, (const void* const*)b.wt_ptrs,
                              b.pseudo + (size_t)m->slot_first[g] * c.d_model, m->slot_first[g], m->slot_count[g], 0,
                              c.d_model, nullptr, s));
-    if ((rc = run_pass(m, b.chain.dev(), PassStart{nullptr, nullptr}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
+    if ((rc = run_pass(m, b.chain.dev(), PassStart{}, 0, c.transfer_layer[0], false, b.dlogits, nullptr, s, kFromBuffer))) return rc;
     HT_HIP(launch_topk(b.dlogits, b.cand, b.width, b.topk_scratch, c.k, c.k, nullptr, c.vocab, s));
-    if ((rc = build_tree(m, s))) return rc;
-    if ((rc = run_pass(m, b.tree.dev(), PassStart{b.tok, nullptr}, T, 0, true, b.logits, b.g, s))) return rc;
+    PassStart from;
+    if ((rc = build_tree(m, from, s))) return rc;
+    if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, b.g, s))) return rc;
     HT_HIP(launch_accept_compact(c.dtype, b.state, b.tree.dev(), b.tok, b.g, T, b.log, 0, st & 1, b.kc_ptrs, b.vc_ptrs, c.n_layers,
                                  c.n_kv_heads, c.head_dim, c.max_cache, b.saved_h, (size_t)m->Mp * c.d_model, slots, b.h_src,
                                  c.d_model, s));

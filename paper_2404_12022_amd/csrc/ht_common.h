@@ -152,9 +152,17 @@ struct WeightSegs {
 // ------------------------------------------------------------------------------------------------
 // launchers (definitions in the .hip files); all enqueue on `s` and return the launch status
 // ------------------------------------------------------------------------------------------------
-// x[m] = emb[tok[m]], or rows_in[m] when tok is NULL, m < rows (0: none); cs[m] = rotary factors of position n + depth[m]
+// Where the tokens of a pass come from: tok[m], or, with `cand`, the tree's rule: the pending root and, for a node of depth e
+// and rank r, cand[e - 1][r].  They are kept in `keep`, if given (`tok` itself is fine).
+struct TokenSource {
+  const int32_t* tok = nullptr;
+  const StepState* st = nullptr;
+  const int32_t *cand = nullptr, *depth = nullptr, *rank = nullptr;
+  int32_t* keep = nullptr;
+};
+// x[m] = emb[token m], or rows_in[m] when that is given, m < rows (0: none); cs[m] = rotary factors of position n + depth[m]
 // (n + m without depths), m < cs_rows
-hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, const float* rows_in, float* x, int rows, int d,
+hipError_t launch_start_pass(int dtype, const void* emb, TokenSource tokens, const float* rows_in, float* x, int rows, int d,
                              float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
                              const int32_t* n_dev = nullptr);
 hipError_t launch_load_rows(const float* src, float* x, int M, int d, hipStream_t s);
@@ -186,11 +194,10 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
 hipError_t launch_silu_mul(const float* gu, void* act, int M, int f, hipStream_t s);
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s);
 // cand[i] = top width[i % period + 1] entries of logit row src_row[i] (row i when src_row is NULL), i < rows;
-// scratch: topk_scratch_bytes(rows) bytes for the per-slice survivors
+// scratch: topk_scratch_bytes(rows) bytes for the per-slice survivors.  With `g`: also g[m] = arg-max of row m of z, m < T (rows of V)
 size_t topk_scratch_bytes(int rows);
 hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void* scratch, int rows, int period,
-                       const int32_t* src_row, int V, hipStream_t s);
-hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev tree, int32_t* tok, int T, hipStream_t s);
+                       const int32_t* src_row, int V, hipStream_t s, const float* z = nullptr, int32_t* g = nullptr, int T = 0);
 // kl[p] = KL(softmax(za[p]) || softmax(zb[p])), p < pairs, rows of V floats (Sec. 3.3 loss term)
 hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, float* kl, hipStream_t s);
 // Tree chosen from the draft distributions: lp[k][kMaxTopK] = log-probabilities of the b best candidates of every
@@ -260,10 +267,10 @@ int gemm_mfma_splits(int M, int N, int K);
 // interleaved block by block (gate block i, up block i, gate block i+1, ..); mode 2: segments (q, k, v), in
 // every q and k head the 16-row block p is followed by its rotary partner block p + head_dim/32
 hipError_t launch_repack(WeightSegs w, int K, int mode, int head_dim, void* dst, hipStream_t s);
-// out[s][m][n], s < nsplit (split-K partial sums, fp32).  Up to 128 rows stream the weights, more run on the token-tiled
-// kernel.
-hipError_t launch_gemm_packed(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s,
-                              RowScale rs = RowScale{});
+// out[s][m][n], s < nsplit (split-K partial sums, fp32); with nsplit 1, rows below first_rows go to `first` if that is given.  Up
+// to 128 rows stream the weights, more run on the token-tiled kernel.
+hipError_t launch_gemm_packed(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs = RowScale{},
+                              float* first = nullptr, int first_rows = 0);
 // w packed with mode 1 from (gate, up): act[m][j] = silu(a.gate_j) * (a.up_j), bf16 [M][N/2]
 hipError_t launch_gemm_packed_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs = RowScale{});
 // w packed with mode 2 from (q, k, v): rotary at the row's position, q rows to `q`, k/v rows appended to the

@@ -86,6 +86,12 @@ __global__ void repack_kernel(WeightSegs w, int K, int KS, int n_rb, int mode, i
 }
 
 // --------------------------------------------------------------------------------------------- epilogues
+struct Epilogue : QkvEpilogue {
+  float* first = nullptr;            // EPI_F32 without a K split: where the rows below first_rows go, in place of the output
+  int32_t first_rows = 0;
+  Epilogue() = default;
+  Epilogue(const QkvEpilogue& q) : QkvEpilogue(q) {}
+};
 // Results of two row blocks, a and b, of the sixteen tokens of a tile, a token to a lane of sixteen: exchanged between the
 // halves of the sixteen lanes so that `first` holds both blocks' results of the first eight tokens (a's in the lower lanes, b's
 // in the upper) and `second` those of the others.  A store then touches half as many lines: what a compute unit needs for
@@ -103,7 +109,7 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // token-tiled kernel, which stores results of two row blocks together.
 template <int MT, int R, int EPI, bool TILED = false>
 __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float4 (&row_ss)[MT], int rb0, int wg1, int M,
-                                            int N, void* __restrict__ outp, const QkvEpilogue& qe, const RowScale& rs,
+                                            int N, void* __restrict__ outp, const Epilogue& qe, const RowScale& rs,
                                             int row0, int split) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int r16 = row0 + (lane & 15);                    // token row of tile mt: mt * 16 + r16, counted over the whole pass
@@ -135,8 +141,9 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
         }
         const int m = row0 + mt * 16 + (lane & 7);
         if (rb < wg1) {
-          if (m < M) __builtin_nontemporal_store(first, (u32x4_t*)(dst + (size_t)m * N + n0));
-          if (m + 8 < M) __builtin_nontemporal_store(second, (u32x4_t*)(dst + (size_t)(m + 8) * N + n0));
+          if (m < M) __builtin_nontemporal_store(first, (u32x4_t*)((m < qe.first_rows ? qe.first : dst) + (size_t)m * N + n0));
+          if (m + 8 < M)
+            __builtin_nontemporal_store(second, (u32x4_t*)((m + 8 < qe.first_rows ? qe.first : dst) + (size_t)(m + 8) * N + n0));
         }
       }
     }
@@ -149,7 +156,7 @@ __device__ __forceinline__ void finish_rows(floatx4_t (&acc)[R][MT], const float
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int m = mt * 16 + r16;
-        if (m < M) *(floatx4_t*)(dst + (size_t)m * N + n0) = acc[r][mt];
+        if (m < M) *(floatx4_t*)((m < qe.first_rows ? qe.first : dst) + (size_t)m * N + n0) = acc[r][mt];
       }
     }
   } else if (EPI == EPI_SILU) {
@@ -281,7 +288,7 @@ template <int MT, int R, int WAVES, int EPI, int KC = kChunkCols, int PD = kRing
 __global__ __launch_bounds__(64 * WAVES) void gemm_packed_kernel(const bf16_t* __restrict__ a,
                                                                  const bf16_t* __restrict__ wp, int M, int N, int K,
                                                                  int KS, void* __restrict__ outp, int nsplit,
-                                                                 QkvEpilogue qe, RowScale rs) {
+                                                                 Epilogue qe, RowScale rs) {
   constexpr int STEPS = KC / 32;                         // MFMA steps per chunk
   // LDS row stride in bytes.  Measured with the bank-conflict counter, a 128-bit operand read of the sixteen rows of
   // a fragment takes 4 cycles with rows padded by 32 bytes, 8 with 16 bytes of padding and 16 with none.
@@ -490,7 +497,7 @@ template <int WF, int R_, int WT, int MT, int ST> struct TileShape {
 template <int WF, int R, int WT, int MT, int ST, int EPI>
 __global__ __launch_bounds__(64 * WF * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(
     const bf16_t* __restrict__ a, const bf16_t* __restrict__ wp, int M, int N, int K, int KS, void* __restrict__ outp,
-    QkvEpilogue qe, RowScale rs, int tile0, int n_tiles, int m_tiles, int nsplit) {
+    Epilogue qe, RowScale rs, int tile0, int n_tiles, int m_tiles, int nsplit) {
   using TS = TileShape<WF, R, WT, MT, ST>;
   constexpr int FB = TS::BLOCKS, NW = TS::NW, NA = TS::NA, STAGE = TS::STAGE, WBYTES = TS::WBYTES;
   extern __shared__ __attribute__((aligned(1024))) unsigned char tile_lds[];
@@ -636,7 +643,7 @@ int wide_split(int M, int N, int K) {
 }
 
 template <int MT>
-hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, int epi, const QkvEpilogue& qe,
+hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, int epi, const Epilogue& qe,
                      const RowScale& rs, hipStream_t s) {
   const int n_rb = w.N / 16;
   const int KS = w.Kp / 32;
@@ -688,7 +695,7 @@ hipError_t launch_mt(const bf16_t* a, const PackedW& w, int M, void* out, int ns
 
 // A pass of up to 128 rows: the instance with the fewest token tiles that hold them.
 hipError_t launch_rows(const bf16_t* ap, const PackedW& w, int rows, void* out, int nsplit, int epi,
-                       const QkvEpilogue& qe, const RowScale& rs, hipStream_t s) {
+                       const Epilogue& qe, const RowScale& rs, hipStream_t s) {
   if (rows <= 16) return launch_mt<1>(ap, w, rows, out, nsplit, epi, qe, rs, s);
   if (rows <= 32) return launch_mt<2>(ap, w, rows, out, nsplit, epi, qe, rs, s);
   if (rows <= 48) return launch_mt<3>(ap, w, rows, out, nsplit, epi, qe, rs, s);
@@ -699,14 +706,14 @@ hipError_t launch_rows(const bf16_t* ap, const PackedW& w, int rows, void* out, 
 }
 
 template <int EPI>
-hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const Epilogue& qe, const RowScale& rs,
                        hipStream_t s);
 
 // A workgroup of the streaming kernel holds at most 128 token rows (accumulators and the activation ring are registers):
 // a pass of more rows goes to the token-tiled kernel.  The K split is the caller's.  At 256 rows of 4096 columns, against
 // two launches of 128 rows: 12288 features 72 -> 39 us, 22016 81 -> 58, 4096 24 -> 18, 32000 105 -> 67; 4096 x 11008
 // 51 -> 34.
-hipError_t launch_any(const void* a, const PackedW& w, int M, void* out, int nsplit, int epi, const QkvEpilogue& qe,
+hipError_t launch_any(const void* a, const PackedW& w, int M, void* out, int nsplit, int epi, const Epilogue& qe,
                       const RowScale& rs, hipStream_t s) {
   if (M <= 128) return launch_rows((const bf16_t*)a, w, M, out, nsplit, epi, qe, rs, s);
   if (epi == EPI_SILU) return launch_wide<EPI_SILU>(a, w, M, out, 1, qe, rs, s);
@@ -750,8 +757,13 @@ hipError_t launch_repack(WeightSegs w, int K, int mode, int head_dim, void* dst,
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_packed(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs) {
-  return launch_any(a, w, M, out, nsplit, EPI_F32, QkvEpilogue{}, rs, s);
+hipError_t launch_gemm_packed(const void* a, PackedW w, int M, float* out, int nsplit, hipStream_t s, RowScale rs, float* first,
+                              int first_rows) {
+  if (first && nsplit != 1) return hipErrorInvalidValue;
+  Epilogue ep;
+  ep.first = first;
+  ep.first_rows = first ? first_rows : 0;
+  return launch_any(a, w, M, out, nsplit, EPI_F32, ep, rs, s);
 }
 
 hipError_t launch_gemm_packed_silu(const void* a, PackedW w, int M, void* act, hipStream_t s, RowScale rs) {
@@ -780,7 +792,7 @@ hipError_t allow_tile_lds() {
 
 // Features [from, to) of the product, `from` a multiple of the tile.
 template <int WF, int R, int WT, int MT, int ST, int EPI>
-hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+hipError_t launch_tile(const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const Epilogue& qe, const RowScale& rs,
                        int from, int to, hipStream_t s) {
   using TS = TileShape<WF, R, WT, MT, ST>;
   const int n_tiles = (to - from + TS::FEATURES - 1) / TS::FEATURES, m_tiles = (M + TS::TOKENS - 1) / TS::TOKENS;
@@ -843,7 +855,7 @@ TileChoice best_tile(int M, int N, int K, int nsplit) {
 
 // `tile`: index into kTileCosts
 template <int EPI>
-hipError_t launch_tile_of(int tile, const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe,
+hipError_t launch_tile_of(int tile, const bf16_t* a, const PackedW& w, int M, void* out, int nsplit, const Epilogue& qe,
                           const RowScale& rs, int from, int to, hipStream_t s) {
   switch (tile) {
     case 0: return launch_tile<4, 4, 2, 8, 2, EPI>(a, w, M, out, nsplit, qe, rs, from, to, s);
@@ -859,7 +871,7 @@ hipError_t launch_tile_of(int tile, const bf16_t* a, const PackedW& w, int M, vo
 }
 
 template <int EPI>
-hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const QkvEpilogue& qe, const RowScale& rs,
+hipError_t launch_wide(const void* a, const PackedW& w, int M, void* out, int nsplit, const Epilogue& qe, const RowScale& rs,
                        hipStream_t s) {
   const bf16_t* ap = (const bf16_t*)a;
   const TileChoice c = best_tile(M, w.N, w.K, nsplit);

@@ -281,17 +281,22 @@ hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int 
 // ------------------------------------------------------------------------------------------------ start of a pass
 // The rows of a pass that are there when it starts, from the embedding table (by token) or from a buffer of fp32 rows, and
 // the rotary factors of all rows it will end with, in one launch: workgroups 0 .. rows * shares - 1 copy, the others work
-// out factors (they do not depend on one another; a launch of its own for each was two latencies in a row).
+// out factors (they do not depend on one another; a launch of its own for each was two latencies in a row).  The tokens of a
+// tree are put together here too (a launch, or a copy of the caller's, in front of this one took some 3 us).
 template <typename T>
-__global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok,
+__global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, TokenSource tokens,
                                                          const float* __restrict__ rows_in, float* __restrict__ x, int rows,
                                                          int shares, int d, float2* __restrict__ cs, const int32_t* __restrict__ depth,
                                                          int n, int cs_rows, int half, double2 step, const int32_t* __restrict__ n_dev) {
   const int wg = blockIdx.x;
   if (wg < rows * shares) {
     const int m = wg / shares, part = wg % shares;          // part: which share of the row's columns
-    if (tok) {
-      const T* row = emb + (size_t)tok[m] * d;
+    if (!rows_in) {
+      const int tok = !tokens.cand ? tokens.tok[m]
+                      : m == 0     ? tokens.st->root
+                                   : tokens.cand[(tokens.depth[m] - 1) * kMaxTopK + tokens.rank[m]];
+      if (tokens.keep && part == 0 && threadIdx.x == 0) tokens.keep[m] = tok;
+      const T* row = emb + (size_t)tok * d;
       for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = Conv<T>::load(row + c);
     } else {
       for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = rows_in[(size_t)m * d + c];
@@ -304,13 +309,13 @@ __global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ e
   const int m = i / half, j = i % half;
   cs[i] = rope_factor(n + (depth ? depth[m] : m), rope_turns(j, step));
 }
-hipError_t launch_start_pass(int dtype, const void* emb, const int32_t* tok, const float* rows_in, float* x, int rows, int d,
+hipError_t launch_start_pass(int dtype, const void* emb, TokenSource tokens, const float* rows_in, float* x, int rows, int d,
                              float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
                              const int32_t* n_dev) {
   const int shares = d >= 2048 ? 4 : 1;         // a few workgroups per row: a row is one dependent round trip per pass
   const int groups = rows * shares + (cs_rows * (hd / 2) + 255) / 256;
   if (!groups) return hipSuccess;
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(256), 0, s, (const T*)emb, tok, rows_in, x,
+  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(256), 0, s, (const T*)emb, tokens, rows_in, x,
                                               rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, rope_step(base, hd / 2), n_dev);)
   return hipGetLastError();
 }
@@ -552,11 +557,10 @@ __device__ inline void block_best_any(float& v, int& i, float* sv, int* si) {
 // 32000: 7.0 -> 5.2 us).
 constexpr int kArgmaxAhead = 8;               // 16-byte pieces per thread
 template <bool AHEAD>
-__global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int V,
-                                                      int vec) {
+__device__ __forceinline__ void argmax_row(const float* __restrict__ z, int32_t* __restrict__ g, int V, int vec, int at) {
   __shared__ float sv[16];
   __shared__ int si[16];
-  const float* row = z + (size_t)blockIdx.x * V;
+  const float* row = z + (size_t)at * V;
   float bv = -INFINITY;
   int bi = 0x7fffffff;
   auto four = [&](const float4& q, int j) {
@@ -584,13 +588,19 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
       if (better(row[j], j, bv, bi)) { bv = row[j]; bi = j; }
   }
   block_best_any(bv, bi, sv, si);
-  if (threadIdx.x == 0) g[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
+  if (threadIdx.x == 0) g[at] = bi == 0x7fffffff ? 0 : bi;
 }
+template <bool AHEAD>
+__global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int V, int vec) {
+  argmax_row<AHEAD>(z, g, V, vec, blockIdx.x);
+}
+// rows on 16 bytes; below three pieces per thread the eight fixed requests cost more than they hide (1000: 3.5 and 4.0 us,
+// 8192: 4.0 and 4.35, 16384: 4.5 both, 32000: 5.6 and 5.0)
+int argmax_vec(const float* z, int V) { return !((uintptr_t)z & 15) && !(V & 3); }
+bool argmax_ahead(int vec, int V) { return vec && V > 12288 && V <= 4096 * kArgmaxAhead; }
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s) {
-  const int vec = !((uintptr_t)z & 15) && !(V & 3);
-  // below three pieces per thread the eight fixed requests cost more than they hide (1000: 3.5 and 4.0 us, 8192: 4.0 and 4.35,
-  // 16384: 4.5 both, 32000: 5.6 and 5.0)
-  if (vec && V > 12288 && V <= 4096 * kArgmaxAhead) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, z, g, V, vec);
+  const int vec = argmax_vec(z, V);
+  if (argmax_ahead(vec, V)) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, z, g, V, vec);
   else hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, z, g, V, vec);
   return hipGetLastError();
 }
@@ -677,16 +687,13 @@ __device__ inline void wave_select(float (&v)[E], int (&id)[E], int b, float* ou
 // WHOLE: one stage over a row of up to 2048 entries (rows that short are over before a second launch has started).
 enum TopkStage { SLICE, FINAL, WHOLE };
 template <int E, int STAGE>
-__global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict__ d, const float* __restrict__ sv_in,
-                                                        const int32_t* __restrict__ si_in, float* __restrict__ sv_out,
-                                                        int32_t* __restrict__ si_out, int32_t* __restrict__ cand,
-                                                        const int32_t* __restrict__ width, int period,
-                                                        const int32_t* __restrict__ src_row, int V) {
-  __shared__ float list_v[5][kMaxTopK];
-  __shared__ int list_i[5][kMaxTopK];
-  const int i = blockIdx.x, slice = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+__device__ __forceinline__ void topk_block(const float* __restrict__ d, const float* __restrict__ sv_in, const int32_t* __restrict__ si_in,
+                                           float* __restrict__ sv_out, int32_t* __restrict__ si_out, int32_t* __restrict__ cand,
+                                           const int32_t* __restrict__ width, int period, const int32_t* __restrict__ src_row, int V,
+                                           int i, int slice, int wave, float (*list_v)[kMaxTopK], int (*list_i)[kMaxTopK]) {
+  const int lane = threadIdx.x & 63;
   const int b = width[i % period + 1];      // row i drafts the tree level i % period + 1
-  if (b <= 0) return;                       // uniform over the block
+  if (b <= 0) return;                       // uniform over the workgroup
   int lo, hi;
   if (STAGE == FINAL) { lo = 0; hi = kTopkSlices * b; }
   else if (STAGE == WHOLE) { lo = 0; hi = V; }
@@ -731,10 +738,42 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
   }
 }
 
+template <int E, int STAGE>
+__global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict__ d, const float* __restrict__ sv_in,
+                                                        const int32_t* __restrict__ si_in, float* __restrict__ sv_out,
+                                                        int32_t* __restrict__ si_out, int32_t* __restrict__ cand,
+                                                        const int32_t* __restrict__ width, int period,
+                                                        const int32_t* __restrict__ src_row, int V) {
+  __shared__ float list_v[5][kMaxTopK];
+  __shared__ int list_i[5][kMaxTopK];
+  topk_block<E, STAGE>(d, sv_in, si_in, sv_out, si_out, cand, width, period, src_row, V, blockIdx.x, blockIdx.y, threadIdx.x >> 6,
+                       list_v, list_i);
+}
+
+// The arg-max of T rows and the first stage of the selection over others in one launch (both read what one product has
+// written): workgroups 0 .. T - 1 a row each, the others four slices of a row.  Together with the launch that starts a pass
+// putting its tokens together and the head storing the caller's rows itself, a step of 64 nodes on four 7B-wide blocks 549 -> 538
+// us with 12 draft rows, 710 -> 703 with 192, 903 -> 892 on two of 70B width.
+template <bool AHEAD, int E>
+__global__ __launch_bounds__(1024) void argmax_topk_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int vec, int T,
+                                                           const float* __restrict__ d, float* __restrict__ sv_out,
+                                                           int32_t* __restrict__ si_out, const int32_t* __restrict__ width, int period,
+                                                           const int32_t* __restrict__ src_row, int V) {
+  if ((int)blockIdx.x < T) {
+    argmax_row<AHEAD>(z, g, V, vec, blockIdx.x);
+    return;
+  }
+  __shared__ float list_v[4][5][kMaxTopK];
+  __shared__ int list_i[4][5][kMaxTopK];
+  const int at = (blockIdx.x - T) * 4, quad = threadIdx.x >> 8;
+  topk_block<E, SLICE>(d, nullptr, nullptr, sv_out, si_out, nullptr, width, period, src_row, V, at / kTopkSlices,
+                       at % kTopkSlices + quad, (threadIdx.x >> 6) & 3, list_v[quad], list_i[quad]);
+}
+
 // scratch: float[rows][kTopkSlices][kMaxTopK] followed by int32 of the same shape
 size_t topk_scratch_bytes(int rows) { return (size_t)rows * kTopkSlices * kMaxTopK * 8; }
 hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void* scratch, int rows, int period,
-                       const int32_t* src_row, int V, hipStream_t s) {
+                       const int32_t* src_row, int V, hipStream_t s, const float* z, int32_t* g, int T) {
   float* sv = (float*)scratch;
   int32_t* si = (int32_t*)(sv + (size_t)rows * kTopkSlices * kMaxTopK);
   // entries per lane of the first stage: a quarter of a slice over 64 lanes; of the second: a quarter of
@@ -742,11 +781,30 @@ hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void
   const int per_lane = (((V + kTopkSlices - 1) / kTopkSlices + 3) / 4 + 63) / 64;
   const dim3 g1(rows, kTopkSlices), g2(rows, 1);
 #define HT_TOPK_ARGS(in_v, in_i, out_v, out_i) d, in_v, in_i, out_v, out_i, cand, width, period, src_row, V
+  if (g && (V <= 2048 || per_lane > 16)) {
+    const hipError_t e = launch_argmax(z, g, T, V, s);
+    if (e != hipSuccess) return e;
+    g = nullptr;
+  }
   if (V <= 2048) {
     hipLaunchKernelGGL((topk_wave_kernel<8, WHOLE>), g2, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, nullptr, nullptr));
     return hipGetLastError();
   }
-  if (per_lane <= 4)
+  static_assert(kTopkSlices % 4 == 0, "the four slices of a workgroup are of one row");
+  if (g) {
+    const int vec = argmax_vec(z, V);
+    const dim3 both(T + rows * (kTopkSlices / 4));
+#define HT_BOTH(AHEAD, E) \
+  hipLaunchKernelGGL((argmax_topk_kernel<AHEAD, E>), both, dim3(1024), 0, s, z, g, vec, T, d, sv, si, width, period, src_row, V)
+    if (argmax_ahead(vec, V)) {
+      if (per_lane <= 4) HT_BOTH(true, 4);
+      else HT_BOTH(true, 16);
+    } else {
+      if (per_lane <= 4) HT_BOTH(false, 4);
+      else HT_BOTH(false, 16);
+    }
+#undef HT_BOTH
+  } else if (per_lane <= 4)
     hipLaunchKernelGGL((topk_wave_kernel<4, SLICE>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
   else if (per_lane <= 16)
     hipLaunchKernelGGL((topk_wave_kernel<16, SLICE>), g1, dim3(256), 0, s, HT_TOPK_ARGS(nullptr, nullptr, sv, si));
@@ -757,19 +815,7 @@ hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------------------------ tree build / accept / compact
-__global__ void tree_build_kernel(const StepState* __restrict__ st, const int32_t* __restrict__ cand, TreeDev tree,
-                                  int32_t* __restrict__ tok, int T) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= T) return;
-  tok[v] = v == 0 ? st->root : cand[(tree.depth[v] - 1) * kMaxTopK + tree.rank[v]];
-}
-hipError_t launch_tree_build(const StepState* st, const int32_t* cand, TreeDev tree, int32_t* tok, int T,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(tree_build_kernel, dim3((T + 63) / 64), dim3(64), 0, s, st, cand, tree, tok, T);
-  return hipGetLastError();
-}
-
+// ------------------------------------------------------------------------------------------------ tree choice / accept / compact
 // ---- tree chosen from the draft distributions
 // lp[i][r] = log-softmax value of candidate r of draft row i:  z - (max + log(sum exp(z - max))) over the whole row.
 // One block of 1024 threads per row, few rows: bound by what one compute unit takes in (50 GB/s) and by the reductions

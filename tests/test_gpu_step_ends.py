@@ -1,0 +1,95 @@
+"""What a step does in front of its first block and behind its last one: the tokens put together in the launch that starts the
+pass, the logits stored where the caller wants them, arg-max and selection in one launch.  Needs a real MI355X.
+
+Whole numbers are compared exactly with the rules applied to the logits that the call returned."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_harness as H
+from ht_inputs import WORKLOADS, make_weights, prune_tree
+from helpers import prompt_of, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+B = H.B
+
+
+def _model(wl, fused, T):
+    tensors = make_weights(wl, wl.seed, H.DEV, torch_dtype(wl))
+    parent, rank = prune_tree(wl.branching, T)
+    m = B.HTModel(B.make_config(wl, max_tree=T + len(fused) * wl.k), tensors, H.DEV)
+    m.ht_set_tree(parent, rank)
+    m.ht_set_fused_nodes(fused)
+    m.ht_prefill(prompt_of(wl))
+    return m, parent, rank
+
+
+def _top(row, b):
+    """The first b ids by (value descending, id ascending)."""
+    return np.lexsort((np.arange(row.size), -row))[:b]
+
+
+# vocabularies of one stage, of one to four, five to sixteen and more entries a lane in the first of two, of up to and more
+# than the rows that are requested whole; passes below and above 128 rows
+@pytest.mark.parametrize("base,vocab,T,every", [("tiny_bf16", 1024, 8, False), ("tiny_bf16", 2064, 8, True), ("tiny_bf16", 12304, 8, False),
+                                                ("tiny_bf16", 32768, 7, True), ("tiny_bf16", 32784, 6, True),
+                                                ("tiny_bf16", 131088, 5, False), ("tiny", 4096, 8, True), ("tiny_bf16", 4112, 64, True)])
+def test_logits_choices_and_tokens_of_a_step(base, vocab, T, every):
+    wl = WORKLOADS[base].with_(vocab=vocab, branching=(8, 7) if T > 8 else (2, 2, 2)[:2] if T <= 7 else (3, 2), tree_size=T, max_cache=256)
+    fused = list(range(T)) if every else [0, 1]
+    m, parent, rank = _model(wl, fused, T)
+    tokens = torch.arange(3, 3 + T, dtype=torch.int32, device=H.DEV) * 7 % vocab
+    seen = []
+    for offset in (0, 1):                    # floats past a 16-byte address: the caller's rows stored by the head, or copied
+        raw = torch.full((T * vocab + 8,), 5.0, device=H.DEV)
+        z = raw[offset:offset + T * vocab].view(T, vocab)
+        g = torch.full((T,), -1, dtype=torch.int32, device=H.DEV)
+        print(f"step of {T} nodes, {len(fused)} drafting, vocabulary {vocab}, offset {offset}", flush=True)
+        m.ht_tree_verify_step(tokens, g, z)
+        torch.cuda.synchronize()
+        zz = z.cpu().numpy()
+        assert np.isfinite(zz).all() and bool((raw[offset + T * vocab:] == 5.0).all()) and bool((raw[:offset] == 5.0).all())
+        assert np.array_equal(g.cpu().numpy(), zz.argmax(1))
+        assert torch.equal(m.ht_get_buffer(B.HT_BUF_TREE_TOKENS)[:T], tokens)
+        drafts = m.ht_get_buffer(B.HT_BUF_FUSED_DRAFT_LOGITS).cpu().numpy()
+        cand = m.ht_get_buffer(B.HT_BUF_FUSED_CANDIDATES).cpu().numpy()
+        depth = [0] * T
+        for v in range(1, T):
+            depth[v] = depth[parent[v]] + 1
+        for f in range(len(fused)):
+            for i in range(wl.k):
+                width = max([rank[v] + 1 for v in range(T) if depth[v] == i + 1], default=0)
+                assert np.array_equal(cand[f, i, :width], _top(drafts[f * wl.k + i], width)), (f, i)
+        seen.append((zz, drafts[:len(fused) * wl.k].copy()))
+        root = int(m.ht_get_buffer(B.HT_BUF_ROOT)[0])
+        count, emitted, nxt, path = m.ht_accept_and_compact()
+        assert count == 1 + sum(1 for _ in path[1:]) and emitted[0] == int(tokens[0]) and nxt == int(zz.argmax(1)[path[-1]]), root
+        m.ht_prefill(prompt_of(wl))          # the same step again
+    assert np.array_equal(seen[0][0], seen[1][0]) and np.array_equal(seen[0][1], seen[1][1])
+
+
+@pytest.mark.parametrize("base", ["tiny", "tiny_bf16"])
+@pytest.mark.parametrize("fused", [[], [0]])
+def test_tokens_of_the_tree_follow_its_rule(base, fused):
+    """Tokens from the draft pass's candidates and from those of the pass before: the root, and cand[depth - 1][rank]."""
+    wl = WORKLOADS[base]
+    T = wl.tree_size
+    m, parent, rank = _model(wl, fused, T)
+    depth = [0] * T
+    for v in range(1, T):
+        depth[v] = depth[parent[v]] + 1
+    in_pass = None
+    for step in range(4):
+        print(f"tokens of step {step} of {base}, drafting in the pass: {fused}", flush=True)
+        root = int(m.ht_get_buffer(B.HT_BUF_ROOT)[0])
+        if in_pass is None:
+            m.ht_transfer()
+        m.ht_tree_verify_step()
+        torch.cuda.synchronize()
+        cand = in_pass if in_pass is not None else m.ht_get_buffer(B.HT_BUF_CANDIDATES).cpu().numpy()
+        want = [root] + [int(cand[depth[v] - 1][rank[v]]) for v in range(1, T)]
+        assert m.ht_get_buffer(B.HT_BUF_TREE_TOKENS)[:T].cpu().tolist() == want
+        drafted = m.ht_get_buffer(B.HT_BUF_FUSED_CANDIDATES).cpu().numpy().copy() if fused else None
+        path = m.ht_accept_and_compact()[3]
+        in_pass = drafted[fused.index(path[-1])] if fused and path[-1] in fused else None
