@@ -677,6 +677,13 @@ __global__ __launch_bounds__(64 * NW) void attn_tile_kernel(const bf16_t* __rest
 // pieces, so every lane picks the global piece that belongs at its place.  Same arithmetic in the same order as
 // attn_tile_kernel: the two give the same bits.
 //
+// Bound: the chain of one tile in a wavefront that has a SIMD nearly to itself, 1450 cycles at 128-wide heads (products with K 290,
+// softmax 460, products with V^T 290, 350 for either operand's way from LDS), and beside it the issue of the tile's 32 loads.
+// Tried on top of that and not kept, 128 rows of 32 heads over 4096 keys (27.5 us with the merge): two load wavefronts, four stages
+// and the next operands requested ahead of the softmax (1310 cycles a tile; 27.3, the call on the caller's rows 24.4 -> 26.1);
+// eight arithmetic wavefronts, 32 columns to a wavefront with half of the keys each, loads issued by all of them (32.7: two
+// wavefronts on a SIMD take twice as long as one).
+//
 // FRESH (the attention call on up to 128 rows as the caller has them): rotary, append and attention in one launch instead of
 // two or three, whatever the number of keys.  What bounds it is latency: a workgroup needs its depths, then the factors, then
 // its first rotated tile, one after the other.  So the first tiles of the cache are requested before anything else and arrive
@@ -739,27 +746,56 @@ __device__ __forceinline__ void ring_attention(const bf16_t* q, const bf16_t* kc
     const bf16_t* kbase = kc + (size_t)hk * HD;
     const bf16_t* vbase = vc + (size_t)hk * HD * cap;
     const unsigned krow_stride = (unsigned)(Hkv * HD);
+    // What a lane adds to the base of a load: the rows of a load are whole (64 / PK of K, eight of V^T), so the swizzle leaves
+    // four and two forms of it, and an interior tile's load is a scalar addition and the load: 35 cycles each.  With the addresses
+    // worked out for every load, 48, the loads were what a tile took, 1760 cycles (84 rows of 64 heads on 8 over 4096 keys 34.9 ->
+    // 32.3 us, 64 rows 23.4 -> 21.7, 128 of 32 heads 28.3 -> 27.5).
+    uint32_t klane[4], vlane[2];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const int kl = f * 8 % TK + lane / PK;                // a load of rows 8 f + (0 or 64 / PK) + lane / PK
+      const int sw = (f << 2 | (kl & 3)) & (PK - 1);
+      klane[f] = ((unsigned)(lane / PK) * krow_stride + ((lane % PK) ^ sw) * 8) * 2;
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f) vlane[f] = ((unsigned)(lane / 8) * cap + ((lane % 8) ^ ((f * 4 + (lane >> 4)) & 7)) * 8) * 2;
+    auto load = [&](const char* base, uint32_t off, unsigned char* to) __attribute__((always_inline)) {
+      __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(base + off),
+                                       (void __attribute__((address_space(3)))*)to, 16, 0, 0);
+    };
     auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
       t = t < te - 1 ? t : te - 1;                          // past the slice: a redundant in-bounds reload, never read
       const int j0 = t * TK;
       unsigned char* base = ring + stage * STAGE;
+      if (j0 + TK <= cap) {
+        const char* kt = (const char*)(kbase + (size_t)j0 * krow_stride);
+        const char* vt = (const char*)(vbase + j0);
+#pragma unroll
+        for (int li = 0; li < NLK; ++li) {
+          load(kt, klane[(li * (64 / PK) >> 3) & 3], base + li * 1024);
+          kt += (size_t)(64 / PK) * krow_stride * 2;
+        }
+#pragma unroll
+        for (int li = 0; li < NL - NLK; ++li) {
+          load(vt, vlane[li & 1], base + KBYTES + li * 1024);
+          vt += (size_t)8 * cap * 2;
+        }
+        return;
+      }
 #pragma unroll
       for (int li = 0; li < NLK; ++li) {
         const int piece = li * 64 + lane, kl = piece / PK, pos = piece % PK;
         const int sw = ((((kl >> 3) & 3) << 2) | (kl & 3)) & (PK - 1);
         int key = j0 + kl;
         key = key < cap ? key : cap - 1;
-        __builtin_amdgcn_global_load_lds(
-            (const void __attribute__((address_space(1)))*)(kbase + (unsigned)key * krow_stride + (pos ^ sw) * 8),
-            (void __attribute__((address_space(3)))*)(base + li * 1024), 16, 0, 0);
+        load((const char*)(kbase + (unsigned)key * krow_stride + (pos ^ sw) * 8), 0, base + li * 1024);
       }
 #pragma unroll
       for (int li = 0; li < NL - NLK; ++li) {
         const int piece = li * 64 + lane, e = piece / (TK / 8), pos = piece % (TK / 8);
         int kv = j0 + (pos ^ ((e >> 1) & 7)) * 8;
         kv = kv + 8 <= cap ? kv : cap - 8;
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(vbase + (size_t)e * cap + kv),
-                                         (void __attribute__((address_space(3)))*)(base + KBYTES + li * 1024), 16, 0, 0);
+        load((const char*)(vbase + (size_t)e * cap + kv), 0, base + KBYTES + li * 1024);
       }
     };
     // V columns of keys past the last tree row hold whatever the cache holds there: zeroed in LDS once the tile has
