@@ -1098,31 +1098,56 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_fresh_kernel(const b
 }
 
 // out[m][h] = sum_s exp2(m_s - m*) O_s / sum_s exp2(m_s - m*) l_s, splits added in index order.
-// HD / 4 lanes per (row, head) pair, four output elements per lane; 256-thread blocks.
-template <int HD>
+// HD / 4 lanes per (row, head) pair, four output elements per lane; 256-thread blocks.  Bound by latency: what all slices left is
+// requested before any of it is used, so their number is the kernel's own up to eight (NS; 16: up to that many, the last one's
+// over again).  With a loop over them each slice cost a round trip, twice.  Attention and merge, us, before / now: one row of 64 heads
+// on 8 over 4096 keys (16 slices) 17.2 / 12.5, 64 rows of 32 over 512 (5) 12.5 / 10.7, 128 of 16 on 4 of 64 over 3000 16.4 / 12.7.
+template <int HD, int NS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplit, int M, int Hq, bf16_t* __restrict__ out) {
   constexpr int LANES = HD / 4, PAIRS = 256 / LANES;               // grid = (row groups of PAIRS rows, heads)
   const int h = blockIdx.y, m = blockIdx.x * PAIRS + threadIdx.x / LANES;
   const int e = (threadIdx.x % LANES) * 4;
   if (m >= M) return;
-  float ms[kMaxSplits], mall = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) {
-    ms[s] = part_ml[(((size_t)h * nsplit + s) * M + m) * 2];
-    mall = fmaxf(mall, ms[s]);
+  const int slices = NS <= 8 ? NS : nsplit;
+  float2 ml[NS];
+  float4 v[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int at = s < slices ? s : slices - 1;
+    ml[s] = *(const float2*)(part_ml + (((size_t)h * slices + at) * M + m) * 2);
   }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int at = s < slices ? s : slices - 1;
+    v[s] = *(const float4*)(part_o + (((size_t)h * slices + at) * M + m) * HD + e);
+  }
+  float mall = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) mall = fmaxf(mall, ml[s].x);
   const float msafe = mall == -INFINITY ? 0.f : mall;
   float l = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < nsplit; ++s) {
-    const size_t idx = ((size_t)h * nsplit + s) * M + m;
-    const float f = __builtin_amdgcn_exp2f(ms[s] - msafe);          // exp2(-inf) = 0 for empty slices
-    l += f * part_ml[idx * 2 + 1];
-    const float4 v = *(const float4*)(part_o + idx * HD + e);
-    o.x += f * v.x; o.y += f * v.y; o.z += f * v.z; o.w += f * v.w;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (s >= slices) continue;
+    const float f = __builtin_amdgcn_exp2f(ml[s].x - msafe);        // exp2(-inf) = 0 for empty slices
+    l += f * ml[s].y;
+    o.x += f * v[s].x; o.y += f * v[s].y; o.z += f * v[s].z; o.w += f * v[s].w;
   }
   const float inv = __builtin_amdgcn_rcpf(l);
   *(uint2*)(out + (size_t)m * Hq * HD + (size_t)h * HD + e) = pack4_bf16(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+}
+template <int HD>
+void launch_merge(const float* part_o, const float* part_ml, int nsplit, int M, int Hq, bf16_t* out, hipStream_t s) {
+  constexpr int PAIRS = 256 / (HD / 4);
+  const dim3 grid((M + PAIRS - 1) / PAIRS, Hq);
+#define HT_MERGE(NS) \
+  case NS: hipLaunchKernelGGL((attn_merge_kernel<HD, NS>), grid, dim3(256), 0, s, part_o, part_ml, nsplit, M, Hq, out); return;
+  switch (nsplit <= 8 ? nsplit : kMaxSplits) {
+    HT_MERGE(2) HT_MERGE(3) HT_MERGE(4) HT_MERGE(5) HT_MERGE(6) HT_MERGE(7) HT_MERGE(8) HT_MERGE(kMaxSplits)
+  }
+#undef HT_MERGE
 }
 
 // One more slice for attn_merge_kernel: every row's own key and value, taken from buffers of their own (`ks`
@@ -1254,9 +1279,7 @@ hipError_t launch_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int ca
     hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, HT_ATTN_ARGS, 0);
   }
 #undef HT_ATTN_ARGS
-  if (p.nsplit > 1)
-    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((M + 256 / (HD / 4) - 1) / (256 / (HD / 4)), Hq), dim3(256), 0, s,
-                       part_o, part_ml, p.nsplit, M, Hq, out);
+  if (p.nsplit > 1) launch_merge<HD>(part_o, part_ml, p.nsplit, M, Hq, out, s);
   return hipSuccess;
 }
 
@@ -1298,8 +1321,7 @@ hipError_t launch_causal_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc,
                      part_ml, 2, scale_log2, nullptr, kCausalChunk);
   hipLaunchKernelGGL((attn_self_slice_kernel<HD>), dim3(rows, (Hq + 3) / 4), dim3(256), 0, s, q, self_k, self_v, self_cap, rows,
                      Hq, Hkv, scale_log2, part_o, part_ml, 2, 1);
-  hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((rows + 256 / (HD / 4) - 1) / (256 / (HD / 4)), Hq), dim3(256), 0, s, part_o,
-                     part_ml, 2, rows, Hq, out);
+  launch_merge<HD>(part_o, part_ml, 2, rows, Hq, out, s);
   return hipGetLastError();
 }
 }  // namespace
