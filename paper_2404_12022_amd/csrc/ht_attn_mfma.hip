@@ -1150,30 +1150,52 @@ void launch_merge(const float* part_o, const float* part_ml, int nsplit, int M, 
 #undef HT_MERGE
 }
 
-// One more slice for attn_merge_kernel: every row's own key and value, taken from buffers of their own (`ks`
-// [M][Hkv][HD], `vs` [Hkv][HD][cap], as the rotary/append kernel writes them): m = q.k in scaled log2 units, l = 1,
-// O = v.  One wavefront per (row, head), four heads per workgroup.
+// The merge of a slice, `part_o` and `part_ml` as attn_tile_kernel leaves slice 0 of 2, with every row's own key and value, taken
+// from buffers of their own (`ks` [M][Hkv][HD], `vs` [Hkv][HD][cap], on 16 bytes, cap a multiple of 8): m = q.k in scaled log2
+// units, l = 1, O = v.  A workgroup takes 32 rows of a head; their values, contiguous by row, come in 16 bytes at a time and change
+// direction in LDS.  (A slice of its own for them, written by one wavefront per row that read 2 bytes of a line at a time, and
+// the general merge behind it: 2047 rows of 32 heads of 128 49 + 18 us, now 21.)
 template <int HD>
-__global__ __launch_bounds__(256) void attn_self_slice_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ ks,
+__global__ __launch_bounds__(256) void attn_self_merge_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ ks,
                                                               const bf16_t* __restrict__ vs, int cap, int M, int Hq, int Hkv,
-                                                              float scale_log2, float* __restrict__ part_o,
-                                                              float* __restrict__ part_ml, int nsplit, int split) {
-  constexpr int PER = HD / 64;
-  const int m = blockIdx.x, h = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (h >= Hq) return;
-  const int hk = h / (Hq / Hkv), e = lane * PER;
-  float dot = 0.f;
+                                                              float scale_log2, const float* __restrict__ part_o,
+                                                              const float* __restrict__ part_ml, bf16_t* __restrict__ out) {
+  constexpr int ROWS = 32, LANES = HD / 4, PAIRS = 256 / LANES, LDV = ROWS + 2;
+  __shared__ bf16_t values[HD * LDV];
+  const int h = blockIdx.y, hk = h / (Hq / Hkv), base = blockIdx.x * ROWS, tid = threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < PER; ++i)
-    dot += bf16_to_float(q[((size_t)m * Hq + h) * HD + e + i]) * bf16_to_float(ks[((size_t)m * Hkv + hk) * HD + e + i]);
+  for (int i = 0; i < HD * (ROWS / 8) / 256; ++i) {
+    const int piece = i * 256 + tid, e = piece / (ROWS / 8), r = piece % (ROWS / 8) * 8;
+    Frag v;
+    v.nat = u32x4_t{0, 0, 0, 0};
+    if (base + r < M) v.nat = *(const u32x4_t*)(vs + ((size_t)hk * HD + e) * cap + base + r);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-  const size_t idx = ((size_t)h * nsplit + split) * M + m;
+    for (int x = 0; x < 4; ++x) *(uint32_t*)(values + e * LDV + r + 2 * x) = v.u[x];
+  }
+  __syncthreads();
+  const int e = (tid % LANES) * 4;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) part_o[idx * HD + e + i] = bf16_to_float(vs[((size_t)hk * HD + e + i) * cap + m]);
-  if (lane == 0) {
-    part_ml[idx * 2] = dot * scale_log2;
-    part_ml[idx * 2 + 1] = 1.0f;
+  for (int i = 0; i < ROWS / PAIRS; ++i) {
+    const int r = i * PAIRS + tid / LANES, m = base + r;
+    const bool in = m < M;
+    const int mc = in ? m : M - 1;
+    const size_t idx = ((size_t)h * 2) * M + mc;
+    const uint2 q4 = *(const uint2*)(q + ((size_t)mc * Hq + h) * HD + e), k4 = *(const uint2*)(ks + ((size_t)mc * Hkv + hk) * HD + e);
+    const float4 o = *(const float4*)(part_o + idx * HD + e);
+    const float2 ml = *(const float2*)(part_ml + idx * 2);
+    float dot = __uint_as_float(q4.x << 16) * __uint_as_float(k4.x << 16) +
+                __uint_as_float(q4.x & 0xffff0000u) * __uint_as_float(k4.x & 0xffff0000u) +
+                __uint_as_float(q4.y << 16) * __uint_as_float(k4.y << 16) +
+                __uint_as_float(q4.y & 0xffff0000u) * __uint_as_float(k4.y & 0xffff0000u);
+#pragma unroll
+    for (int off = LANES / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
+    const float own = dot * scale_log2, top = fmaxf(ml.x, own);
+    const float f0 = __builtin_amdgcn_exp2f(ml.x - top), f1 = __builtin_amdgcn_exp2f(own - top);      // exp2(-inf) = 0: no key before
+    const float inv = __builtin_amdgcn_rcpf(f0 * ml.y + f1);
+    float t[4] = {f0 * o.x, f0 * o.y, f0 * o.z, f0 * o.w};
+#pragma unroll
+    for (int x = 0; x < 4; ++x) t[x] = (t[x] + f1 * bf16_to_float(values[(e + x) * LDV + r])) * inv;
+    if (in) *(uint2*)(out + (size_t)m * Hq * HD + (size_t)h * HD + e) = pack4_bf16(t[0], t[1], t[2], t[3]);
   }
 }
 
@@ -1319,9 +1341,8 @@ hipError_t launch_causal_hd(const bf16_t* q, const bf16_t* kc, const bf16_t* vc,
   float* part_ml = part_o + (size_t)Hq * 2 * rows * HD;
   hipLaunchKernelGGL((attn_tile_kernel<HD, 1, 4>), grid, dim3(256), 0, s, q, kc, vc, cap, n, rows, anc, Hq, Hkv, out, part_o,
                      part_ml, 2, scale_log2, nullptr, kCausalChunk);
-  hipLaunchKernelGGL((attn_self_slice_kernel<HD>), dim3(rows, (Hq + 3) / 4), dim3(256), 0, s, q, self_k, self_v, self_cap, rows,
-                     Hq, Hkv, scale_log2, part_o, part_ml, 2, 1);
-  launch_merge<HD>(part_o, part_ml, 2, rows, Hq, out, s);
+  hipLaunchKernelGGL((attn_self_merge_kernel<HD>), dim3((rows + 31) / 32, Hq), dim3(256), 0, s, q, self_k, self_v, self_cap, rows, Hq,
+                     Hkv, scale_log2, part_o, part_ml, out);
   return hipGetLastError();
 }
 }  // namespace
@@ -1334,7 +1355,8 @@ hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int
                               int hd, void* out, hipStream_t s, const void* self_k, const void* self_v, int self_cap,
                               void* scratch) {
   if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || n < 0 || rows < 1 || n + rows > cap) return hipErrorInvalidValue;
-  if ((self_k != nullptr) != (self_v != nullptr) || (self_k && (!scratch || self_cap < rows))) return hipErrorInvalidValue;
+  if ((self_k != nullptr) != (self_v != nullptr) || (self_k && (!scratch || self_cap < rows || self_cap % 8))) return hipErrorInvalidValue;
+  if (((uintptr_t)self_v & 15) || ((uintptr_t)self_k & 7)) return hipErrorInvalidValue;
   const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;
   if (hd == 128)
     return launch_causal_hd<128>(qp, kp, vp, cap, n, rows, tree.anc, Hq, Hkv, (bf16_t*)out, (const bf16_t*)self_k,
