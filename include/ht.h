@@ -210,7 +210,8 @@ int ht_tree_verify_step(ht_model *m, const int32_t *tree_tokens, int32_t *argmax
  * first child (lowest node index) whose token equals the greedy token after the current node.  The m >= 1
  * nodes on that path are accepted: their K/V rows move to cache slots n..n+m-1, n += m, the pending root
  * becomes the greedy token after the last accepted node and its layer-t residual becomes the transfer
- * source.  All outputs are HOST pointers (may be NULL) filled before return: this call waits for `stream`.
+ * source.  All outputs are HOST pointers (may be NULL) filled before return: this call returns when everything
+ * enqueued on `stream` before it is done (it looks for the step's state in pinned memory, not at the stream).
  * accepted_tokens, path_out: [k+1]. HT_ESTATE unless it follows a verify step. */
 int ht_accept_and_compact(ht_model *m, int32_t *n_accepted, int32_t *accepted_tokens, int32_t *next_root,
                           int32_t *path_out, void *stream);
