@@ -371,6 +371,14 @@ PassStart tokens_at(const int32_t* tok, int32_t* keep = nullptr) {
   p.tokens.keep = keep;
   return p;
 }
+FirstNorm first_norm_of(const ht_model* m, bool parts, int layer_from, int layer_end, void* u, float* ss) {
+  FirstNorm f;
+  if (!parts || !m->packed || layer_from >= (layer_end >= 0 ? layer_end : m->cfg.n_layers)) return f;   // no block to norm for
+  const void* gain = m->attn_norm[layer_from];
+  if (!(((uintptr_t)m->tok_emb | (uintptr_t)gain) & 7))
+    f = FirstNorm{(const bf16_t*)gain, (bf16_t*)u, ss};
+  return f;
+}
 PassStart rows_at(const float* rows) {
   PassStart p;
   p.rows = rows;
@@ -390,15 +398,18 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
   const bool joins_first = join == kFromBuffer && M == 0 && m->slot_of_layer[layer_from] >= 0;
   if (joins_first) from = rows_at(b.pseudo + (size_t)m->slot_first[m->slot_of_layer[layer_from]] * d);
   const int first_rows = M;
-  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, from.tokens, from.rows, b.x,
-                           joins_first ? m->slot_count[m->slot_of_layer[layer_from]] : M, d, b.cs, tree.depth, n, M + joining,
-                           c.head_dim, c.rope_base, s, m->n_dev));
-  int pending = 0;
   // Residual add + RMSNorm.  On packed weights the row is split over kNormParts workgroups (one workgroup per row
   // takes in its 80 KB at the pace of a single compute unit) and the 1/rms factor moves into the epilogue of the
   // product that reads u; everywhere else one workgroup normalises the whole row.
   const bool parts = m->packed && d % (4 * kNormParts) == 0;
   const RowScale rs = parts ? RowScale{b.ss, 1.0f / (float)d, c.rms_eps} : RowScale{};
+  // the rows the pass starts with are normalised by the launch that brings them in
+  const FirstNorm first_norm = first_norm_of(m, parts, layer_from, layer_end, b.u, b.ss);
+  bool normed = first_norm.gain != nullptr;
+  HT_HIP(launch_start_pass(c.dtype, m->tok_emb, from.tokens, from.rows, b.x,
+                           joins_first ? m->slot_count[m->slot_of_layer[layer_from]] : M, d, b.cs, tree.depth, n, M + joining,
+                           c.head_dim, c.rope_base, s, m->n_dev, first_norm));
+  int pending = 0;
   auto add_norm = [&](float* x, int nsplit, size_t stride, const void* gain, void* u, float* save, float* ss, int rows) {
     return parts ? launch_add_norm_parts(x, b.part, nsplit, stride, gain, u, save, ss, rows, d, s)
                  : launch_add_norm(x, b.part, nsplit, stride, gain, u, save, rows, d, c.rms_eps, s);
@@ -417,7 +428,7 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
     const int slot = m->slot_of_layer[l];
     if (M > 0) {
       float* save = (save_hidden && slot >= 0) ? b.saved_h + slot * slot_stride : nullptr;
-      HT_HIP(add_norm(b.x, pending, pstride, m->attn_norm[l], b.u, save, b.ss, M));
+      if (!normed || save) HT_HIP(add_norm(b.x, pending, pstride, m->attn_norm[l], b.u, save, b.ss, M));
     }
     if (join == kTrainStep) {
       if (l == c.transfer_layer[step]) {
@@ -441,11 +452,13 @@ int run_pass(ht_model* m, const TreeDev& tree, PassStart from, int M, int layer_
         extra = cnt;
         if (M > 0) HT_HIP(launch_load_rows(b.pseudo + (size_t)i0 * d, b.x + (size_t)M * d, cnt, d, s));   // else: in b.x already
       }
-      HT_HIP(add_norm(b.x + (size_t)M * d, 0, 0, m->attn_norm[l], (char*)b.u + (size_t)M * d * es, nullptr,
-                      b.ss + (size_t)M * kNormParts, extra));
+      if (!normed || !joins_first)
+        HT_HIP(add_norm(b.x + (size_t)M * d, 0, 0, m->attn_norm[l], (char*)b.u + (size_t)M * d * es, nullptr,
+                        b.ss + (size_t)M * kNormParts, extra));
       M += extra;
       pstride = (size_t)M * d;
     }
+    normed = false;
     if (M == 0) continue;
     if (m->qkv_fused && !qkv_prefer_split(M, qd + 2 * kvd)) {
       QkvEpilogue qe{b.cs, (bf16_t*)b.q, (bf16_t*)b.kc[l], (bf16_t*)b.vc[l], n, c.n_heads, c.n_kv_heads, c.head_dim,
@@ -517,11 +530,12 @@ int prompt_pass(ht_model* m, int start, int rows, bool last, hipStream_t s) {
     return sp;
   };
   const int o_splits = splits(qd), down_splits = splits(f);
+  const FirstNorm first_norm = first_norm_of(m, d % (4 * kNormParts) == 0, 0, -1, p.u, p.ss);
   HT_HIP(launch_start_pass(c.dtype, m->tok_emb, tokens_at(b.prompt + start).tokens, nullptr, p.x, rows, d, p.cs, nullptr, start, rows, c.head_dim,
-                           c.rope_base, s));
+                           c.rope_base, s, nullptr, first_norm));
   int pending = 0;
   for (int l = 0; l < c.n_layers; ++l) {
-    HT_HIP(launch_add_norm_parts(p.x, p.part, pending, pstride, m->attn_norm[l], p.u, nullptr, p.ss, rows, d, s));
+    if (l || !first_norm.gain) HT_HIP(launch_add_norm_parts(p.x, p.part, pending, pstride, m->attn_norm[l], p.u, nullptr, p.ss, rows, d, s));
     const int slot = m->slot_of_layer[l];
     if (last && slot >= 0) HT_HIP(launch_load_rows(p.x + end, b.saved_h + (size_t)slot * m->Mp * d, 1, d, s));
     if (rows <= 128 && rows <= m->Mp && qkv_prefer_split(rows, n_qkv)) {

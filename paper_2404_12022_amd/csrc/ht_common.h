@@ -160,11 +160,17 @@ struct TokenSource {
   const int32_t *cand = nullptr, *depth = nullptr, *rank = nullptr;
   int32_t* keep = nullptr;
 };
+// The first norm of a pass, as launch_add_norm_parts works it out (bf16, d a multiple of 4 kNormParts)
+struct FirstNorm {
+  const bf16_t* gain = nullptr;
+  bf16_t* u = nullptr;
+  float* ss = nullptr;
+};
 // x[m] = emb[token m], or rows_in[m] when that is given, m < rows (0: none); cs[m] = rotary factors of position n + depth[m]
-// (n + m without depths), m < cs_rows
+// (n + m without depths), m < cs_rows; with norm.gain (emb and gain on 8 bytes) also the norm of the rows
 hipError_t launch_start_pass(int dtype, const void* emb, TokenSource tokens, const float* rows_in, float* x, int rows, int d,
                              float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
-                             const int32_t* n_dev = nullptr);
+                             const int32_t* n_dev = nullptr, FirstNorm norm = FirstNorm{});
 hipError_t launch_load_rows(const float* src, float* x, int M, int d, hipStream_t s);
 // bf16 models that do not pack: x[m] += part[m] (nsplit 0 or 1); optional save; u[m] = rmsnorm(x[m]) * gain
 hipError_t launch_add_norm(float* x, const float* part, int nsplit, size_t part_stride, const void* gain,

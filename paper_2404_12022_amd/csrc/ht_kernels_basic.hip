@@ -282,41 +282,76 @@ hipError_t launch_rope_table(float* cs, const int32_t* depth, int n, int M, int 
 // The rows of a pass that are there when it starts, from the embedding table (by token) or from a buffer of fp32 rows, and
 // the rotary factors of all rows it will end with, in one launch: workgroups 0 .. rows * shares - 1 copy, the others work
 // out factors (they do not depend on one another; a launch of its own for each was two latencies in a row).  The tokens of a
-// tree are put together here too (a launch, or a copy of the caller's, in front of this one took some 3 us).
+// tree are put together here too (a launch, or a copy of the caller's, in front of this one took some 3 us), and with
+// norm.gain the rows are normalised for the first block, kNormParts workgroups to a row as add_norm_parts_kernel does it: the
+// launch behind this one that did it took 2 to 3 us (a step of four 7B-wide blocks 528 -> 526, of 70B-wide ones 887 -> 884).
 template <typename T>
-__global__ __launch_bounds__(256) void start_pass_kernel(const T* __restrict__ emb, TokenSource tokens,
+__global__ __launch_bounds__(1024) void start_pass_kernel(const T* __restrict__ emb, TokenSource tokens,
                                                          const float* __restrict__ rows_in, float* __restrict__ x, int rows,
                                                          int shares, int d, float2* __restrict__ cs, const int32_t* __restrict__ depth,
-                                                         int n, int cs_rows, int half, double2 step, const int32_t* __restrict__ n_dev) {
+                                                         int n, int cs_rows, int half, double2 step, const int32_t* __restrict__ n_dev,
+                                                         FirstNorm norm) {
   const int wg = blockIdx.x;
   if (wg < rows * shares) {
     const int m = wg / shares, part = wg % shares;          // part: which share of the row's columns
+    const T* row = nullptr;
     if (!rows_in) {
       const int tok = !tokens.cand ? tokens.tok[m]
                       : m == 0     ? tokens.st->root
                                    : tokens.cand[(tokens.depth[m] - 1) * kMaxTopK + tokens.rank[m]];
       if (tokens.keep && part == 0 && threadIdx.x == 0) tokens.keep[m] = tok;
-      const T* row = emb + (size_t)tok * d;
-      for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = Conv<T>::load(row + c);
+      row = emb + (size_t)tok * d;
+    }
+    if constexpr (sizeof(T) == 2) {
+      if (norm.gain) {                                        // uniform; shares == kNormParts
+        __shared__ float red[16];
+        const int dq = d / kNormParts;
+        float ss = 0.f;
+        for (int c = part * dq + threadIdx.x * 4; c < (part + 1) * dq; c += blockDim.x * 4) {
+          float4 v;
+          if (row) {
+            const uint2 r = *(const uint2*)(row + c);
+            v = make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16),
+                            __uint_as_float(r.y & 0xffff0000u));
+          } else {
+            v = *(const float4*)(rows_in + (size_t)m * d + c);
+          }
+          *(float4*)(x + (size_t)m * d + c) = v;
+          ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+          const uint2 g4 = *(const uint2*)(norm.gain + c);
+          *(uint2*)(norm.u + (size_t)m * d + c) =
+              pack4_bf16(v.x * __uint_as_float(g4.x << 16), v.y * __uint_as_float(g4.x & 0xffff0000u), v.z * __uint_as_float(g4.y << 16),
+                         v.w * __uint_as_float(g4.y & 0xffff0000u));
+        }
+        ss = block_sum_any(ss, red);
+        if (threadIdx.x == 0) norm.ss[(size_t)m * kNormParts + part] = ss;
+        return;
+      }
+    }
+    if (row) {
+      for (int c = part * blockDim.x + threadIdx.x; c < d; c += shares * blockDim.x) x[(size_t)m * d + c] = Conv<T>::load(row + c);
     } else {
-      for (int c = part * 256 + threadIdx.x; c < d; c += shares * 256) x[(size_t)m * d + c] = rows_in[(size_t)m * d + c];
+      for (int c = part * blockDim.x + threadIdx.x; c < d; c += shares * blockDim.x) x[(size_t)m * d + c] = rows_in[(size_t)m * d + c];
     }
     return;
   }
   n = cache_len(n, n_dev);
-  const int i = (wg - rows * shares) * 256 + threadIdx.x;
+  const int i = (wg - rows * shares) * blockDim.x + threadIdx.x;
   if (i >= cs_rows * half) return;
   const int m = i / half, j = i % half;
   cs[i] = rope_factor(n + (depth ? depth[m] : m), rope_turns(j, step));
 }
 hipError_t launch_start_pass(int dtype, const void* emb, TokenSource tokens, const float* rows_in, float* x, int rows, int d,
                              float* cs, const int32_t* depth, int n, int cs_rows, int hd, float base, hipStream_t s,
-                             const int32_t* n_dev) {
-  const int shares = d >= 2048 ? 4 : 1;         // a few workgroups per row: a row is one dependent round trip per pass
-  const int groups = rows * shares + (cs_rows * (hd / 2) + 255) / 256;
+                             const int32_t* n_dev, FirstNorm norm) {
+  if (norm.gain && (dtype == 0 || d % (4 * kNormParts) || ((uintptr_t)emb & 7) || ((uintptr_t)norm.gain & 7))) return hipErrorInvalidValue;
+  const int shares = norm.gain ? kNormParts : d >= 2048 ? 4 : 1;         // a few workgroups per row: a row is one dependent round trip per pass
+  int nt = 256;
+  while (norm.gain && nt < 1024 && nt * 4 * kNormParts < d) nt *= 2;     // the sum of squares in the order of the norm's own launch
+  const int groups = rows * shares + (cs_rows * (hd / 2) + nt - 1) / nt;
   if (!groups) return hipSuccess;
-  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(256), 0, s, (const T*)emb, tokens, rows_in, x,
-                                              rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, rope_step(base, hd / 2), n_dev);)
+  HT_DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(start_pass_kernel<T>, dim3(groups), dim3(nt), 0, s, (const T*)emb, tokens, rows_in, x,
+                                              rows, shares, d, (float2*)cs, depth, n, cs_rows, hd / 2, rope_step(base, hd / 2), n_dev, norm);)
   return hipGetLastError();
 }
 

@@ -93,3 +93,34 @@ def test_tokens_of_the_tree_follow_its_rule(base, fused):
         drafted = m.ht_get_buffer(B.HT_BUF_FUSED_CANDIDATES).cpu().numpy().copy() if fused else None
         path = m.ht_accept_and_compact()[3]
         in_pass = drafted[fused.index(path[-1])] if fused and path[-1] in fused else None
+
+
+# the sum of squares over a fraction of a workgroup, one and two rounds of 256 threads; pseudo rows that start a pass of their own
+@pytest.mark.parametrize("base,d", [("tiny_bf16", 256), ("tiny_t123_bf16", 320), ("tiny_bf16", 4096), ("tiny_bf16", 8192)])
+def test_first_norm_in_the_launch_that_starts_the_pass(base, d):
+    """A table on 8 bytes has its rows normalised where they are read, one 2 bytes past that by the norm's own launch: same bits."""
+    wl = WORKLOADS[base].with_(d_model=d)
+    got = []
+    for offset in (0, 1):
+        tensors = make_weights(wl, wl.seed, H.DEV, torch_dtype(wl))
+        raw = torch.empty(tensors["tok_emb"].numel() + 8, dtype=torch.bfloat16, device=H.DEV)
+        table = raw[offset:offset + tensors["tok_emb"].numel()].view(tensors["tok_emb"].shape)
+        table.copy_(tensors["tok_emb"])
+        tensors["tok_emb"] = table
+        parent, rank = prune_tree(wl.branching, wl.tree_size)
+        m = B.HTModel(B.make_config(wl), tensors, H.DEV)
+        m.ht_set_tree(parent, rank)
+        m.ht_prefill(prompt_of(wl))
+        print(f"first norm of {base}, d = {d}, table offset {offset}", flush=True)
+        z = torch.empty(wl.tree_size, wl.vocab, device=H.DEV)
+        steps = []
+        for _ in range(2):
+            m.ht_transfer()
+            m.ht_tree_verify_step(None, None, z)
+            torch.cuda.synchronize()
+            steps.append(z.cpu().numpy().copy())
+            steps.append(m.ht_get_buffer(B.HT_BUF_DRAFT_LOGITS).cpu().numpy().copy())
+            m.ht_accept_and_compact()
+        got.append(steps)
+    for a, b in zip(*got):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
