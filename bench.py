@@ -186,7 +186,7 @@ def time_attention_op(dev):
             "us_per_call_with_tree_upload": round(us_upload, 2),
             "algorithmic_bytes": by, "GBps": round(by / (us * 1e-6) / 1e9, 1),
             "frac_of_hbm_peak": round(by / (us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-            "note": "per call: rotary/append kernel + attention kernel + slice merge kernel; the "
+            "note": "per call: attention kernel with rotary and append inside + slice merge kernel; the "
                     "static tree's tables are uploaded once"}
 
 
