@@ -945,11 +945,13 @@ __device__ __forceinline__ void ring_attention(const bf16_t* q, const bf16_t* kc
   };
 
   if constexpr (FRESH) {
-    // Rotary factors by depth, [deepest row + 1][HD / 2], shared by queries and keys (a tree of a hundred rows is a few deep; no
-    // row is deeper than its number, which bounds the table).
+    // Rotary factors by depth, [deepest row + 1][HD / 2], shared by queries and keys (a tree of a hundred rows is a few deep).  No
+    // row of a tree is deeper than its number; the depths are the caller's memory all the same, so they are held to the rows of
+    // the table here, which bounds the loop over it and every access whatever lies there.
     constexpr int half = HD / 2, PAIRS = PK / 2, KI = TK * PAIRS / (64 * NCW), VPW = PK / NCW;
     float2* factors = (float2*)(ring + ST * STAGE);
-    const int dep0 = fr.depth[lane < M ? lane : M - 1], dep1 = fr.depth[lane + 64 < M ? lane + 64 : M - 1];     // (128 rows at most)
+    auto held_depth = [&](int row) { return min(max(fr.depth[row < M ? row : M - 1], 0), M - 1); };
+    const int dep0 = held_depth(lane), dep1 = held_depth(lane + 64);                                            // (128 rows at most)
     auto depth_of = [&](int row) __attribute__((always_inline)) {
       const int a = __shfl(dep0, row & 63, 64), b = __shfl(dep1, row & 63, 64);
       return row < 64 ? a : b;

@@ -195,3 +195,34 @@ def test_one_launch_of_up_to_128_rows_agrees_with_the_general_route_and_with_flo
         over = q.clone()
         again, _, _ = _call(B, over, k, v, kc, vc, cap, n, T, parent, Hq, Hkv, hd, out=over.view(T, Hq * hd))
         assert torch.equal(again, out)
+
+
+@pytest.mark.parametrize("T,hd", [(17, 64), (64, 128), (100, 128)])
+def test_depths_that_are_no_tree_s_stay_inside_the_table_of_factors(T, hd):
+    """parent = NULL takes the depths as they lie in `scratch`.  Rows whose depth was written over are rotated somehow; the others
+    and every value are as with the tree, and the call ends."""
+    B = _B()
+    Hq, Hkv, n = 4, 2, 72
+    cap = (n + T + 7) // 8 * 8
+    g = torch.Generator(device=DEV).manual_seed(T)
+    mk = lambda *s: torch.randn(*s, generator=g, device=DEV).bfloat16()
+    q, k, v, kc, vc = mk(T, Hq, hd), mk(T, Hkv, hd), mk(T, Hkv, hd), mk(cap, Hkv, hd), mk(Hkv, hd, cap)
+    parent = [r - 1 if r < 9 else (r - 1) // 3 for r in range(T)]
+    depth = [0] * T
+    for r in range(1, T):
+        depth[r] = depth[parent[r]] + 1
+    scratch = torch.zeros(B.ht_tree_attention_scratch_bytes(T, Hq, hd), dtype=torch.uint8, device=DEV)
+    out = torch.zeros(T, Hq * hd, dtype=torch.bfloat16, device=DEV)
+    k1, v1, k2, v2 = kc.clone(), vc.clone(), kc.clone(), vc.clone()
+    B.ht_tree_attention(q, k, v, k1, v1, cap, n, T, parent, Hq, Hkv, hd, B.HT_BF16, BASE, out, scratch)
+    table = scratch.view(torch.int32)[B.HT_MAX_ROWS:2 * B.HT_MAX_ROWS]          # behind the parents
+    assert table[:T].tolist() == depth
+    over = {3: 1 << 30, 8: -1, T - 2: 0x7fffffff, T - 1: -(1 << 31)}
+    for r, e in over.items():
+        table[r] = e
+    say(f"depths written over: {T} rows of {hd}")
+    B.ht_tree_attention(q, k, v, k2, v2, cap, n, T, None, Hq, Hkv, hd, B.HT_BF16, BASE, out, scratch)
+    torch.cuda.synchronize()
+    kept = [n + r for r in range(T) if r not in over]
+    assert torch.equal(k1[:n], k2[:n]) and torch.equal(k1[kept], k2[kept]) and torch.equal(v1, v2)
+    assert torch.isfinite(out).all()
