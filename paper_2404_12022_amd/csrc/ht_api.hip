@@ -1278,6 +1278,20 @@ int ht_transfer(ht_model* m, const void* h_src, float* pseudo_out, void* stream)
   return HT_OK;
 }
 
+namespace {
+// Memory of the current device, which a kernel may read and write where it is.  A caller's buffer that is anything else (host
+// memory, another device's) is copied by the runtime, which takes any address.  Asking costs 0.1 us.
+bool on_this_device(const void* p) {
+  hipPointerAttribute_t at;
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();                 // an address the runtime does not know is no error here
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && at.device == dev;
+}
+}  // namespace
+
 int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax_out, float* logits_out, void* stream) {
   if (!m) return fail(HT_EINVAL, "model is NULL");
   if (!m->has_tree) return fail(HT_ESTATE, "no tree: call ht_set_tree first");
@@ -1295,7 +1309,13 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
   int rc;
   PassStart from;
   if (tree_tokens) {
-    from = tokens_at(tree_tokens, b.tok);
+    // read where they are by the launch that starts the pass, if they are whole words of this device's memory
+    if (((uintptr_t)tree_tokens & 3) || !on_this_device(tree_tokens)) {
+      HT_HIP(hipMemcpyAsync(b.tok, tree_tokens, sizeof(int32_t) * T, hipMemcpyDeviceToDevice, s));
+      from = tokens_at(b.tok);
+    } else {
+      from = tokens_at(tree_tokens, b.tok);
+    }
   } else if (m->drafts_of >= 0 && !m->transfer_ready) {
     // the last verify pass carried pseudo rows for the node the acceptance ended on: its candidates are the tree
     from = tree_tokens_of(m, b.cand_fused + (size_t)m->drafts_of * c.k * kMaxTopK);
@@ -1311,8 +1331,8 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
     if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, z, b.g, s))) return rc;
   } else {
     // rows T.. of the logits are the draft distributions of the fused nodes (k rows per node)
-    // the head stores the tree's rows where the caller wants them, if it may (16 bytes at a time)
-    float* const first = m->packed && !((uintptr_t)logits_out & 15) ? logits_out : nullptr;
+    // the head stores the tree's rows where the caller wants them, if it may (16 bytes at a time; the arg-max reads them there)
+    float* const first = m->packed && !((uintptr_t)logits_out & 15) && logits_out && on_this_device(logits_out) ? logits_out : nullptr;
     if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, nullptr, s, kFromTree, fused, 0, -1, first))) return rc;
     HT_HIP(launch_topk(b.logits + (size_t)T * c.vocab, b.cand_fused, b.width, b.topk_scratch, fused * c.k, c.k, b.fused_src,
                        c.vocab, s, first ? first : b.logits, b.g, T));

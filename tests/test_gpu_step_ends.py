@@ -124,3 +124,33 @@ def test_first_norm_in_the_launch_that_starts_the_pass(base, d):
         got.append(steps)
     for a, b in zip(*got):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("base", ["tiny", "tiny_bf16"])
+def test_tokens_and_logits_that_are_not_this_device_s_memory(base):
+    """Tokens in host memory, pageable and pinned, and 2 bytes past a word; logits into host memory: the runtime's copies take
+    them, and a kernel never gets such an address."""
+    wl = WORKLOADS[base]
+    T = wl.tree_size
+    m, _, _ = _model(wl, [0], T)
+    tokens = torch.arange(3, 3 + T, dtype=torch.int32) * 7 % wl.vocab
+    raw = torch.zeros(4 * T + 4, dtype=torch.uint8, device=H.DEV)
+    raw[2:2 + 4 * T] = tokens.to(H.DEV).view(torch.uint8)
+    on_device = tokens.to(H.DEV)
+    z, zh = torch.zeros(T, wl.vocab, device=H.DEV), torch.zeros(T, wl.vocab).pin_memory()
+    g = torch.zeros(T, dtype=torch.int32, device=H.DEV)
+    seen = []
+    for name, t, out in (("device", on_device, z), ("pageable", tokens, z), ("pinned", tokens.pin_memory(), z),
+                         ("off a word", raw.data_ptr() + 2, z), ("logits to the host", on_device, zh)):
+        print(f"{base}: {name}", flush=True)
+        ptr = t if isinstance(t, int) else t.data_ptr()
+        z.zero_()
+        B._check(B.lib.ht_tree_verify_step(m.handle, ptr, g.data_ptr(), out.data_ptr(), B._stream_ptr()))
+        torch.cuda.synchronize()
+        assert torch.equal(m.ht_get_buffer(B.HT_BUF_TREE_TOKENS)[:T], on_device)
+        seen.append((out.cpu().clone(), g.cpu().clone()))
+        assert torch.isfinite(seen[-1][0]).all() and torch.equal(seen[-1][1].long(), seen[-1][0].argmax(1))
+        m.ht_accept_and_compact()
+        m.ht_prefill(prompt_of(wl))
+    for zz, gg in seen[1:]:
+        assert torch.equal(zz, seen[0][0]) and torch.equal(gg, seen[0][1])
