@@ -4,6 +4,7 @@
 #include "../../include/ht.h"
 #include "ht_common.h"
 
+#include <algorithm>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
@@ -257,6 +258,7 @@ struct ht_model {
   std::vector<int> slot_layer, slot_first, slot_count, slot_of_layer;
   std::vector<int32_t> fused;   // tree nodes with pseudo rows in the verify pass (empty: draft after accept only)
   int drafts_of = -1;           // index into `fused` of the node the last acceptance ended on, -1 if none
+  int widest = 0;               // most candidates that a level of the fixed tree takes
   int dyn_b = 0;                // > 0: every drafting step chooses its own tree among the dyn_b best candidates per level
   // pinned host staging
   int32_t* h_stage = nullptr;     // [max(max_cache, two table images)] + the pointer tables
@@ -841,6 +843,7 @@ int ht_set_tree(ht_model* m, int32_t T, const int32_t* parent, const int32_t* ra
   m->depth.assign(depth, depth + T);
   m->parent.assign(parent, parent + T);
   m->rank.assign(rank, rank + T);
+  m->widest = *std::max_element(width, width + kMaxTransfer + 2);
   m->fused.clear();
   m->drafts_of = -1;
   m->dyn_b = 0;
@@ -1335,7 +1338,7 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
     float* const first = m->packed && !((uintptr_t)logits_out & 15) && logits_out && on_this_device(logits_out) ? logits_out : nullptr;
     if ((rc = run_pass(m, b.tree.dev(), from, T, 0, true, b.logits, nullptr, s, kFromTree, fused, 0, -1, first))) return rc;
     HT_HIP(launch_topk(b.logits + (size_t)T * c.vocab, b.cand_fused, b.width, b.topk_scratch, fused * c.k, c.k, b.fused_src,
-                       c.vocab, s, first ? first : b.logits, b.g, T));
+                       c.vocab, s, first ? first : b.logits, b.g, T, m->widest));
     if (logits_out && !first)
       HT_HIP(hipMemcpyAsync(logits_out, b.logits, sizeof(float) * T * c.vocab, hipMemcpyDeviceToDevice, s));
   }

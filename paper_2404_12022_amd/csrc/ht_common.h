@@ -200,10 +200,11 @@ hipError_t launch_rope_append_split(int dtype, const void* q_in, const void* k_i
 hipError_t launch_silu_mul(const float* gu, void* act, int M, int f, hipStream_t s);
 hipError_t launch_argmax(const float* z, int32_t* g, int M, int V, hipStream_t s);
 // cand[i] = top width[i % period + 1] entries of logit row src_row[i] (row i when src_row is NULL), i < rows;
-// scratch: topk_scratch_bytes(rows) bytes for the per-slice survivors.  With `g`: also g[m] = arg-max of row m of z, m < T (rows of V)
+// scratch: topk_scratch_bytes(rows) bytes for the per-slice survivors.  With `g`: also g[m] = arg-max of row m of z, m < T (rows of
+// V); `widest`: the largest width then, which says whether the two share a launch
 size_t topk_scratch_bytes(int rows);
 hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void* scratch, int rows, int period,
-                       const int32_t* src_row, int V, hipStream_t s, const float* z = nullptr, int32_t* g = nullptr, int T = 0);
+                       const int32_t* src_row, int V, hipStream_t s, const float* z = nullptr, int32_t* g = nullptr, int T = 0, int widest = 0);
 // kl[p] = KL(softmax(za[p]) || softmax(zb[p])), p < pairs, rows of V floats (Sec. 3.3 loss term)
 hipError_t launch_kl_rows(const float* za, const float* zb, int pairs, int V, float* kl, hipStream_t s);
 // Tree chosen from the draft distributions: lp[k][kMaxTopK] = log-probabilities of the b best candidates of every

@@ -786,7 +786,8 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
 }
 
 // The arg-max of T rows and the first stage of the selection over others in one launch (both read what one product has
-// written): workgroups 0 .. T - 1 a row each, the others four slices of a row.  Together with the launch that starts a pass
+// written): workgroups 0 .. T - 1 a row each, the others four slices of a row.  Where there is room on the chip (joint_selection
+// says where) that saves a launch and hides one under the other.  Together with the launch that starts a pass
 // putting its tokens together and the head storing the caller's rows itself, a step of 64 nodes on four 7B-wide blocks 549 -> 538
 // us with 12 draft rows, 710 -> 703 with 192, 903 -> 892 on two of 70B width.
 template <bool AHEAD, int E>
@@ -805,10 +806,25 @@ __global__ __launch_bounds__(1024) void argmax_topk_kernel(const float* __restri
                        at % kTopkSlices + quad, (threadIdx.x >> 6) & 3, list_v[quad], list_i[quad]);
 }
 
+// Whether the joint launch is the faster one for draft rows of which the widest level takes b candidates.  Its workgroups hold four
+// slices each, so four selecting wavefronts share a SIMD where workgroups of one slice have one, and up to 32 rows they are one
+// workgroup a compute unit; beyond that a second one waits for sixteen free places at once.  What it saves (a launch, and the
+// arg-max beside the selection) is 2.5 to 4 us, more for long rows; what it costs grows with b, and with the rows beyond 32.  Us, both
+// stages and the arg-max of 64 rows, joint / separate, V = 32000: 12 rows of 4 candidates 11.5 / 15.3, of 10 21.4 / 23.5, of 40 70.8 /
+// 64.4; 64 rows of 4 17.1 / 17.8, of 10 30.4 / 29.4; 192 of 2 22.2 / 22.4, of 4 31.5 / 28.6, of 10 60.0 / 48.7.  V = 4096: 64 of 4 15.5 /
+// 16.1, 96 of 4 18.5 / 18.0.  V = 40000 (slices of sixteen entries a lane): 8 of 8 0.3 more, of 10 1.4 more, 40 of 4 0.8 less, of 8 3.2
+// more.  V = 65536: 24 of 10 29.8 / 33.4, 80 of 6 38.4 / 42.4, 40 of 8 1.6 more.  V = 128000: 12 of 10 34.3 / 46.0, 24 of 16 49.0 /
+// 61.3, 64 of 12 60.8 / 67.8, 128 of 10 79.9 / 84.2, of 40 247 / 239.
+bool joint_selection(int rows, int b, int V) {
+  if (V > 98304) return b <= (rows <= 32 ? 16 : 12);
+  if (V > 49152) return b <= (rows <= 32 ? 10 : 6);
+  if (V > 32768) return b <= (rows <= 32 ? 8 : 4);
+  return rows <= 32 ? b <= 10 : b <= 4 && rows * b <= 256;
+}
 // scratch: float[rows][kTopkSlices][kMaxTopK] followed by int32 of the same shape
 size_t topk_scratch_bytes(int rows) { return (size_t)rows * kTopkSlices * kMaxTopK * 8; }
 hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void* scratch, int rows, int period,
-                       const int32_t* src_row, int V, hipStream_t s, const float* z, int32_t* g, int T) {
+                       const int32_t* src_row, int V, hipStream_t s, const float* z, int32_t* g, int T, int widest) {
   float* sv = (float*)scratch;
   int32_t* si = (int32_t*)(sv + (size_t)rows * kTopkSlices * kMaxTopK);
   // entries per lane of the first stage: a quarter of a slice over 64 lanes; of the second: a quarter of
@@ -816,7 +832,7 @@ hipError_t launch_topk(const float* d, int32_t* cand, const int32_t* width, void
   const int per_lane = (((V + kTopkSlices - 1) / kTopkSlices + 3) / 4 + 63) / 64;
   const dim3 g1(rows, kTopkSlices), g2(rows, 1);
 #define HT_TOPK_ARGS(in_v, in_i, out_v, out_i) d, in_v, in_i, out_v, out_i, cand, width, period, src_row, V
-  if (g && (V <= 2048 || per_lane > 16)) {
+  if (g && (V <= 2048 || per_lane > 16 || !joint_selection(rows, widest, V))) {
     const hipError_t e = launch_argmax(z, g, T, V, s);
     if (e != hipSuccess) return e;
     g = nullptr;

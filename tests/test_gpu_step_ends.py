@@ -31,12 +31,14 @@ def _top(row, b):
 
 
 # vocabularies of one stage, of one to four, five to sixteen and more entries a lane in the first of two, of up to and more
-# than the rows that are requested whole; passes below and above 128 rows
-@pytest.mark.parametrize("base,vocab,T,every", [("tiny_bf16", 1024, 8, False), ("tiny_bf16", 2064, 8, True), ("tiny_bf16", 12304, 8, False),
+# than the rows that are requested whole; passes below and above 128 rows; arg-max and selection in a launch each (64 nodes of up to 8
+# candidates) and, with 40 draft rows of up to 4, in one
+@pytest.mark.parametrize("base,vocab,T,every", [("tiny_bf16", 4112, 20, True), ("tiny_bf16", 40000, 20, True),
+                                                ("tiny_bf16", 1024, 8, False), ("tiny_bf16", 2064, 8, True), ("tiny_bf16", 12304, 8, False),
                                                 ("tiny_bf16", 32768, 7, True), ("tiny_bf16", 32784, 6, True),
                                                 ("tiny_bf16", 131088, 5, False), ("tiny", 4096, 8, True), ("tiny_bf16", 4112, 64, True)])
 def test_logits_choices_and_tokens_of_a_step(base, vocab, T, every):
-    wl = WORKLOADS[base].with_(vocab=vocab, branching=(8, 7) if T > 8 else (2, 2, 2)[:2] if T <= 7 else (3, 2), tree_size=T, max_cache=256)
+    wl = WORKLOADS[base].with_(vocab=vocab, branching=(8, 7) if T > 20 else (4, 4) if T > 8 else (2, 2, 2)[:2] if T <= 7 else (3, 2), tree_size=T, max_cache=256)
     fused = list(range(T)) if every else [0, 1]
     m, parent, rank = _model(wl, fused, T)
     tokens = torch.arange(3, 3 + T, dtype=torch.int32, device=H.DEV) * 7 % vocab
