@@ -1350,22 +1350,31 @@ int ht_tree_verify_step(ht_model* m, const int32_t* tree_tokens, int32_t* argmax
 }
 
 namespace {
-// Until the state of step `step_number` is there.  A wait of the runtime's own takes some 10 us longer to come back (a caller
-// that waits for the device all the same pays 30 us there, 3 after the runtime's wait: loops of steps do not); it follows where
-// a step takes so long (a prompt in front of it, a device shared with others) that it no longer matters, and where an error keeps
-// the state from ever coming.
+inline void spin_hint() {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+  __builtin_ia32_pause();
+#endif
+}
+// Until the state of step `step_number` is there.  The host looks for its number: a wait of the runtime's own takes some 10 us longer
+// to come back (a caller that waits for the device all the same pays 30 us there, 3 after the runtime's wait: loops of steps do not).
+// The runtime's wait is taken by a process that asked its device for one that blocks or yields, which spinning would deny it; where
+// a step takes so long (other work in front of it, a device shared with others) that 10 us no longer matter; and with it the error
+// that keeps the state from ever coming.
 int wait_for_state(ht_model* m, hipStream_t s) {
   const int32_t* number = (const int32_t*)(m->h_state + 1);
-  const auto start = std::chrono::steady_clock::now();
-  for (unsigned spins = 1; __atomic_load_n(number, __ATOMIC_ACQUIRE) != m->step_number; ++spins) {
-    asm volatile("pause");
-    if (spins % 256 == 0 && std::chrono::steady_clock::now() - start > std::chrono::milliseconds(20)) {
-      HT_HIP(hipStreamSynchronize(s));
-      if (__atomic_load_n(number, __ATOMIC_ACQUIRE) != m->step_number) return fail(HT_EHIP, "the step's state did not arrive");
-      break;
+  const auto there = [&] { return __atomic_load_n(number, __ATOMIC_ACQUIRE) == m->step_number; };
+  unsigned flags = 0;
+  HT_HIP(hipGetDeviceFlags(&flags));
+  if (!(flags & (hipDeviceScheduleBlockingSync | hipDeviceScheduleYield))) {
+    const auto start = std::chrono::steady_clock::now();
+    for (unsigned spins = 1; !there(); ++spins) {
+      spin_hint();
+      if (spins % 256 == 0 && std::chrono::steady_clock::now() - start > std::chrono::milliseconds(20)) break;
     }
+    if (there()) return HT_OK;
   }
-  return HT_OK;
+  HT_HIP(hipStreamSynchronize(s));
+  return there() ? HT_OK : fail(HT_EHIP, "the step's state did not arrive");
 }
 }  // namespace
 

@@ -2,6 +2,9 @@
 pass, the logits stored where the caller wants them, arg-max and selection in one launch.  Needs a real MI355X.
 
 Whole numbers are compared exactly with the rules applied to the logits that the call returned."""
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -156,3 +159,79 @@ def test_tokens_and_logits_that_are_not_this_device_s_memory(base):
         m.ht_prefill(prompt_of(wl))
     for zz, gg in seen[1:]:
         assert torch.equal(zz, seen[0][0]) and torch.equal(gg, seen[0][1])
+
+
+def _busy(ms):
+    """Some `ms` of products on the current stream; returns once they are enqueued."""
+    a = torch.randn(4096, 4096, device=H.DEV).bfloat16()
+    c = torch.empty_like(a)
+    torch.mm(a, a, out=c)
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    for _ in range(10):
+        torch.mm(a, a, out=c)
+    torch.cuda.synchronize()
+    for _ in range(int(ms / ((time.perf_counter() - t) * 100)) + 1):
+        torch.mm(a, a, out=c)
+
+
+def _decode(m, steps, stream):
+    out = []
+    for _ in range(steps):
+        m.ht_transfer(stream=stream)
+        m.ht_tree_verify_step(stream=stream)
+        out.append(m.ht_accept_and_compact(stream=stream))
+    return out
+
+
+@pytest.mark.parametrize("ms", [3, 60])
+def test_acceptance_behind_other_work(ms):
+    """A step with milliseconds of products in front of it on its stream: within the time that the host looks for the state, and
+    beyond, where it waits for the stream."""
+    wl = WORKLOADS["tiny_bf16"]
+    m, _, _ = _model(wl, [], wl.tree_size)
+    want = _decode(m, 2, None)
+    m.ht_prefill(prompt_of(wl))
+    for k in range(2):
+        print(f"step {k} behind {ms} ms of products", flush=True)
+        _busy(ms)
+        m.ht_transfer()
+        m.ht_tree_verify_step()
+        start = time.perf_counter()
+        assert m.ht_accept_and_compact() == want[k]
+        if k:
+            assert time.perf_counter() - start > ms * 5e-4
+
+
+def test_two_models_on_two_threads_and_streams():
+    wl = WORKLOADS["tiny_bf16"]
+    models = [_model(wl, [], wl.tree_size)[0] for _ in range(2)]
+    want = _decode(models[0], 12, None)
+    got, streams = [None, None], [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def work(i):
+        for _ in range(4):
+            models[i].ht_prefill(prompt_of(wl), stream=streams[i])
+            got[i] = _decode(models[i], 12, streams[i])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    print("two threads", flush=True)
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got[0] == want and got[1] == want
+
+
+def test_models_freed_right_behind_the_acceptance():
+    wl = WORKLOADS["tiny_bf16"]
+    want = None
+    for k in range(6):
+        print(f"model {k}", flush=True)
+        m, _, _ = _model(wl, [], wl.tree_size)
+        got = _decode(m, 1, None)
+        m.close()
+        want = want or got
+        assert got == want
+    torch.cuda.synchronize()
