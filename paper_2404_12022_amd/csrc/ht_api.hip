@@ -1571,6 +1571,7 @@ int ht_tree_attention(const void* q, const void* k_new, const void* v_new, void*
     std::vector<int32_t> stage(kTableInts);
     fill_tables(T, parent, nullptr, stage.data());
     if ((rc = upload_tables(tt, stage.data(), s))) return rc;
+    if (dtype == HT_BF16) HT_HIP(attn_mfma_prepare(hd));
   }
   const char* env = getenv("HT_FORCE_SIMPLE");
   const bool simple = env && env[0] == '1';
@@ -1582,7 +1583,7 @@ int ht_tree_attention(const void* q, const void* k_new, const void* v_new, void*
     return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
   };
   const size_t q_bytes = (size_t)T * Hq * hd * 2, kv_bytes = (size_t)T * Hkv * hd * 2, cache_bytes = (size_t)cap * Hkv * hd * 2;
-  if (k_new && dtype == HT_BF16 && !simple && attn_fresh_supported(T, Hq, Hkv, hd, n) &&
+  if (k_new && dtype == HT_BF16 && !simple && attn_fresh_supported(T, Hq, Hkv, hd) &&
       !(((uintptr_t)q | (uintptr_t)k_new | (uintptr_t)v_new | (uintptr_t)k_cache | (uintptr_t)v_cache) & 15) &&
       apart(k_new, kv_bytes, k_cache, cache_bytes) && apart(v_new, kv_bytes, k_cache, cache_bytes) && apart(q, q_bytes, k_cache, cache_bytes) &&
       apart(k_new, kv_bytes, v_cache, cache_bytes) && apart(v_new, kv_bytes, v_cache, cache_bytes) &&

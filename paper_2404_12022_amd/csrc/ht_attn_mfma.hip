@@ -1247,7 +1247,7 @@ AttnPlan plan_attention(int M, int Hq, int Hkv, int S) {
 }
 
 // The ring's LDS is more than a kernel may use without asking: asked for once per device (attn_mfma_prepare does it
-// when a model is set up, so that no launch inside a stream capture has to).
+// when a model is set up and when the attention call uploads a tree, so that no launch inside a stream capture has to).
 template <int HD, int NCW, bool FRESH>
 hipError_t allow_ring_lds() {
   static bool allowed[64] = {};
@@ -1314,9 +1314,12 @@ bool attn_mfma_supported(int M, int Hq, int Hkv, int hd) {
 }
 
 hipError_t attn_mfma_prepare(int hd) {
-  if (hd == 128) return allow_ring_lds<128, 4, false>();
-  if (hd == 64) return allow_ring_lds<64, 4, false>();
-  return hipSuccess;
+  hipError_t e = hipSuccess;
+  if (hd == 128) e = allow_ring_lds<128, 4, false>();
+  if (hd == 128 && e == hipSuccess) e = allow_ring_lds<128, 4, true>();
+  if (hd == 64) e = allow_ring_lds<64, 4, false>();
+  if (hd == 64 && e == hipSuccess) e = allow_ring_lds<64, 4, true>();
+  return e;
 }
 
 // A causal sequence of `rows` rows at positions n .. whose K/V are in the cache already (slot = position): row r sees the
@@ -1370,10 +1373,10 @@ hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int
 }
 
 // The rows of a call of up to 128 as the caller has them.
-bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n) { return M <= 128 && attn_mfma_supported(M, Hq, Hkv, hd); }
+bool attn_fresh_supported(int M, int Hq, int Hkv, int hd) { return M <= 128 && attn_mfma_supported(M, Hq, Hkv, hd); }
 hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new, const int32_t* depth, float base, void* kc, void* vc,
                              int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s) {
-  if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || !attn_fresh_supported(M, Hq, Hkv, hd, n)) return hipErrorInvalidValue;
+  if ((size_t)cap * Hkv * hd >= ((size_t)1 << 31) || !attn_fresh_supported(M, Hq, Hkv, hd)) return hipErrorInvalidValue;
   AttnPlan p = plan_attention(M, Hq, Hkv, n + M);
   if (p.tiled || p.ring_waves) {
     const int units = (n + 63) / 64 + 2 * ((M + 63) / 64);                // as the kernel shares them out

@@ -322,7 +322,7 @@ hipError_t launch_attn_mfma(const void* q, const void* kc, const void* vc, int c
                             int Hkv, int hd, void* out, void* scratch, hipStream_t s, const int32_t* n_dev = nullptr);
 // up to 128 rows as the caller has them: rotary at positions n + depth[m], append at slots n + m, attention, in one launch (and
 // the merge of key slices); depth[m] <= m, as in every tree whose parents come before their children
-bool attn_fresh_supported(int M, int Hq, int Hkv, int hd, int n);
+bool attn_fresh_supported(int M, int Hq, int Hkv, int hd);
 hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new, const int32_t* depth, float base, void* kc, void* vc,
                              int cap, int n, int M, TreeDev tree, int Hq, int Hkv, int hd, void* out, void* scratch, hipStream_t s);
 hipError_t launch_attn_causal(const void* q, const void* kc, const void* vc, int cap, int n, int rows, TreeDev tree, int Hq, int Hkv,
