@@ -279,6 +279,19 @@ def test_generic_attention_forms(dtype, T, n, Hq, Hkv, hd):
     _attention_case(dtype, T, n, Hq, Hkv, hd, chain_tree(T)[0], T + hd + 1, poison=True)
 
 
+# rows that lie in the cache already, as every pass of a model has them: the ring kernel over 24 tiles of keys and more, the tile
+# kernel below, with the last tile holding 1, 2, 14, 63 and 64 keys and others; caches that end there and ones with a tile and more of
+# NaN behind (the loads of a tile inside the cache and of one past its end)
+@pytest.mark.parametrize("spare", [0, 80])
+@pytest.mark.parametrize("T,n,Hq,Hkv,hd", [
+    (50, 2000, 4, 2, 128), (5, 1900, 8, 2, 128), (1, 4099, 16, 2, 64), (40, 1777, 6, 1, 64), (64, 1985, 4, 4, 128), (63, 1984, 4, 1, 64),
+    (100, 1948, 3, 3, 128), (128, 4096, 32, 32, 128), (64, 4096, 64, 8, 128), (70, 203, 3, 3, 128), (17, 100, 2, 2, 64)])
+def test_tree_attention_on_rows_in_the_cache(T, n, Hq, Hkv, hd, spare):
+    say(f"attention on rows in the cache T={T} n={n} {Hq}/{Hkv} x {hd}, {spare} slots behind")
+    _attention_case("bf16", T, n, Hq, Hkv, hd, random_tree(T, T, 6)[0], T + n, cap=(n + T + 7) // 8 * 8 + spare, rotate=False,
+                    poison=True)
+
+
 def test_tree_attention_at_the_op_workload_size():
     a = ATTENTION_OP
     say("attention bf16 op workload")
