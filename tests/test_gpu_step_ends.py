@@ -11,6 +11,7 @@ import torch
 
 import gpu_harness as H
 from ht_inputs import WORKLOADS, make_weights, prune_tree
+from oracle import ht_oracle as O
 from helpers import prompt_of, torch_dtype
 
 pytestmark = pytest.mark.gpu
@@ -45,6 +46,15 @@ def test_logits_choices_and_tokens_of_a_step(base, vocab, T, every):
     fused = list(range(T)) if every else [0, 1]
     m, parent, rank = _model(wl, fused, T)
     tokens = torch.arange(3, 3 + T, dtype=torch.int32, device=H.DEV) * 7 % vocab
+    # a path of the tree that greedy decoding takes, down to a leaf, over last children
+    children = [[v for v in range(1, T) if parent[v] == u] for u in range(T)]
+    chosen, g = [0], torch.full((T,), -1, dtype=torch.int32, device=H.DEV)
+    while children[chosen[-1]]:
+        m.ht_tree_verify_step(tokens, g)
+        child = children[chosen[-1]][-1]
+        tokens[child] = g[chosen[-1]]
+        chosen.append(child)
+    m.ht_prefill(prompt_of(wl))
     seen = []
     for offset in (0, 1):                    # floats past a 16-byte address: the caller's rows stored by the head, or copied
         raw = torch.full((T * vocab + 8,), 5.0, device=H.DEV)
@@ -67,9 +77,11 @@ def test_logits_choices_and_tokens_of_a_step(base, vocab, T, every):
                 width = max([rank[v] + 1 for v in range(T) if depth[v] == i + 1], default=0)
                 assert np.array_equal(cand[f, i, :width], _top(drafts[f * wl.k + i], width)), (f, i)
         seen.append((zz, drafts[:len(fused) * wl.k].copy()))
-        root = int(m.ht_get_buffer(B.HT_BUF_ROOT)[0])
         count, emitted, nxt, path = m.ht_accept_and_compact()
-        assert count == 1 + sum(1 for _ in path[1:]) and emitted[0] == int(tokens[0]) and nxt == int(zz.argmax(1)[path[-1]]), root
+        toks, greedy = tokens.tolist(), zz.argmax(1).tolist()
+        want, want_next = O.accept_walk(parent, toks, greedy)
+        assert len(want) >= len(chosen) and want[0] == 0
+        assert (path, count, nxt) == (want, len(want), want_next) and emitted == [toks[v] for v in want]
         m.ht_prefill(prompt_of(wl))          # the same step again
     assert np.array_equal(seen[0][0], seen[1][0]) and np.array_equal(seen[0][1], seen[1][1])
 
@@ -100,8 +112,10 @@ def test_tokens_of_the_tree_follow_its_rule(base, fused):
         in_pass = drafted[fused.index(path[-1])] if fused and path[-1] in fused else None
 
 
-# the sum of squares over a fraction of a workgroup, one and two rounds of 256 threads; pseudo rows that start a pass of their own
-@pytest.mark.parametrize("base,d", [("tiny_bf16", 256), ("tiny_t123_bf16", 320), ("tiny_bf16", 4096), ("tiny_bf16", 8192)])
+# the sum of squares over a fraction of a workgroup, one round of 256, 512 and 1024 threads and, above 16384, a second one; pseudo rows
+# that start a pass of their own
+@pytest.mark.parametrize("base,d", [("tiny_bf16", 256), ("tiny_t123_bf16", 320), ("tiny_bf16", 4096), ("tiny_bf16", 8192),
+                                    ("tiny_bf16", 16384), ("tiny_bf16", 16448)])
 def test_first_norm_in_the_launch_that_starts_the_pass(base, d):
     """A table on 8 bytes has its rows normalised where they are read, one 2 bytes past that by the norm's own launch: same bits."""
     wl = WORKLOADS[base].with_(d_model=d)
