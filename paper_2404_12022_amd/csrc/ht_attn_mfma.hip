@@ -677,12 +677,14 @@ __global__ __launch_bounds__(64 * NW) void attn_tile_kernel(const bf16_t* __rest
 // pieces, so every lane picks the global piece that belongs at its place.  Same arithmetic in the same order as
 // attn_tile_kernel: the two give the same bits.
 //
-// Bound: the chain of one tile in a wavefront that has a SIMD nearly to itself, 1450 cycles at 128-wide heads (products with K 290,
-// softmax 460, products with V^T 290, 350 for either operand's way from LDS), and beside it the issue of the tile's 32 loads.
-// Tried on top of that and not kept, 128 rows of 32 heads over 4096 keys (27.5 us with the merge): two load wavefronts, four stages
-// and the next operands requested ahead of the softmax (1310 cycles a tile; 27.3, the call on the caller's rows 24.4 -> 26.1);
-// eight arithmetic wavefronts, 32 columns to a wavefront with half of the keys each, loads issued by all of them (32.7: two
-// wavefronts on a SIMD take twice as long as one).
+// Bound: the chain of one tile in a wavefront that has a SIMD nearly to itself, 0.67 us or 1600 cycles at 128-wide heads (the slope
+// over the keys, 128 rows of 32 heads in four slices), and beside it the issue of the tile's 32 loads.  Its sections, with stamps
+// between them that keep them apart: K's way from LDS 346, products with K 348, softmax 457, V^T's way and its products 573.
+// What a launch costs whatever the keys is as much again: 11 us with the merge.
+// Tried on top of that and not kept, 128 rows of 32 heads over 4096 keys (27.5 us with the merge of that time, which took 3 more):
+// two load wavefronts, four stages and the next operands requested ahead of the softmax (270 cycles a tile less; 27.3, the call on
+// the caller's rows 24.4 -> 26.1); eight arithmetic wavefronts, 32 columns to a wavefront with half of the keys each, loads issued by
+// all of them (32.7: two wavefronts on a SIMD take twice as long as one).
 //
 // FRESH (the attention call on up to 128 rows as the caller has them): rotary, append and attention in one launch instead of
 // two or three, whatever the number of keys.  What bounds it is latency: a workgroup needs its depths, then the factors, then
@@ -690,9 +692,10 @@ __global__ __launch_bounds__(64 * NW) void attn_tile_kernel(const bf16_t* __rest
 // meanwhile; the factors are worked out once per depth, not per row (a factor is some 75 double precision instructions; by
 // rows, 64 of them, they were 3 us of the start, by depths 0.4); and the pass's own keys are tiles of their own, in front of
 // the cache's (rows of the caller have no other place in LDS that is free this early: the stage the loads use last), shared
-// out over the key slices with the others.  The last workgroup of a head needs all of them and appends them.  Us before / now:
-// 128 rows of 32 heads over 4096 keys 31.1 / 27.9, 64 over 512 16.9 / 14.3, 17 of 4 heads of 64 over 40 8.3 / 7.1, 20 of 40 on 5
-// heads over 6000 33.2 / 24.5, 90 of 40 over 1400 27.9 / 19.2.  129 - 256 rows keep the general route: at 128-wide heads a table
+// out over the key slices with the others.  The last workgroup of a head needs all of them and appends them.  Calls with their
+// merge, us, as two or three launches with the merge and the addresses of that time / now: 128 rows of 32 heads over 4096 keys 30.4 /
+// 24.8, 64 over 512 16.6 / 11.7, 17 of 4 heads of 64 over 40 7.9 / 6.7, 20 of 40 on 5 heads over 6000 32.6 / 18.9, 90 of 40 over
+// 1400 27.3 / 17.0.  129 - 256 rows keep the general route: at 128-wide heads a table
 // for them does not fit beside the ring.
 template <int N> __device__ __forceinline__ void attn_wait_vm_then_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
@@ -728,7 +731,7 @@ __device__ __forceinline__ void ring_attention(const bf16_t* q, const bf16_t* kc
   // ancestors come before it), in the last workgroup of a head all of them
   const int blk1 = blk0 + NCW < blocks ? blk0 + NCW - 1 : blocks - 1;
   const int own = !FRESH ? 0 : (blk1 / row_blocks != blk0 / row_blocks ? row_blocks - 1 : blk1 % row_blocks) * 16 / TK + 1;
-  constexpr int OWN = 2;                                  // an own tile takes 2.0 us to make and multiply, a tile of the cache 0.9
+  constexpr int OWN = 2;                                  // an own tile takes 2.0 us to make and multiply, a tile of the cache 0.7 to 0.9
   int ts, te;
   even_share(OWN * own + tiles, nsplit, split, ts, te);
   const int os = ts < OWN * own ? (ts + OWN - 1) / OWN : own, oe = te < OWN * own ? (te + OWN - 1) / OWN : own;
@@ -748,8 +751,8 @@ __device__ __forceinline__ void ring_attention(const bf16_t* q, const bf16_t* kc
     const unsigned krow_stride = (unsigned)(Hkv * HD);
     // What a lane adds to the base of a load: the rows of a load are whole (64 / PK of K, eight of V^T), so the swizzle leaves
     // four and two forms of it, and an interior tile's load is a scalar addition and the load: 35 cycles each.  With the addresses
-    // worked out for every load, 48, the loads were what a tile took, 1760 cycles (84 rows of 64 heads on 8 over 4096 keys 34.9 ->
-    // 32.3 us, 64 rows 23.4 -> 21.7, 128 of 32 heads 28.3 -> 27.5).
+    // worked out for every load, 48, the loads were what a tile took, 1760 cycles (with the merge of that time: 84 rows of 64 heads on
+    // 8 over 4096 keys 34.9 -> 32.3 us, 64 rows 23.4 -> 21.7, 128 of 32 heads 28.3 -> 27.5).
     uint32_t klane[4], vlane[2];
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
@@ -1102,8 +1105,10 @@ __global__ __launch_bounds__(64 * (NCW + 1)) void attn_ring_fresh_kernel(const b
 // out[m][h] = sum_s exp2(m_s - m*) O_s / sum_s exp2(m_s - m*) l_s, splits added in index order.
 // HD / 4 lanes per (row, head) pair, four output elements per lane; 256-thread blocks.  Bound by latency: what all slices left is
 // requested before any of it is used, so their number is the kernel's own up to eight (NS; 16: up to that many, the last one's
-// over again).  With a loop over them each slice cost a round trip, twice.  Attention and merge, us, before / now: one row of 64 heads
-// on 8 over 4096 keys (16 slices) 17.2 / 12.5, 64 rows of 32 over 512 (5) 12.5 / 10.7, 128 of 16 on 4 of 64 over 3000 16.4 / 12.7.
+// over again: nine slices as well as sixteen).  With a loop over them each slice cost a round trip, twice.  Attention and merge, us,
+// with the loop / now: one row of 64 heads on 8 over 4096 keys (16 slices) 16.2 / 11.7, 64 rows of 32 over 512 (5) 12.3 / 10.5, 128 of
+// 16 on 4 of 64 over 3000 16.9 / 13.2; 48 rows over 3000 keys in 8, 9, 10, 12, 14 and 16 slices 19.6 / 16.2, 19.7 / 16.3, 19.1 / 15.1,
+// 19.9 / 14.9, 19.9 / 14.0, 21.2 / 14.1.  In a step of four 7B-wide blocks 535 / 528.
 template <int HD, int NS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplit, int M, int Hq, bf16_t* __restrict__ out) {
@@ -1381,7 +1386,9 @@ hipError_t launch_attn_fresh(const void* q, const void* k_new, const void* v_new
   if (p.tiled || p.ring_waves) {
     const int units = (n + 63) / 64 + 2 * ((M + 63) / 64);                // as the kernel shares them out
     p = plan_ring(M, Hq, Hkv, units);
-    if (units < 6) p.nsplit = 1;       // a unit takes 1 us, the merge 3 (128 rows of 40 heads over 60 keys 13.0 us, in two slices 14.9)
+    // a unit takes 0.7 to 1 us, the merge 2 to 3: 128 rows of 40 heads over 64 keys 11.8 us, in two slices 13.9; 64 rows over 192 10.5 and
+    // 11.5 (17 rows over 128, whose own tile is mostly empty, 9.3 and 8.3)
+    if (units < 6) p.nsplit = 1;
   }
   const FreshRows fr{(const bf16_t*)k_new, (const bf16_t*)v_new, (bf16_t*)kc, (bf16_t*)vc, depth, rope_step(base, hd / 2)};
   const bf16_t *qp = (const bf16_t*)q, *kp = (const bf16_t*)kc, *vp = (const bf16_t*)vc;

@@ -789,7 +789,7 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
 // written): workgroups 0 .. T - 1 a row each, the others four slices of a row.  Where there is room on the chip (joint_selection
 // says where) that saves a launch and hides one under the other.  Together with the launch that starts a pass
 // putting its tokens together and the head storing the caller's rows itself, a step of 64 nodes on four 7B-wide blocks 549 -> 538
-// us with 12 draft rows, 710 -> 703 with 192, 903 -> 892 on two of 70B width.
+// us with 12 draft rows, 903 -> 892 on two of 70B width with 16.
 template <bool AHEAD, int E>
 __global__ __launch_bounds__(1024) void argmax_topk_kernel(const float* __restrict__ z, int32_t* __restrict__ g, int vec, int T,
                                                            const float* __restrict__ d, float* __restrict__ sv_out,
